@@ -85,15 +85,39 @@ __global__ void __launch_bounds__(256) patchify_band_k(const bf16* __restrict__ 
 
 template <typename T>
 __global__ void __launch_bounds__(256) unpatchify_k(const T* __restrict__ dpat, T* __restrict__ dpix, long long total,
-                                                    int S, int P) {
+                                                    int S, int P, int lead) {
   long long i = (long long)blockIdx.x * 256 + threadIdx.x;  // index into dpix
   if (i >= total) return;
   int g = S / P, Kp = 3 * P * P;
   int x = (int)(i % S), y = (int)((i / S) % S), c = (int)((i / ((long long)S * S)) % 3);
   long long n = i / (3LL * S * S);
-  long long row = (n * g + y / P) * g + x / P;
+  long long row = n * (g * g + lead) + lead + (y / P) * g + x / P;
   int col = c * P * P + (y % P) * P + (x % P);
   dpix[i] = dpat[row * Kp + col];
+}
+
+// patchify_band_k the other way round: a band's patch rows into LDS with contiguous 16-byte reads, out as image rows
+// (moving 2 bytes per lane, the kernel above ran at a third of the rate)
+__global__ void __launch_bounds__(256) unpatchify_band_k(const bf16* __restrict__ dpat, bf16* __restrict__ dpix, int S, int P,
+                                                         int lead) {
+  extern __shared__ uint4 band[];   // [3 * P][S / 8] chunks of 8 pixels
+  const int g = S / P, SC = S / 8, PC = P / 8, rows = 3 * P, KC = rows * PC;
+  const long long n = blockIdx.x / g;
+  const int gy = blockIdx.x % g;
+  const bf16* in = dpat + ((n * (g * g + lead) + lead) + gy * g) * (long long)(3 * P * P);
+  for (int i = threadIdx.x; i < g * KC; i += 256) {
+    int gx = i / KC, k = i % KC, r = k / PC, pc = k % PC;   // r = c * P + py
+    band[r * SC + gx * PC + pc] = *reinterpret_cast<const uint4*>(in + (long long)i * 8);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < rows * SC; i += 256) {
+    int r = i / SC, xc = i % SC, c = r / P, py = r % P;
+    *reinterpret_cast<uint4*>(dpix + ((n * 3 + c) * S + gy * P + py) * (long long)S + xc * 8) = band[i];
+  }
+}
+
+static bool bands_ok(long long n, int S, int P) {   // P % 8 == 0, a whole number of patches, a band that fits 64 KB
+  return P % 8 == 0 && S % P == 0 && n * (S / P) < (1LL << 31) && (size_t)3 * P * S * 2 <= 65536;
 }
 
 hipError_t launch_patchify(int dt, const void* pixels, void* patches, long long n, int S, int P, hipStream_t s, int lead) {
@@ -101,7 +125,7 @@ hipError_t launch_patchify(int dt, const void* pixels, void* patches, long long 
   unsigned grid = (unsigned)((total + 255) / 256);
   if (dt == DT_F32)
     hipLaunchKernelGGL(patchify_k<float>, dim3(grid), dim3(256), 0, s, (const float*)pixels, (float*)patches, total, S, P, lead);
-  else if (P % 8 == 0 && S % P == 0 && n * (S / P) < (1LL << 31) && (size_t)3 * P * S * 2 <= 65536)
+  else if (bands_ok(n, S, P))
     hipLaunchKernelGGL(patchify_band_k, dim3((unsigned)(n * (S / P))), dim3(256), (size_t)3 * P * S * 2, s,
                        (const bf16*)pixels, (bf16*)patches, S, P, lead);
   else
@@ -109,13 +133,16 @@ hipError_t launch_patchify(int dt, const void* pixels, void* patches, long long 
   return hipGetLastError();
 }
 
-hipError_t launch_unpatchify(int dt, const void* dpatches, void* dpix, long long n, int S, int P, hipStream_t s) {
+hipError_t launch_unpatchify(int dt, const void* dpatches, void* dpix, long long n, int S, int P, hipStream_t s, int lead) {
   long long total = n * 3LL * S * S;
   unsigned grid = (unsigned)((total + 255) / 256);
   if (dt == DT_F32)
-    hipLaunchKernelGGL(unpatchify_k<float>, dim3(grid), dim3(256), 0, s, (const float*)dpatches, (float*)dpix, total, S, P);
+    hipLaunchKernelGGL(unpatchify_k<float>, dim3(grid), dim3(256), 0, s, (const float*)dpatches, (float*)dpix, total, S, P, lead);
+  else if (bands_ok(n, S, P) && ((uintptr_t)dpix & 15) == 0)
+    hipLaunchKernelGGL(unpatchify_band_k, dim3((unsigned)(n * (S / P))), dim3(256), (size_t)3 * P * S * 2, s,
+                       (const bf16*)dpatches, (bf16*)dpix, S, P, lead);
   else
-    hipLaunchKernelGGL(unpatchify_k<bf16>, dim3(grid), dim3(256), 0, s, (const bf16*)dpatches, (bf16*)dpix, total, S, P);
+    hipLaunchKernelGGL(unpatchify_k<bf16>, dim3(grid), dim3(256), 0, s, (const bf16*)dpatches, (bf16*)dpix, total, S, P, lead);
   return hipGetLastError();
 }
 

@@ -133,7 +133,7 @@ enum {
   EPI_BIAS_GELU = 3,   // m = acc + bias[n];  out(T) = gelu(m);  out2 = gelu'(m) (float / one-byte code, dgelu_store<T>)
   EPI_DGELU = 4,       // out(T)  = acc * pre[m][n]   (pre holds the gelu'(m) the forward stored, same format)
   EPI_PATCH = 5,       // out(RS)[rowmap(m)] = acc + bias[n] + pos[1 + m % g2][n]
-  EPI_ROWTAB = 6,      // out(RS) = acc + resid(RS)[m % rperiod][n]: a table of rperiod rows added periodically (large-M kernel only)
+  EPI_ROWTAB = 6,      // out(RS) = acc + resid(RS)[m % rperiod][n]: a table of rperiod rows added periodically (bf16 matrix-core kernels only)
 };
 
 struct GemmNT {
@@ -174,10 +174,11 @@ bool gemm_tn_fuses_colsum(int dt, const GemmTN& g, bool use_mfma);  // will laun
 hipError_t launch_cast_transpose(int dt, const float* src, int R, int C, void* dstW, void* dstWT, hipStream_t s);
 // patches: [n * (g*g + lead)][3 P P], every tile's g*g patch rows behind `lead` rows of zeros
 hipError_t launch_patchify(int dt, const void* pixels, void* patches, long long n, int S, int P, hipStream_t s, int lead);
-hipError_t launch_unpatchify(int dt, const void* dpatches, void* dpix, long long n, int S, int P, hipStream_t s);
+// the inverse, from the same row layout (the `lead` rows of a tile are skipped)
+hipError_t launch_unpatchify(int dt, const void* dpatches, void* dpix, long long n, int S, int P, hipStream_t s, int lead);
 hipError_t launch_cls_rows(int dt, void* x, const float* cls, const float* pos, long long n, int T, int D, hipStream_t s);
 hipError_t launch_pos_table(void* tab, const float* cls, const float* pos, const float* bias, int T, int D, hipStream_t s);
-bool gemm_nt_big_ok(const GemmNT& g);
+bool gemm_nt_mfma_ok(const GemmNT& g);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_calib_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t launch_gelu(int dt, const void* m, void* a, long long count, hipStream_t s);

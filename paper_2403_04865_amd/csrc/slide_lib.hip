@@ -194,7 +194,7 @@ Layout make_layout(const slide_ctx* c, long long n, long long pool_N, int keep) 
   y.e_u1 = take(0); cur += (size_t)inst * align256(M * D * e);
   y.s_u2 = save ? align256(M * D * e) : 0;
   y.e_u2 = take(0); cur += (size_t)inst * align256(M * D * e);
-  size_t abytes = M * c->F * e, pbytes = (size_t)nn * c->g2 * c->Kp * e;
+  size_t abytes = M * c->F * e, pbytes = M * c->Kp * e;
   y.s_a = save ? align256(abytes) : 0;
   y.e_a = take(0); cur += (size_t)inst * align256(abytes);
   if (bwd) {
@@ -496,7 +496,7 @@ int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool
   gt.M = n * T; gt.N = D; gt.K = c->Kp;
   gt.epi = EPI_ROWTAB; gt.resid = ar + y.e_postab; gt.ldr = D; gt.rperiod = T;
   gt.out = ar + y.e_x; gt.ldc = D;
-  if (dt == DT_BF16 && c->use_mfma && gemm_nt_big_ok(gt)) {
+  if (dt == DT_BF16 && c->use_mfma && gemm_nt_mfma_ok(gt)) {
     launch(r, K_ELEMWISE, 0, 0, [&] {
       return launch_pos_table(ar + y.e_postab, c->params + c->o_cls, c->params + c->o_pos, c->params + c->o_peb, T, D, s);
     });
@@ -669,17 +669,15 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
     launch(r, K_ELEMWISE, 0, 0,
            [&] { return launch_reduce_partials(wpart + D, T - 1, D, D, G + c->o_peb, accumulate, s); });
   }
-  RowMap pm{c->g2, T};
-  long long Mp = n * c->g2;
   // all token rows: the CLS rows meet rows of zeros in the patch matrix
   gemm_tn(r, dxAt, D, id, ar + y.e_patches, c->Kp, id, M, D, c->Kp, wpart, wcap, G + c->o_peW, accumulate);
-  if (pixel_grad) {
+  if (pixel_grad) {   // over all token rows like the forward (the CLS slots' rows are not read)
     GemmNT g{};
-    g.A = dxAt; g.lda = D; g.amap = pm; g.B = weight_t(c, 0); g.ldb = D; g.M = Mp; g.N = c->Kp; g.K = D;
+    g.A = dxAt; g.lda = D; g.B = weight_t(c, 0); g.ldb = D; g.M = M; g.N = c->Kp; g.K = D;
     g.epi = EPI_PLAIN; g.out = dm; g.ldc = c->Kp;
     gemm_nt(r, g);
-    launch(r, K_ELEMWISE, 0, 2.0 * Mp * c->Kp * e,
-           [&] { return launch_unpatchify(dt, dm, pixel_grad, n, c->cfg.tile, c->cfg.patch, s); });
+    launch(r, K_ELEMWISE, 0, 2.0 * M * c->Kp * e,
+           [&] { return launch_unpatchify(dt, dm, pixel_grad, n, c->cfg.tile, c->cfg.patch, s, T - c->g2); });
   }
   return finish(r);
 }

@@ -1,0 +1,33 @@
+"""Whole steps at the bag sizes where the choice of kernel changes: a few tiles to a few dozen, ViT-S and ViT-B widths
+with two blocks, against the CPU oracle (needs an MI355X)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import gen
+
+pytestmark = pytest.mark.gpu
+
+BF16_TOL = 2e-2   # the bound of every bf16 parity test of the step (test_gpu_parity.py)
+
+
+# token rows = 197 x tiles (of two tiles the gate gradients are one difference of two feature rows, no sum to average
+# its rounding).  5: every GEMM on 64 x 64 tiles, a last tile of 25 rows; 13: 64 x 64 and 64 x 128 tiles,
+# 2561 = 40 * 64 + 1 rows; 33: 64 x 128, 128 x 128 and 256 x 192 tiles, 6501 rows.  ViT-B width: contractions of 3072.
+@pytest.mark.parametrize("name,tiles", [("small", 5), ("small", 13), ("small", 33), ("full", 4)])
+def test_bf16_step_small_bags(name, tiles):
+    from oracle import slide_oracle as so
+    from slide_harness import GpuSlide, compare_step
+    cfg = replace(gen.CONFIGS[name][0], layers=2)
+    ds, ws, ls = gen.SEEDS[name]
+    prm = {k: gen.to_bf16_grid(v) for k, v in gen.make_params(cfg, ws, perturbed=True).items()}
+    X = gen.to_bf16_grid(gen.make_pixels(cfg, tiles, ds))
+    lab = gen.make_label(cfg, ls)
+    print(f"case {name} layers=2 n={tiles} dtype=1 label={lab}", flush=True)
+    out = GpuSlide(cfg, prm, 1, tiles).step(X, lab)
+    ref = so.slide_step(prm, X.astype(np.float64), lab, cfg)
+    _, pool_same = so.pool_bwd(so.pool_fwd(prm, out["H"], lab, cfg)[4])
+    errs, bad, kappa = compare_step(out, ref, BF16_TOL, cfg, None, pool_same)
+    print(f"kappa={kappa:.1f} worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:6], flush=True)
+    assert not bad, bad
