@@ -1,4 +1,4 @@
-// Softmax attention inside one tile, plain-ALU version (fp32 path and fall-back).
+// Softmax attention inside one tile, plain-ALU version (head dimension 8, tiles beyond the matrix-core kernels).
 // One workgroup per (tile, head); K and V (or Q and dO) of that head live in LDS as fp32.
 //
 // qkv is the token matrix [n*T, 3D]: columns [0,D) queries, [D,2D) keys, [2D,3D) values,
@@ -12,6 +12,10 @@ hipError_t launch_attn_fwd_mfma(const void* qkv, void* O, float* lse, long long 
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* O, const float* lse, const void* dO, void* dqkv, float* delta_ws,
                                 long long n, int T, int H, int dh, int cls_only, hipStream_t s);
 bool attn_mfma_ok(int T, int dh);
+bool attn_f32_ok(int T, int dh);
+hipError_t launch_attn_fwd_f32(const float* qkv, float* O, float* lse, long long n, int T, int H, int dh, hipStream_t s);
+hipError_t launch_attn_bwd_f32(const float* qkv, const float* O, const float* lse, const float* dO, float* dqkv, long long n,
+                               int T, int H, int dh, hipStream_t s);
 
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) attn_fwd_k(const T* __restrict__ qkv, T* __restrict__ O,
@@ -170,6 +174,7 @@ hipError_t launch_attn_fwd(int dt, const void* qkv, void* O, float* lse, long lo
   if (n <= 0) return hipSuccess;
   if (dt == DT_BF16 && use_mfma && attn_mfma_ok(T, dh)) return launch_attn_fwd_mfma(qkv, O, lse, n, T, H, dh, cls_only, s);
   if (cls_only) return hipErrorInvalidValue;
+  if (dt == DT_F32 && use_mfma && attn_f32_ok(T, dh)) return launch_attn_fwd_f32((const float*)qkv, (float*)O, lse, n, T, H, dh, s);
   size_t lds = attn_lds_bytes(T, dh);
   dim3 grid((unsigned)(n * H));
   hipError_t e = hipSuccess;
@@ -193,6 +198,8 @@ hipError_t launch_attn_bwd(int dt, const void* qkv, const void* O, const float* 
     return launch_attn_bwd_mfma(qkv, O, lse, dO, dqkv, delta_ws, n, T, H, dh, cls_only, s);
   }
   if (cls_only) return hipErrorInvalidValue;
+  if (dt == DT_F32 && use_mfma && attn_f32_ok(T, dh))
+    return launch_attn_bwd_f32((const float*)qkv, (const float*)O, lse, (const float*)dO, (float*)dqkv, n, T, H, dh, s);
   size_t lds = attn_lds_bytes(T, dh);
   dim3 grid((unsigned)(n * H));
   hipError_t e = hipSuccess;

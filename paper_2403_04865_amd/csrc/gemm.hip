@@ -1,4 +1,4 @@
-// Plain FMA GEMMs (fp32 path, and the fall-back of the bf16 path) + dispatch to the MFMA kernels.
+// Plain FMA GEMMs (shapes and alignments that the matrix-core kernels do not take) + dispatch to those kernels.
 #include "gemm_epi.h"
 
 namespace sl {
@@ -6,6 +6,11 @@ namespace sl {
 hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s);  // gemm_mfma.hip
 hipError_t launch_gemm_tn_mfma(const GemmTN& g, hipStream_t s);
 bool gemm_tn_mfma_ok(const GemmTN& g);
+bool gemm_nt_f32_ok(const GemmNT& g);                            // gemm_f32.hip
+hipError_t launch_gemm_nt_f32(const GemmNT& g, hipStream_t s);
+bool gemm_tn_f32_ok(const GemmTN& g);
+hipError_t launch_gemm_tn_f32(const GemmTN& g, hipStream_t s);
+int gemm_tn_f32_slabs(const GemmTN& g, int max_slabs);
 
 // C[m][n] = sum_k A[amap(m)][k] * B[n][k]; 64x64 tile, 4x4 per thread, BK = 16
 template <typename T, typename RS>
@@ -108,7 +113,11 @@ __global__ void __launch_bounds__(256) gemm_tn_fma_k(GemmTN g) {
   }
 }
 
-int gemm_tn_pick_slabs(long long M, int N1, int N2, int max_slabs) {
+int gemm_tn_pick_slabs(int dt, const GemmTN& g, bool use_mfma, int max_slabs) {
+  const long long M = g.M;
+  const int N1 = g.N1, N2 = g.N2;
+  if (dt == DT_F32 && use_mfma && gemm_tn_f32_ok(g)) return gemm_tn_f32_slabs(g, max_slabs);
+  if (max_slabs > 32) max_slabs = 32;
   // enough workgroups to cover the chip several times, slabs of at least 256 rows
   long long tiles = (long long)((N1 + 127) / 128) * ((N2 + 127) / 128);
   long long want = (2048 + tiles - 1) / tiles;
@@ -120,7 +129,7 @@ int gemm_tn_pick_slabs(long long M, int N1, int N2, int max_slabs) {
 }
 
 bool gemm_tn_fuses_colsum(int dt, const GemmTN& g, bool use_mfma) {
-  return dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g);
+  return use_mfma && (dt == DT_BF16 ? gemm_tn_mfma_ok(g) : gemm_tn_f32_ok(g));
 }
 
 hipError_t launch_gemm_nt(int dt, const GemmNT& g, bool use_mfma, hipStream_t s) {
@@ -128,6 +137,7 @@ hipError_t launch_gemm_nt(int dt, const GemmNT& g, bool use_mfma, hipStream_t s)
   // the periodic-table epilogue exists in the matrix-core kernels only (callers ask gemm_nt_mfma_ok first)
   if (g.epi == EPI_ROWTAB && !(dt == DT_BF16 && use_mfma && gemm_nt_mfma_ok(g))) return hipErrorInvalidValue;
   if (dt == DT_BF16 && use_mfma && gemm_nt_mfma_ok(g)) return launch_gemm_nt_mfma(g, s);
+  if (dt == DT_F32 && use_mfma && gemm_nt_f32_ok(g)) return launch_gemm_nt_f32(g, s);
   dim3 grid((unsigned)((g.M + 63) / 64), (g.N + 63) / 64);
   if (dt == DT_F32)
     hipLaunchKernelGGL((gemm_nt_fma_k<float, float>), grid, dim3(256), 0, s, g);
@@ -140,6 +150,7 @@ hipError_t launch_gemm_tn(int dt, const GemmTN& g, bool use_mfma, hipStream_t s)
   if (g.N1 <= 0 || g.N2 <= 0 || g.slabs <= 0) return hipSuccess;
   if (dt == DT_BF16 && use_mfma && g.big) return launch_gemm_tn_big(g, s);
   if (dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g)) return launch_gemm_tn_mfma(g, s);
+  if (dt == DT_F32 && use_mfma && gemm_tn_f32_ok(g)) return launch_gemm_tn_f32(g, s);
   dim3 grid((g.N1 + 63) / 64, (g.N2 + 63) / 64, g.slabs);
   if (dt == DT_F32)
     hipLaunchKernelGGL(gemm_tn_fma_k<float>, grid, dim3(256), 0, s, g);

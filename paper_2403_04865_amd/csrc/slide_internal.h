@@ -168,7 +168,7 @@ hipError_t launch_gemm_tn_big(const GemmTN& g, hipStream_t s);
 // All launchers enqueue on `s` and return the launch status.
 hipError_t launch_gemm_nt(int dt, const GemmNT& g, bool use_mfma, hipStream_t s);
 hipError_t launch_gemm_tn(int dt, const GemmTN& g, bool use_mfma, hipStream_t s);
-int gemm_tn_pick_slabs(long long M, int N1, int N2, int max_slabs);
+int gemm_tn_pick_slabs(int dt, const GemmTN& g, bool use_mfma, int max_slabs);
 bool gemm_tn_fuses_colsum(int dt, const GemmTN& g, bool use_mfma);  // will launch_gemm_tn fill cs_part?
 
 hipError_t launch_cast_transpose(int dt, const float* src, int R, int C, void* dstW, void* dstWT, hipStream_t s);

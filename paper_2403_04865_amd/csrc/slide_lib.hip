@@ -259,7 +259,7 @@ void gemm_tn(Run& r, const void* A, long long lda, RowMap amap, const void* B, l
   size_t fit = part_floats / ((size_t)N1 * N2);
   int bs = (dt == DT_BF16 && r.c->use_mfma) ? gemm_tn_big_slabs(g, fit > 256 ? 256 : (int)fit) : 0;
   if (bs) { g.slabs = bs; g.big = 1; }
-  else g.slabs = gemm_tn_pick_slabs(M, N1, N2, 32);
+  else g.slabs = gemm_tn_pick_slabs(dt, g, r.c->use_mfma, fit > 64 ? 64 : (int)fit);
   bool fused = bias_out && gemm_tn_fuses_colsum(dt, g, r.c->use_mfma);
   if (fused) g.cs_part = cpart;
   if (bias_out && !fused) {

@@ -31,3 +31,23 @@ def test_bf16_step_small_bags(name, tiles):
     errs, bad, kappa = compare_step(out, ref, BF16_TOL, cfg, None, pool_same)
     print(f"kappa={kappa:.1f} worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:6], flush=True)
     assert not bad, bad
+
+
+# float32: 5 tiles = 985 rows (64 x 64 tiles with a last one of 25 rows, slabs of a few 32-row steps, four wavefronts per
+# head), 45 tiles: eight wavefronts per head in both directions; ViT-B width: contractions of 3072
+@pytest.mark.parametrize("name,tiles", [("small", 5), ("small", 45), ("full", 3)])
+def test_fp32_step_small_bags(name, tiles):
+    from oracle import slide_oracle as so
+    from slide_harness import GpuSlide, compare_step
+    cfg = replace(gen.CONFIGS[name][0], layers=2)
+    ds, ws, ls = gen.SEEDS[name]
+    prm = gen.make_params(cfg, ws, perturbed=True)
+    X = gen.make_pixels(cfg, tiles, ds)
+    lab = gen.make_label(cfg, ls)
+    print(f"case {name} layers=2 n={tiles} dtype=0 label={lab}", flush=True)
+    out = GpuSlide(cfg, prm, 0, tiles).step(X, lab)
+    ref = so.slide_step(prm, X.astype(np.float64), lab, cfg)
+    _, pool_same = so.pool_bwd(so.pool_fwd(prm, out["H"], lab, cfg)[4])
+    errs, bad, kappa = compare_step(out, ref, 1e-4, cfg, None, pool_same)   # the bound of every fp32 parity test
+    print(f"kappa={kappa:.1f} worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:6], flush=True)
+    assert not bad, bad
