@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
   // z = zv + zlo to fp64 accuracy; the zlo part of the dot product is a constant of the thread's 12 columns
   float kz = 0.f;
   {
-    const float* zv = p.scal + 4 + 2 * p.C;
+    const float* zv = p.scal + pool_z_off(p.C);
     const float* dz = zv + D;
     const float* zlo = dz + D;
     for (int d = tid; d < D; d += 256) { zds[d] = zv[d]; zds[D + d] = dz[d]; }
@@ -287,7 +287,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
   bf16x8 wt[NT][KS];
   float dzr[NT];
   {
-    const float* dz = p.scal + 4 + 2 * p.C + D;
+    const float* dz = p.scal + pool_z_off(p.C) + D;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       dzr[t] = dz[dcol + 32 * t];

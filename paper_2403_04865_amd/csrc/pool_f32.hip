@@ -1,0 +1,309 @@
+// Gated-attention MIL pooling over the feature rows in float32 on the matrix cores: every shape and row count that has no
+// bf16 kernel (float32 path, short bags, feature widths of the convolutional encoders, the backward at D = 768).
+//
+// The three contractions are taken as blocks of 32 rows x 32 gate units (or features), one per workgroup, with the
+// contracted index dealt to the workgroup's wavefronts and their partial blocks added through LDS: a bag of 16 to 1,000
+// rows is a few thousand MFMAs altogether and what bounds it is the serial chain of one wavefront, so the work is cut
+// along all three indices.  (One workgroup per 16 rows with all gate units on the vector units, one dot product per
+// wavefront at a time: 37 x 384 rows, M_h = 128 209 us forward and 279 us backward; 300 x 2048 682 and 1032 us.)
+// MFMA operands come straight from global memory: a lane reads four consecutive elements of its row and gives one to each
+// of four MFMAs (which index an MFMA contracts does not matter as long as both operands agree).  Weights are the first
+// operand: a lane then owns one feature row and runs of four neighbouring gate units (features).
+#include "slide_internal.h"
+
+namespace sl {
+
+namespace {
+
+constexpr int U = 6;   // steps of a contraction whose loads are issued together
+
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.f;
+  return z;
+}
+
+// elements k .. k + 3 of a row of n, zeros behind its end; VEC: n and the row's address allow 16-byte reads
+template <bool VEC>
+__device__ __forceinline__ f32x4 ld4(const float* row, int k, int n) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (k < n) v = *reinterpret_cast<const f32x4*>(row + k);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + e < n) v[e] = row[k + e];
+  }
+  return v;
+}
+
+// Pre-activations of 32 rows x 32 gate units of V and of U, K split over the wavefronts, then per element
+//   forward   w t s summed over the gate units: part[blockIdx.y][n] (blockIdx.y walks over blocks of gate units)
+//   backward  Dp[n] = [dpV | dpU] (2 M_h), dwp[blockIdx.x][j] = sum over the 32 rows of da t s
+// where t = tanh(V h + b_V), s = sigmoid(U h + b_U), da_n = alpha_n dz . (h_n - z).  All of it stays float32: the column
+// sums of the backward's terms cancel almost completely (the da of a slide add up to zero).
+template <bool VEC, bool BWD>
+__global__ void __launch_bounds__(512) pool_gate_f32_k(PoolArgs p, float* __restrict__ out, float* __restrict__ dwp) {
+  extern __shared__ float red[];   // [W][32][64] partial blocks, then [W][64] dot products / partial logits
+  const int W = blockDim.x >> 6, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
+  const int D = p.D, Mh = p.Mh, nc = (D + 7) / 8;
+  float* aux = red + W * 32 * 64;
+  const long long n = (long long)blockIdx.x * 32 + li;
+  const bool ok = n < p.N;
+  const float* hrow = p.H + (ok ? n : p.N - 1) * D;
+  const float* zv = p.scal + pool_z_off(p.C);
+  if (!BWD && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.ticket = 0;
+  float part = 0.f;
+  for (int ub = blockIdx.y; ub * 32 < Mh; ub += gridDim.y) {
+    const int u = ub * 32 + li < Mh ? ub * 32 + li : Mh - 1;
+    const float *vr = p.VW + (size_t)u * D, *ur = p.UW + (size_t)u * D;
+    f32x16 av = zero16(), au = zero16();
+    float dot = 0.f;
+    for (int c0 = wave; c0 < nc; c0 += U * W) {   // U steps' loads in flight
+      f32x4 h[U], v[U], w[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const int k = (c0 + i * W) * 8 + half * 4;
+        h[i] = ld4<VEC>(hrow, k, D);
+        v[i] = ld4<VEC>(vr, k, D);
+        w[i] = ld4<VEC>(ur, k, D);
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (c0 + i * W < nc) {
+          if constexpr (BWD) {
+            const int k = (c0 + i * W) * 8 + half * 4;
+            const f32x4 z = ld4<VEC>(zv, k, D), dz = ld4<VEC>(zv + D, k, D), zl = ld4<VEC>(zv + 2 * D, k, D);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dot += ((h[i][e] - z[e]) - zl[e]) * dz[e];
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            av = __builtin_amdgcn_mfma_f32_32x32x2f32(v[i][e], h[i][e], av, 0, 0, 0);
+            au = __builtin_amdgcn_mfma_f32_32x32x2f32(w[i][e], h[i][e], au, 0, 0, 0);
+          }
+        }
+    }
+    float* mine = red + wave * 32 * 64 + lane;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { mine[r * 64] = av[r]; mine[(16 + r) * 64] = au[r]; }
+    if constexpr (BWD) aux[wave * 64 + lane] = dot;
+    __syncthreads();
+    if (wave < 4) {   // wavefront q: gate units q * 8 + half * 4 .. + 3 of the block, row li
+      const int j0 = ub * 32 + wave * 8 + half * 4;
+      float xv[4] = {0.f, 0.f, 0.f, 0.f}, xu[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int w = 0; w < W; ++w)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          xv[e] += red[(w * 32 + wave * 4 + e) * 64 + lane];
+          xu[e] += red[(w * 32 + 16 + wave * 4 + e) * 64 + lane];
+        }
+      float da = 0.f;
+      if constexpr (BWD) {
+        for (int w = 0; w < W; ++w) da += aux[w * 64 + li] + aux[w * 64 + 32 + li];
+        da = ok ? da * (__expf(p.a[n] - p.scal[0]) / p.scal[1]) : 0.f;
+      }
+      float dv[4], du[4], dw[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + e < Mh ? j0 + e : Mh - 1;
+        const float t = tanhf(xv[e] + p.Vb[j]), s = 1.0f / (1.0f + __expf(-(xu[e] + p.Ub[j]))), wj = p.w[j];
+        if constexpr (BWD) {
+          dv[e] = da * wj * s * (1.f - t * t);
+          du[e] = da * wj * t * s * (1.f - s);
+          dw[e] = da * t * s;
+        } else if (j0 + e < Mh) {
+          part += wj * t * s;
+        }
+      }
+      if constexpr (BWD) {
+        float* row = out + n * 2 * Mh + j0;
+        if (ok) {
+          if (VEC && j0 < Mh) {
+            *reinterpret_cast<f32x4*>(row) = f32x4{dv[0], dv[1], dv[2], dv[3]};
+            *reinterpret_cast<f32x4*>(row + Mh) = f32x4{du[0], du[1], du[2], du[3]};
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (j0 + e < Mh) { row[e] = dv[e]; row[Mh + e] = du[e]; }
+          }
+        }
+#pragma unroll
+        for (int o = 1; o < 32; o <<= 1)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dw[e] += __shfl_xor(dw[e], o, 64);
+        if (li == 0) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (j0 + e < Mh) dwp[(size_t)blockIdx.x * Mh + j0 + e] = dw[e];
+        }
+      }
+    }
+    __syncthreads();   // the partial blocks have been read
+  }
+  if constexpr (!BWD) {
+    if (wave < 4) aux[wave * 64 + lane] = part;
+    __syncthreads();
+    if (threadIdx.x < 32 && ok) {
+      float a = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a += aux[q * 64 + li] + aux[q * 64 + 32 + li];
+      out[blockIdx.y * p.N + n] = a;
+    }
+  }
+}
+
+// Attention logits from their `parts` partial sums (part[i][n]), and per workgroup {max, sum, weighted feature sum} over
+// its groups of 16 rows (the weighted sum in fp64: it feeds a cancelling difference in the backward).
+__global__ void __launch_bounds__(256) pool_softmax_part_k(PoolArgs p, const float* __restrict__ part, int parts) {
+  extern __shared__ double zb[];   // [D]
+  __shared__ float er[16];
+  __shared__ float resc;
+  const int D = p.D, tid = threadIdx.x;
+  for (int d = tid; d < D; d += 256) zb[d] = 0.0;
+  float m = -INFINITY;   // of the rows so far; lanes 0 .. 15 of every wavefront compute the same
+  double l = 0.0;
+  const long long groups = (p.N + 15) / 16;
+  for (long long g = blockIdx.x; g < groups; g += gridDim.x) {
+    const long long n0 = g * 16;
+    if (tid < 16) {
+      float a = -INFINITY;
+      if (n0 + tid < p.N) {
+        a = 0.f;
+        for (int i = 0; i < parts; ++i) a += part[i * p.N + n0 + tid];
+        p.a[n0 + tid] = a;
+      }
+      float mx = a;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 16));
+      mx = fmaxf(m, mx);
+      const float sc = __expf(m - mx), e = __expf(a - mx);   // exp(-inf) = 0 on the first group
+      float es = e;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) es += __shfl_xor(es, o, 16);
+      l = l * (double)sc + (double)es;
+      m = mx;
+      er[tid] = e;
+      if (tid == 0) resc = sc;
+    }
+    __syncthreads();
+    const double sc = (double)resc;
+    for (int d = tid; d < D; d += 256) {
+      const float* h = p.H + n0 * D + d;
+      float v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = h[(n0 + r < p.N ? r : 0) * (long long)D];
+      double z = zb[d] * sc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z += (double)er[r] * (double)v[r];   // rows past the end have weight zero
+      zb[d] = z;
+    }
+    __syncthreads();
+  }
+  double* out = p.part + (size_t)blockIdx.x * (2 + D);
+  if (tid == 0) { out[0] = (double)m; out[1] = l; }
+  for (int d = tid; d < D; d += 256) out[2 + d] = zb[d];
+}
+
+// G[n][d] = alpha_n dz[d] + sum_j Dp[n][j] [V;U][j][d]: 32 rows x 32 features per workgroup, gate units split over four
+// wavefronts
+constexpr int UG = 4;
+template <bool VEC>
+__global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __restrict__ Dp) {
+  __shared__ float red[4][16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
+  const int D = p.D, Mh = p.Mh, K = 2 * Mh, nc = (K + 7) / 8;
+  const long long n = (long long)blockIdx.x * 32 + li;
+  const bool ok = n < p.N;
+  const int d = blockIdx.y * 32 + li, dc = d < D ? d : D - 1;
+  const float* drow = Dp + (ok ? n : p.N - 1) * K;
+  f32x16 acc = zero16();
+  for (int c0 = wave; c0 < nc; c0 += 4 * UG) {
+    f32x4 g[UG];
+    float w[UG][4];
+#pragma unroll
+    for (int i = 0; i < UG; ++i) {
+      const int j0 = (c0 + i * 4) * 8 + half * 4;
+      g[i] = ld4<VEC>(drow, j0, K);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + e < K ? j0 + e : K - 1;   // its factor is zero
+        w[i][e] = (j < Mh ? p.VW + (size_t)j * D : p.UW + (size_t)(j - Mh) * D)[dc];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < UG; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[i][e], g[i][e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+  __syncthreads();
+  if (!ok) return;
+  const float alpha = __expf(p.a[n] - p.scal[0]) / p.scal[1];
+  const float* dz = p.scal + pool_z_off(p.C) + D;
+  const int d0 = blockIdx.y * 32 + wave * 8 + half * 4;
+  f32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int r = wave * 4 + e;
+    v[e] = alpha * dz[d0 + e < D ? d0 + e : D - 1] + ((red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]));
+  }
+  float* o = p.G + n * D + d0;
+  if constexpr (VEC) {
+    if (d0 < D) *reinterpret_cast<f32x4*>(o) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (d0 + e < D) o[e] = v[e];
+  }
+}
+
+// 16-byte accesses to rows of D features and of M_h gate units
+bool vec_ok(const PoolArgs& p) {
+  auto al = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
+  return p.D % 4 == 0 && p.Mh % 4 == 0 && al(p.H) && al(p.VW) && al(p.UW) && (!p.G || al(p.G));
+}
+
+// Wavefronts that share a contraction over D: about six steps of eight each, all of whose loads a wavefront keeps in flight.
+int gate_waves(int D) { return D <= 256 ? 4 : 8; }
+size_t gate_lds(int W) { return (size_t)W * 33 * 64 * sizeof(float); }
+
+template <bool VEC, bool BWD>
+hipError_t go_gate(const PoolArgs& p, float* out, float* dwp, int parts, hipStream_t s) {
+  const int W = gate_waves(p.D);
+  auto kern = pool_gate_f32_k<VEC, BWD>;
+  if (gate_lds(W) > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gate_lds(W));
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)((p.N + 31) / 32), parts), dim3(64 * W), gate_lds(W), s, p, out, dwp);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
+  int parts = (p.Mh + 31) / 32;
+  if ((size_t)parts * p.N > p.a_room) parts = (int)(p.a_room / p.N);
+  if (parts < 1) return hipErrorInvalidValue;
+  hipError_t e = vec_ok(p) ? go_gate<true, false>(p, p.a_tmp, nullptr, parts, s) : go_gate<false, false>(p, p.a_tmp, nullptr, parts, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pool_softmax_part_k, dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, parts);
+  return hipGetLastError();
+}
+
+// Dp: [N][2 M_h]; dwp: [ceil(N / 32)][M_h] partial sums of dw; writes p.G
+hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s) {
+  const int parts = (p.Mh + 31) / 32;
+  const bool vec = vec_ok(p);
+  hipError_t e = vec ? go_gate<true, true>(p, Dp, dwp, parts, s) : go_gate<false, true>(p, Dp, dwp, parts, s);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)((p.N + 31) / 32), (p.D + 31) / 32);
+  if (vec) hipLaunchKernelGGL(pool_g_f32_k<true>, grid, dim3(256), 0, s, p, Dp);
+  else hipLaunchKernelGGL(pool_g_f32_k<false>, grid, dim3(256), 0, s, p, Dp);
+  return hipGetLastError();
+}
+
+}  // namespace sl

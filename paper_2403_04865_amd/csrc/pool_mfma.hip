@@ -45,9 +45,10 @@ __device__ __forceinline__ bf16x8 cvt8(float4 a, float4 b) {
   return r;
 }
 
-// [V;U] fp32 -> bf16, rows 0..Mh-1 = V, Mh..2Mh-1 = U
+// [V;U] fp32 -> bf16, rows 0..Mh-1 = V, Mh..2Mh-1 = U; clears the combine kernel's arrival counter
 __global__ void __launch_bounds__(256) pool_cast_vu_k(const float* __restrict__ V, const float* __restrict__ U,
-                                                      bf16* __restrict__ out, long long n) {
+                                                      bf16* __restrict__ out, long long n, unsigned* __restrict__ ticket) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
   long long i = (long long)blockIdx.x * 256 + threadIdx.x;
   if (i < n) { out[i] = (bf16)V[i]; out[n + i] = (bf16)U[i]; }
 }
@@ -528,7 +529,7 @@ hipError_t go_reg(const PoolArgs& p, hipStream_t s) {
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   long long n = (long long)MH * p.D;
-  hipLaunchKernelGGL(pool_cast_vu_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, n);
+  hipLaunchKernelGGL(pool_cast_vu_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, n, p.ticket);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(256), lds, s, p, (const bf16*)p.vub);
   return hipGetLastError();
@@ -559,7 +560,7 @@ hipError_t go(const PoolArgs& p, hipStream_t s) {
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   long long n = (long long)p.Mh * p.D;
-  hipLaunchKernelGGL(pool_cast_vu_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, n);
+  hipLaunchKernelGGL(pool_cast_vu_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, n, p.ticket);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(256), lds, s, p, (const bf16*)p.vub);
   return hipGetLastError();

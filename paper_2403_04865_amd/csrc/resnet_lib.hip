@@ -547,7 +547,7 @@ int resnet_slide_step_bwd(resnet_ctx* c, int accumulate, void* stream) {
   if (rc) return rc;
   Run r{c, (hipStream_t)stream};
   launch(r, RK_MIL_POOL, 16.0 * N * c->D * c->Mh, 3.0 * N * c->D * 4, [&] {
-    rc = mil_pool_bwd(c->agg, c->arena + c->lay.H, N, c->step_label, c->arena + c->lay.G, accumulate, stream);
+    rc = pool_step_bwd(c->agg, c->arena + c->lay.H, N, c->step_label, c->arena + c->lay.G, accumulate, (hipStream_t)stream);
     return rc == SLIDE_OK ? hipSuccess : hipErrorUnknown;
   });
   if (rc) return rc;

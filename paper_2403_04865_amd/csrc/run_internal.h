@@ -98,6 +98,9 @@ inline int prof_family(const Prof& p, int kernel_id, int families, double* total
 
 // aggregator-only context (slide_lib.hip); destroyed with slide_ctx_destroy
 int pool_ctx_create(int D, int Mh, int C, int dt, slide_ctx** out);
+// mil_pool_bwd right behind mil_pool_fwd over the same features on the same context, whose work space nothing has touched in
+// between: the forward is not run again
+int pool_step_bwd(slide_ctx* c, const void* feats, long long N, int label, void* G, int accumulate, hipStream_t s);
 
 inline void prof_destroy(Prof& p) {
   for (hipEvent_t e : p.ev) (void)hipEventDestroy(e);

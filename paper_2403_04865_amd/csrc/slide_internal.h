@@ -222,12 +222,14 @@ hipError_t launch_attn_bwd(int dt, const void* qkv, const void* O, const float* 
 size_t attn_lds_bytes(int T, int dh);
 
 // Gated-attention MIL pool.
+__host__ __device__ inline int pool_z_off(int C) { return (4 + 2 * C + 3) & ~3; }   // 16-byte aligned rows
+inline size_t pool_scal_floats(int C, int D) { return (size_t)pool_z_off(C) + 3 * D + 1; }
 struct PoolArgs {
   const float* H; long long N; int D, Mh, C; int label;  // features are fp32 in both paths
   const float *VW, *Vb, *UW, *Ub, *w, *cW, *cb;
   float* a;     // [N] attention logits
   double* part; // [blocks][2 + D] forward partials {max, sum, weighted feature sum}
-  float* scal;  // [4 + 2C + 3D]: m, Z, loss, z.dz, logits[C], dy[C], z[D], dz[D], zlo[D]
+  float* scal;  // m, Z, loss, z.dz, logits[C], dy[C], then from pool_z_off(C) on z[D], dz[D], zlo[D], ticket
   int blocks;
   float *loss, *logits, *alpha;  // outputs, may be null
   float* G;                      // [N,D]
@@ -240,13 +242,16 @@ struct PoolArgs {
   // its partial logits (partial = 1), the second adds them (a_in) and does everything else; w_other = the other half's w
   // (the softmax shift is a bound over all gate units).  a_tmp: [N] floats of scratch for the partial logits.
   const float* a_in; int partial; const float* w_other; float* a_tmp;
+  size_t a_room;      // floats behind a_tmp (the float32 kernels keep partial logits of blocks of gate units there)
+  unsigned* ticket;   // arrival counter of the combine kernel's workgroups, cleared by the kernels of stage 1
 };
 int pool_blocks(long long N);
 bool pool_mfma_ok(const PoolArgs& p);
 int pool_mfma_rows(const PoolArgs& p);
 hipError_t launch_pool_gate_part_mfma(const PoolArgs& p, hipStream_t s);
 hipError_t launch_pool_fwd(const PoolArgs& p, hipStream_t s);
-hipError_t launch_pool_bwd_rows(const PoolArgs& p, float* Dp, hipStream_t s);
+hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s);
+hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s);
 hipError_t launch_pool_head_grads(const PoolArgs& p, hipStream_t s);
 
 // fp32 lane of the CLS rows (bf16 path, cls_lane.hip)

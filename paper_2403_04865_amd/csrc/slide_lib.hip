@@ -97,6 +97,7 @@ struct slide_ctx {
   Layout enc_layout;
   bool step_saved = false;    // slide_step_fwd state (features in arena, label)
   int step_label = 0;
+  bool pool_saved = false;    // ... and no other aggregator call has used the work space since
   bool use_mfma = true;
   bool use_lane = false;      // bf16 path: the CLS rows' stream and row-wise work are repeated in fp32 (cls_lane.hip)
   bool pool_only = false;     // aggregator of another encoder family: only mil.* / head.* exist, encoder calls are refused
@@ -144,7 +145,7 @@ Layout make_layout(const slide_ctx* c, long long n, long long pool_N, int keep) 
   int D = c->D, Mh = c->Mh, C = c->C;
   y.p_a = take((size_t)PN * 4);
   y.p_part = take((size_t)1024 * (2 + D) * 8);
-  y.p_scal = take((size_t)(4 + 2 * C + 3 * D) * 4);
+  y.p_scal = take(pool_scal_floats(C, D) * 4);
   y.p_Dp = take((size_t)PN * 3 * Mh * 4);
   y.p_tn = take((size_t)64 * 2 * Mh * D * 4);
   y.p_cs = take((size_t)1024 * 3 * Mh * 4);
@@ -696,6 +697,8 @@ PoolArgs pool_args(slide_ctx* c, const Layout& y, const void* feats, long long N
   p.grads = c->grads; p.ocW = c->o_cW; p.ocb = c->o_cb;
   p.vub = ar + y.p_vub; p.use_mfma = c->use_mfma && c->dt == DT_BF16;
   p.a_tmp = (float*)(ar + y.p_Dp);   // the backward's work space is idle during the forward
+  p.a_room = (size_t)N * 3 * c->Mh;
+  p.ticket = (unsigned*)(p.scal + pool_scal_floats(c->C, c->D) - 1);
   return p;
 }
 
@@ -708,14 +711,16 @@ int pool_fwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
   return finish(r);
 }
 
+// fwd_done: the forward's logits and scalars over the same feature rows are still in the arena
 int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int label, void* G, int accumulate,
-             hipStream_t s) {
+             hipStream_t s, bool fwd_done) {
   Run r{c, s};
   char* ar = c->arena;
   PoolArgs p = pool_args(c, y, feats, N, label);
   p.G = (float*)G; p.accumulate = accumulate;
   int D = c->D, Mh = c->Mh;
-  launch(r, K_POOL_FWD, 4.0 * N * D * Mh, (double)N * D * 4, [&] { return launch_pool_fwd(p, s); });
+  if (!fwd_done)
+    launch(r, K_POOL_FWD, 4.0 * N * D * Mh, (double)N * D * 4, [&] { return launch_pool_fwd(p, s); });
   char* Dp = ar + y.p_Dp;
   RowMap id{0, 0};
   float* tn = (float*)(ar + y.p_tn);
@@ -744,22 +749,24 @@ int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
     }
     return finish(r);
   }
-  launch(r, K_POOL_BWD, 8.0 * N * D * Mh, 2.0 * N * D * 4, [&] { return launch_pool_bwd_rows(p, (float*)Dp, s); });
-  gemm_tn(r, Dp, 3 * Mh, id, feats, D, id, N, Mh, D, tn, tncap, c->grads + c->o_VW, accumulate, DT_F32);
-  gemm_tn(r, Dp + (size_t)Mh * 4, 3 * Mh, id, feats, D, id, N, Mh, D, tn, tncap, c->grads + c->o_UW, accumulate, DT_F32);
-  int slabs = colsum_slabs(N);
-  launch(r, K_COLSUM, 0, (double)N * 3 * Mh * 4,
-         [&] { return launch_colsum_part(DT_F32, Dp, 3 * Mh, id, N, 3 * Mh, cs, slabs, s); });
+  // float32: [dpV dpU] and the partial sums of dw share the room; db_V and db_U are column sums of the GEMM's first operand
+  float* dwp = (float*)Dp + (size_t)N * 2 * Mh;
+  const int rblocks = (int)((N + 31) / 32);
+  launch(r, K_POOL_BWD, 8.0 * N * D * Mh, 2.0 * N * D * 4, [&] { return launch_pool_bwd_f32(p, (float*)Dp, dwp, s); });
+  launch(r, K_ELEMWISE, 0, 0, [&] { return launch_pool_head_grads(p, s); });
   launch(r, K_ELEMWISE, 0, 0,
-         [&] { return launch_reduce_partials(cs, slabs, 3 * Mh, Mh, c->grads + c->o_Vb, accumulate, s); });
-  launch(r, K_ELEMWISE, 0, 0,
-         [&] { return launch_reduce_partials(cs + Mh, slabs, 3 * Mh, Mh, c->grads + c->o_Ub, accumulate, s); });
-  launch(r, K_ELEMWISE, 0, 0,
-         [&] { return launch_reduce_partials(cs + 2 * Mh, slabs, 3 * Mh, Mh, c->grads + c->o_w, accumulate, s); });
+         [&] { return launch_reduce_partials(dwp, rblocks, Mh, Mh, c->grads + c->o_w, accumulate, s); });
+  gemm_tn(r, Dp, 2 * Mh, id, feats, D, id, N, 2 * Mh, D, tn, tncap, c->grads + c->o_VW, accumulate, DT_F32,
+          c->grads + c->o_Vb, cs, c->grads + c->o_UW, c->grads + c->o_Ub);
   return finish(r);
 }
 
 }  // namespace
+
+int sl::pool_step_bwd(slide_ctx* c, const void* feats, long long N, int label, void* G, int accumulate, hipStream_t s) {
+  const Layout y = make_layout(c, 0, N, KEEP_NONE);
+  return pool_bwd(c, y, feats, N, label, G, accumulate, s, true);
+}
 
 // A context that holds the aggregator alone (tensors mil.V.W, mil.V.b, mil.U.W, mil.U.b, mil.w, head.W, head.b in
 // this order from offset 0): the other encoder families run mil_pool_fwd / mil_pool_bwd on it over their own features.
@@ -935,6 +942,7 @@ static int pool_check(slide_ctx* c, const void* feats, int64_t N, int32_t label,
   // (the pool part is laid out front to back with sizes that grow with N)
   if (c->enc_saved && y->pool_end > c->enc_layout.enc_begin) { c->enc_saved = false; c->step_saved = false; }
   if (c->step_saved && N > c->enc_n) c->step_saved = false;
+  c->pool_saved = false;
   return SLIDE_OK;
 }
 
@@ -952,7 +960,7 @@ int mil_pool_bwd(slide_ctx* c, const void* feats, int64_t N, int32_t label, void
   int rc = pool_check(c, feats, N, label, &y);
   if (rc) return rc;
   if (!dfeats_out) return SLIDE_EINVAL;
-  return pool_bwd(c, y, feats, N, label, dfeats_out, accumulate, (hipStream_t)stream);
+  return pool_bwd(c, y, feats, N, label, dfeats_out, accumulate, (hipStream_t)stream, false);
 }
 
 int mil_pool_fwd_static(const slide_ctx* c, const float* params, const void* feats, int64_t N, int32_t label,
@@ -965,7 +973,7 @@ int mil_pool_fwd_static(const slide_ctx* c, const float* params, const void* fea
   auto take = [&](size_t bytes) { size_t o = cur; cur = align256(cur + bytes); return o; };
   const int D = c->D, Mh = c->Mh, C = c->C;
   const size_t o_a = take((size_t)N * 4), o_part = take((size_t)1024 * (2 + D) * 8);
-  const size_t o_scal = take((size_t)(4 + 2 * C + 3 * D) * 4), o_vub = take((size_t)2 * 2 * Mh * D * 2);
+  const size_t o_scal = take(pool_scal_floats(C, D) * 4), o_vub = take((size_t)2 * 2 * Mh * D * 2);
   const size_t o_tmp = take((size_t)N * 4);
   if (cur > SLIDE_STATIC_POOL_BYTES) return SLIDE_EARENA;
   hipError_t e;
@@ -978,7 +986,9 @@ int mil_pool_fwd_static(const slide_ctx* c, const float* params, const void* fea
   p.a = (float*)(ws + o_a); p.part = (double*)(ws + o_part); p.scal = (float*)(ws + o_scal);
   p.blocks = pool_blocks(N);
   p.vub = ws + o_vub; p.use_mfma = c->use_mfma && c->dt == DT_BF16;
-  p.a_tmp = (float*)(ws + o_tmp);
+  p.a_tmp = (float*)(ws + o_tmp);   // the last piece: it may use what is left of the array
+  p.a_room = (SLIDE_STATIC_POOL_BYTES - o_tmp) / 4;
+  p.ticket = (unsigned*)(p.scal + pool_scal_floats(C, D) - 1);
   p.loss = loss; p.logits = logits; p.alpha = alpha;
   (void)hipGetLastError();
   e = launch_pool_fwd(p, (hipStream_t)stream);
@@ -999,6 +1009,7 @@ int slide_step_fwd(slide_ctx* c, const void* pixels, int64_t N, int32_t label, f
   rc = pool_fwd(c, y, c->arena + y.p_H, N, label, loss, logits, alpha, (hipStream_t)stream);
   if (rc) { c->enc_saved = false; return rc; }
   c->step_saved = true;
+  c->pool_saved = true;
   c->step_label = label;
   return SLIDE_OK;
 }
@@ -1009,7 +1020,7 @@ int slide_step_bwd(slide_ctx* c, int accumulate, void* pixel_grad, void* stream)
   if (!c->step_saved || !c->enc_saved) return SLIDE_ESTATE;
   const Layout y = c->enc_layout;
   long long N = c->enc_n;
-  rc = pool_bwd(c, y, c->arena + y.p_H, N, c->step_label, c->arena + y.p_G, accumulate, (hipStream_t)stream);
+  rc = pool_bwd(c, y, c->arena + y.p_H, N, c->step_label, c->arena + y.p_G, accumulate, (hipStream_t)stream, c->pool_saved);
   if (rc) return rc;
   rc = enc_bwd(c, c->arena + y.p_G, N, accumulate, pixel_grad, (hipStream_t)stream);
   c->step_saved = false;  // activations are consumed (work buffers were overwritten)
@@ -1048,7 +1059,7 @@ int slide_step_chunked(slide_ctx* c, const void* pixels, int64_t N, int64_t chun
   // aggregator and loss on the whole slide, then the gradient of every feature row
   rc = pool_fwd(c, y, H, N, label, loss, logits, alpha, s);
   if (rc) return rc;
-  rc = pool_bwd(c, y, H, N, label, G, accumulate, s);
+  rc = pool_bwd(c, y, H, N, label, G, accumulate, s, true);
   if (rc) return rc;
   // pass 2: chunk by chunk, forward again with the activations kept, backward seeded with the chunk's rows of G
   for (int64_t t0 = 0; t0 < N; t0 += chunk_tiles) {

@@ -156,3 +156,11 @@ def test_pool_over_more_rows_invalidates_a_saved_step():
         g.lib.slide_step_bwd(0, None)
     assert e.value.code == -4
     torch.cuda.synchronize()
+
+
+# float32 matrix-core kernels: blocks of 32 rows x 32 gate units; unit counts that are no multiple of 32 or of 4 (no 16-byte
+# accesses), a feature width below one block, row counts around a block, the backward at D = 768
+@pytest.mark.parametrize("name,N,mil_hidden,dtype", [("probe", 5, 4, 0), ("tiny", 31, 33, 0), ("tiny", 33, 36, 1),
+                                                     ("small", 64, 128, 1), ("full", 300, 256, 0), ("full", 513, 128, 1)])
+def test_pool_f32_blocks(name, N, mil_hidden, dtype):
+    _pool_case(name, N, dtype, mil_hidden=mil_hidden)
