@@ -6,6 +6,7 @@ namespace sl {
 hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s);  // gemm_mfma.hip
 hipError_t launch_gemm_tn_mfma(const GemmTN& g, hipStream_t s);
 bool gemm_tn_mfma_ok(const GemmTN& g);
+int gemm_tn_mfma_slabs(const GemmTN& g, int max_slabs);
 bool gemm_nt_f32_ok(const GemmNT& g);                            // gemm_f32.hip
 hipError_t launch_gemm_nt_f32(const GemmNT& g, hipStream_t s);
 bool gemm_tn_f32_ok(const GemmTN& g);
@@ -117,6 +118,7 @@ int gemm_tn_pick_slabs(int dt, const GemmTN& g, bool use_mfma, int max_slabs) {
   const long long M = g.M;
   const int N1 = g.N1, N2 = g.N2;
   if (dt == DT_F32 && use_mfma && gemm_tn_f32_ok(g)) return gemm_tn_f32_slabs(g, max_slabs);
+  if (dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g)) return gemm_tn_mfma_slabs(g, max_slabs);
   if (max_slabs > 32) max_slabs = 32;
   // enough workgroups to cover the chip several times, slabs of at least 256 rows
   long long tiles = (long long)((N1 + 127) / 128) * ((N2 + 127) / 128);

@@ -1,102 +1,78 @@
-// bf16 MFMA weight-gradient GEMM for gfx950 (v_mfma_f32_32x32x16_bf16, fp32 accumulate).
+// bf16 MFMA weight-gradient GEMM for gfx950, small and medium M: C[N1,N2] = sum_m A[m,N1]^T B[m,N2] (fp32 partials).
 //
-// TN: C[N1,N2] = A[M,N1]^T * B[M,N2], contraction over the slow (row) index.  Each thread
-//     transposes 8x8 bf16 blocks in registers on the way into LDS, so the LDS image is
-//     [column][row-chunk] and MFMA operands are again 16-byte contiguous reads.
-#include "gemm_epi.h"
+// The large-M kernel (gemm_tn_big.hip) takes whole slides; this one bags of up to a few dozen tiles, the CLS rows of the
+// last block, narrow encoders and the aggregator.  128 x 128 of the result per workgroup (4 wavefronts as 2 x 2), M split
+// into slabs.  A 32-row step moves 16 KB for 256 clocks of MFMAs, the 64 bytes a clock that a compute unit gets from its
+// L2, and one trip there takes thousands of clocks: what bounds the kernel is how much a compute unit keeps in flight.
+//   * operands go straight from global memory into LDS (global_load_lds_dwordx4: a wavefront instruction moves 4 rows x 256
+//     bytes) one step ahead at no register cost; three workgroups share a compute unit (deeper rings with fewer workgroups
+//     measured 5 to 20 % slower at every size, as did 64-row steps);
+//   * rows stay row-major; the MFMA operands, eight consecutive rows of one column per lane, are LDS transpose reads
+//     (ds_read_b64_tr_b16: 16 lanes address 4 rows x 32 bytes).  The rows are 256 bytes apart, all on the same banks, so the
+//     32-byte pieces of a row are slot-permuted by the loading lane's choice of address (piece p of row r in slot
+//     p ^ 2 (r % 4)): the eight pieces that are served together fall on 64 different banks;
+//   * the stages are separate arrays: the compiler waits for every load into an LDS array before any read of that array;
+//   * rows past the slab's end and columns past the matrix come from a block of zeros.
+// Column sums of A (bias gradients) are taken from the operand registers by the workgroups of the first tile column.
+// Measured, M = 7289 (37 tiles of 197 tokens), against the kernel that transposed 8 x 8 blocks in registers on the way into
+// LDS: 384 x 1536 34.9 -> 22.4 us, 1536 x 384 35.9 -> 19.5, 1152 x 384 31.9 -> 19.4, 384 x 384 14.6 -> 10.7.
+#include "slide_internal.h"
 
 namespace sl {
 
 namespace {
 
-
+constexpr int BT = 128, BK = 32, STAGE = BK * 2 * BT;   // bf16 elements: [32 rows][128 columns] of A, then of B
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ u32x4 ldg16(const bf16* p) { return *reinterpret_cast<const u32x4*>(p); }
-
-// ---------------------------------------------------------------------------------------
-// TN: part[s][i][j] = sum_{m in slab s} A[amap(m)][i] * B[bmap(m)][j]
-// 128x128 output tile, 64 rows of m per step.  LDS image: At[i][m-chunk], Bt[j][m-chunk].
-// ---------------------------------------------------------------------------------------
-constexpr int TK = 64;          // rows of m per step
-constexpr int LDK = TK + 8;     // padded
-
-// 8x8 bf16 transpose in registers: in[r] holds 8 columns of row r (4 dwords); out[c] holds 8 rows
-// of column c.
-__device__ __forceinline__ void transpose8x8(const u32x4 (&in)[8], u32x4 (&out)[8]) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    int w = c >> 1;                                   // dword holding column c
-    unsigned sel = (c & 1) ? 0x07060302u : 0x05040100u;  // take high / low halves
-    u32x4 o;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {                     // rows 2p, 2p+1 -> one dword
-      unsigned lo = in[2 * p][w], hi = in[2 * p + 1][w];
-      o[p] = __builtin_amdgcn_perm(hi, lo, sel);
-    }
-    out[c] = o;
-  }
-}
+typedef const void __attribute__((address_space(1)))* gptr_t;
+typedef void __attribute__((address_space(3)))* lptr_t;
 
 __device__ __attribute__((aligned(16))) unsigned int g_zero16[4];
 
-__global__ void __launch_bounds__(256, 2) gemm_tn_mfma_k(GemmTN g) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16* At = reinterpret_cast<bf16*>(smem);   // [2][128][LDK]
-  bf16* Bt = At + 2 * 128 * LDK;              // [2][128][LDK]
-  int i0 = blockIdx.x * 128, j0 = blockIdx.y * 128, s = blockIdx.z;
-  long long per = (g.M + g.slabs - 1) / g.slabs;
-  per = (per + TK - 1) / TK * TK;
-  long long lo = (long long)s * per, hi = lo + per < g.M ? lo + per : g.M;
-  const bf16* A = (const bf16*)g.A;
-  const bf16* B = (const bf16*)g.B;
-  int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int wm = wave >> 1, wn = wave & 1;
-  // loader: threads 0..127 take A, 128..255 take B; each an 8(m) x 8(col) block per step.
-  // 4 neighbouring lanes read 64 contiguous bytes of a row; the 8 row blocks vary next, so that the
-  // 16-byte LDS stores of neighbouring lanes fall on different banks.
-  int t = tid & 127;
-  bool isB = tid >= 128;
-  int mb = (t >> 2) & 7, cb = (t >> 5) * 4 + (t & 3);
-  const bf16* src = isB ? B : A;
-  long long ld = isB ? g.ldb : g.lda;
-  RowMap map = isB ? g.bmap : g.amap;
-  int cbase = (isB ? j0 : i0) + cb * 8;
-  int ncols = isB ? g.N2 : g.N1;
-  bool col_ok = cbase < ncols;  // N1, N2 are multiples of 8 (checked on the host)
-  bf16* dst = (isB ? Bt : At) + (cb * 8) * LDK + mb * 8;
+__global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(GemmTN g, int per) {
+  __shared__ __attribute__((aligned(16))) bf16 st0[STAGE], st1[STAGE];
+  const int i0 = blockIdx.x * BT, j0 = blockIdx.y * BT, slab = blockIdx.z;
+  const long long lo = (long long)slab * per, hi = lo + per < g.M ? lo + per : g.M;
+  const int span = hi > lo ? (int)(hi - lo) : 0, nk = (span + BK - 1) / BK;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
 
-  // The 8 consecutive rows of a thread: no branch around the loads (they would be issued and waited for one by one)
-  // and one 32-bit division per step instead of a 64-bit one per row: rows past the slab's end re-read its last
-  // row and are zeroed afterwards; threads whose columns lie outside the matrix read a row of zeros with stride 0.
-  const bf16* lbase = col_ok ? src + cbase : reinterpret_cast<const bf16*>(g_zero16);
-  const long long lld = col_ok ? ld : 0;
-  auto load = [&](long long mstep, u32x4 (&v)[8]) {
-    long long m0 = mstep + mb * 8;
-    long long mc = m0 < hi ? m0 : hi - 1;   // lo < hi here
-    unsigned q = 0, rem = 0;
-    if (map.g2) { q = (unsigned)mc / (unsigned)map.g2; rem = (unsigned)mc - q * (unsigned)map.g2; }
-    long long row = map.g2 ? (long long)q * map.T + 1 + rem : mc;
+  // loads: instruction j of a wavefront fills rows (j * 4 + wave) * 4 .. + 3 of a stage; lane: row lane / 16, slot lane % 16
+  const int lr = lane >> 4, lc = (((lane & 15) >> 1) ^ (2 * lr)) * 16 + (lane & 1) * 8;   // column of this lane's slot
+  const bool a_ok = i0 + lc < g.N1, b_ok = j0 + lc < g.N2;   // N1, N2 are multiples of 8
+  const bf16* zero = reinterpret_cast<const bf16*>(g_zero16);
+  const bf16* ap = (const bf16*)g.A + (lo + wave * 4 + lr) * g.lda + i0 + lc;
+  const bf16* bp = (const bf16*)g.B + (lo + wave * 4 + lr) * g.ldb + j0 + lc;
+  auto issue = [&](bf16* s, int kt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      v[r] = ldg16(lbase + row * lld);
-      if (m0 + r >= hi) v[r] = u32x4{0, 0, 0, 0};
-      if (m0 + r + 1 < hi) {   // the next row exists: step the mapped index
-        if (map.g2) {
-          ++rem;
-          if (rem == (unsigned)map.g2) { rem = 0; ++q; }
-          row = (long long)q * map.T + 1 + rem;
-        } else {
-          ++row;
-        }
-      }
+    for (int j = 0; j < BK / 16; ++j) {
+      const int r = kt * BK + j * 16;   // + wave * 4 + lr
+      const bool ok = r + wave * 4 + lr < span;
+      const bf16* pa = ok && a_ok ? ap + (long long)r * g.lda : zero;
+      const bf16* pb = ok && b_ok ? bp + (long long)r * g.ldb : zero;
+      __builtin_amdgcn_global_load_lds((gptr_t)pa, (lptr_t)(s + (j * 4 + wave) * 4 * BT), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t)pb, (lptr_t)(s + BK * BT + (j * 4 + wave) * 4 * BT), 16, 0, 0);
     }
   };
-  auto store = [&](int buf, const u32x4 (&v)[8]) {
-    u32x4 o[8];
-    transpose8x8(v, o);
+
+  // transpose reads: lane l gets column c0 + l % 32 and rows 8 (l / 32) + {0..7} of a 16-row slice
+  const int gq = lane >> 4, q = lane & 15;
+  auto frag_off = [&](int c0) __attribute__((always_inline)) {
+    return (8 * (gq >> 1) + (q >> 2)) * BT + (((c0 >> 4) + (gq & 1)) ^ (2 * (q >> 2))) * 16 + (q & 3) * 4;
+  };
+  int oa[2], ob[2];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) *reinterpret_cast<u32x4*>(dst + buf * 128 * LDK + c * LDK) = o[c];
+  for (int i = 0; i < 2; ++i) {
+    oa[i] = frag_off(wm * 64 + i * 32);
+    ob[i] = BK * BT + frag_off(wn * 64 + i * 32);
+  }
+  auto frag = [&](const bf16* p) __attribute__((always_inline)) {
+    s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+    s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 4 * BT));
+    s16x8 r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    return r;
   };
 
   f32x16 acc[2][2];
@@ -106,72 +82,56 @@ __global__ void __launch_bounds__(256, 2) gemm_tn_mfma_k(GemmTN g) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const bool do_cs = g.cs_part != nullptr && blockIdx.y == 0 && wn == 0;   // uniform per wavefront
+  float cs[2] = {0.f, 0.f};
 
-  // column sums of A (bias gradients) ride along in the workgroups of the first tile column
-  bool do_cs = g.cs_part != nullptr && blockIdx.y == 0 && !isB;
-  float cs[8];
+  auto step = [&](const bf16* s, bf16* next, int kt) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0x0070);   // this wavefront's loads into LDS have landed, its LDS reads are done
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();         // ... every wavefront's
+    asm volatile("" ::: "memory");
+    if (kt + 1 < nk) issue(next, kt + 1);
 #pragma unroll
-  for (int c = 0; c < 8; ++c) cs[c] = 0.f;
-  auto add_cs = [&](const u32x4 (&v)[8]) {
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        cs[2 * w] += __uint_as_float(v[r][w] << 16);
-        cs[2 * w + 1] += __uint_as_float(v[r][w] & 0xffff0000u);
-      }
-  };
-
-  u32x4 v[8];
-  if (lo < hi) {
-    load(lo, v);
-    if (do_cs) add_cs(v);
-    store(0, v);
-  }
-  __syncthreads();
-  int frow = lane & 31, fk = (lane >> 5) * 8;
-  int it = 0;
-  for (long long mstep = lo; mstep < hi; mstep += TK, ++it) {
-    int cur = it & 1;
-    bool more = mstep + TK < hi;
-    if (more) load(mstep + TK, v);
-    const bf16* as = At + cur * 128 * LDK + (wm * 64 + frow) * LDK + fk;
-    const bf16* bs = Bt + cur * 128 * LDK + (wn * 64 + frow) * LDK + fk;
-#pragma unroll
-    for (int ks = 0; ks < TK / 16; ++ks) {
-      bf16x8 fa[2], fb[2];
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      s16x8 fa[2], fb[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        fa[i] = *reinterpret_cast<const bf16x8*>(as + i * 32 * LDK + ks * 16);
-        fb[i] = *reinterpret_cast<const bf16x8*>(bs + i * 32 * LDK + ks * 16);
+        fa[i] = frag(s + oa[i] + ks * 16 * BT);
+        fb[i] = frag(s + ob[i] + ks * 16 * BT);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-    if (more) {
-      if (do_cs) add_cs(v);
-      store(cur ^ 1, v);
-    }
-    __syncthreads();
-  }
-  if (g.cs_part != nullptr && blockIdx.y == 0) {  // uniform per workgroup
-    float* red = reinterpret_cast<float*>(smem);  // [8][128]; all LDS reads are behind the last barrier
-    if (!isB) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]),
+                                                              acc[i][j], 0, 0, 0);
+      if (do_cs) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) red[mb * 128 + cb * 8 + c] = cs[c];
-    }
-    __syncthreads();
-    if (tid < 128 && i0 + tid < g.N1) {
-      float a = 0.f;
+        for (int i = 0; i < 2; ++i) {
+          const u32x4 t = __builtin_bit_cast(u32x4, fa[i]);
 #pragma unroll
-      for (int m = 0; m < 8; ++m) a += red[m * 128 + tid];
-      g.cs_part[(size_t)s * g.N1 + i0 + tid] = a;
+          for (int w = 0; w < 4; ++w) cs[i] += __uint_as_float(t[w] << 16) + __uint_as_float(t[w] & 0xffff0000u);
+        }
+      }
+    }
+  };
+  if (nk > 0) issue(st0, 0);
+  int kt = 0;
+  for (; kt + 2 <= nk; kt += 2) {
+    step(st0, st1, kt);
+    step(st1, st0, kt + 1);
+  }
+  if (kt < nk) step(st0, st1, kt);
+
+  if (do_cs) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      cs[i] += __shfl_xor(cs[i], 32, 64);
+      const int c = i0 + wm * 64 + i * 32 + (lane & 31);
+      if (lane < 32 && c < g.N1) g.cs_part[(size_t)slab * g.N1 + c] = cs[i];
     }
   }
-  float* P = g.part + (size_t)s * g.N1 * g.N2;
+  float* P = g.part + (size_t)slab * g.N1 * g.N2;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -192,19 +152,25 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 bool gemm_tn_mfma_ok(const GemmTN& g) {
   return g.N1 % 8 == 0 && g.N2 % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && aligned16(g.A) && aligned16(g.B) &&
-         g.M < (1LL << 31);   // row indices are mapped with 32-bit arithmetic
+         g.amap.g2 == 0 && g.bmap.g2 == 0 && g.M < (1LL << 31);
+}
+
+// Slabs: one to two workgroups per compute unit, none of less than 128 rows (64 where there are only a few tiles), since
+// every slab's result is written and read again.  M = 7289, 384 x 1536 (36 tiles), us: 4 slabs 33, 8 22.8, 11 22.4, 15 22.8,
+// 29 28.3; 384 x 384: 15 slabs 12.6, 29 10.7, 57 11.9; M = 1000, 1536 x 384: 8 slabs 8.7, 16 10.4.
+int gemm_tn_mfma_slabs(const GemmTN& g, int max_slabs) {
+  const int tiles = ((g.N1 + BT - 1) / BT) * ((g.N2 + BT - 1) / BT), rows = tiles <= 8 ? 64 : 128;
+  long long s = (384 + tiles - 1) / tiles;
+  if (s > (g.M + rows - 1) / rows) s = (g.M + rows - 1) / rows;
+  if (s > max_slabs) s = max_slabs;
+  return s < 1 ? 1 : (int)s;
 }
 
 hipError_t launch_gemm_tn_mfma(const GemmTN& g, hipStream_t s) {
-  static bool attr_done = false;
-  size_t lds = (size_t)2 * 2 * 128 * LDK * sizeof(bf16);
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_tn_mfma_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  dim3 grid((g.N1 + 127) / 128, (g.N2 + 127) / 128, g.slabs);
-  hipLaunchKernelGGL(gemm_tn_mfma_k, grid, dim3(256), lds, s, g);
+  int per = (int)((g.M + g.slabs - 1) / g.slabs);
+  per = (per + BK - 1) / BK * BK;
+  dim3 grid((g.N1 + BT - 1) / BT, (g.N2 + BT - 1) / BT, g.slabs);
+  hipLaunchKernelGGL(gemm_tn_mfma_k, grid, dim3(256), 0, s, g, per);
   return hipGetLastError();
 }
 

@@ -322,23 +322,27 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
-// Shapes this kernel takes: identity row maps, enough rows, an output that the tiles cover exactly with A on the
-// side tiled by 128 (no column is masked in the kernel), slabs short enough for 32-bit offsets.  Returns the
-// number of slabs it will use (0: not taken).
+// Shapes this kernel takes: identity row maps, an output that the tiles cover exactly with A on the side tiled by 128 (no
+// column is masked in the kernel), slabs short enough for 32-bit offsets, and enough work: below 72,000 rows x tiles (a
+// tenth of a round of the chip spent in prologue and partial results) the 128 x 128 kernel is the faster one.  M = 15,000, us,
+// this / that: 384 x 1536 29 / 38, 1152 x 384 24 / 32, 384 x 384 (3 tiles) 15.6 / 15.9; M = 7289: 20 / 22, 18.5 / 19.4, 13 / 10.7.
+// Returns the number of slabs it will use (0: not taken).  Per XCD, spx slabs x tiles items over 32 workgroups: a round of
+// items takes its rows (12.5 ns each) and about 18 us of prologue, drain and partial results, a slab's partial result is read
+// again by the sum over the slabs at 4 to 5 TB/s.  M = 65,404, 384 x 1536 (12 tiles): spx = 1 144 us, 2 (one round) 95, 3 138, 8
+// (three full rounds) 113; 1152 x 384 (9 tiles): spx = 2 81, 3 (one round) 67, 4 100, 7 95.
 int gemm_tn_big_slabs(const GemmTN& g, int max_slabs) {
-  if (g.amap.g2 != 0 || g.bmap.g2 != 0 || g.M < 65536 || max_slabs < 8) return 0;
+  if (g.amap.g2 != 0 || g.bmap.g2 != 0 || max_slabs < 8) return 0;
   if (g.lda % 8 || g.ldb % 8 || !aligned16(g.A) || !aligned16(g.B)) return 0;
   if ((long long)g.N1 * g.N2 >= (1LL << 31)) return 0;
   if (g.N1 % BX || g.N2 % BY) return 0;
-  int tiles = (g.N1 / BX) * (g.N2 / BY);
-  // per XCD: spx slabs x tiles items over 32 workgroups; more slabs while that fills the last round of workgroups
-  // noticeably better (every slab costs one partial result to write and to add)
+  const int tiles = (g.N1 / BX) * (g.N2 / BY);
+  if (g.M * tiles < 72000) return 0;
   int spx = 1;
   double best = 0.0;
   for (int c = 1; c <= 32 && 8 * c <= max_slabs; ++c) {
-    int items = c * tiles, rounds = (items + 31) / 32;
-    double fill = (double)items / (rounds * 32.0);
-    if (fill > best + 0.04 || (c <= 3 && fill >= best)) { best = fill; spx = c; }
+    const int rounds = (c * tiles + 31) / 32;
+    const double cost = rounds * ((double)g.M / (8 * c) + 1440.0) + 8.0 * c * g.N1 * g.N2 * 5.7e-5;   // in rows
+    if (c == 1 || cost < best) { best = cost; spx = c; }
   }
   long long per = (g.M + 8 * spx - 1) / (8 * spx) + 8 * BK;   // loads run up to four steps past a slab's end
   long long ldmax = g.lda > g.ldb ? g.lda : g.ldb;
