@@ -4,35 +4,52 @@
 namespace sl {
 
 // ---------------------------------------------------------------------------------------
-// fp32 master weight [R,C] -> T copy [R,C] (optional) and T transpose [C,R] (optional)
+// fp32 master weights [R,C] -> T copies [R,C] (bf16 path) and T transposes [C,R], every matrix of the encoder in one
+// launch: a launch per matrix is 49 launches of 2 to 5 us for a 12-block encoder, more than the bytes take.
 // ---------------------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(256) cast_transpose_k(const float* __restrict__ src, int R, int C,
-                                                        T* __restrict__ dstW, T* __restrict__ dstWT) {
+__global__ void __launch_bounds__(256) cast_transpose_k(CastTable t, const float* __restrict__ params, char* __restrict__ shadow) {
   __shared__ float tile[32][33];
-  int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+  int b = blockIdx.x, i = 0;
+  long long l = 0;
+  if (b >= t.blocks0) {   // matrices 1 .. 4 repeat per layer
+    b -= t.blocks0;
+    l = b / t.blocks_layer;
+    b -= (int)l * t.blocks_layer;
+    i = 1;
+    while (i < 4 && b >= t.m[i].blocks) { b -= t.m[i].blocks; ++i; }
+  }
+  const CastTable::Mat m = t.m[i];
+  const float* src = params + m.poff + l * t.stride_p;
+  T* dstW = sizeof(T) == 4 ? nullptr : (T*)(shadow + m.w + l * t.stride_s);
+  T* dstWT = (T*)(shadow + m.wt + l * t.stride_s);
+  const int tc = (m.C + 31) / 32, c0 = b % tc * 32, r0 = b / tc * 32;
   int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+#pragma unroll
   for (int i = ty; i < 32; i += 8) {
     int r = r0 + i, c = c0 + tx;
-    float v = (r < R && c < C) ? src[(size_t)r * C + c] : 0.f;
+    float v = (r < m.R && c < m.C) ? src[(size_t)r * m.C + c] : 0.f;
     tile[i][tx] = v;
-    if (dstW && r < R && c < C) dstW[(size_t)r * C + c] = from_f<T>(v);
+    if (sizeof(T) == 2 && r < m.R && c < m.C) dstW[(size_t)r * m.C + c] = from_f<T>(v);
   }
   __syncthreads();
-  if (dstWT) {
-    for (int i = ty; i < 32; i += 8) {
-      int c = c0 + i, r = r0 + tx;
-      if (r < R && c < C) dstWT[(size_t)c * R + r] = from_f<T>(tile[tx][i]);
-    }
+#pragma unroll
+  for (int i = ty; i < 32; i += 8) {
+    int c = c0 + i, r = r0 + tx;
+    if (r < m.R && c < m.C) dstWT[(size_t)c * m.R + r] = from_f<T>(tile[tx][i]);
   }
 }
 
-hipError_t launch_cast_transpose(int dt, const float* src, int R, int C, void* dstW, void* dstWT, hipStream_t s) {
-  dim3 grid((C + 31) / 32, (R + 31) / 32);
-  if (dt == DT_F32)
-    hipLaunchKernelGGL(cast_transpose_k<float>, grid, dim3(256), 0, s, src, R, C, (float*)dstW, (float*)dstWT);
-  else
-    hipLaunchKernelGGL(cast_transpose_k<bf16>, grid, dim3(256), 0, s, src, R, C, (bf16*)dstW, (bf16*)dstWT);
+hipError_t launch_cast_transpose(int dt, CastTable t, int layers, const float* params, char* shadow, hipStream_t s) {
+  t.blocks_layer = 0;
+  for (int i = 0; i < 5; ++i) {
+    t.m[i].blocks = ((t.m[i].C + 31) / 32) * ((t.m[i].R + 31) / 32);
+    if (i) t.blocks_layer += t.m[i].blocks;
+  }
+  t.blocks0 = t.m[0].blocks;
+  const dim3 grid((unsigned)(t.blocks0 + (long long)layers * t.blocks_layer));
+  if (dt == DT_F32) hipLaunchKernelGGL(cast_transpose_k<float>, grid, dim3(256), 0, s, t, params, shadow);
+  else hipLaunchKernelGGL(cast_transpose_k<bf16>, grid, dim3(256), 0, s, t, params, shadow);
   return hipGetLastError();
 }
 
@@ -307,94 +324,103 @@ int colsum_slabs(long long M) {
   return (int)s;
 }
 
-// 64 outputs per workgroup; the slabs are dealt to 4 quarter-groups whose sums are then added
-// in a fixed order, so the result does not depend on scheduling.
-__global__ void __launch_bounds__(256) reduce_partials_k(const float* __restrict__ part, int slabs, long long stride,
-                                                         long long len, float* __restrict__ out, int accumulate) {
-  __shared__ float red[4][64];
-  int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
-  long long i = (long long)blockIdx.x * 64 + cl;
-  float acc = 0.f;
-  if (i < len)
-    for (int s = q; s < slabs; s += 4) acc += part[(size_t)s * stride + i];
-  red[q][cl] = acc;
-  __syncthreads();
-  if (q == 0 && i < len) {
-    float v = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
-    out[i] = accumulate ? out[i] + v : v;
-  }
-}
-
-// The same sums in the same order, four neighbouring outputs per thread (16-byte accesses): 256 outputs per workgroup.
-__global__ void __launch_bounds__(256) reduce_partials4_k(const float* __restrict__ part, int slabs, long long stride,
-                                                          long long len, float* __restrict__ out, int accumulate) {
-  __shared__ float4 red[4][64];
-  int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
-  long long i = ((long long)blockIdx.x * 64 + cl) * 4;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (i < len)
-    for (int s = q; s < slabs; s += 4) {
-      float4 v = *reinterpret_cast<const float4*>(part + (size_t)s * stride + i);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+// Sums over slab partials, any number of results in one launch (a launch per weight, bias, gain and shift gradient is nine
+// per block of the encoder, most of them shorter than a launch).  The additions of a result have a fixed order that does not
+// depend on scheduling.  A result's kind says how its outputs and slabs are dealt to a workgroup:
+//   RED_4   256 outputs, four neighbours per thread (16-byte accesses), slabs dealt to 4 quarter groups
+//   RED_1   64 outputs, otherwise the same
+//   RED_16  16 outputs, slabs dealt to 16 groups of lanes (short results of up to a thousand slabs), the 16 group sums added
+//           as a binary tree
+__global__ void __launch_bounds__(256) reduce_partials_k(RedList L) {
+  __shared__ float4 red4[4][64];
+  int i = 0;
+  while (i + 1 < L.n && (int)blockIdx.x >= L.seg[i + 1].block0) ++i;
+  const RedSeg sg = L.seg[i];
+  const float* __restrict__ part = sg.part;
+  const long long b = blockIdx.x - sg.block0;
+  if (sg.kind == RED_4) {
+    const int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const long long o = (b * 64 + cl) * 4;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (o < sg.len) {
+#pragma unroll 4
+      for (int s = q; s < sg.slabs; s += 4) {
+        float4 v = *reinterpret_cast<const float4*>(part + (size_t)s * sg.stride + o);
+        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+      }
     }
-  red[q][cl] = acc;
-  __syncthreads();
-  if (q == 0 && i < len) {
-    float4 a = red[0][cl], b = red[1][cl], c = red[2][cl], d = red[3][cl];
-    float4 v = make_float4((a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y), (a.z + b.z) + (c.z + d.z),
-                           (a.w + b.w) + (c.w + d.w));
-    float4* o = reinterpret_cast<float4*>(out + i);
-    if (accumulate) { float4 w = *o; v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w; }
-    *o = v;
-  }
-}
-
-// Short results (bias, gain and shift gradients: a few hundred outputs, up to a thousand slabs): 16 outputs per
-// workgroup and the slabs dealt to 16 groups of lanes, so that a launch has four times the workgroups and a quarter of
-// the loads per thread of the kernel above; the 16 group sums are added as a fixed binary tree.
-__global__ void __launch_bounds__(256) reduce_partials16_k(const float* __restrict__ part, int slabs, long long stride,
-                                                           long long len, float* __restrict__ out, int accumulate) {
-  __shared__ float red[16][17];
-  const int cl = threadIdx.x & 15, q = threadIdx.x >> 4;
-  const long long i = (long long)blockIdx.x * 16 + cl;
-  float a0 = 0.f, a1 = 0.f;
-  if (i < len) {
-    int s = q;
-    for (; s + 16 < slabs; s += 32) {
-      a0 += part[(size_t)s * stride + i];
-      a1 += part[(size_t)(s + 16) * stride + i];
+    red4[q][cl] = acc;
+    __syncthreads();
+    if (q == 0 && o < sg.len) {
+      float4 x = red4[0][cl], y = red4[1][cl], z = red4[2][cl], w = red4[3][cl];
+      float4 v = make_float4((x.x + y.x) + (z.x + w.x), (x.y + y.y) + (z.y + w.y), (x.z + y.z) + (z.z + w.z),
+                             (x.w + y.w) + (z.w + w.w));
+      float4* out = reinterpret_cast<float4*>(sg.out + o);
+      if (sg.accumulate) { float4 t = *out; v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; }
+      *out = v;
     }
-    if (s < slabs) a0 += part[(size_t)s * stride + i];
-  }
-  red[q][cl] = a0 + a1;
-  __syncthreads();
-  if (q == 0 && i < len) {
-    float t[16];
+  } else if (sg.kind == RED_1) {
+    float (*red)[64] = reinterpret_cast<float (*)[64]>(red4);
+    const int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const long long o = b * 64 + cl;
+    float acc = 0.f;
+    if (o < sg.len) {
+#pragma unroll 4
+      for (int s = q; s < sg.slabs; s += 4) acc += part[(size_t)s * sg.stride + o];
+    }
+    red[q][cl] = acc;
+    __syncthreads();
+    if (q == 0 && o < sg.len) {
+      float v = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
+      sg.out[o] = sg.accumulate ? sg.out[o] + v : v;
+    }
+  } else {
+    float (*red)[17] = reinterpret_cast<float (*)[17]>(red4);
+    const int cl = threadIdx.x & 15, q = threadIdx.x >> 4;
+    const long long o = b * 16 + cl;
+    float a0 = 0.f, a1 = 0.f;
+    if (o < sg.len) {
+      int s = q;
+#pragma unroll 4
+      for (; s + 16 < sg.slabs; s += 32) {
+        a0 += part[(size_t)s * sg.stride + o];
+        a1 += part[(size_t)(s + 16) * sg.stride + o];
+      }
+      if (s < sg.slabs) a0 += part[(size_t)s * sg.stride + o];
+    }
+    red[q][cl] = a0 + a1;
+    __syncthreads();
+    if (q == 0 && o < sg.len) {
+      float t[16];
 #pragma unroll
-    for (int g = 0; g < 16; ++g) t[g] = red[g][cl];
+      for (int g = 0; g < 16; ++g) t[g] = red[g][cl];
 #pragma unroll
-    for (int w = 8; w > 0; w >>= 1)
+      for (int w = 8; w > 0; w >>= 1)
 #pragma unroll
-      for (int g = 0; g < w; ++g) t[g] += t[g + w];
-    out[i] = accumulate ? out[i] + t[0] : t[0];
+        for (int g = 0; g < w; ++g) t[g] += t[g + w];
+      sg.out[o] = sg.accumulate ? sg.out[o] + t[0] : t[0];
+    }
   }
 }
 
-hipError_t launch_reduce_partials(const float* part, int slabs, long long stride, long long len, float* out,
-                                  int accumulate, hipStream_t s) {
-  if (len <= 0) return hipSuccess;
-  if (len < 4096 && slabs >= 64) {
-    hipLaunchKernelGGL(reduce_partials16_k, dim3((unsigned)((len + 15) / 16)), dim3(256), 0, s, part, slabs, stride, len, out,
-                       accumulate);
-    return hipGetLastError();
-  }
-  if (len >= 4096 && len % 4 == 0 && stride % 4 == 0 && ((uintptr_t)part & 15) == 0 && ((uintptr_t)out & 15) == 0) {
-    hipLaunchKernelGGL(reduce_partials4_k, dim3((unsigned)((len / 4 + 63) / 64)), dim3(256), 0, s, part, slabs, stride,
-                       len, out, accumulate);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(reduce_partials_k, dim3((unsigned)((len + 63) / 64)), dim3(256), 0, s, part, slabs, stride, len,
-                     out, accumulate);
+bool red_add(RedList& L, const float* part, int slabs, long long stride, long long len, float* out, int accumulate) {
+  if (len <= 0) return true;
+  if (L.n >= RED_MAX) return false;
+  RedSeg& g = L.seg[L.n];
+  g.part = part; g.out = out; g.stride = stride; g.len = (int)len; g.slabs = slabs; g.accumulate = (short)accumulate;
+  if (len < 4096 && slabs >= 64) g.kind = RED_16;
+  else if (len >= 4096 && len % 4 == 0 && stride % 4 == 0 && ((uintptr_t)part & 15) == 0 && ((uintptr_t)out & 15) == 0) g.kind = RED_4;
+  else g.kind = RED_1;
+  g.block0 = L.blocks;
+  const int per = g.kind == RED_16 ? 16 : g.kind == RED_4 ? 256 : 64;
+  L.blocks += (int)((len + per - 1) / per);
+  ++L.n;
+  return true;
+}
+
+hipError_t launch_reduce_partials(const RedList& L, hipStream_t s) {
+  if (L.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(reduce_partials_k, dim3((unsigned)L.blocks), dim3(256), 0, s, L);
   return hipGetLastError();
 }
 

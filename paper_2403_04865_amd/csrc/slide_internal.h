@@ -171,7 +171,14 @@ hipError_t launch_gemm_tn(int dt, const GemmTN& g, bool use_mfma, hipStream_t s)
 int gemm_tn_pick_slabs(int dt, const GemmTN& g, bool use_mfma, int max_slabs);
 bool gemm_tn_fuses_colsum(int dt, const GemmTN& g, bool use_mfma);  // will launch_gemm_tn fill cs_part?
 
-hipError_t launch_cast_transpose(int dt, const float* src, int R, int C, void* dstW, void* dstWT, hipStream_t s);
+// weight matrices of the encoder: 0 = patch embedding, 1 .. 4 = those of block 0, whose parameters and copies repeat at a
+// fixed stride (poff, stride_p in floats of the parameter vector; w, wt, stride_s in bytes of the shadow region)
+struct CastTable {
+  struct Mat { size_t poff, w, wt; int R, C, blocks; } m[5];
+  long long stride_p, stride_s;
+  int blocks0, blocks_layer;
+};
+hipError_t launch_cast_transpose(int dt, CastTable t, int layers, const float* params, char* shadow, hipStream_t s);
 // patches: [n * (g*g + lead)][3 P P], every tile's g*g patch rows behind `lead` rows of zeros
 hipError_t launch_patchify(int dt, const void* pixels, void* patches, long long n, int S, int P, hipStream_t s, int lead);
 // the inverse, from the same row layout (the `lead` rows of a tile are skipped)
@@ -186,9 +193,13 @@ hipError_t launch_gelu(int dt, const void* m, void* a, long long count, hipStrea
 int colsum_slabs(long long M);
 hipError_t launch_colsum_part(int elem, const void* A, long long lda, RowMap map, long long M, int N, float* part,
                               int slabs, hipStream_t s);
-// out[i] = (accumulate ? out[i] : 0) + sum_s part[s*stride + i], i < len
-hipError_t launch_reduce_partials(const float* part, int slabs, long long stride, long long len, float* out,
-                                  int accumulate, hipStream_t s);
+// out[i] = (accumulate ? out[i] : 0) + sum_s part[s*stride + i], i < len, for a list of results in one launch
+enum { RED_1 = 0, RED_4 = 1, RED_16 = 2 };
+struct RedSeg { const float* part; float* out; long long stride; int len, slabs, block0; short kind, accumulate; };
+constexpr int RED_MAX = 64;
+struct RedList { int n = 0, blocks = 0; RedSeg seg[RED_MAX]; };
+bool red_add(RedList& L, const float* part, int slabs, long long stride, long long len, float* out, int accumulate);   // false: full
+hipError_t launch_reduce_partials(const RedList& L, hipStream_t s);
 
 // LayerNorm.  x rows at x + r*x_stride (RS), out rows at out + r*out_stride (T, or fp32 when out_f32).
 hipError_t launch_ln_fwd(int dt, const void* x, long long x_stride, const float* gam, const float* bet, void* out,

@@ -61,7 +61,7 @@ struct Layout {
   // pool
   size_t p_a, p_part, p_scal, p_Dp, p_tn, p_cs, p_vub, p_H, p_G, pool_end;
   // shared reduction work space
-  size_t w_wpart, w_cpart, w_lnpart;
+  size_t w_part, part_floats;
   // encoder
   size_t enc_begin;
   size_t e_patches, e_x, e_qkv, e_O, e_lse, e_xmid, e_m;              // first instance
@@ -157,9 +157,9 @@ Layout make_layout(const slide_ctx* c, long long n, long long pool_N, int keep) 
   size_t M = (size_t)nn * c->T;
   size_t maxcols = (size_t)(c->F > 3 * D ? c->F : 3 * D);
   size_t tokcols = (size_t)c->T * D;
-  y.w_wpart = take((size_t)64 * c->max_w * 4);
-  y.w_cpart = take((size_t)128 * (maxcols > tokcols ? maxcols : tokcols) * 4);
-  y.w_lnpart = take((size_t)1024 * 2 * D * 4);
+  // slab partials: 64 of the largest weight gradient, 128 of the longest column sum, 1024 of a gain and shift gradient
+  y.part_floats = (size_t)64 * c->max_w + (size_t)128 * (maxcols > tokcols ? maxcols : tokcols) + (size_t)1024 * 2 * D;
+  y.w_part = take(y.part_floats * 4);
   y.enc_begin = cur;
   y.s_xc = align256((size_t)nn * D * 4);
   y.l_xc = take(0); cur += (size_t)(c->L + 1) * y.s_xc;
@@ -223,14 +223,49 @@ const void* weight_t(const slide_ctx* c, int idx) { return c->arena + c->sh[idx]
 
 void cast_weights(Run& r) {
   slide_ctx* c = r.c;
-  for (size_t i = 0; i < c->sh.size(); ++i) {
+  CastTable t{};
+  double elems = 0;
+  for (int i = 0; i < 5 && i < (int)c->sh.size(); ++i) {
     const ShadowMat& m = c->sh[i];
-    void* w = c->dt == DT_BF16 ? (void*)(c->arena + m.w) : nullptr;
-    void* wt = c->arena + m.wt;
-    launch(r, K_ELEMWISE, 0, (double)m.R * m.C * (4 + 2 * elem_size(c->dt)),
-           [&] { return launch_cast_transpose(c->dt, c->params + m.poff, m.R, m.C, w, wt, r.s); });
+    t.m[i] = {m.poff, m.w, m.wt, m.R, m.C, 0};
+    elems += (double)m.R * m.C * (i ? c->L : 1);
   }
+  if (c->L > 1) {
+    t.stride_p = (long long)(c->sh[5].poff - c->sh[1].poff);
+    t.stride_s = (long long)(c->sh[5].wt - c->sh[1].wt);
+  }
+  launch(r, K_ELEMWISE, 0, elems * (4 + (c->dt == DT_BF16 ? 4 : 4)),
+         [&] { return launch_cast_transpose(c->dt, t, c->L, c->params, c->arena, r.s); });
 }
+
+// Slab partials that wait for their sum: kernels write them to room handed out here, the sums of as many results as fit the
+// room and the list run as one launch.  room() may run what waits, so it is called once per kernel, before its launch.
+struct Sums {
+  Run& r;
+  float* base;
+  size_t cap, used = 0;   // floats
+  double bytes = 0;
+  RedList list;
+  Sums(Run& run, float* b, size_t n) : r(run), base(b), cap(n) {}
+  float* room(size_t floats) {
+    floats = (floats + 63) & ~(size_t)63;
+    if (used + floats > cap || list.n + 6 > RED_MAX) flush();
+    if (floats > cap) { if (r.ok()) r.err = hipErrorInvalidValue; floats = 0; }
+    float* p = base + used;
+    used += floats;
+    return p;
+  }
+  void add(const float* part, int slabs, long long stride, long long len, float* out, int accumulate) {
+    bytes += (double)(slabs + 1) * len * 4;
+    if (!red_add(list, part, slabs, stride, len, out, accumulate) && r.ok()) r.err = hipErrorInvalidValue;
+  }
+  void flush() {
+    if (list.n) launch(r, K_ELEMWISE, 0, bytes, [&] { return launch_reduce_partials(list, r.s); });
+    list.n = list.blocks = 0;
+    used = 0;
+    bytes = 0;
+  }
+};
 
 void gemm_nt(Run& r, const GemmNT& g) {
   size_t e = elem_size(r.c->dt);
@@ -242,61 +277,53 @@ void gemm_nt(Run& r, const GemmNT& g) {
   launch(r, K_GEMM_NT, 2.0 * g.M * g.N * g.K, bytes, [&] { return launch_gemm_nt(r.c->dt, g, r.c->use_mfma, r.s); });
 }
 
-void colsum(Run& r, int elem, const void* A, long long lda, RowMap map, long long M, int N, float* part, float* out,
-            int accumulate);
+void colsum(Sums& q, int elem, const void* A, long long lda, RowMap map, long long M, int N, float* out, int accumulate) {
+  Run& r = q.r;
+  int slabs = colsum_slabs(M);
+  float* part = q.room((size_t)slabs * N);
+  launch(r, K_COLSUM, 0, (double)M * N * elem_size(elem),
+         [&] { return launch_colsum_part(elem, A, lda, map, M, N, part, slabs, r.s); });
+  q.add(part, slabs, N, N, out, accumulate);
+}
 
 // dW (+)= A^T B through split partials; optionally also db (+)= column sums of A
-void gemm_tn(Run& r, const void* A, long long lda, RowMap amap, const void* B, long long ldb, RowMap bmap, long long M,
-             int N1, int N2, float* part, size_t part_floats, float* out, int accumulate, int dt_override = -1,
-             float* bias_out = nullptr, float* cpart = nullptr, float* out2 = nullptr, float* bias_out2 = nullptr) {
-  // part: room for part_floats floats of slab partials (at least 64 results).
+void gemm_tn(Sums& q, const void* A, long long lda, const void* B, long long ldb, long long M, int N1, int N2, float* out,
+             int accumulate, float* bias_out = nullptr, int dt_override = -1, float* out2 = nullptr, float* bias_out2 = nullptr) {
   // out2 / bias_out2: the result rows N1/2 .. N1-1 (and their column sums) belong to a second tensor
+  Run& r = q.r;
   GemmTN g;
   int dt = dt_override >= 0 ? dt_override : r.c->dt;
-  g.A = A; g.lda = lda; g.amap = amap; g.B = B; g.ldb = ldb; g.bmap = bmap; g.M = M; g.N1 = N1; g.N2 = N2;
-  g.part = part;
+  const RowMap id{0, 0};
+  g.A = A; g.lda = lda; g.amap = id; g.B = B; g.ldb = ldb; g.bmap = id; g.M = M; g.N1 = N1; g.N2 = N2;
   g.cs_part = nullptr;
   g.big = 0;
-  size_t fit = part_floats / ((size_t)N1 * N2);
+  size_t fit = (q.cap - 64) / ((size_t)N1 * N2 + N1);
   int bs = (dt == DT_BF16 && r.c->use_mfma) ? gemm_tn_big_slabs(g, fit > 256 ? 256 : (int)fit) : 0;
   if (bs) { g.slabs = bs; g.big = 1; }
   else g.slabs = gemm_tn_pick_slabs(dt, g, r.c->use_mfma, fit > 64 ? 64 : (int)fit);
   bool fused = bias_out && gemm_tn_fuses_colsum(dt, g, r.c->use_mfma);
-  if (fused) g.cs_part = cpart;
   if (bias_out && !fused) {
     if (bias_out2) {
-      colsum(r, dt, A, lda, amap, M, N1 / 2, cpart, bias_out, accumulate);
-      colsum(r, dt, (const char*)A + (size_t)(N1 / 2) * elem_size(dt), lda, amap, M, N1 / 2, cpart, bias_out2, accumulate);
+      colsum(q, dt, A, lda, id, M, N1 / 2, bias_out, accumulate);
+      colsum(q, dt, (const char*)A + (size_t)(N1 / 2) * elem_size(dt), lda, id, M, N1 / 2, bias_out2, accumulate);
     } else {
-      colsum(r, dt, A, lda, amap, M, N1, cpart, bias_out, accumulate);
+      colsum(q, dt, A, lda, id, M, N1, bias_out, accumulate);
     }
   }
+  const long long len = (long long)N1 * N2, len1 = out2 ? len / 2 : len;
+  float* part = q.room((size_t)g.slabs * (len + (fused ? N1 : 0)));
+  g.part = part;
+  if (fused) g.cs_part = part + (size_t)g.slabs * len;
   size_t e = elem_size(dt);
   launch(r, K_GEMM_TN, 2.0 * M * N1 * N2, (double)M * (N1 + N2) * e + (double)g.slabs * N1 * N2 * 4,
          [&] { return launch_gemm_tn(dt, g, r.c->use_mfma, r.s); });
-  const long long len = (long long)N1 * N2, len1 = out2 ? len / 2 : len;
-  launch(r, K_ELEMWISE, 0, (double)(g.slabs + 1) * len1 * 4,
-         [&] { return launch_reduce_partials(part, g.slabs, len, len1, out, accumulate, r.s); });
-  if (out2)
-    launch(r, K_ELEMWISE, 0, (double)(g.slabs + 1) * len1 * 4,
-           [&] { return launch_reduce_partials(part + len1, g.slabs, len, len1, out2, accumulate, r.s); });
+  q.add(part, g.slabs, len, len1, out, accumulate);
+  if (out2) q.add(part + len1, g.slabs, len, len1, out2, accumulate);
   if (fused) {
     const int n1 = bias_out2 ? N1 / 2 : N1;
-    launch(r, K_ELEMWISE, 0, 0,
-           [&] { return launch_reduce_partials(cpart, g.slabs, N1, n1, bias_out, accumulate, r.s); });
-    if (bias_out2)
-      launch(r, K_ELEMWISE, 0, 0,
-             [&] { return launch_reduce_partials(cpart + n1, g.slabs, N1, n1, bias_out2, accumulate, r.s); });
+    q.add(g.cs_part, g.slabs, N1, n1, bias_out, accumulate);
+    if (bias_out2) q.add(g.cs_part + n1, g.slabs, N1, n1, bias_out2, accumulate);
   }
-}
-
-void colsum(Run& r, int elem, const void* A, long long lda, RowMap map, long long M, int N, float* part, float* out,
-            int accumulate) {
-  int slabs = colsum_slabs(M);
-  launch(r, K_COLSUM, 0, (double)M * N * elem_size(elem),
-         [&] { return launch_colsum_part(elem, A, lda, map, M, N, part, slabs, r.s); });
-  launch(r, K_ELEMWISE, 0, (double)slabs * N * 4,
-         [&] { return launch_reduce_partials(part, slabs, N, N, out, accumulate, r.s); });
 }
 
 void ln_fwd(Run& r, const void* x, long long xs, const float* g, const float* b, void* out, long long os, long long rows,
@@ -306,34 +333,25 @@ void ln_fwd(Run& r, const void* x, long long xs, const float* g, const float* b,
          [&] { return launch_ln_fwd(c->dt, x, xs, g, b, out, os, rows, c->D, c->cfg.ln_eps, out_f32, r.s); });
 }
 
-// u_out: the forward output of this LayerNorm (needed by the weight gradient of the linear map behind it, not kept by
-// the forward) is produced as well: by the backward kernel itself where it can, else by a forward launch
-void ln_bwd(Run& r, const void* x, long long xs, const void* dy, long long dys, size_t o_gam, size_t o_bet,
-            const void* dres, void* dxo, void* dxo_t, long long os, long long rows, float* part, int accumulate,
-            bool dy_f32 = false, void* u_out = nullptr, int dres_period = 0) {
+void ln_bwd(Sums& q, const void* x, long long xs, const void* dy, long long dys, size_t o_gam, size_t o_bet,
+            const void* dres, void* dxo, void* dxo_t, long long os, long long rows, int accumulate,
+            bool dy_f32 = false, int dres_period = 0) {
+  Run& r = q.r;
   slide_ctx* c = r.c;
   size_t rs = rs_size(c->dt), e = elem_size(c->dt);
-  bool emit = u_out && ln_bwd_emits_u(c->dt, x, xs, dy, dys, c->params + o_gam, dres, dxo, os, c->D, dy_f32,
-                                      c->params + o_bet, u_out, c->D);
-  if (u_out && !emit) ln_fwd(r, x, xs, c->params + o_gam, c->params + o_bet, u_out, c->D, rows);
-  double bytes = (double)rows * c->D * (rs + e + (dres && !dres_period ? rs : 0) + rs + (rs != e ? e : 0) + (emit ? e : 0));
+  double bytes = (double)rows * c->D * (rs + e + (dres && !dres_period ? rs : 0) + rs + (rs != e ? e : 0));
+  int slabs = ln_bwd_slabs(rows);
+  float* part = q.room((size_t)slabs * 2 * c->D);
   launch(r, K_LN_BWD, 0, bytes, [&] {
     return launch_ln_bwd(c->dt, x, xs, dy, dys, c->params + o_gam, dres, dxo, dxo_t, os, rows, c->D, c->cfg.ln_eps, part,
-                         dy_f32, r.s, c->params + o_bet, emit ? u_out : nullptr, c->D, dres_period);
+                         dy_f32, r.s, nullptr, nullptr, 0, dres_period);
   });
-  int slabs = ln_bwd_slabs(rows);
   if (o_bet == o_gam + (size_t)c->D) {   // gain and shift are neighbours in the parameter vector, as in a slab's partials
-    launch(r, K_ELEMWISE, 0, 0, [&] {
-      return launch_reduce_partials(part, slabs, 2LL * c->D, 2LL * c->D, c->grads + o_gam, accumulate, r.s);
-    });
-    return;
+    q.add(part, slabs, 2LL * c->D, 2LL * c->D, c->grads + o_gam, accumulate);
+  } else {
+    q.add(part, slabs, 2LL * c->D, c->D, c->grads + o_gam, accumulate);
+    q.add(part + c->D, slabs, 2LL * c->D, c->D, c->grads + o_bet, accumulate);
   }
-  launch(r, K_ELEMWISE, 0, 0, [&] {
-    return launch_reduce_partials(part, slabs, 2LL * c->D, c->D, c->grads + o_gam, accumulate, r.s);
-  });
-  launch(r, K_ELEMWISE, 0, 0, [&] {
-    return launch_reduce_partials(part + c->D, slabs, 2LL * c->D, c->D, c->grads + o_bet, accumulate, r.s);
-  });
 }
 
 int check_bound(const slide_ctx* c) {
@@ -474,8 +492,9 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay) {
 // ------------------------------------------------------------------------------------------
 // encoder forward
 // ------------------------------------------------------------------------------------------
+// cast: the low-precision and transposed weight copies are made first (false: an earlier pass of the same call has made them)
 int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool save, long long pool_N,
-            hipStream_t s) {
+            hipStream_t s, bool cast = true) {
   if (c->pool_only) return SLIDE_EUNSUPPORTED;
   int keep = !save ? KEEP_NONE : (c->cfg.recompute ? KEEP_INPUTS : KEEP_ALL);
   Layout y = make_layout(c, n, pool_N, keep);
@@ -485,7 +504,7 @@ int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool
   Run r{c, s};
   char* ar = c->arena;
   int D = c->D, T = c->T, dt = c->dt;
-  cast_weights(r);
+  if (cast) cast_weights(r);
   launch(r, K_ELEMWISE, 0, 2.0 * n * 3 * c->cfg.tile * c->cfg.tile * elem_size(dt),
          [&] { return launch_patchify(dt, pixels, ar + y.e_patches, n, c->cfg.tile, c->cfg.patch, s, T - c->g2); });
   // the patch matrix has the token matrix's rows (a row of zeros in each tile's CLS slot): its weight gradient is
@@ -543,10 +562,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
   size_t rs = rs_size(dt), e = elem_size(dt);
   bool dual = rs != e;
   int rs_elem = rs == 4 ? DT_F32 : DT_BF16;
-  float* wpart = (float*)(ar + y.w_wpart);
-  const size_t wcap = (size_t)64 * c->max_w;   // floats of room behind wpart (make_layout)
-  float* cpart = (float*)(ar + y.w_cpart);
-  float* lnpart = (float*)(ar + y.w_lnpart);
+  Sums q(r, (float*)(ar + y.w_part), y.part_floats);
   char *dxA = ar + y.e_dxA, *dxB = ar + y.e_dxB, *dxAt = ar + y.e_dxAt, *dxBt = ar + y.e_dxBt;
   char *du = ar + y.e_du, *dqkv = ar + y.e_dqkv, *dm = ar + y.e_dm;
   RowMap id{0, 0};
@@ -559,7 +575,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
     if (dual) launch(r, K_ELEMWISE, 0, (double)M * D * e, [&] { return launch_fill_zero(dxAt, (size_t)M * D * e, s); });
   }
   char* xL = ar + y.e_x + (size_t)c->L * y.s_x;
-  ln_bwd(r, xL, (long long)T * D, dfeats, D, c->o_lnfg, c->o_lnfb, nullptr, dxA, dxAt, (long long)T * D, n, lnpart,
+  ln_bwd(q, xL, (long long)T * D, dfeats, D, c->o_lnfg, c->o_lnfb, nullptr, dxA, dxAt, (long long)T * D, n,
          accumulate, true);
   for (int l = c->L - 1; l >= 0; --l) {
     const LayerOff& o = c->lo[l];
@@ -591,16 +607,16 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
         g.epi = EPI_DGELU; g.pre = m; g.ldpre = F; g.out = dm; g.ldc = F;
         gemm_nt(r, g);
       }
-      gemm_tn(r, dxAt, TD, id, a, F, id, n, D, F, wpart, wcap, G + o.fc2W, accumulate, -1, G + o.fc2b, cpart);
-      gemm_tn(r, dm, F, id, u2, D, id, n, F, D, wpart, wcap, G + o.fc1W, accumulate, -1, G + o.fc1b, cpart);
+      gemm_tn(q, dxAt, TD, a, F, n, D, F, G + o.fc2W, accumulate, G + o.fc2b);
+      gemm_tn(q, dm, F, u2, D, n, F, D, G + o.fc1W, accumulate, G + o.fc1b);
       {
         GemmNT g{};
         g.A = dm; g.lda = F; g.B = weight_t(c, wi + 2); g.ldb = F; g.M = n; g.N = D; g.K = F;
         g.epi = EPI_PLAIN; g.out = du; g.ldc = D;   // compact [n, D]
         gemm_nt(r, g);
       }
-      ln_bwd(r, xmid, TD, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, TD, n, lnpart, accumulate);
-      gemm_tn(r, dxBt, TD, id, O, TD, id, n, D, D, wpart, wcap, G + o.projW, accumulate, -1, G + o.projb, cpart);
+      ln_bwd(q, xmid, TD, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, TD, n, accumulate);
+      gemm_tn(q, dxBt, TD, O, TD, n, D, D, G + o.projW, accumulate, G + o.projb);
       {
         GemmNT g{};
         g.A = dxBt; g.lda = TD; g.B = weight_t(c, wi + 1); g.ldb = D; g.M = n; g.N = D; g.K = D;
@@ -609,14 +625,14 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       }
       launch(r, K_ATTN_BWD, 10.0 * n * c->H * (double)T * c->dh, (double)M * 7 * D * e,
              [&] { return launch_attn_bwd(dt, qkv, O, lse, du, dqkv, n, T, c->H, c->dh, c->use_mfma, s, true, (float*)(ar + y.e_dl)); });
-      gemm_tn(r, dqkv, 3 * D, id, u1, D, id, M, 3 * D, D, wpart, wcap, G + o.qkvW, accumulate, -1, G + o.qkvb, cpart);
+      gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb);
       {
         GemmNT g{};
         g.A = dqkv; g.lda = 3 * D; g.B = weight_t(c, wi + 0); g.ldb = 3 * D; g.M = M; g.N = D; g.K = 3 * D;
         g.epi = EPI_PLAIN; g.out = du; g.ldc = D;
         gemm_nt(r, g);
       }
-      ln_bwd(r, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, lnpart, accumulate, false, nullptr, periodic ? T : 0);
+      ln_bwd(q, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, accumulate, false, periodic ? T : 0);
       continue;
     }
     // ---- MLP half: x_out = x_mid + gelu(LN2(x_mid) W1^T + b1) W2^T + b2
@@ -626,17 +642,17 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       g.epi = EPI_DGELU; g.pre = m; g.ldpre = F; g.out = dm; g.ldc = F;
       gemm_nt(r, g);
     }
-    gemm_tn(r, dxAt, D, id, a, F, id, M, D, F, wpart, wcap, G + o.fc2W, accumulate, -1, G + o.fc2b, cpart);
+    gemm_tn(q, dxAt, D, a, F, M, D, F, G + o.fc2W, accumulate, G + o.fc2b);
     {
       GemmNT g{};
       g.A = dm; g.lda = F; g.B = weight_t(c, wi + 2); g.ldb = F; g.M = M; g.N = D; g.K = F;
       g.epi = EPI_PLAIN; g.out = du; g.ldc = D;
       gemm_nt(r, g);
     }
-    ln_bwd(r, xmid, D, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, D, M, lnpart, accumulate);
-    gemm_tn(r, dm, F, id, u2, D, id, M, F, D, wpart, wcap, G + o.fc1W, accumulate, -1, G + o.fc1b, cpart);
+    ln_bwd(q, xmid, D, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, D, M, accumulate);
+    gemm_tn(q, dm, F, u2, D, M, F, D, G + o.fc1W, accumulate, G + o.fc1b);
     // ---- attention half: x_mid = x_in + attn(LN1(x_in)) Wo^T + bo
-    gemm_tn(r, dxBt, D, id, O, D, id, M, D, D, wpart, wcap, G + o.projW, accumulate, -1, G + o.projb, cpart);
+    gemm_tn(q, dxBt, D, O, D, M, D, D, G + o.projW, accumulate, G + o.projb);
     {
       GemmNT g{};
       g.A = dxBt; g.lda = D; g.B = weight_t(c, wi + 1); g.ldb = D; g.M = M; g.N = D; g.K = D;
@@ -651,27 +667,31 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       g.epi = EPI_PLAIN; g.out = du; g.ldc = D;
       gemm_nt(r, g);
     }
-    ln_bwd(r, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, lnpart, accumulate);
-    gemm_tn(r, dqkv, 3 * D, id, u1, D, id, M, 3 * D, D, wpart, wcap, G + o.qkvW, accumulate, -1, G + o.qkvb, cpart);
+    ln_bwd(q, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, accumulate);
+    gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb);
   }
   // ---- token assembly: x0[n,0] = cls + pos[0]; x0[n,1+j] = patch_j W_pe^T + b_pe + pos[1+j]
   {
     long long cols = (long long)T * D;
     int slabs = colsum_slabs(n);
+    float* part = q.room((size_t)(slabs + 1) * cols);
     launch(r, K_COLSUM, 0, (double)M * D * rs,
-           [&] { return launch_colsum_part(rs_elem, dxA, cols, id, n, (int)cols, cpart, slabs, s); });
-    launch(r, K_ELEMWISE, 0, 0,
-           [&] { return launch_reduce_partials(cpart, slabs, cols, cols, G + c->o_pos, accumulate, s); });
-    launch(r, K_ELEMWISE, 0, 0,
-           [&] { return launch_reduce_partials(cpart, slabs, cols, D, G + c->o_cls, accumulate, s); });
+           [&] { return launch_colsum_part(rs_elem, dxA, cols, id, n, (int)cols, part, slabs, s); });
     // the patch-embedding bias sees every patch token: its gradient is this step's position gradient summed over the
-    // patch positions (rows 1 .. T - 1), taken from the same partial sums
-    launch(r, K_ELEMWISE, 0, 0, [&] { return launch_reduce_partials(cpart, slabs, cols, cols, wpart, 0, s); });
-    launch(r, K_ELEMWISE, 0, 0,
-           [&] { return launch_reduce_partials(wpart + D, T - 1, D, D, G + c->o_peb, accumulate, s); });
+    // patch positions (rows 1 .. T - 1), taken from the same partial sums (a single slab is that gradient already)
+    float* dpos = part;
+    if (slabs > 1) {
+      dpos = part + (size_t)slabs * cols;
+      RedList one;
+      red_add(one, part, slabs, cols, cols, dpos, 0);
+      launch(r, K_ELEMWISE, 0, 0, [&] { return launch_reduce_partials(one, s); });
+    }
+    q.add(part, slabs, cols, cols, G + c->o_pos, accumulate);
+    q.add(part, slabs, cols, D, G + c->o_cls, accumulate);
+    q.add(dpos + D, T - 1, D, D, G + c->o_peb, accumulate);
   }
   // all token rows: the CLS rows meet rows of zeros in the patch matrix
-  gemm_tn(r, dxAt, D, id, ar + y.e_patches, c->Kp, id, M, D, c->Kp, wpart, wcap, G + c->o_peW, accumulate);
+  gemm_tn(q, dxAt, D, ar + y.e_patches, c->Kp, M, D, c->Kp, G + c->o_peW, accumulate);
   if (pixel_grad) {   // over all token rows like the forward (the CLS slots' rows are not read)
     GemmNT g{};
     g.A = dxAt; g.lda = D; g.B = weight_t(c, 0); g.ldb = D; g.M = M; g.N = c->Kp; g.K = D;
@@ -680,6 +700,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
     launch(r, K_ELEMWISE, 0, 2.0 * M * c->Kp * e,
            [&] { return launch_unpatchify(dt, dm, pixel_grad, n, c->cfg.tile, c->cfg.patch, s, T - c->g2); });
   }
+  q.flush();
   return finish(r);
 }
 
@@ -722,31 +743,25 @@ int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
   if (!fwd_done)
     launch(r, K_POOL_FWD, 4.0 * N * D * Mh, (double)N * D * 4, [&] { return launch_pool_fwd(p, s); });
   char* Dp = ar + y.p_Dp;
-  RowMap id{0, 0};
-  float* tn = (float*)(ar + y.p_tn);
-  // room for 64 results of [2 M_h, D]; the column-sum partials behind it are laid out for 64 slabs, so a
-  // weight gradient of half the gate units must not take more either
-  const size_t tncap = (size_t)64 * (2 * Mh >= 256 ? 256 : 2 * Mh) * D;
-  float* cs = (float*)(ar + y.p_cs);
+  Sums q(r, (float*)(ar + y.p_tn), (size_t)((y.p_cs - y.p_tn) / 4 + (size_t)1024 * 3 * Mh));
   // the matrix-core path keeps [dpV dpU] and a feature copy as bf16 in the room of the fp32 [N, 3 Mh] array; db_V and
   // db_U come out of the weight-gradient GEMM as column sums of its first operand
   if (pool_bwd_mfma_ok(p) && (size_t)(2 * Mh + D) * 2 <= (size_t)3 * Mh * 4) {
     // M_h = 256 runs as two halves of 128 gate units: Dp is then [2][N][256], the dw partials [2][blocks][128]
     const int MHK = 128, halves = Mh / MHK;
     char* Hb16 = Dp + (size_t)N * 2 * Mh * 2;
-    float* csw = cs + (size_t)64 * 2 * MHK;   // behind the column-sum partials of the GEMM (at most 64 slabs)
     int blocks = pool_bwd_mfma_blocks(p);
+    float* csw = q.room((size_t)blocks * Mh);
     launch(r, K_POOL_BWD, 12.0 * N * D * Mh, 2.0 * N * D * 4, [&] { return launch_pool_bwd_mfma(p, Dp, Hb16, csw, s); });
     launch(r, K_ELEMWISE, 0, 0, [&] { return launch_pool_head_grads(p, s); });
+    for (int h = 0; h < halves; ++h)
+      q.add(csw + (size_t)h * blocks * MHK, blocks, MHK, MHK, c->grads + c->o_w + h * MHK, accumulate);
     for (int h = 0; h < halves; ++h) {
-      launch(r, K_ELEMWISE, 0, 0, [&] {
-        return launch_reduce_partials(csw + (size_t)h * blocks * MHK, blocks, MHK, MHK, c->grads + c->o_w + h * MHK,
-                                      accumulate, s);
-      });
       const size_t ow = (size_t)h * MHK * D;
-      gemm_tn(r, Dp + (size_t)h * N * 2 * MHK * 2, 2 * MHK, id, Hb16, D, id, N, 2 * MHK, D, tn, tncap, c->grads + c->o_VW + ow,
-              accumulate, DT_BF16, c->grads + c->o_Vb + h * MHK, cs, c->grads + c->o_UW + ow, c->grads + c->o_Ub + h * MHK);
+      gemm_tn(q, Dp + (size_t)h * N * 2 * MHK * 2, 2 * MHK, Hb16, D, N, 2 * MHK, D, c->grads + c->o_VW + ow, accumulate,
+              c->grads + c->o_Vb + h * MHK, DT_BF16, c->grads + c->o_UW + ow, c->grads + c->o_Ub + h * MHK);
     }
+    q.flush();
     return finish(r);
   }
   // float32: [dpV dpU] and the partial sums of dw share the room; db_V and db_U are column sums of the GEMM's first operand
@@ -754,10 +769,10 @@ int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
   const int rblocks = (int)((N + 31) / 32);
   launch(r, K_POOL_BWD, 8.0 * N * D * Mh, 2.0 * N * D * 4, [&] { return launch_pool_bwd_f32(p, (float*)Dp, dwp, s); });
   launch(r, K_ELEMWISE, 0, 0, [&] { return launch_pool_head_grads(p, s); });
-  launch(r, K_ELEMWISE, 0, 0,
-         [&] { return launch_reduce_partials(dwp, rblocks, Mh, Mh, c->grads + c->o_w, accumulate, s); });
-  gemm_tn(r, Dp, 2 * Mh, id, feats, D, id, N, 2 * Mh, D, tn, tncap, c->grads + c->o_VW, accumulate, DT_F32,
-          c->grads + c->o_Vb, cs, c->grads + c->o_UW, c->grads + c->o_Ub);
+  q.add(dwp, rblocks, Mh, Mh, c->grads + c->o_w, accumulate);
+  gemm_tn(q, Dp, 2 * Mh, feats, D, N, 2 * Mh, D, c->grads + c->o_VW, accumulate, c->grads + c->o_Vb, DT_F32,
+          c->grads + c->o_UW, c->grads + c->o_Ub);
+  q.flush();
   return finish(r);
 }
 
@@ -1053,7 +1068,7 @@ int slide_step_chunked(slide_ctx* c, const void* pixels, int64_t N, int64_t chun
   // pass 1: features of every tile, nothing kept
   for (int64_t t0 = 0; t0 < N; t0 += chunk_tiles) {
     int64_t n = N - t0 < chunk_tiles ? N - t0 : chunk_tiles;
-    rc = enc_fwd(c, (const char*)pixels + t0 * tile_bytes, n, H + t0 * row_bytes, false, N, s);
+    rc = enc_fwd(c, (const char*)pixels + t0 * tile_bytes, n, H + t0 * row_bytes, false, N, s, t0 == 0);
     if (rc) return rc;
   }
   // aggregator and loss on the whole slide, then the gradient of every feature row
@@ -1064,7 +1079,7 @@ int slide_step_chunked(slide_ctx* c, const void* pixels, int64_t N, int64_t chun
   // pass 2: chunk by chunk, forward again with the activations kept, backward seeded with the chunk's rows of G
   for (int64_t t0 = 0; t0 < N; t0 += chunk_tiles) {
     int64_t n = N - t0 < chunk_tiles ? N - t0 : chunk_tiles;
-    rc = enc_fwd(c, (const char*)pixels + t0 * tile_bytes, n, H + t0 * row_bytes, true, N, s);
+    rc = enc_fwd(c, (const char*)pixels + t0 * tile_bytes, n, H + t0 * row_bytes, true, N, s, false);
     if (rc) return rc;
     rc = enc_bwd(c, G + t0 * row_bytes, n, (accumulate || t0 > 0) ? 1 : 0,
                  pixel_grad ? (char*)pixel_grad + t0 * tile_bytes : nullptr, s);
