@@ -271,10 +271,11 @@ hipError_t launch_lane_init(const float* cls, const float* pos, float* xc, long 
 hipError_t launch_lane_ln(const float* x, long long xs, const float* gam, const float* bet, float* out, long long os,
                           long long rows, int D, float eps, hipStream_t s);
 // out[n,N] (fp32) = A[n,K] W[N,K]^T + bias, then + resid (fp32) or, with gelu, gelu(.).  A: fp32, or bf16 with a_bf16;
-// W: bf16.  copy (may be null): bf16 copy of the result rows (row stride ldcopy), residual mode only.
+// W: bf16.  gam, bet (may be null, gelu only): A goes through a LayerNorm first (lnout: room for [n,K]).  copy (may be null): bf16 copy of the result rows (row stride ldcopy), residual mode only.
 hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda, const void* W, long long ldw, long long n,
                             int N, int K, const float* bias, const float* resid, long long ldr, float* out, long long ldc,
-                            void* copy, long long ldcopy, hipStream_t s);
+                            void* copy, long long ldcopy, const float* gam, const float* bet, float eps, float* lnout,
+                            hipStream_t s);
 
 // theta, m, v updated in place (fp32, n elements); step counts from 1
 hipError_t launch_adamw(float* theta, const float* g, float* m, float* v, size_t n, long long step, float lr, float b1,

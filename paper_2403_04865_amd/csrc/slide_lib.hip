@@ -384,7 +384,7 @@ void lane_attn_half(Run& r, const Layout& y, int l, long long n, const void* O, 
   float* xcm = (float*)(c->arena + y.l_xcm);
   launch(r, K_CLS_LANE, 2.0 * n * D * D, (double)n * D * 14, [&] {
     return launch_lane_gemm(false, true, O, TD, weight(c, 2 + 4 * l), D, n, D, D, c->params + o.projb, lane_xc(c, y, l), D,
-                            xcm, D, xmid, TD, r.s);
+                            xcm, D, xmid, TD, nullptr, nullptr, 0.f, nullptr, r.s);
   });
 }
 
@@ -398,16 +398,13 @@ void lane_mlp_half(Run& r, const Layout& y, int l, long long n, void* xout) {
   float* xcm = (float*)(c->arena + y.l_xcm);
   float* u2c = (float*)(c->arena + y.l_u2c);
   float* ac = (float*)(c->arena + y.l_ac);
-  launch(r, K_CLS_LANE, 0, (double)n * D * 8, [&] {
-    return launch_lane_ln(xcm, D, c->params + o.ln2g, c->params + o.ln2b, u2c, D, n, D, c->cfg.ln_eps, r.s);
-  });
   launch(r, K_CLS_LANE, 4.0 * n * D * F, (double)n * (D + F) * 4, [&] {
-    return launch_lane_gemm(true, false, u2c, D, weight(c, 3 + 4 * l), D, n, F, D, c->params + o.fc1b, nullptr, 0, ac, F,
-                            nullptr, 0, r.s);
+    return launch_lane_gemm(true, false, xcm, D, weight(c, 3 + 4 * l), D, n, F, D, c->params + o.fc1b, nullptr, 0, ac, F,
+                            nullptr, 0, c->params + o.ln2g, c->params + o.ln2b, c->cfg.ln_eps, u2c, r.s);
   });
   launch(r, K_CLS_LANE, 4.0 * n * D * F, (double)n * (F * 4 + D * 10), [&] {
     return launch_lane_gemm(false, false, ac, F, weight(c, 4 + 4 * l), F, n, D, F, c->params + o.fc2b, xcm, D,
-                            lane_xc(c, y, l + 1), D, xout, TD, r.s);
+                            lane_xc(c, y, l + 1), D, xout, TD, nullptr, nullptr, 0.f, nullptr, r.s);
   });
 }
 
