@@ -4,7 +4,7 @@
 //
 // Reductions over the rows (statistics, gain / shift gradients) are two-stage and deterministic: a fixed number of
 // workgroups each sums a contiguous range of rows in fp32 (8 channels per thread, rows strided over the threads, then
-// one pass through LDS), and one wavefront per channel adds the workgroups' partial sums in double, in a fixed order.
+// one pass through LDS), and one workgroup per 16 channels adds the workgroups' partial sums in double, in a fixed order.
 #include "resnet_internal.h"
 
 namespace sl {
@@ -35,12 +35,13 @@ __device__ __forceinline__ void ld8f(const float* p, float (&v)[8]) {
   v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
 }
 
-constexpr int BN_MAX_BLOCKS = 4096;
+constexpr int BN_MAX_BLOCKS = 2048, BN_MAX_RUNS = 4096;
 
-// Two per-channel sums over the rows of one workgroup's range.  F(row pointer offset, channel base, out a[8], out b[8])
-// yields the two summands of 8 channels of one row.
-template <typename F>
-__device__ __forceinline__ void two_sums(long long M, int C, float* part, F f) {
+// Two per-channel sums over the rows of one workgroup's range.  F(row pointer offset, channel base) fetches what 8 channels
+// of one row need, G(fetched, channel base, out a[8], out b[8]) yields their two summands; four rows of a thread are in
+// flight (with one row the loop waits for memory once per row: 76 us for 14,700 rows of 2048 channels against 30).
+template <typename F, typename G>
+__device__ __forceinline__ void two_sums(long long M, int C, float* part, F f, G g) {
   __shared__ float red[2][256 * 8];
   const int tcols = C >> 3, rpp = 256 / tcols;          // threads per row, rows per pass
   const int tc = threadIdx.x % tcols, tr = threadIdx.x / tcols;
@@ -49,9 +50,23 @@ __device__ __forceinline__ void two_sums(long long M, int C, float* part, F f) {
   float s[8], q[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) s[e] = q[e] = 0.f;
-  for (long long m = lo + tr; m < hi; m += rpp) {
+  constexpr int U = 4;
+  long long m = lo + tr;
+  for (; m + (U - 1) * rpp < hi; m += U * rpp) {
+    decltype(f(0LL)) t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = f((m + u * rpp) * C + tc * 8);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float a[8], b[8];
+      g(t[u], tc * 8, a, b);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { s[e] += a[e]; q[e] += b[e]; }
+    }
+  }
+  for (; m < hi; m += rpp) {
     float a[8], b[8];
-    f(m * C + tc * 8, tc * 8, a, b);
+    g(f(m * C + tc * 8), tc * 8, a, b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) { s[e] += a[e]; q[e] += b[e]; }
   }
@@ -67,27 +82,64 @@ __device__ __forceinline__ void two_sums(long long M, int C, float* part, F f) {
   }
 }
 
-// The workgroups' partial sums of one channel, added in double by one wavefront: lane l takes partials l, l + 64, ...
-// in order, then the lanes are combined in a fixed butterfly (the same bits on every run).
-__device__ __forceinline__ void channel_sums(const float* __restrict__ part, int blocks, int C, int ch, double& s, double& q) {
-  const int lane = threadIdx.x & 63;
+// The partial sums of 16 channels, added in double by one workgroup of 1024: group g of 16 lanes takes partials g, g + 64,
+// ... in order (64 bytes of a partial row per group), then the 64 groups' sums are added in a fixed order (the same bits on
+// every run).  RUN > 1: a partial is a run of that many rows of `part` (`blocks` rows in all), added in float first.  Thread
+// t returns those of channel ch0 + t % 16.
+template <int RUN>
+__device__ __forceinline__ void channel_sums(const float* __restrict__ part, int blocks, int C, int ch0, double& s, double& q) {
+  __shared__ double rs[64][17], rq[64][17], ws[8][17], wq[8][17];
+  const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
   s = 0.0; q = 0.0;
-  for (int b = lane; b < blocks; b += 64) {
-    s += (double)part[((long long)b * 2) * C + ch];
-    q += (double)part[((long long)b * 2 + 1) * C + ch];
-  }
+  const float* p = part + ch0 + c;
+  if constexpr (RUN == 1) {
+#pragma unroll 8
+    for (int b = g; b < blocks; b += 64) {
+      s += (double)p[((long long)b * 2) * C];
+      q += (double)p[((long long)b * 2 + 1) * C];
+    }
+  } else {
+    for (int b = g * RUN; b < blocks; b += 64 * RUN) {
+      float v[RUN], w[RUN];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { s += __shfl_xor(s, o, 64); q += __shfl_xor(q, o, 64); }
+      for (int i = 0; i < RUN; ++i) {
+        const bool ok = b + i < blocks;
+        v[i] = ok ? p[((long long)(b + i) * 2) * C] : 0.f;
+        w[i] = ok ? p[((long long)(b + i) * 2 + 1) * C] : 0.f;
+      }
+      float a = 0.f, d = 0.f;
+#pragma unroll
+      for (int i = 0; i < RUN; ++i) { a += v[i]; d += w[i]; }
+      s += (double)a;
+      q += (double)d;
+    }
+  }
+  rs[g][c] = s; rq[g][c] = q;
+  __syncthreads();
+  // 32 lanes per channel (threads 0 .. 511), two groups each, then the lanes 16 apart, then the wavefronts
+  if (threadIdx.x < 512) {
+    s = rs[g][c] + rs[g + 32][c];
+    q = rq[g][c] + rq[g + 32][c];
+    s += __shfl_xor(s, 16, 64); q += __shfl_xor(q, 16, 64);
+    s += __shfl_xor(s, 32, 64); q += __shfl_xor(q, 32, 64);
+    if ((threadIdx.x & 63) < 16) { ws[threadIdx.x >> 6][c] = s; wq[threadIdx.x >> 6][c] = q; }
+  }
+  __syncthreads();
+  s = q = 0.0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) { s += ws[w][c]; q += wq[w][c]; }
 }
 
-__global__ void __launch_bounds__(256) bn_stats_final_k(const float* __restrict__ part, int blocks, long long M, int C,
+constexpr int TILE_RUN = 16;   // row tiles whose sums are added in float
+
+template <int RUN>
+__global__ void __launch_bounds__(1024) bn_stats_final_k(const float* __restrict__ part, int blocks, long long M, int C,
                                                          const float* __restrict__ gamma, const float* __restrict__ beta,
                                                          float eps, float* __restrict__ stats) {
-  const int ch = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (ch >= C) return;
   double s, q;
-  channel_sums(part, blocks, C, ch, s, q);
-  if (threadIdx.x & 63) return;
+  channel_sums<RUN>(part, blocks, C, blockIdx.x * 16, s, q);   // C is a multiple of 16
+  if (threadIdx.x >= 16) return;
+  const int ch = blockIdx.x * 16 + threadIdx.x;
   const double mean = s / (double)M;
   double var = q / (double)M - mean * mean;
   if (var < 0.0) var = 0.0;
@@ -99,15 +151,18 @@ __global__ void __launch_bounds__(256) bn_stats_final_k(const float* __restrict_
   stats[3 * C + ch] = (float)((double)beta[ch] - mean * a);
 }
 
-// tile_part[tiles][2 C] -> part[workgroups][2 C]: every workgroup adds a contiguous range of tiles, column by column
+// tile_part[tiles][2 C] -> part[ceil(tiles / TILE_RUN)][2 C]: 64 columns and four runs of tiles per workgroup
 __global__ void __launch_bounds__(256) bn_tiles_part_k(const float* __restrict__ tp, int tiles, int C2, float* __restrict__ part) {
-  const int per = (tiles + gridDim.x - 1) / gridDim.x;
-  const int lo = blockIdx.x * per, hi = lo + per < tiles ? lo + per : tiles;
-  for (int col = threadIdx.x; col < C2; col += 256) {
-    float a = 0.f;
-    for (int t = lo; t < hi; ++t) a += tp[(long long)t * C2 + col];
-    part[(long long)blockIdx.x * C2 + col] = a;
-  }
+  const int col = blockIdx.x * 64 + (threadIdx.x & 63);   // C2 is a multiple of 128
+  const int run = blockIdx.y * 4 + (threadIdx.x >> 6), lo = run * TILE_RUN;
+  if (lo >= tiles) return;
+  float v[TILE_RUN];
+#pragma unroll
+  for (int i = 0; i < TILE_RUN; ++i) v[i] = lo + i < tiles ? tp[(long long)(lo + i) * C2 + col] : 0.f;
+  float a = 0.f;
+#pragma unroll
+  for (int i = 0; i < TILE_RUN; ++i) a += v[i];
+  part[(long long)run * C2 + col] = a;
 }
 
 // A thread of the two streaming kernels below takes SPT pieces 256 pieces apart: C / 8 divides 256, so they are the
@@ -174,29 +229,35 @@ __global__ void __launch_bounds__(256) bn_apply_k(const bf16* __restrict__ x, lo
 __global__ void __launch_bounds__(256) bn_bwd_part_k(const bf16* __restrict__ dy, const unsigned char* __restrict__ mask,
                                                       const bf16* __restrict__ x, long long M, int C,
                                                       const float* __restrict__ stats, float* __restrict__ part) {
-  two_sums(M, C, part, [&](long long off, int c0, float (&a)[8], float (&b)[8]) {
-    float xv[8];
-    unpack8(ld16(dy + off), a);
-    unpack8(ld16(x + off), xv);
-    if (mask) {
-      const unsigned m = mask[off >> 3];
+  struct Row { u32x4 d, x; unsigned m; };
+  float mean[8], rstd[8];   // of this thread's 8 channels
+  {
+    const int c0 = (int)(threadIdx.x & ((C >> 3) - 1)) * 8;
+    ld8f(stats + c0, mean);
+    ld8f(stats + C + c0, rstd);
+  }
+  two_sums(M, C, part,
+           [&](long long off) __attribute__((always_inline)) { return Row{ld16(dy + off), ld16(x + off), mask ? (unsigned)mask[off >> 3] : 0xffu}; },
+           [&](const Row& t, int, float (&a)[8], float (&b)[8]) __attribute__((always_inline)) {
+             float xv[8];
+             unpack8(t.d, a);
+             unpack8(t.x, xv);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] = (m >> e) & 1u ? a[e] : 0.f;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) b[e] = a[e] * ((xv[e] - stats[c0 + e]) * stats[C + c0 + e]);
-  });
+             for (int e = 0; e < 8; ++e) {
+               a[e] = (t.m >> e) & 1u ? a[e] : 0.f;
+               b[e] = a[e] * ((xv[e] - mean[e]) * rstd[e]);
+             }
+           });
 }
 
 // coef[0][c] = dbeta / M, coef[1][c] = dgamma / M; parameter gradients written or added to
-__global__ void __launch_bounds__(256) bn_bwd_final_k(const float* __restrict__ part, int blocks, long long M, int C,
+__global__ void __launch_bounds__(1024) bn_bwd_final_k(const float* __restrict__ part, int blocks, long long M, int C,
                                                        float* __restrict__ coef, float* __restrict__ dgamma,
                                                        float* __restrict__ dbeta, int accumulate) {
-  const int ch = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (ch >= C) return;
   double s, q;
-  channel_sums(part, blocks, C, ch, s, q);
-  if (threadIdx.x & 63) return;
+  channel_sums<1>(part, blocks, C, blockIdx.x * 16, s, q);   // C is a multiple of 16
+  if (threadIdx.x >= 16) return;
+  const int ch = blockIdx.x * 16 + threadIdx.x;
   coef[ch] = (float)(s / (double)M);
   coef[C + ch] = (float)(q / (double)M);
   dbeta[ch] = accumulate ? dbeta[ch] + (float)s : (float)s;
@@ -365,21 +426,26 @@ unsigned stream_grid(long long chunks) {
 
 }  // namespace
 
+// workgroups of a sum over rows: sixteen passes of 2,048 elements each, at most eight workgroups per compute unit
 int bn_blocks(long long M, int C) {
-  (void)C;
-  long long b = M / 128;
+  long long b = (M * C + 16 * 2048 - 1) / (16 * 2048);
   return (int)(b < 1 ? 1 : (b > BN_MAX_BLOCKS ? BN_MAX_BLOCKS : b));
 }
 
 hipError_t launch_bn_stats_tiles(const float* tile_part, int tiles, long long M, int C, const float* gamma, const float* beta,
                                  float eps, float* part, float* stats, hipStream_t s) {
   if (!tile_part || tiles <= 0 || !gamma || !beta || !part || !stats || M <= 0 || !chan_ok(C)) return hipErrorInvalidValue;
-  int blocks = (tiles + 15) / 16;
-  if (blocks > BN_MAX_BLOCKS) blocks = BN_MAX_BLOCKS;
-  hipLaunchKernelGGL(bn_tiles_part_k, dim3(blocks), dim3(256), 0, s, tile_part, tiles, 2 * C, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bn_stats_final_k, dim3((C + 3) / 4), dim3(256), 0, s, part, blocks, M, C, gamma, beta, eps, stats);
+  // up to 4,096 tiles in one launch; beyond, where a lane of the final sum would add more than four runs, the runs are added
+  // by a launch of their own (part has room for BN_MAX_RUNS of them)
+  const int runs = (tiles + TILE_RUN - 1) / TILE_RUN;
+  if (runs > 256 && runs <= BN_MAX_RUNS) {
+    hipLaunchKernelGGL(bn_tiles_part_k, dim3(2 * C / 64, (runs + 3) / 4), dim3(256), 0, s, tile_part, tiles, 2 * C, part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(bn_stats_final_k<1>, dim3(C / 16), dim3(1024), 0, s, part, runs, M, C, gamma, beta, eps, stats);
+  } else {
+    hipLaunchKernelGGL(bn_stats_final_k<TILE_RUN>, dim3(C / 16), dim3(1024), 0, s, tile_part, tiles, M, C, gamma, beta, eps, stats);
+  }
   return hipGetLastError();
 }
 
@@ -404,7 +470,7 @@ hipError_t launch_bn_bwd(const bf16* dy, const unsigned char* mask, const bf16* 
   hipLaunchKernelGGL(bn_bwd_part_k, dim3(blocks), dim3(256), 0, s, dy, mask, x, M, C, stats, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bn_bwd_final_k, dim3((C + 3) / 4), dim3(256), 0, s, part, blocks, M, C, coef, dgamma, dbeta, accumulate);
+  hipLaunchKernelGGL(bn_bwd_final_k, dim3(C / 16), dim3(1024), 0, s, part, blocks, M, C, coef, dgamma, dbeta, accumulate);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const long long chunks = M * (C >> 3);

@@ -1006,42 +1006,45 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_win_k(ConvWG p) {
 
 __global__ void __launch_bounds__(256) wgrad_reduce_k(const float* __restrict__ part, int slabs, int Co, int Cin, int taps,
                                                        int ldk, float* __restrict__ dW, int accumulate) {
-  const int K = taps * Cin;
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)Co * K) return;
+  // 64 results per workgroup, the slabs dealt to its four wavefronts, eight slabs of each in flight; fixed order of additions
+  __shared__ float red[4][64];
+  const int K = taps * Cin, cl = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const long long i = (long long)blockIdx.x * 64 + cl;   // Co * K is a multiple of 64
   const int co = (int)(i / K), col = (int)(i - (long long)co * K);
   const int tap = col / Cin, ci = col - tap * Cin;
-  // eight independent running sums (slab s goes to sum s % 8), combined in a fixed order: the loads of eight slabs are
-  // in flight together and the result is still the same bits on every run
   float a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const long long st = (long long)Co * ldk;
   const float* pp = part + (long long)co * ldk + col;
-  int s = 0;
-  for (; s + 8 <= slabs; s += 8) {
+  int s = w;
+  for (; s + 28 < slabs; s += 32) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) a8[u] += pp[(s + u) * st];
+    for (int u = 0; u < 8; ++u) a8[u] += pp[(s + 4 * u) * st];
   }
-  for (; s < slabs; ++s) a8[s & 7] += pp[s * st];
-  const float a = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
+  for (; s < slabs; s += 4) a8[0] += pp[s * st];
+  red[w][cl] = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
+  __syncthreads();
+  if (w) return;
+  const float a = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
   const long long o = ((long long)co * Cin + ci) * taps + tap;
   dW[o] = accumulate ? dW[o] + a : a;
 }
 
-__global__ void __launch_bounds__(256) conv_cast_w_k(const float* __restrict__ W, int Co, int Cin, int taps, int ldk,
-                                                      bf16* __restrict__ Wk, bf16* __restrict__ Wt, bf16* __restrict__ Wf,
-                                                      bf16* __restrict__ Wtf) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)Co * ldk) return;
-  const int co = (int)(i / ldk), col = (int)(i - (long long)co * ldk);
+__global__ void __launch_bounds__(256) conv_cast_w_k(ConvCastList L) {
+  int k = 0;
+  while (k + 1 < L.n && (int)blockIdx.x >= L.m[k + 1].block0) ++k;
+  const ConvCast m = L.m[k];
+  const long long i = (long long)(blockIdx.x - m.block0) * 256 + threadIdx.x;
+  if (i >= (long long)m.Co * m.ldk) return;
+  const int co = (int)(i / m.ldk), col = (int)(i - (long long)co * m.ldk);
   float v = 0.f;
-  if (col < taps * Cin) {
-    const int tap = col / Cin, ci = col - tap * Cin;
-    v = W[((long long)co * Cin + ci) * taps + tap];
-    if (Wt) Wt[(long long)ci * taps * Co + (long long)tap * Co + co] = (bf16)v;
-    if (Wf) Wf[frag_index(co, col, taps * Cin)] = (bf16)v;
-    if (Wtf) Wtf[frag_index(ci, tap * Co + co, taps * Co)] = (bf16)v;
+  if (col < m.taps * m.Cin) {
+    const int tap = col / m.Cin, ci = col - tap * m.Cin;
+    v = m.W[((long long)co * m.Cin + ci) * m.taps + tap];
+    if (m.Wt) m.Wt[(long long)ci * m.taps * m.Co + (long long)tap * m.Co + co] = (bf16)v;
+    if (m.Wf) m.Wf[frag_index(co, col, m.taps * m.Cin)] = (bf16)v;
+    if (m.Wtf) m.Wtf[frag_index(ci, tap * m.Co + co, m.taps * m.Co)] = (bf16)v;
   }
-  Wk[i] = (bf16)v;
+  m.Wk[i] = (bf16)v;
 }
 
 // one thread per pixel of the padded image
@@ -1075,13 +1078,22 @@ __global__ void __launch_bounds__(256) stem_cast_w_k(const float* __restrict__ W
 
 __global__ void __launch_bounds__(256) stem_wgrad_reduce_k(const float* __restrict__ part, int slabs, int Co,
                                                             float* __restrict__ dW, int accumulate) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= Co * 147) return;
+  // 16 results per workgroup, the slabs dealt to 16 groups of lanes (Co * 147 is a multiple of 16); fixed order of additions
+  __shared__ float red[16][17];
+  const int cl = threadIdx.x & 15, q = threadIdx.x >> 4;
+  const int i = blockIdx.x * 16 + cl;
   const int co = i / 147, r = i - co * 147;
   const int ch = r / 49, kh = (r - ch * 49) / 7, kw = r - ch * 49 - kh * 7;
   const int col = kh * 32 + kw * 4 + ch;
   float a = 0.f;
-  for (int s = 0; s < slabs; ++s) a += part[((long long)s * Co + co) * 256 + col];
+#pragma unroll 8
+  for (int s = q; s < slabs; s += 16) a += part[((long long)s * Co + co) * 256 + col];
+  red[q][cl] = a;
+  __syncthreads();
+  if (q) return;
+  a = 0.f;
+#pragma unroll
+  for (int g = 0; g < 16; ++g) a += red[g][cl];
   dW[i] = accumulate ? dW[i] + a : a;
 }
 
@@ -1205,6 +1217,26 @@ hipError_t launch_conv_nt(const ConvNT& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+namespace {
+
+bool wgrad_pointwise(const ConvWG& p) {
+  return !p.g.stem && p.g.KH == 1 && p.g.KW == 1 && p.g.stride == 1 && p.g.pad == 0 && p.g.YS == p.g.YO && p.g.XS == p.g.XO;
+}
+
+}  // namespace
+
+// Slabs of a weight gradient: one full round of the workgroups that fit the chip together (two 3x3, three pointwise, four stem
+// or eight 64 x 64 workgroups per compute unit).  Every slab's result is written and read again, 2.4 MB for a 256-channel 3x3
+// layer, and a second round of workgroups that fills less than its share costs as much as it saves.  ResNet18 step, 1024
+// tiles, by workgroups of the 3x3 layers: 4096 26.0 ms, 2048 25.2, 1024 24.6, 768 25.7, 512 24.2, 256 26.5.
+int conv_wgrad_slabs(const ConvWG& p) {
+  const int blocks = (p.Co / 64) * (p.Cs / 64);
+  if (p.g.stem) return (1024 + blocks - 1) / blocks;
+  if (p.g.KH == 3) return (512 + blocks - 1) / blocks;
+  const bool big = wgrad_pointwise(p) && ((p.Co % 128 == 0 && p.Cs % 128 == 0) || p.Co % 256 == 0 || p.Cs % 256 == 0);
+  return big ? (4 * 768 + blocks - 1) / blocks : (2048 + blocks - 1) / blocks;
+}
+
 hipError_t launch_conv_wgrad(const ConvWG& p, hipStream_t s) {
   const int taps = p.g.KH * p.g.KW;
   if (!geom_ok(p.g) || p.g.transposed || (taps != 1 && !(p.g.KH == 3 && p.g.KW == 3)) || p.M <= 0 ||
@@ -1232,7 +1264,7 @@ hipError_t launch_conv_wgrad(const ConvWG& p, hipStream_t s) {
     return hipGetLastError();
   }
   if (p.g.stem) hipLaunchKernelGGL((conv_wgrad_k<4, true>), grid, dim3(256), lds_of(4), s, p);
-  else if (taps == 1 && p.g.stride == 1 && p.g.pad == 0 && p.g.YS == p.g.YO && p.g.XS == p.g.XO) {
+  else if (wgrad_pointwise(p)) {
     const unsigned g8 = (unsigned)((p.slabs + 7) / 8 * 8);
     if (p.Co % 128 == 0 && p.Cs % 128 == 0)
       hipLaunchKernelGGL((conv_wgrad_pw_k<128, 128>), dim3(g8 * (p.Co / 128) * (p.Cs / 128)), dim3(256), 0, s, p);
@@ -1250,19 +1282,24 @@ hipError_t launch_conv_wgrad(const ConvWG& p, hipStream_t s) {
 
 hipError_t launch_wgrad_reduce(const float* part, int slabs, int Co, int Cin, int taps, int ldk, float* dW, int accumulate,
                                hipStream_t s) {
-  if (!part || !dW || slabs <= 0 || Co <= 0 || Cin <= 0 || taps <= 0 || ldk < taps * Cin) return hipErrorInvalidValue;
+  if (!part || !dW || slabs <= 0 || Co <= 0 || Co % 64 || Cin <= 0 || taps <= 0 || ldk < taps * Cin) return hipErrorInvalidValue;
   const long long total = (long long)Co * taps * Cin;
-  hipLaunchKernelGGL(wgrad_reduce_k, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, part, slabs, Co, Cin, taps, ldk,
+  hipLaunchKernelGGL(wgrad_reduce_k, dim3((unsigned)(total / 64)), dim3(256), 0, s, part, slabs, Co, Cin, taps, ldk,
                      dW, accumulate);
   return hipGetLastError();
 }
 
-hipError_t launch_conv_cast_w(const float* W, int Co, int Cin, int taps, int ldk, bf16* Wk, bf16* Wt, bf16* Wf, bf16* Wtf,
-                              hipStream_t s) {
-  if (!W || !Wk || Co <= 0 || Cin <= 0 || taps <= 0 || ldk < taps * Cin) return hipErrorInvalidValue;
-  if ((Wf || Wtf) && (Co % 32 || Cin % 32 || ldk != taps * Cin)) return hipErrorInvalidValue;   // whole fragments only
-  const long long total = (long long)Co * ldk;
-  hipLaunchKernelGGL(conv_cast_w_k, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, W, Co, Cin, taps, ldk, Wk, Wt, Wf, Wtf);
+hipError_t launch_conv_cast_w(ConvCastList& L, hipStream_t s) {
+  long long blocks = 0;
+  for (int k = 0; k < L.n; ++k) {
+    ConvCast& m = L.m[k];
+    if (!m.W || !m.Wk || m.Co <= 0 || m.Cin <= 0 || m.taps <= 0 || m.ldk < m.taps * m.Cin) return hipErrorInvalidValue;
+    if ((m.Wf || m.Wtf) && (m.Co % 32 || m.Cin % 32 || m.ldk != m.taps * m.Cin)) return hipErrorInvalidValue;   // whole fragments only
+    m.block0 = (int)blocks;
+    blocks += ((long long)m.Co * m.ldk + 255) / 256;
+  }
+  if (blocks >= (1LL << 31)) return hipErrorInvalidValue;
+  if (blocks) hipLaunchKernelGGL(conv_cast_w_k, dim3((unsigned)blocks), dim3(256), 0, s, L);
   return hipGetLastError();
 }
 
@@ -1281,8 +1318,8 @@ hipError_t launch_stem_cast_w(const float* W, int Co, bf16* Wk, hipStream_t s) {
 }
 
 hipError_t launch_stem_wgrad_reduce(const float* part, int slabs, int Co, float* dW, int accumulate, hipStream_t s) {
-  if (!part || !dW || slabs <= 0 || Co <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(stem_wgrad_reduce_k, dim3((unsigned)((Co * 147 + 255) / 256)), dim3(256), 0, s, part, slabs, Co, dW,
+  if (!part || !dW || slabs <= 0 || Co <= 0 || Co % 16) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(stem_wgrad_reduce_k, dim3((unsigned)(Co * 147 / 16)), dim3(256), 0, s, part, slabs, Co, dW,
                      accumulate);
   return hipGetLastError();
 }

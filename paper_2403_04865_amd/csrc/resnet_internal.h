@@ -63,6 +63,7 @@ struct ConvWG {
   ConvGeom g;
   int slabs; long long per;
 };
+int conv_wgrad_slabs(const ConvWG& p);   // before any limit of rows or room
 hipError_t launch_conv_wgrad(const ConvWG& p, hipStream_t s);
 
 // dW[co][ci][kh][kw] (fp32, the parameter's own layout) = (accumulate ? dW : 0) + sum_s part[s][co][tap * Cin + ci],
@@ -72,8 +73,14 @@ hipError_t launch_wgrad_reduce(const float* part, int slabs, int Co, int Cin, in
 // fp32 W[co][ci][kh][kw] -> bf16 Wk[co][ldk] (column tap * Cin + ci, zero beyond taps * Cin) and, if Wt is not null,
 // Wt[ci][tap * Co + co]; Wf / Wtf (optional): the same two matrices in fragment order: for every block of 32 rows and
 // 16 columns, the 64 MFMA lanes' operands (row l % 32, columns 8 (l / 32) .. + 7) back to back
-hipError_t launch_conv_cast_w(const float* W, int Co, int Cin, int taps, int ldk, bf16* Wk, bf16* Wt, bf16* Wf, bf16* Wtf,
-                              hipStream_t s);
+struct ConvCast {
+  const float* W;
+  int Co, Cin, taps, ldk, block0;
+  bf16 *Wk, *Wt, *Wf, *Wtf;   // all but Wk may be null
+};
+constexpr int CONV_CAST_MAX = 48;   // matrices of one launch
+struct ConvCastList { int n; ConvCast m[CONV_CAST_MAX]; };
+hipError_t launch_conv_cast_w(ConvCastList& L, hipStream_t s);
 // planar pixels [n][3][S][S] (bf16) -> padded image [n][S + 6][S + 8][4] (see ConvGeom::stem), borders and the fourth
 // channel zero
 hipError_t launch_stem_pad_pixels(const bf16* pixels, bf16* img, long long n, int S, hipStream_t s);

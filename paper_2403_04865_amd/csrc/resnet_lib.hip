@@ -187,14 +187,21 @@ double conv_bytes(const resnet_ctx* c, const ConvL& L, long long M, long long n)
 
 void cast_weights(Run& r) {
   resnet_ctx* c = r.c;
+  launch(r, RK_ELEMWISE, 0, 0, [&] { return launch_stem_cast_w(c->params + c->convs[0].oW, c->convs[0].Cout, (bf16*)(c->arena + c->convs[0].w), r.s); });
+  ConvCastList list{};
+  auto flush = [&] {
+    if (list.n) launch(r, RK_ELEMWISE, 0, 0, [&] { return launch_conv_cast_w(list, r.s); });
+    list.n = 0;
+  };
   for (const ConvL& L : c->convs) {
-    launch(r, RK_ELEMWISE, 0, 0, [&] {
-      if (is_stem(L)) return launch_stem_cast_w(c->params + L.oW, L.Cout, (bf16*)(c->arena + L.w), r.s);
-      return launch_conv_cast_w(c->params + L.oW, L.Cout, L.kCs, L.kK * L.kK, L.ldk(), (bf16*)(c->arena + L.w),
-                                L.need_wt ? (bf16*)(c->arena + L.wt) : nullptr, L.wf ? (bf16*)(c->arena + L.wf) : nullptr,
-                                L.wtf ? (bf16*)(c->arena + L.wtf) : nullptr, r.s);
-    });
+    if (is_stem(L)) continue;
+    ConvCast& e = list.m[list.n++];
+    e = ConvCast{c->params + L.oW, L.Cout, L.kCs, L.kK * L.kK, L.ldk(), 0, (bf16*)(c->arena + L.w),
+                 L.need_wt ? (bf16*)(c->arena + L.wt) : nullptr, L.wf ? (bf16*)(c->arena + L.wf) : nullptr,
+                 L.wtf ? (bf16*)(c->arena + L.wtf) : nullptr};
+    if (list.n == CONV_CAST_MAX) flush();
   }
+  flush();
 }
 
 // convolution forward + batch statistics of its output
@@ -247,8 +254,7 @@ void conv_wgrad(Run& r, int id, long long n, const bf16* dout, int accumulate) {
   p.Cs = is_stem(L) ? 64 : L.kCs;   // the stem's 256 columns are four groups of 64 handled like taps
   p.part = (float*)(c->arena + c->lay.wpart);
   p.M = rows_of(c, L.t_conv, n); p.g = geom_fwd(L);
-  const long long tiles = (long long)(L.Cout / 64) * (p.Cs / 64);
-  long long slabs = (4096 + tiles - 1) / tiles;
+  long long slabs = conv_wgrad_slabs(p);
   const long long by_rows = (p.M + 255) / 256;
   const long long by_room = (long long)(c->lay.wpart_bytes / ((size_t)L.Cout * L.ldk() * 4));
   if (slabs > by_rows) slabs = by_rows;
