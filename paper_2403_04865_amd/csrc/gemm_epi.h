@@ -20,7 +20,7 @@ __device__ __forceinline__ void epi_store_mode(int mode, const GemmNT& g, long l
       float gl, dg;
       gelu_both(acc + g.bias[n], &gl, &dg);
       ((T*)g.out)[m * g.ldc + n] = from_f<T>(gl);
-      ((typename dgelu_store<T>::type*)g.out2)[m * g.ldc2 + n] = dgelu_store<T>::put(dg);
+      if (g.out2) ((typename dgelu_store<T>::type*)g.out2)[m * g.ldc2 + n] = dgelu_store<T>::put(dg);
       break;
     }
     case EPI_DGELU:

@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(256, BM + BN == 256 ? 2 : BM + BN == 192 ? 3 :
           f32x4 d;
 #pragma unroll
           for (int e = 0; e < 4; ++e) { float a, b; gelu_both(v[e], &a, &b); v[e] = a; d[e] = b; }
-          *reinterpret_cast<f32x4*>((float*)g.out2 + m * g.ldc2 + n) = d;
+          if (g.out2) *reinterpret_cast<f32x4*>((float*)g.out2 + m * g.ldc2 + n) = d;
         }
         *reinterpret_cast<f32x4*>((float*)g.out + mo * g.ldc + n) = v;
       }

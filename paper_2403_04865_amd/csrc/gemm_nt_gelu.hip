@@ -59,6 +59,7 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
 // the derivative in the code space of its one-byte storage: *dgc comes out ready for the conversion
 // (entries are four halves: 8 bytes per look-up instead of 16 keep the table's LDS traffic, which every wavefront's
 // epilogue shares, and its bank conflicts at half; a half has 11 significant bits against the 8 of the results)
+typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void gelu_both_tab(const h16x4* tab, float x, float* gl, float* dgc) {
   float t = __builtin_amdgcn_fmed3f(x * 32.0f + 224.0f, 0.0f, (float)TAB_N - 0.001f);
@@ -68,12 +69,22 @@ __device__ __forceinline__ void gelu_both_tab(const h16x4* tab, float x, float* 
   *gl = x * ((float)e[0] + f * (float)e[1]);
   *dgc = (float)e[2] + f * (float)e[3];
 }
+// the same value without the derivative, from a table of the first two halves
+__device__ __forceinline__ float gelu_tab(const h16x2* tab, float x) {
+  float t = __builtin_amdgcn_fmed3f(x * 32.0f + 224.0f, 0.0f, (float)TAB_N - 0.001f);
+  h16x2 e = tab[(int)t];
+  return x * ((float)e[0] + __builtin_amdgcn_fractf(t) * (float)e[1]);
+}
 
 template <int V> using IC = std::integral_constant<int, V>;
 
+// DG: the derivative is wanted (no backward follows a forward that keeps nothing, and a block whose activations are
+// re-created in the backward has it made there): a third of the bytes written, half of the table's
+template <bool DG>
 __global__ void __launch_bounds__(NTH) gemm_nt_gelu_k(GemmNT g, int MT, int NTL) {
+  typedef std::conditional_t<DG, h16x4, h16x2> tab_t;
   __shared__ __attribute__((aligned(16))) bf16 ring[2 * STAGE];
-  __shared__ h16x4 tab[TAB_N];
+  __shared__ tab_t tab[TAB_N];
   __shared__ __attribute__((aligned(16))) float lbias[BN];   // the tile's bias columns (zeros without a bias)
   bf16* const ring0 = ring;
   bf16* const ring1 = ring + STAGE;
@@ -92,7 +103,8 @@ __global__ void __launch_bounds__(NTH) gemm_nt_gelu_k(GemmNT g, int MT, int NTL)
       float c0 = 0.5f * (1.0f + erff(x0 * 0.70710678118654752f)), c1 = 0.5f * (1.0f + erff(x1 * 0.70710678118654752f));
       float d0 = c0 + x0 * 0.39894228040143268f * expf(-0.5f * x0 * x0);
       float d1 = c1 + x1 * 0.39894228040143268f * expf(-0.5f * x1 * x1);
-      tab[k] = h16x4{(_Float16)c0, (_Float16)(c1 - c0), (_Float16)dg8_code(d0), (_Float16)(dg8_code(d1) - dg8_code(d0))};
+      if constexpr (DG) tab[k] = h16x4{(_Float16)c0, (_Float16)(c1 - c0), (_Float16)dg8_code(d0), (_Float16)(dg8_code(d1) - dg8_code(d0))};
+      else tab[k] = h16x2{(_Float16)c0, (_Float16)(c1 - c0)};
     }
   }
 
@@ -234,17 +246,23 @@ __global__ void __launch_bounds__(NTH) gemm_nt_gelu_k(GemmNT g, int MT, int NTL)
           float t[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            float gl, dg;
-            gelu_both_tab(tab, v[e], &gl, &dg);
-            v[e] = gl;
-            t[e] = dg;
+            if constexpr (DG) {
+              float gl, dg;
+              gelu_both_tab(tab, v[e], &gl, &dg);
+              v[e] = gl;
+              t[e] = dg;
+            } else {
+              v[e] = gelu_tab(tab, v[e]);
+            }
           }
           const bool ok = p * 5 + erc < lim && p * 5 + er < 32;
           char* o = (char*)g.out + ((ms + p * 5) * (long long)ldc_b + 2 * nw);
-          char* o2 = (char*)g.out2 + ((ms + p * 5) * (long long)ldc2_b + nw);
           if (ok) __builtin_nontemporal_store(pack8(v), reinterpret_cast<u32x4*>(o + (unsigned)er * ldc_b + esg * 16));
-          if (ok) __builtin_nontemporal_store(u32x2{dg8_pack4_code(t[0], t[1], t[2], t[3]), dg8_pack4_code(t[4], t[5], t[6], t[7])},
-                                              reinterpret_cast<u32x2*>(o2 + (unsigned)er * ldc2_b + esg * 8));
+          if constexpr (DG) {
+            char* o2 = (char*)g.out2 + ((ms + p * 5) * (long long)ldc2_b + nw);
+            if (ok) __builtin_nontemporal_store(u32x2{dg8_pack4_code(t[0], t[1], t[2], t[3]), dg8_pack4_code(t[4], t[5], t[6], t[7])},
+                                                reinterpret_cast<u32x2*>(o2 + (unsigned)er * ldc2_b + esg * 8));
+          }
         }
       }
     }
@@ -323,7 +341,8 @@ hipError_t launch_gemm_nt_gelu(const GemmNT& g, hipStream_t s) {
   int MT = (int)((g.M + BM - 1) / BM), NTL = (g.N + BN - 1) / BN;
   long long total = (long long)((MT + NXCD - 1) / NXCD) * NXCD * NTL;
   long long wgs = total < cus ? total : cus;
-  hipLaunchKernelGGL(gemm_nt_gelu_k, dim3((unsigned)wgs), dim3(NTH), 0, s, g, MT, NTL);
+  if (g.out2) hipLaunchKernelGGL(gemm_nt_gelu_k<true>, dim3((unsigned)wgs), dim3(NTH), 0, s, g, MT, NTL);
+  else hipLaunchKernelGGL(gemm_nt_gelu_k<false>, dim3((unsigned)wgs), dim3(NTH), 0, s, g, MT, NTL);
   return hipGetLastError();
 }
 

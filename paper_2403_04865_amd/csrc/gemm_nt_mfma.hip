@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
           float d[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) gelu_both(v[e], &v[e], &d[e]);
-          *reinterpret_cast<u32x2*>((unsigned char*)g.out2 + m * g.ldc2 + n) =
+          if (g.out2) *reinterpret_cast<u32x2*>((unsigned char*)g.out2 + m * g.ldc2 + n) =
               u32x2{dg8_pack4(d[0], d[1], d[2], d[3]), dg8_pack4(d[4], d[5], d[6], d[7])};
         }
         *reinterpret_cast<u32x4*>((bf16*)g.out + m * g.ldc + n) = pack8(v);

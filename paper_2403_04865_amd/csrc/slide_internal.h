@@ -130,7 +130,7 @@ enum {
   EPI_PLAIN = 0,       // out(T)  = acc
   EPI_BIAS = 1,        // out(T)  = acc + bias[n]
   EPI_BIAS_RESID = 2,  // out(RS) = acc + bias[n] + resid(RS)[m][n]
-  EPI_BIAS_GELU = 3,   // m = acc + bias[n];  out(T) = gelu(m);  out2 = gelu'(m) (float / one-byte code, dgelu_store<T>)
+  EPI_BIAS_GELU = 3,   // m = acc + bias[n];  out(T) = gelu(m);  out2 (may be null) = gelu'(m) (float / one-byte code, dgelu_store<T>)
   EPI_DGELU = 4,       // out(T)  = acc * pre[m][n]   (pre holds the gelu'(m) the forward stored, same format)
   EPI_PATCH = 5,       // out(RS)[rowmap(m)] = acc + bias[n] + pos[1 + m % g2][n]
   EPI_ROWTAB = 6,      // out(RS) = acc + resid(RS)[m % rperiod][n]: a table of rperiod rows added periodically (bf16 matrix-core kernels only)

@@ -273,7 +273,7 @@ void gemm_nt(Run& r, const GemmNT& g) {
   double bytes = (double)g.M * g.K * e + (double)g.N * g.K * e + (double)g.M * g.N * e;
   if (g.epi == EPI_BIAS_RESID) bytes += (double)g.M * g.N * rs_size(r.c->dt);
   if (g.epi == EPI_ROWTAB) bytes += (double)g.rperiod * g.N * rs_size(r.c->dt);
-  if (g.epi == EPI_BIAS_GELU || g.epi == EPI_DGELU) bytes += (double)g.M * g.N * dgelu_elem_size(r.c->dt);
+  if ((g.epi == EPI_BIAS_GELU && g.out2) || g.epi == EPI_DGELU) bytes += (double)g.M * g.N * dgelu_elem_size(r.c->dt);
   launch(r, K_GEMM_NT, 2.0 * g.M * g.N * g.K, bytes, [&] { return launch_gemm_nt(r.c->dt, g, r.c->use_mfma, r.s); });
 }
 
@@ -408,7 +408,8 @@ void lane_mlp_half(Run& r, const Layout& y, int l, long long n, void* xout) {
   });
 }
 
-void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay) {
+// dg: the derivative of the activation is kept for the backward
+void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg) {
   slide_ctx* c = r.c;
   hipStream_t s = r.s;
   char* ar = c->arena;
@@ -448,7 +449,7 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay) {
     {
       GemmNT g{};
       g.A = u2; g.lda = D; g.B = weight(c, wi + 2); g.ldb = D; g.M = n; g.N = F; g.K = D;
-      g.epi = EPI_BIAS_GELU; g.bias = c->params + o.fc1b; g.out = a; g.ldc = F; g.out2 = m; g.ldc2 = F;
+      g.epi = EPI_BIAS_GELU; g.bias = c->params + o.fc1b; g.out = a; g.ldc = F; g.out2 = dg ? m : nullptr; g.ldc2 = F;
       gemm_nt(r, g);
     }
     {
@@ -474,7 +475,7 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay) {
     GemmNT g{};
     g.A = u2; g.lda = D; g.B = weight(c, wi + 2); g.ldb = D; g.M = M; g.N = F; g.K = D;
     g.epi = EPI_BIAS_GELU; g.bias = c->params + o.fc1b; g.out = a; g.ldc = F;
-    g.out2 = m; g.ldc2 = F;   // m slot: gelu'(pre-activation), all the backward needs of it
+    g.out2 = dg ? m : nullptr; g.ldc2 = F;   // m slot: gelu'(pre-activation), all the backward needs of it
     gemm_nt(r, g);
   }
   if (!replay) {
@@ -532,7 +533,8 @@ int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool
   if (c->use_lane)
     launch(r, K_CLS_LANE, 0, (double)n * D * 4,
            [&] { return launch_lane_init(c->params + c->o_cls, c->params + c->o_pos, lane_xc(c, y, 0), n, D, s); });
-  for (int l = 0; l < c->L; ++l) block_fwd(r, y, l, n, false);
+  // the derivative of the activation: for the backward only, and of blocks that run again there not yet
+  for (int l = 0; l < c->L; ++l) block_fwd(r, y, l, n, false, save && (!c->cfg.recompute || l == c->L - 1));
   char* xL = ar + y.e_x + (size_t)c->L * y.s_x;
   if (c->use_lane)   // the features are the final LayerNorm of the lane's stream (its rounded copy is the CLS row of xL)
     launch(r, K_CLS_LANE, 0, (double)n * D * 8, [&] {
@@ -587,7 +589,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
     int wi = 1 + 4 * l;
     // block inputs only were kept: re-create this block's activations in the shared slots (the
     // last block's are still there from the forward)
-    if (c->cfg.recompute && l != c->L - 1) block_fwd(r, y, l, n, true);
+    if (c->cfg.recompute && l != c->L - 1) block_fwd(r, y, l, n, true, true);
     char* a = ar + y.e_a + (size_t)l * y.s_a;
     if (l == c->L - 1 && prune_last_block(c)) {
       // the gradient of the last block's output is zero away from the CLS rows: its MLP, LN2 and projection
