@@ -4,9 +4,6 @@
 namespace sl {
 
 hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s);  // gemm_mfma.hip
-hipError_t launch_gemm_tn_mfma(const GemmTN& g, hipStream_t s);
-bool gemm_tn_mfma_ok(const GemmTN& g);
-int gemm_tn_mfma_slabs(const GemmTN& g, int max_slabs);
 bool gemm_nt_f32_ok(const GemmNT& g);                            // gemm_f32.hip
 hipError_t launch_gemm_nt_f32(const GemmNT& g, hipStream_t s);
 bool gemm_tn_f32_ok(const GemmTN& g);
@@ -114,11 +111,14 @@ __global__ void __launch_bounds__(256) gemm_tn_fma_k(GemmTN g) {
   }
 }
 
-int gemm_tn_pick_slabs(int dt, const GemmTN& g, bool use_mfma, int max_slabs) {
+int gemm_tn_pick_slabs(int dt, GemmTN& g, bool use_mfma, int max_slabs) {
   const long long M = g.M;
   const int N1 = g.N1, N2 = g.N2;
   if (dt == DT_F32 && use_mfma && gemm_tn_f32_ok(g)) return gemm_tn_f32_slabs(g, max_slabs);
-  if (dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g)) return gemm_tn_mfma_slabs(g, max_slabs);
+  if (dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g)) {
+    gemm_tn_mfma_slabs(&g, 1, max_slabs);
+    return g.slabs;
+  }
   if (max_slabs > 32) max_slabs = 32;
   // enough workgroups to cover the chip several times, slabs of at least 256 rows
   long long tiles = (long long)((N1 + 127) / 128) * ((N2 + 127) / 128);
@@ -151,7 +151,7 @@ hipError_t launch_gemm_nt(int dt, const GemmNT& g, bool use_mfma, hipStream_t s)
 hipError_t launch_gemm_tn(int dt, const GemmTN& g, bool use_mfma, hipStream_t s) {
   if (g.N1 <= 0 || g.N2 <= 0 || g.slabs <= 0) return hipSuccess;
   if (dt == DT_BF16 && use_mfma && g.big) return launch_gemm_tn_big(g, s);
-  if (dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g)) return launch_gemm_tn_mfma(g, s);
+  if (dt == DT_BF16 && use_mfma && gemm_tn_mfma_ok(g)) return launch_gemm_tn_mfma(&g, 1, s);
   if (dt == DT_F32 && use_mfma && gemm_tn_f32_ok(g)) return launch_gemm_tn_f32(g, s);
   dim3 grid((g.N1 + 63) / 64, (g.N2 + 63) / 64, g.slabs);
   if (dt == DT_F32)

@@ -31,9 +31,25 @@ typedef void __attribute__((address_space(3)))* lptr_t;
 
 __device__ __attribute__((aligned(16))) unsigned int g_zero16[4];
 
-__global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(GemmTN g, int per) {
+// problems of one launch: workgroups block0 .. of problem i, row tiles of the result innermost, then column tiles, then slabs
+struct TnGroup {
+  struct Prob {
+    const bf16 *A, *B;
+    long long lda, ldb, M;
+    float *part, *cs_part;
+    int N1, N2, per, block0;
+  };
+  int n;
+  Prob p[TN_GROUP_MAX];
+};
+
+__global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(TnGroup G) {
   __shared__ __attribute__((aligned(16))) bf16 st0[STAGE], st1[STAGE];
-  const int i0 = blockIdx.x * BT, j0 = blockIdx.y * BT, slab = blockIdx.z;
+  int pi = 0;
+  while (pi + 1 < G.n && (int)blockIdx.x >= G.p[pi + 1].block0) ++pi;
+  const TnGroup::Prob& g = G.p[pi];
+  const int per = g.per, ti = (g.N1 + BT - 1) / BT, b = blockIdx.x - g.block0;
+  const int i0 = b % ti * BT, r = b / ti, tj = (g.N2 + BT - 1) / BT, j0 = r % tj * BT, slab = r / tj;
   const long long lo = (long long)slab * per, hi = lo + per < g.M ? lo + per : g.M;
   const int span = hi > lo ? (int)(hi - lo) : 0, nk = (span + BK - 1) / BK;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -43,15 +59,15 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(GemmTN g, int per) {
   const int lr = lane >> 4, lc = (((lane & 15) >> 1) ^ (2 * lr)) * 16 + (lane & 1) * 8;   // column of this lane's slot
   const bool a_ok = i0 + lc < g.N1, b_ok = j0 + lc < g.N2;   // N1, N2 are multiples of 8
   const bf16* zero = reinterpret_cast<const bf16*>(g_zero16);
-  const bf16* ap = (const bf16*)g.A + (lo + wave * 4 + lr) * g.lda + i0 + lc;
-  const bf16* bp = (const bf16*)g.B + (lo + wave * 4 + lr) * g.ldb + j0 + lc;
+  const bf16* ap = g.A + (lo + wave * 4 + lr) * g.lda + i0 + lc;
+  const bf16* bp = g.B + (lo + wave * 4 + lr) * g.ldb + j0 + lc;
   auto issue = [&](bf16* s, int kt) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < BK / 16; ++j) {
-      const int r = kt * BK + j * 16;   // + wave * 4 + lr
-      const bool ok = r + wave * 4 + lr < span;
-      const bf16* pa = ok && a_ok ? ap + (long long)r * g.lda : zero;
-      const bf16* pb = ok && b_ok ? bp + (long long)r * g.ldb : zero;
+      const int row = kt * BK + j * 16;   // + wave * 4 + lr
+      const bool ok = row + wave * 4 + lr < span;
+      const bf16* pa = ok && a_ok ? ap + (long long)row * g.lda : zero;
+      const bf16* pb = ok && b_ok ? bp + (long long)row * g.ldb : zero;
       __builtin_amdgcn_global_load_lds((gptr_t)pa, (lptr_t)(s + (j * 4 + wave) * 4 * BT), 16, 0, 0);
       __builtin_amdgcn_global_load_lds((gptr_t)pb, (lptr_t)(s + BK * BT + (j * 4 + wave) * 4 * BT), 16, 0, 0);
     }
@@ -82,7 +98,7 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(GemmTN g, int per) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  const bool do_cs = g.cs_part != nullptr && blockIdx.y == 0 && wn == 0;   // uniform per wavefront
+  const bool do_cs = g.cs_part != nullptr && j0 == 0 && wn == 0;   // uniform per wavefront
   float cs[2] = {0.f, 0.f};
 
   auto step = [&](const bf16* s, bf16* next, int kt) __attribute__((always_inline)) {
@@ -155,22 +171,42 @@ bool gemm_tn_mfma_ok(const GemmTN& g) {
          g.amap.g2 == 0 && g.bmap.g2 == 0 && g.M < (1LL << 31);
 }
 
-// Slabs: one to two workgroups per compute unit, none of less than 128 rows (64 where there are only a few tiles), since
-// every slab's result is written and read again.  M = 7289, 384 x 1536 (36 tiles), us: 4 slabs 33, 8 22.8, 11 22.4, 15 22.8,
-// 29 28.3; 384 x 384: 15 slabs 12.6, 29 10.7, 57 11.9; M = 1000, 1536 x 384: 8 slabs 8.7, 16 10.4.
-int gemm_tn_mfma_slabs(const GemmTN& g, int max_slabs) {
-  const int tiles = ((g.N1 + BT - 1) / BT) * ((g.N2 + BT - 1) / BT), rows = tiles <= 8 ? 64 : 128;
-  long long s = (384 + tiles - 1) / tiles;
-  if (s > (g.M + rows - 1) / rows) s = (g.M + rows - 1) / rows;
-  if (s > max_slabs) s = max_slabs;
-  return s < 1 ? 1 : (int)s;
+// Rows of a slab, for problems that run as one launch: about two workgroups per compute unit over all of them, no slab of less
+// than 128 rows (64 where there are only a few tiles), since every slab's result is written and read again.  M = 7289, 384 x
+// 1536 alone (36 tiles), us: 4 slabs 33, 8 22.8, 11 22.4, 15 22.8, 29 28.3; 384 x 384: 15 slabs 12.6, 29 10.7, 57 11.9; M =
+// 1000, 1536 x 384: 8 slabs 8.7, 16 10.4.  Step of 37 ViT-S tiles, the four problems of a block together, by workgroups: 256 3.79
+// ms, 384 3.70, 512 3.69, 768 3.72, 1024 3.84; each problem on its own 3.86.
+void gemm_tn_mfma_slabs(GemmTN* g, int n, int max_slabs) {
+  long long work = 0, tiles = 0;   // rows x tiles
+  for (int i = 0; i < n; ++i) {
+    const long long t = (long long)((g[i].N1 + BT - 1) / BT) * ((g[i].N2 + BT - 1) / BT);
+    work += t * g[i].M;
+    tiles += t;
+  }
+  long long per = (work + 511) / 512, least = tiles <= 8 ? 64 : 128;
+  if (per < least) per = least;
+  for (int i = 0; i < n; ++i) {
+    long long s = (g[i].M + per - 1) / per;
+    if (s > max_slabs) s = max_slabs;
+    g[i].slabs = s < 1 ? 1 : (int)s;
+  }
 }
 
-hipError_t launch_gemm_tn_mfma(const GemmTN& g, hipStream_t s) {
-  int per = (int)((g.M + g.slabs - 1) / g.slabs);
-  per = (per + BK - 1) / BK * BK;
-  dim3 grid((g.N1 + BT - 1) / BT, (g.N2 + BT - 1) / BT, g.slabs);
-  hipLaunchKernelGGL(gemm_tn_mfma_k, grid, dim3(256), 0, s, g, per);
+hipError_t launch_gemm_tn_mfma(const GemmTN* g, int n, hipStream_t s) {
+  if (n < 1 || n > TN_GROUP_MAX) return hipErrorInvalidValue;
+  TnGroup G;
+  G.n = n;
+  long long blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    TnGroup::Prob& p = G.p[i];
+    p.A = (const bf16*)g[i].A; p.lda = g[i].lda; p.B = (const bf16*)g[i].B; p.ldb = g[i].ldb; p.M = g[i].M;
+    p.N1 = g[i].N1; p.N2 = g[i].N2; p.part = g[i].part; p.cs_part = g[i].cs_part;
+    p.per = (int)(((g[i].M + g[i].slabs - 1) / g[i].slabs + BK - 1) / BK * BK);
+    p.block0 = (int)blocks;
+    blocks += (long long)((p.N1 + BT - 1) / BT) * ((p.N2 + BT - 1) / BT) * g[i].slabs;
+  }
+  if (blocks >= (1LL << 31)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gemm_tn_mfma_k, dim3((unsigned)blocks), dim3(256), 0, s, G);
   return hipGetLastError();
 }
 

@@ -163,12 +163,17 @@ struct GemmTN {
   int big;         // use the large-M kernel (slabs was chosen by gemm_tn_big_slabs)
 };
 int gemm_tn_big_slabs(const GemmTN& g, int max_slabs);   // 0: the large-M kernel does not take this problem
+// the 128 x 128 kernel, which takes several problems in one launch
+constexpr int TN_GROUP_MAX = 4;
+bool gemm_tn_mfma_ok(const GemmTN& g);
+void gemm_tn_mfma_slabs(GemmTN* g, int n, int max_slabs);   // sets the slabs of problems that run together
+hipError_t launch_gemm_tn_mfma(const GemmTN* g, int n, hipStream_t s);
 hipError_t launch_gemm_tn_big(const GemmTN& g, hipStream_t s);
 
 // All launchers enqueue on `s` and return the launch status.
 hipError_t launch_gemm_nt(int dt, const GemmNT& g, bool use_mfma, hipStream_t s);
 hipError_t launch_gemm_tn(int dt, const GemmTN& g, bool use_mfma, hipStream_t s);
-int gemm_tn_pick_slabs(int dt, const GemmTN& g, bool use_mfma, int max_slabs);
+int gemm_tn_pick_slabs(int dt, GemmTN& g, bool use_mfma, int max_slabs);
 bool gemm_tn_fuses_colsum(int dt, const GemmTN& g, bool use_mfma);  // will launch_gemm_tn fill cs_part?
 
 // weight matrices of the encoder: 0 = patch embedding, 1 .. 4 = those of block 0, whose parameters and copies repeat at a

@@ -246,10 +246,15 @@ struct Sums {
   size_t cap, used = 0;   // floats
   double bytes = 0;
   RedList list;
+  // weight gradients that wait for their launch (gemm_tn, wait): their operands stay as they are until run_group
+  struct Later { float *out, *bias_out; int accumulate; };
+  GemmTN group[TN_GROUP_MAX];
+  Later later[TN_GROUP_MAX];
+  int ngroup = 0;
   Sums(Run& run, float* b, size_t n) : r(run), base(b), cap(n) {}
   float* room(size_t floats) {
     floats = (floats + 63) & ~(size_t)63;
-    if (used + floats > cap || list.n + 6 > RED_MAX) flush();
+    if (used + floats > cap || list.n + 8 > RED_MAX) flush();
     if (floats > cap) { if (r.ok()) r.err = hipErrorInvalidValue; floats = 0; }
     float* p = base + used;
     used += floats;
@@ -286,9 +291,43 @@ void colsum(Sums& q, int elem, const void* A, long long lda, RowMap map, long lo
   q.add(part, slabs, N, N, out, accumulate);
 }
 
+// the waiting weight gradients in one launch: a bag of a few dozen tiles fills the chip with none of them alone
+void run_group(Sums& q) {
+  Run& r = q.r;
+  if (!q.ngroup) return;
+  const int n = q.ngroup;
+  q.ngroup = 0;
+  size_t all = 64;
+  for (int i = 0; i < n; ++i) all += (size_t)q.group[i].N1 * q.group[i].N2 + q.group[i].N1;
+  const size_t fit = q.cap / all;   // slabs of each that fit together
+  gemm_tn_mfma_slabs(q.group, n, fit > 64 ? 64 : fit < 1 ? 1 : (int)fit);
+  size_t need = 0;
+  double flops = 0, bytes = 0;
+  for (int i = 0; i < n; ++i) need += (size_t)q.group[i].slabs * ((size_t)q.group[i].N1 * q.group[i].N2 + q.group[i].N1);
+  float* part = q.room(need);
+  for (int i = 0; i < n; ++i) {
+    GemmTN& g = q.group[i];
+    const size_t len = (size_t)g.N1 * g.N2;
+    g.part = part;
+    part += g.slabs * len;
+    if (q.later[i].bias_out) { g.cs_part = part; part += (size_t)g.slabs * g.N1; }
+    flops += 2.0 * g.M * len;
+    bytes += (double)g.M * (g.N1 + g.N2) * 2 + (double)g.slabs * len * 4;
+  }
+  launch(r, K_GEMM_TN, flops, bytes, [&] { return launch_gemm_tn_mfma(q.group, n, r.s); });
+  for (int i = 0; i < n; ++i) {
+    const GemmTN& g = q.group[i];
+    const long long len = (long long)g.N1 * g.N2;
+    q.add(g.part, g.slabs, len, len, q.later[i].out, q.later[i].accumulate);
+    if (g.cs_part) q.add(g.cs_part, g.slabs, g.N1, g.N1, q.later[i].bias_out, q.later[i].accumulate);
+  }
+}
+
 // dW (+)= A^T B through split partials; optionally also db (+)= column sums of A
 void gemm_tn(Sums& q, const void* A, long long lda, const void* B, long long ldb, long long M, int N1, int N2, float* out,
-             int accumulate, float* bias_out = nullptr, int dt_override = -1, float* out2 = nullptr, float* bias_out2 = nullptr) {
+             int accumulate, float* bias_out = nullptr, int dt_override = -1, float* out2 = nullptr, float* bias_out2 = nullptr,
+             bool wait = false) {
+  // wait: may run together with others of its kind at run_group (no out2 then)
   // out2 / bias_out2: the result rows N1/2 .. N1-1 (and their column sums) belong to a second tensor
   Run& r = q.r;
   GemmTN g;
@@ -298,6 +337,15 @@ void gemm_tn(Sums& q, const void* A, long long lda, const void* B, long long ldb
   g.cs_part = nullptr;
   g.big = 0;
   size_t fit = (q.cap - 64) / ((size_t)N1 * N2 + N1);
+  // Together up to 900,000 rows x 128 x 384 tiles of a block's four problems (25,000 rows at D = 384), beyond which the
+  // large-M kernel is the faster one on each.  Step of 90 ViT-S tiles (17,730 rows): 6.78 ms together, 6.83 with the large-M kernel.
+  const long long block_tiles = (4LL * r.c->D * r.c->D + 2LL * r.c->D * r.c->F) / (128 * 384);
+  if (wait && M * block_tiles < 900000 && dt == DT_BF16 && r.c->use_mfma && gemm_tn_mfma_ok(g)) {
+    if (q.ngroup == TN_GROUP_MAX) run_group(q);
+    q.later[q.ngroup] = {out, bias_out, accumulate};
+    q.group[q.ngroup++] = g;
+    return;
+  }
   int bs = (dt == DT_BF16 && r.c->use_mfma) ? gemm_tn_big_slabs(g, fit > 256 ? 256 : (int)fit) : 0;
   if (bs) { g.slabs = bs; g.big = 1; }
   else g.slabs = gemm_tn_pick_slabs(dt, g, r.c->use_mfma, fit > 64 ? 64 : (int)fit);
@@ -606,8 +654,8 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
         g.epi = EPI_DGELU; g.pre = m; g.ldpre = F; g.out = dm; g.ldc = F;
         gemm_nt(r, g);
       }
-      gemm_tn(q, dxAt, TD, a, F, n, D, F, G + o.fc2W, accumulate, G + o.fc2b);
-      gemm_tn(q, dm, F, u2, D, n, F, D, G + o.fc1W, accumulate, G + o.fc1b);
+      gemm_tn(q, dxAt, TD, a, F, n, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, nullptr, nullptr, true);
+      gemm_tn(q, dm, F, u2, D, n, F, D, G + o.fc1W, accumulate, G + o.fc1b, -1, nullptr, nullptr, true);
       {
         GemmNT g{};
         g.A = dm; g.lda = F; g.B = weight_t(c, wi + 2); g.ldb = F; g.M = n; g.N = D; g.K = F;
@@ -615,7 +663,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
         gemm_nt(r, g);
       }
       ln_bwd(q, xmid, TD, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, TD, n, accumulate);
-      gemm_tn(q, dxBt, TD, O, TD, n, D, D, G + o.projW, accumulate, G + o.projb);
+      gemm_tn(q, dxBt, TD, O, TD, n, D, D, G + o.projW, accumulate, G + o.projb, -1, nullptr, nullptr, true);
       {
         GemmNT g{};
         g.A = dxBt; g.lda = TD; g.B = weight_t(c, wi + 1); g.ldb = D; g.M = n; g.N = D; g.K = D;
@@ -624,13 +672,14 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       }
       launch(r, K_ATTN_BWD, 10.0 * n * c->H * (double)T * c->dh, (double)M * 7 * D * e,
              [&] { return launch_attn_bwd(dt, qkv, O, lse, du, dqkv, n, T, c->H, c->dh, c->use_mfma, s, true, (float*)(ar + y.e_dl)); });
-      gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb);
+      gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb, -1, nullptr, nullptr, true);
       {
         GemmNT g{};
         g.A = dqkv; g.lda = 3 * D; g.B = weight_t(c, wi + 0); g.ldb = 3 * D; g.M = M; g.N = D; g.K = 3 * D;
         g.epi = EPI_PLAIN; g.out = du; g.ldc = D;
         gemm_nt(r, g);
       }
+      run_group(q);   // LN1's backward overwrites dxA
       ln_bwd(q, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, accumulate, false, periodic ? T : 0);
       continue;
     }
@@ -641,7 +690,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       g.epi = EPI_DGELU; g.pre = m; g.ldpre = F; g.out = dm; g.ldc = F;
       gemm_nt(r, g);
     }
-    gemm_tn(q, dxAt, D, a, F, M, D, F, G + o.fc2W, accumulate, G + o.fc2b);
+    gemm_tn(q, dxAt, D, a, F, M, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, nullptr, nullptr, true);
     {
       GemmNT g{};
       g.A = dm; g.lda = F; g.B = weight_t(c, wi + 2); g.ldb = F; g.M = M; g.N = D; g.K = F;
@@ -649,9 +698,9 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       gemm_nt(r, g);
     }
     ln_bwd(q, xmid, D, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, D, M, accumulate);
-    gemm_tn(q, dm, F, u2, D, M, F, D, G + o.fc1W, accumulate, G + o.fc1b);
+    gemm_tn(q, dm, F, u2, D, M, F, D, G + o.fc1W, accumulate, G + o.fc1b, -1, nullptr, nullptr, true);
     // ---- attention half: x_mid = x_in + attn(LN1(x_in)) Wo^T + bo
-    gemm_tn(q, dxBt, D, O, D, M, D, D, G + o.projW, accumulate, G + o.projb);
+    gemm_tn(q, dxBt, D, O, D, M, D, D, G + o.projW, accumulate, G + o.projb, -1, nullptr, nullptr, true);
     {
       GemmNT g{};
       g.A = dxBt; g.lda = D; g.B = weight_t(c, wi + 1); g.ldb = D; g.M = M; g.N = D; g.K = D;
@@ -666,8 +715,9 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       g.epi = EPI_PLAIN; g.out = du; g.ldc = D;
       gemm_nt(r, g);
     }
+    gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb, -1, nullptr, nullptr, true);
+    run_group(q);   // LN1's backward overwrites dxA
     ln_bwd(q, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, accumulate);
-    gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb);
   }
   // ---- token assembly: x0[n,0] = cls + pos[0]; x0[n,1+j] = patch_j W_pe^T + b_pe + pos[1+j]
   {
