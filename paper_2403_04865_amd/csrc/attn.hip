@@ -13,9 +13,9 @@ hipError_t launch_attn_bwd_mfma(const void* qkv, const void* O, const float* lse
                                 long long n, int T, int H, int dh, int cls_only, hipStream_t s);
 bool attn_mfma_ok(int T, int dh);
 bool attn_f32_ok(int T, int dh);
-hipError_t launch_attn_fwd_f32(const float* qkv, float* O, float* lse, long long n, int T, int H, int dh, hipStream_t s);
+hipError_t launch_attn_fwd_f32(const float* qkv, float* O, float* lse, long long n, int T, int H, int dh, int cls_only, hipStream_t s);
 hipError_t launch_attn_bwd_f32(const float* qkv, const float* O, const float* lse, const float* dO, float* dqkv, long long n,
-                               int T, int H, int dh, hipStream_t s);
+                               int T, int H, int dh, int cls_only, hipStream_t s);
 
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) attn_fwd_k(const T* __restrict__ qkv, T* __restrict__ O,
@@ -167,14 +167,14 @@ static hipError_t set_lds(K kernel, size_t bytes) {
   return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-bool attn_cls_only_ok(int dt, int T, int dh, bool use_mfma) { return dt == DT_BF16 && use_mfma && attn_mfma_ok(T, dh); }
+bool attn_cls_only_ok(int dt, int T, int dh, bool use_mfma) { return use_mfma && (dt == DT_BF16 ? attn_mfma_ok(T, dh) : attn_f32_ok(T, dh)); }
 
 hipError_t launch_attn_fwd(int dt, const void* qkv, void* O, float* lse, long long n, int T, int H, int dh,
                            bool use_mfma, hipStream_t s, bool cls_only) {
   if (n <= 0) return hipSuccess;
   if (dt == DT_BF16 && use_mfma && attn_mfma_ok(T, dh)) return launch_attn_fwd_mfma(qkv, O, lse, n, T, H, dh, cls_only, s);
+  if (dt == DT_F32 && use_mfma && attn_f32_ok(T, dh)) return launch_attn_fwd_f32((const float*)qkv, (float*)O, lse, n, T, H, dh, cls_only, s);
   if (cls_only) return hipErrorInvalidValue;
-  if (dt == DT_F32 && use_mfma && attn_f32_ok(T, dh)) return launch_attn_fwd_f32((const float*)qkv, (float*)O, lse, n, T, H, dh, s);
   size_t lds = attn_lds_bytes(T, dh);
   dim3 grid((unsigned)(n * H));
   hipError_t e = hipSuccess;
@@ -197,9 +197,9 @@ hipError_t launch_attn_bwd(int dt, const void* qkv, const void* O, const float* 
     if (!delta_ws) return hipErrorInvalidValue;
     return launch_attn_bwd_mfma(qkv, O, lse, dO, dqkv, delta_ws, n, T, H, dh, cls_only, s);
   }
-  if (cls_only) return hipErrorInvalidValue;
   if (dt == DT_F32 && use_mfma && attn_f32_ok(T, dh))
-    return launch_attn_bwd_f32((const float*)qkv, (const float*)O, lse, (const float*)dO, (float*)dqkv, n, T, H, dh, s);
+    return launch_attn_bwd_f32((const float*)qkv, (const float*)O, lse, (const float*)dO, (float*)dqkv, n, T, H, dh, cls_only, s);
+  if (cls_only) return hipErrorInvalidValue;
   size_t lds = attn_lds_bytes(T, dh);
   dim3 grid((unsigned)(n * H));
   hipError_t e = hipSuccess;

@@ -85,10 +85,10 @@ __device__ __forceinline__ void store_t(float* row, const f32x16 (&acc)[DH / 32]
     }
 }
 
-// grid (tiles * H, parts): part y takes the query blocks y * W + w, W wavefronts
+// grid (tiles * H, parts): part y takes the query blocks y * W + w, W wavefronts; cls_only: query block 0 only
 template <int DH>
 __global__ void __launch_bounds__(512) attn_fwd_f32_k(const float* __restrict__ qkv, float* __restrict__ O, float* __restrict__ lse,
-                                                      int Tn, int H) {
+                                                      int Tn, int H, int cls_only) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   const int TP = (Tn + 31) & ~31, h = blockIdx.x % H;
   const long long tile = blockIdx.x / H;
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(512) attn_fwd_f32_k(const float* __restrict__ 
   f32x4 qf[DH / 8];
   frag<DH>(qf, base + (long long)i * 3 * D, i < Tn, half, 1.0f / sqrtf((float)DH));
   __syncthreads();
-  if (qb * 32 >= Tn) return;
+  if (qb * 32 >= Tn || (cls_only && qb > 0)) return;
   f32x16 o[DH / 32];
 #pragma unroll
   for (int nb = 0; nb < DH / 32; ++nb) o[nb] = zero16();
@@ -138,11 +138,12 @@ __global__ void __launch_bounds__(512) attn_fwd_f32_k(const float* __restrict__ 
   if (half == 0) lse[(tile * H + h) * Tn + i] = m + logf(l);
 }
 
-// grid (tiles * H, 2 * parts): even y the dQ of a part's query blocks, odd y the dK and dV of its key blocks
+// grid (tiles * H, 2 * parts): even y the dQ of a part's query blocks, odd y the dK and dV of its key blocks.  cls_only: query 0
+// alone carries an output gradient (no other row of dO is read), dQ is zero for every other query
 template <int DH>
 __global__ void __launch_bounds__(512) attn_bwd_f32_k(const float* __restrict__ qkv, const float* __restrict__ O,
                                                       const float* __restrict__ lse, const float* __restrict__ dO,
-                                                      float* __restrict__ dqkv, int Tn, int H) {
+                                                      float* __restrict__ dqkv, int Tn, int H, int cls_only) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   const int TP = (Tn + 31) & ~31, h = blockIdx.x % H;
   const long long tile = blockIdx.x / H;
@@ -156,17 +157,25 @@ __global__ void __launch_bounds__(512) attn_bwd_f32_k(const float* __restrict__ 
   float *Xs = lds, *Ys = lds + TP * (DH + PAD), *ls = Ys + TP * (DH + PAD), *dl = ls + TP;
   const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
   const int blk = (blockIdx.y >> 1) * (blockDim.x >> 6) + (threadIdx.x >> 6), i = blk * 32 + col;
-  const bool ok = i < Tn;
+  const bool ok = i < Tn, gok = cls_only ? i == 0 : ok;   // rows that exist, rows of dO that are defined
+  const int TG = cls_only ? 1 : Tn, TQ = cls_only ? 32 : TP;
   if ((blockIdx.y & 1) == 0) {
+    if (cls_only && blockIdx.y) {   // uniform: later blocks of queries
+      if (ok) {
+        const f32x16 z[DH / 32] = {};
+        store_t<DH>(dbase + (long long)i * 3 * D, z, half, 1.f);
+      }
+      return;
+    }
     stage<DH>(Xs, base + D, 3LL * D, Tn, TP, 1.f);
     stage<DH>(Ys, base + 2 * D, 3LL * D, Tn, TP, 1.f);
     f32x4 qf[DH / 8], gf[DH / 8];
     frag<DH>(qf, base + (long long)i * 3 * D, ok, half, scale);
-    frag<DH>(gf, gob + (long long)i * D, ok, half, 1.f);
+    frag<DH>(gf, gob + (long long)i * D, gok, half, 1.f);
     float delta = 0.f;
 #pragma unroll
     for (int s = 0; s < DH / 8; ++s)
-      if (ok) {
+      if (gok) {
         const f32x4 t = ld4(ob + (long long)i * D + 8 * s + 4 * half) * gf[s];
         delta += (t[0] + t[1]) + (t[2] + t[3]);
       }
@@ -177,7 +186,7 @@ __global__ void __launch_bounds__(512) attn_bwd_f32_k(const float* __restrict__ 
     f32x16 dq[DH / 32];
 #pragma unroll
     for (int nb = 0; nb < DH / 32; ++nb) dq[nb] = zero16();
-    for (int k0 = 0; k0 < TP; k0 += 32) {
+    for (int k0 = 0; k0 < (cls_only && blk > 0 ? 0 : TP); k0 += 32) {
       f32x16 s = scores<DH>(Xs, qf, k0 + col, half);
       const f32x16 dp = scores<DH>(Ys, gf, k0 + col, half);
 #pragma unroll
@@ -190,14 +199,14 @@ __global__ void __launch_bounds__(512) attn_bwd_f32_k(const float* __restrict__ 
     if (ok) store_t<DH>(dbase + (long long)i * 3 * D, dq, half, scale);
     return;
   }
-  stage<DH>(Xs, base, 3LL * D, Tn, TP, scale);
-  stage<DH>(Ys, gob, D, Tn, TP, 1.f);
-  for (int j = threadIdx.x; j < TP; j += blockDim.x) ls[j] = j < Tn ? lb[j] : INFINITY;   // queries past the end: P = 0
+  stage<DH>(Xs, base, 3LL * D, Tn < TQ ? Tn : TQ, TQ, scale);
+  stage<DH>(Ys, gob, D, TG, TQ, 1.f);
+  for (int j = threadIdx.x; j < TQ; j += blockDim.x) ls[j] = j < Tn ? lb[j] : INFINITY;   // queries past the end: P = 0
   constexpr int V = DH / 4;
-  for (int k = threadIdx.x; k < TP * V; k += blockDim.x) {   // V neighbouring lanes share a row, TP * V is a multiple of 64
+  for (int k = threadIdx.x; k < TQ * V; k += blockDim.x) {   // V neighbouring lanes share a row, TQ * V is a multiple of 64
     const int j = k / V, e = (k % V) * 4;
     float d = 0.f;
-    if (j < Tn) {
+    if (j < TG) {
       const f32x4 t = ld4(gob + (long long)j * D + e) * ld4(ob + (long long)j * D + e);
       d = (t[0] + t[1]) + (t[2] + t[3]);
     }
@@ -213,7 +222,7 @@ __global__ void __launch_bounds__(512) attn_bwd_f32_k(const float* __restrict__ 
   f32x16 dk[DH / 32], dv[DH / 32];
 #pragma unroll
   for (int nb = 0; nb < DH / 32; ++nb) dk[nb] = dv[nb] = zero16();
-  for (int q0 = 0; q0 < TP; q0 += 32) {
+  for (int q0 = 0; q0 < TQ; q0 += 32) {
     f32x16 p = scores<DH>(Xs, kf, q0 + col, half);
     f32x16 ds = scores<DH>(Ys, vf, q0 + col, half);
 #pragma unroll
@@ -259,28 +268,28 @@ int waves(long long heads, int blocks, int roles) {
 
 bool attn_f32_ok(int T, int dh) { return (dh == 64 || dh == 32) && lds_bytes(T, dh) <= 160 * 1024; }
 
-hipError_t launch_attn_fwd_f32(const float* qkv, float* O, float* lse, long long n, int T, int H, int dh, hipStream_t s) {
-  const int nb = (T + 31) / 32, w = waves(n * H, nb, 1);
+hipError_t launch_attn_fwd_f32(const float* qkv, float* O, float* lse, long long n, int T, int H, int dh, int cls_only, hipStream_t s) {
+  const int nb = (T + 31) / 32, w = cls_only ? (nb < 4 ? nb : 4) : waves(n * H, nb, 1);
   const size_t lds = lds_bytes(T, dh);
   if (n * H >= (1LL << 31)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(n * H), (nb + w - 1) / w), block(64 * w);
+  const dim3 grid((unsigned)(n * H), cls_only ? 1 : (nb + w - 1) / w), block(64 * w);
   hipError_t e = dh == 64 ? set_lds(attn_fwd_f32_k<64>, lds) : set_lds(attn_fwd_f32_k<32>, lds);
   if (e != hipSuccess) return e;
-  if (dh == 64) hipLaunchKernelGGL(attn_fwd_f32_k<64>, grid, block, lds, s, qkv, O, lse, T, H);
-  else hipLaunchKernelGGL(attn_fwd_f32_k<32>, grid, block, lds, s, qkv, O, lse, T, H);
+  if (dh == 64) hipLaunchKernelGGL(attn_fwd_f32_k<64>, grid, block, lds, s, qkv, O, lse, T, H, cls_only);
+  else hipLaunchKernelGGL(attn_fwd_f32_k<32>, grid, block, lds, s, qkv, O, lse, T, H, cls_only);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd_f32(const float* qkv, const float* O, const float* lse, const float* dO, float* dqkv, long long n,
-                               int T, int H, int dh, hipStream_t s) {
+                               int T, int H, int dh, int cls_only, hipStream_t s) {
   const int nb = (T + 31) / 32, w = waves(n * H, nb, 2);
   const size_t lds = lds_bytes(T, dh);
   if (n * H >= (1LL << 31)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(n * H), 2 * ((nb + w - 1) / w)), block(64 * w);
   hipError_t e = dh == 64 ? set_lds(attn_bwd_f32_k<64>, lds) : set_lds(attn_bwd_f32_k<32>, lds);
   if (e != hipSuccess) return e;
-  if (dh == 64) hipLaunchKernelGGL(attn_bwd_f32_k<64>, grid, block, lds, s, qkv, O, lse, dO, dqkv, T, H);
-  else hipLaunchKernelGGL(attn_bwd_f32_k<32>, grid, block, lds, s, qkv, O, lse, dO, dqkv, T, H);
+  if (dh == 64) hipLaunchKernelGGL(attn_bwd_f32_k<64>, grid, block, lds, s, qkv, O, lse, dO, dqkv, T, H, cls_only);
+  else hipLaunchKernelGGL(attn_bwd_f32_k<32>, grid, block, lds, s, qkv, O, lse, dO, dqkv, T, H, cls_only);
   return hipGetLastError();
 }
 

@@ -226,7 +226,7 @@ bool ln_bwd_emits_u(int dt, const void* x, long long x_stride, const void* dy, l
                     const void* u_out, long long u_stride);
 
 // Attention over qkv [n*T, 3D] (T): O [n*T, D] (T), lse [n,H,T] fp32.
-// cls_only (bf16 MFMA kernels only, see attn_cls_only_ok): only query 0 of every tile is wanted (forward: the rest
+// cls_only (matrix-core kernels only, see attn_cls_only_ok): only query 0 of every tile is wanted (forward: the rest
 // of O and lse beyond the first block of 32 queries is not written) / only query 0 carries an output gradient
 // (backward: other rows of dO are not read; dqkv is complete: dQ is zero for every other query).
 bool attn_cls_only_ok(int dt, int T, int dh, bool use_mfma);
