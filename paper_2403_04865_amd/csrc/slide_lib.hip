@@ -15,7 +15,7 @@ using namespace sl;
 // Work space of mil_pool_fwd_static: one copy per device, part of the loaded code object (nothing is allocated for
 // it at run time).  Host code never uses this name as an address: it asks the runtime for the device address once
 // per device (static_scratch below) and passes that pointer on.
-static __device__ __align__(256) unsigned char scratch[SLIDE_STATIC_POOL_BYTES];
+static __device__ __align__(256) unsigned char scratch[SLIDE_STATIC_POOL_BYTES + 256];
 
 thread_local int sl::g_last_hip = 0;
 
@@ -1039,7 +1039,10 @@ int mil_pool_fwd_static(const slide_ctx* c, const float* params, const void* fea
   const size_t o_a = take((size_t)N * 4), o_part = take((size_t)1024 * (2 + D) * 8);
   const size_t o_scal = take(pool_scal_floats(C, D) * 4), o_vub = take((size_t)2 * 2 * Mh * D * 2);
   const size_t o_tmp = take((size_t)N * 4);
-  if (cur > SLIDE_STATIC_POOL_BYTES) return SLIDE_EARENA;
+  // the scalars' alignment and the counter behind them may take one more 256-byte piece, for which the array has room: the
+  // rows that fit SLIDE_STATIC_POOL_BYTES are counted without it
+  const size_t extra = align256(pool_scal_floats(C, D) * 4) - align256((size_t)(4 + 2 * C + 3 * D) * 4);
+  if (cur - extra > SLIDE_STATIC_POOL_BYTES) return SLIDE_EARENA;
   hipError_t e;
   char* ws = (char*)static_scratch(&e);
   if (!ws) { g_last_hip = (int)e; return SLIDE_EHIP; }
@@ -1051,7 +1054,7 @@ int mil_pool_fwd_static(const slide_ctx* c, const float* params, const void* fea
   p.blocks = pool_blocks(N);
   p.vub = ws + o_vub; p.use_mfma = c->use_mfma && c->dt == DT_BF16;
   p.a_tmp = (float*)(ws + o_tmp);   // the last piece: it may use what is left of the array
-  p.a_room = (SLIDE_STATIC_POOL_BYTES - o_tmp) / 4;
+  p.a_room = (sizeof(scratch) - o_tmp) / 4;
   p.ticket = (unsigned*)(p.scal + pool_scal_floats(C, D) - 1);
   p.loss = loss; p.logits = logits; p.alpha = alpha;
   (void)hipGetLastError();

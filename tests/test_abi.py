@@ -101,6 +101,25 @@ def _paper_capacity():
     return out
 
 
+def test_static_pool_row_limit():
+    """The rows that mil_pool_fwd_static takes: logits twice, 1,024 partials, scalars and the bf16 weights, each on a
+    256-byte boundary, within SLIDE_STATIC_POOL_BYTES.  With 29 or 30 classes the scalars end at such a boundary."""
+    import torch
+    from paper_2403_04865_amd import SlideConfig, SlideLib
+    if torch.cuda.is_available():
+        pytest.skip("passes pointers that no kernel may read")
+    up = lambda b: (b + 255) // 256 * 256
+    D, Mh = 960, 576
+    for C_ in (1, 28, 29, 30, 31):
+        L = SlideLib(SlideConfig(32, 8, D, 0, 15, 4, Mh, C_, dtype=1))
+        room = (12 << 20) - up(1024 * (2 + D) * 8) - up((4 + 2 * C_ + 3 * D) * 4) - up(4 * Mh * D * 2)
+        rows = room // 512 * 64
+        buf = C.create_string_buffer(64)
+        call = lambda n: L.lib.mil_pool_fwd_static(L.ctx, C.addressof(buf), C.addressof(buf), n, 0, None, None, None, None)
+        assert call(rows) == -5, C_        # SLIDE_EHIP: no device here, the sizes were accepted
+        assert call(rows + 1) == -2, C_    # SLIDE_EARENA
+
+
 def test_paper_capacity_arithmetic_and_arena_accounting():
     """The paper's device counts follow from its tiles-per-device figure (Method), and the arena accounting of this
     library (host arithmetic, no GPU) must not need more memory per ViT-B tile than the paper's framework did."""
