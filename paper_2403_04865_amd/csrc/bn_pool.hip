@@ -35,81 +35,86 @@ __device__ __forceinline__ void ld8f(const float* p, float (&v)[8]) {
   v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
 }
 
-constexpr int BN_MAX_BLOCKS = 2048, BN_MAX_RUNS = 4096;
+constexpr int BN_MAX_BLOCKS = 4096, BN_MAX_RUNS = 4096;
+constexpr int TILE_RUN = 16;   // row tiles whose sums are added in float (more where that makes more than BN_MAX_RUNS runs)
 
-// Two per-channel sums over the rows of one workgroup's range.  F(row pointer offset, channel base) fetches what 8 channels
-// of one row need, G(fetched, channel base, out a[8], out b[8]) yields their two summands; four rows of a thread are in
-// flight (with one row the loop waits for memory once per row: 76 us for 14,700 rows of 2048 channels against 30).
-template <typename F, typename G>
+// Rows m, m + rpp, ... below hi in groups of U whose loads are in flight together; returns the first row that is left.
+template <int U, typename F, typename G>
+__device__ __forceinline__ long long row_groups(long long m, long long hi, int rpp, F f, G g) {
+  for (; m + (U - 1) * rpp < hi; m += U * rpp) {
+    decltype(f(0LL)) t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = f(m + u * rpp);
+#pragma unroll
+    for (int u = 0; u < U; ++u) g(t[u]);
+  }
+  return m;
+}
+
+// Two per-channel sums over the rows blockIdx.x's range and the channels of blockIdx.y.  F(row) fetches what 8 channels of
+// one row need, G(fetched, out a[8], out b[8]) yields their two summands.  Up to U rows of a thread are in flight: with one
+// the loop waits for memory once per row.  How rows are dealt to ranges and to a range's threads does not depend on U or
+// on the channel split, and a channel's sums neither.
+template <int U, typename F, typename G>
 __device__ __forceinline__ void two_sums(long long M, int C, float* part, F f, G g) {
   __shared__ float red[2][256 * 8];
-  const int tcols = C >> 3, rpp = 256 / tcols;          // threads per row, rows per pass
-  const int tc = threadIdx.x % tcols, tr = threadIdx.x / tcols;
+  const int tcols = (C >> 3) / gridDim.y, rpp = blockDim.x / tcols;   // threads per row, rows per pass
+  const int tr = threadIdx.x / tcols, Cw = tcols * 8, c0 = blockIdx.y * Cw;
   const long long per = (M + gridDim.x - 1) / gridDim.x;
   const long long lo = (long long)blockIdx.x * per, hi = lo + per < M ? lo + per : M;
   float s[8], q[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) s[e] = q[e] = 0.f;
-  constexpr int U = 4;
-  long long m = lo + tr;
-  for (; m + (U - 1) * rpp < hi; m += U * rpp) {
-    decltype(f(0LL)) t[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = f((m + u * rpp) * C + tc * 8);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float a[8], b[8];
-      g(t[u], tc * 8, a, b);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) { s[e] += a[e]; q[e] += b[e]; }
-    }
-  }
-  for (; m < hi; m += rpp) {
+  auto add = [&](const auto& t) __attribute__((always_inline)) {
     float a[8], b[8];
-    g(f(m * C + tc * 8), tc * 8, a, b);
+    g(t, a, b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) { s[e] += a[e]; q[e] += b[e]; }
-  }
+  };
+  long long m = row_groups<U>(lo + tr, hi, rpp, f, add);
+  if constexpr (U > 4) m = row_groups<4>(m, hi, rpp, f, add);
+  row_groups<1>(m, hi, rpp, f, add);
 #pragma unroll
   for (int e = 0; e < 8; ++e) { red[0][threadIdx.x * 8 + e] = s[e]; red[1][threadIdx.x * 8 + e] = q[e]; }
   __syncthreads();
-  // thread (tr, tc) -> flat index (tr * tcols + tc) * 8 + e = tr * C + channel
-  for (int ch = threadIdx.x; ch < C; ch += 256) {
+  // thread (tr, tc) -> flat index (tr * tcols + tc) * 8 + e = tr * Cw + channel
+  for (int ch = threadIdx.x; ch < Cw; ch += blockDim.x) {
     float a = 0.f, b = 0.f;
-    for (int r = 0; r < rpp; ++r) { a += red[0][r * C + ch]; b += red[1][r * C + ch]; }
-    part[((long long)blockIdx.x * 2 + 0) * C + ch] = a;
-    part[((long long)blockIdx.x * 2 + 1) * C + ch] = b;
+    for (int r = 0; r < rpp; ++r) { a += red[0][r * Cw + ch]; b += red[1][r * Cw + ch]; }
+    part[((long long)blockIdx.x * 2 + 0) * C + c0 + ch] = a;
+    part[((long long)blockIdx.x * 2 + 1) * C + c0 + ch] = b;
   }
 }
 
 // The partial sums of 16 channels, added in double by one workgroup of 1024: group g of 16 lanes takes partials g, g + 64,
 // ... in order (64 bytes of a partial row per group), then the 64 groups' sums are added in a fixed order (the same bits on
-// every run).  RUN > 1: a partial is a run of that many rows of `part` (`blocks` rows in all), added in float first.  Thread
-// t returns those of channel ch0 + t % 16.
-template <int RUN>
-__device__ __forceinline__ void channel_sums(const float* __restrict__ part, int blocks, int C, int ch0, double& s, double& q) {
+// every run).  RUNS: a partial is a run of `run` rows of `part` (`blocks` rows in all), added in float first.  Thread t
+// returns those of channel ch0 + t % 16.
+template <bool RUNS>
+__device__ __forceinline__ void channel_sums(const float* __restrict__ part, int blocks, int run, int C, int ch0, double& s,
+                                             double& q) {
   __shared__ double rs[64][17], rq[64][17], ws[8][17], wq[8][17];
   const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
   s = 0.0; q = 0.0;
   const float* p = part + ch0 + c;
-  if constexpr (RUN == 1) {
+  if constexpr (!RUNS) {
 #pragma unroll 8
     for (int b = g; b < blocks; b += 64) {
       s += (double)p[((long long)b * 2) * C];
       q += (double)p[((long long)b * 2 + 1) * C];
     }
   } else {
-    for (int b = g * RUN; b < blocks; b += 64 * RUN) {
-      float v[RUN], w[RUN];
+    for (int b = g * run; b < blocks; b += 64 * run) {
+      const int n = run < blocks - b ? run : blocks - b;
+      float v[TILE_RUN], w[TILE_RUN];
 #pragma unroll
-      for (int i = 0; i < RUN; ++i) {
-        const bool ok = b + i < blocks;
-        v[i] = ok ? p[((long long)(b + i) * 2) * C] : 0.f;
-        w[i] = ok ? p[((long long)(b + i) * 2 + 1) * C] : 0.f;
+      for (int i = 0; i < TILE_RUN; ++i) {
+        v[i] = i < n ? p[((long long)(b + i) * 2) * C] : 0.f;
+        w[i] = i < n ? p[((long long)(b + i) * 2 + 1) * C] : 0.f;
       }
       float a = 0.f, d = 0.f;
 #pragma unroll
-      for (int i = 0; i < RUN; ++i) { a += v[i]; d += w[i]; }
+      for (int i = 0; i < TILE_RUN; ++i) { a += v[i]; d += w[i]; }
       s += (double)a;
       q += (double)d;
     }
@@ -130,14 +135,12 @@ __device__ __forceinline__ void channel_sums(const float* __restrict__ part, int
   for (int w = 0; w < 8; ++w) { s += ws[w][c]; q += wq[w][c]; }
 }
 
-constexpr int TILE_RUN = 16;   // row tiles whose sums are added in float
-
-template <int RUN>
-__global__ void __launch_bounds__(1024) bn_stats_final_k(const float* __restrict__ part, int blocks, long long M, int C,
+template <bool RUNS>
+__global__ void __launch_bounds__(1024) bn_stats_final_k(const float* __restrict__ part, int blocks, int run, long long M, int C,
                                                          const float* __restrict__ gamma, const float* __restrict__ beta,
                                                          float eps, float* __restrict__ stats) {
   double s, q;
-  channel_sums<RUN>(part, blocks, C, blockIdx.x * 16, s, q);   // C is a multiple of 16
+  channel_sums<RUNS>(part, blocks, run, C, blockIdx.x * 16, s, q);   // C is a multiple of 16
   if (threadIdx.x >= 16) return;
   const int ch = blockIdx.x * 16 + threadIdx.x;
   const double mean = s / (double)M;
@@ -151,17 +154,21 @@ __global__ void __launch_bounds__(1024) bn_stats_final_k(const float* __restrict
   stats[3 * C + ch] = (float)((double)beta[ch] - mean * a);
 }
 
-// tile_part[tiles][2 C] -> part[ceil(tiles / TILE_RUN)][2 C]: 64 columns and four runs of tiles per workgroup
-__global__ void __launch_bounds__(256) bn_tiles_part_k(const float* __restrict__ tp, int tiles, int C2, float* __restrict__ part) {
+// tile_part[tiles][2 C] -> part[ceil(tiles / len)][2 C]: 64 columns and four runs of len tiles per workgroup
+__global__ void __launch_bounds__(256) bn_tiles_part_k(const float* __restrict__ tp, int tiles, int len, int C2,
+                                                        float* __restrict__ part) {
   const int col = blockIdx.x * 64 + (threadIdx.x & 63);   // C2 is a multiple of 128
-  const int run = blockIdx.y * 4 + (threadIdx.x >> 6), lo = run * TILE_RUN;
+  const int run = blockIdx.y * 4 + (threadIdx.x >> 6), lo = run * len;
   if (lo >= tiles) return;
-  float v[TILE_RUN];
-#pragma unroll
-  for (int i = 0; i < TILE_RUN; ++i) v[i] = lo + i < tiles ? tp[(long long)(lo + i) * C2 + col] : 0.f;
+  const int n = len < tiles - lo ? len : tiles - lo;
   float a = 0.f;
+  for (int t = 0; t < n; t += TILE_RUN) {
+    float v[TILE_RUN];
 #pragma unroll
-  for (int i = 0; i < TILE_RUN; ++i) a += v[i];
+    for (int i = 0; i < TILE_RUN; ++i) v[i] = t + i < n ? tp[(long long)(lo + t + i) * C2 + col] : 0.f;
+#pragma unroll
+    for (int i = 0; i < TILE_RUN; ++i) a += v[i];
+  }
   part[(long long)run * C2 + col] = a;
 }
 
@@ -226,28 +233,30 @@ __global__ void __launch_bounds__(256) bn_apply_k(const bf16* __restrict__ x, lo
   }
 }
 
+template <int U>
 __global__ void __launch_bounds__(256) bn_bwd_part_k(const bf16* __restrict__ dy, const unsigned char* __restrict__ mask,
                                                       const bf16* __restrict__ x, long long M, int C,
                                                       const float* __restrict__ stats, float* __restrict__ part) {
   struct Row { u32x4 d, x; unsigned m; };
-  float mean[8], rstd[8];   // of this thread's 8 channels
-  {
-    const int c0 = (int)(threadIdx.x & ((C >> 3) - 1)) * 8;
-    ld8f(stats + c0, mean);
-    ld8f(stats + C + c0, rstd);
-  }
-  two_sums(M, C, part,
-           [&](long long off) __attribute__((always_inline)) { return Row{ld16(dy + off), ld16(x + off), mask ? (unsigned)mask[off >> 3] : 0xffu}; },
-           [&](const Row& t, int, float (&a)[8], float (&b)[8]) __attribute__((always_inline)) {
-             float xv[8];
-             unpack8(t.d, a);
-             unpack8(t.x, xv);
+  const int tcols = (C >> 3) / gridDim.y, c0 = ((int)blockIdx.y * tcols + (int)threadIdx.x % tcols) * 8;   // this thread's 8 channels
+  float mean[8], rstd[8];
+  ld8f(stats + c0, mean);
+  ld8f(stats + C + c0, rstd);
+  two_sums<U>(M, C, part,
+              [&](long long m) __attribute__((always_inline)) {
+                const long long off = m * C + c0;
+                return Row{ld16(dy + off), ld16(x + off), mask ? (unsigned)mask[off >> 3] : 0xffu};
+              },
+              [&](const Row& t, float (&a)[8], float (&b)[8]) __attribute__((always_inline)) {
+                float xv[8];
+                unpack8(t.d, a);
+                unpack8(t.x, xv);
 #pragma unroll
-             for (int e = 0; e < 8; ++e) {
-               a[e] = (t.m >> e) & 1u ? a[e] : 0.f;
-               b[e] = a[e] * ((xv[e] - mean[e]) * rstd[e]);
-             }
-           });
+                for (int e = 0; e < 8; ++e) {
+                  a[e] = (t.m >> e) & 1u ? a[e] : 0.f;
+                  b[e] = a[e] * ((xv[e] - mean[e]) * rstd[e]);
+                }
+              });
 }
 
 // coef[0][c] = dbeta / M, coef[1][c] = dgamma / M; parameter gradients written or added to
@@ -255,7 +264,7 @@ __global__ void __launch_bounds__(1024) bn_bwd_final_k(const float* __restrict__
                                                        float* __restrict__ coef, float* __restrict__ dgamma,
                                                        float* __restrict__ dbeta, int accumulate) {
   double s, q;
-  channel_sums<1>(part, blocks, C, blockIdx.x * 16, s, q);   // C is a multiple of 16
+  channel_sums<false>(part, blocks, 1, C, blockIdx.x * 16, s, q);   // C is a multiple of 16
   if (threadIdx.x >= 16) return;
   const int ch = blockIdx.x * 16 + threadIdx.x;
   coef[ch] = (float)(s / (double)M);
@@ -426,25 +435,32 @@ unsigned stream_grid(long long chunks) {
 
 }  // namespace
 
-// workgroups of a sum over rows: sixteen passes of 2,048 elements each, at most eight workgroups per compute unit
+// Ranges of a sum over rows.  Like the cut of the statistics (launch_bn_stats_tiles) this one shows in the gradients of a
+// deep network: they are sums of terms that cancel, and the last bit of a mean moves the bf16 rounding of every dx below it.
 int bn_blocks(long long M, int C) {
-  long long b = (M * C + 16 * 2048 - 1) / (16 * 2048);
+  (void)C;
+  const long long b = M / 128;
   return (int)(b < 1 ? 1 : (b > BN_MAX_BLOCKS ? BN_MAX_BLOCKS : b));
 }
 
 hipError_t launch_bn_stats_tiles(const float* tile_part, int tiles, long long M, int C, const float* gamma, const float* beta,
                                  float eps, float* part, float* stats, hipStream_t s) {
   if (!tile_part || tiles <= 0 || !gamma || !beta || !part || !stats || M <= 0 || !chan_ok(C)) return hipErrorInvalidValue;
-  // up to 4,096 tiles in one launch; beyond, where a lane of the final sum would add more than four runs, the runs are added
-  // by a launch of their own (part has room for BN_MAX_RUNS of them)
-  const int runs = (tiles + TILE_RUN - 1) / TILE_RUN;
-  if (runs > 256 && runs <= BN_MAX_RUNS) {
-    hipLaunchKernelGGL(bn_tiles_part_k, dim3(2 * C / 64, (runs + 3) / 4), dim3(256), 0, s, tile_part, tiles, 2 * C, part);
+  // Tiles are added in float in runs of equal length, about TILE_RUN of them, at most BN_MAX_RUNS (part's room) runs in all,
+  // then in double.  The cut decides the last bit of the statistics, and with it which pre-activations a deep network rounds
+  // to zero: with another cut the gradients of 300 ResNet50 tiles came out 8 % apart.  Up to 256 runs one launch does both;
+  // beyond, where a lane of the final sum would add more than four, the runs are added by a launch of their own.
+  int runs = (tiles + TILE_RUN - 1) / TILE_RUN;
+  if (runs > BN_MAX_RUNS) runs = BN_MAX_RUNS;
+  const int len = (tiles + runs - 1) / runs;
+  runs = (tiles + len - 1) / len;
+  if (runs > 256) {
+    hipLaunchKernelGGL(bn_tiles_part_k, dim3(2 * C / 64, (runs + 3) / 4), dim3(256), 0, s, tile_part, tiles, len, 2 * C, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bn_stats_final_k<1>, dim3(C / 16), dim3(1024), 0, s, part, runs, M, C, gamma, beta, eps, stats);
+    hipLaunchKernelGGL(bn_stats_final_k<false>, dim3(C / 16), dim3(1024), 0, s, part, runs, 1, M, C, gamma, beta, eps, stats);
   } else {
-    hipLaunchKernelGGL(bn_stats_final_k<TILE_RUN>, dim3(C / 16), dim3(1024), 0, s, tile_part, tiles, M, C, gamma, beta, eps, stats);
+    hipLaunchKernelGGL(bn_stats_final_k<true>, dim3(C / 16), dim3(1024), 0, s, tile_part, tiles, len, M, C, gamma, beta, eps, stats);
   }
   return hipGetLastError();
 }
@@ -467,7 +483,11 @@ hipError_t launch_bn_bwd(const bf16* dy, const unsigned char* mask, const bf16* 
       !al16(x) || !al16(dx) || !al16(stats) || !al16(coef))
     return hipErrorInvalidValue;
   const int blocks = bn_blocks(M, C);
-  hipLaunchKernelGGL(bn_bwd_part_k, dim3(blocks), dim3(256), 0, s, dy, mask, x, M, C, stats, part);
+  // fewer than two workgroups per compute unit: each as four wavefronts of their own channels, sixteen rows in flight
+  if (blocks < 512)
+    hipLaunchKernelGGL(bn_bwd_part_k<16>, dim3(blocks, 4), dim3(64), 0, s, dy, mask, x, M, C, stats, part);
+  else
+    hipLaunchKernelGGL(bn_bwd_part_k<4>, dim3(blocks), dim3(256), 0, s, dy, mask, x, M, C, stats, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(bn_bwd_final_k, dim3(C / 16), dim3(1024), 0, s, part, blocks, M, C, coef, dgamma, dbeta, accumulate);
