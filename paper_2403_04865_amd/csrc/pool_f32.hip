@@ -155,34 +155,43 @@ __global__ void __launch_bounds__(512) pool_gate_f32_k(PoolArgs p, float* __rest
 }
 
 // Attention logits from their `parts` partial sums (part[i][n]), and per workgroup {max, sum, weighted feature sum} over
-// its groups of 16 rows (the weighted sum in fp64: it feeds a cancelling difference in the backward).
+// its groups of GR rows (the weighted sum in fp64: it feeds a cancelling difference in the backward).
+// WIDE: part[n] holds the row's [t | s] (2 M_h) instead, and the logit is summed over the gate units here, in order.
+template <int GR, bool WIDE>
 __global__ void __launch_bounds__(256) pool_softmax_part_k(PoolArgs p, const float* __restrict__ part, int parts) {
   extern __shared__ double zb[];   // [D]
-  __shared__ float er[16];
+  __shared__ float er[GR];
   __shared__ float resc;
   const int D = p.D, tid = threadIdx.x;
   for (int d = tid; d < D; d += 256) zb[d] = 0.0;
-  float m = -INFINITY;   // of the rows so far; lanes 0 .. 15 of every wavefront compute the same
+  float m = -INFINITY;   // of the rows so far
   double l = 0.0;
-  const long long groups = (p.N + 15) / 16;
+  const long long groups = (p.N + GR - 1) / GR;
   for (long long g = blockIdx.x; g < groups; g += gridDim.x) {
-    const long long n0 = g * 16;
-    if (tid < 16) {
+    const long long n0 = g * GR;
+    if (tid < GR) {
       float a = -INFINITY;
       if (n0 + tid < p.N) {
         a = 0.f;
-        for (int i = 0; i < parts; ++i) a += part[i * p.N + n0 + tid];
+        if constexpr (WIDE) {
+          const int Mh = p.Mh;
+          const float* ts = part + (n0 + tid) * 2 * Mh;
+#pragma unroll 8
+          for (int j = 0; j < Mh; ++j) a += p.w[j] * ts[j] * ts[Mh + j];
+        } else {
+          for (int i = 0; i < parts; ++i) a += part[i * p.N + n0 + tid];
+        }
         p.a[n0 + tid] = a;
       }
       float mx = a;
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 16));
+      for (int o = GR / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, GR));
       mx = fmaxf(m, mx);
       const float sc = __expf(m - mx), e = __expf(a - mx);   // exp(-inf) = 0 on the first group
-      float es = e;
+      double es = (double)e;
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) es += __shfl_xor(es, o, 16);
-      l = l * (double)sc + (double)es;
+      for (int o = GR / 2; o > 0; o >>= 1) es += __shfl_xor(es, o, GR);
+      l = l * (double)sc + es;
       m = mx;
       er[tid] = e;
       if (tid == 0) resc = sc;
@@ -191,12 +200,12 @@ __global__ void __launch_bounds__(256) pool_softmax_part_k(PoolArgs p, const flo
     const double sc = (double)resc;
     for (int d = tid; d < D; d += 256) {
       const float* h = p.H + n0 * D + d;
-      float v[16];
+      float v[GR];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) v[r] = h[(n0 + r < p.N ? r : 0) * (long long)D];
+      for (int r = 0; r < GR; ++r) v[r] = h[(n0 + r < p.N ? r : 0) * (long long)D];
       double z = zb[d] * sc;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) z += (double)er[r] * (double)v[r];   // rows past the end have weight zero
+      for (int r = 0; r < GR; ++r) z += (double)er[r] * (double)v[r];   // rows past the end have weight zero
       zb[d] = z;
     }
     __syncthreads();
@@ -260,6 +269,121 @@ __global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __r
   }
 }
 
+// ---- wide rows ----
+// D > 1536 is the feature row of a bottleneck encoder (2048).  The gradient that leaves here runs back through some fifty
+// batch-normalised layers whose parameter gradients are sums of terms that cancel: the last bit of G decides bf16 roundings all the
+// way down and moves them by 1.5 %.  So there every sum keeps one order whatever the shape: a dot product over D is one
+// wavefront's, lane l taking d = l, l + 64, ..., sums over the gate units run in order in one thread.  What is free is cut:
+// gate units over workgroups (all of them in one workgroup per 8 rows: 300 x 2048, M_h = 128 682 us forward, 1032 backward).
+constexpr int WR = 8;    // rows per workgroup: 64 KB of features
+bool wide(const PoolArgs& p) { return p.D > 1536; }
+
+// TS[n] = [tanh(V h + b_V) | sigmoid(U h + b_U)]
+__global__ void __launch_bounds__(256) pool_wide_gate_k(PoolArgs p, float* __restrict__ TS) {
+  extern __shared__ float hs[];   // [WR][D]
+  const int D = p.D, Mh = p.Mh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long n0 = (long long)blockIdx.x * WR;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.ticket = 0;
+#pragma unroll
+  for (int r = 0; r < WR; ++r)
+    for (int d = threadIdx.x; d < D; d += 256) hs[r * D + d] = n0 + r < p.N ? p.H[(n0 + r) * D + d] : 0.f;
+  __syncthreads();
+  for (int j = blockIdx.y * 4 + wave; j < Mh; j += gridDim.y * 4) {
+    const float *vr = p.VW + (size_t)j * D, *ur = p.UW + (size_t)j * D;
+    float av[WR], au[WR];
+#pragma unroll
+    for (int r = 0; r < WR; ++r) av[r] = au[r] = 0.f;
+#pragma unroll 8
+    for (int d = lane; d < D; d += 64) {
+      const float v = vr[d], u = ur[d];
+#pragma unroll
+      for (int r = 0; r < WR; ++r) {
+        const float h = hs[r * D + d];
+        av[r] += v * h;
+        au[r] += u * h;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < WR; ++r) {
+      av[r] = wave_sum(av[r]);
+      au[r] = wave_sum(au[r]);
+    }
+    if (lane == 0) {
+      const float bv = p.Vb[j], bu = p.Ub[j];
+#pragma unroll
+      for (int r = 0; r < WR; ++r)
+        if (n0 + r < p.N) {
+          TS[(n0 + r) * 2 * Mh + j] = tanhf(av[r] + bv);
+          TS[(n0 + r) * 2 * Mh + Mh + j] = 1.0f / (1.0f + __expf(-(au[r] + bu)));
+        }
+    }
+  }
+}
+
+// [t | s] of 32 rows -> [dpV | dpU] in place, dwp[blockIdx.x][j] = sum over the rows of da t s
+__global__ void __launch_bounds__(512) pool_wide_dgate_k(PoolArgs p, float* __restrict__ TS, float* __restrict__ dwp) {
+  __shared__ float da[32];
+  const int D = p.D, Mh = p.Mh, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long n0 = (long long)blockIdx.x * 32;
+  const float* zv = p.scal + pool_z_off(p.C);
+  for (int r = wave; r < 32; r += 8) {   // softmax backward: da_n = alpha_n (h_n - z) . dz
+    const bool ok = n0 + r < p.N;
+    const float* h = p.H + (ok ? n0 + r : p.N - 1) * D;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int d = lane; d < D; d += 64) acc += ((h[d] - zv[d]) - zv[2 * D + d]) * zv[D + d];
+    acc = wave_sum(acc);
+    if (lane == 0) {
+      const float a = ok ? __expf(p.a[n0 + r] - p.scal[0]) / p.scal[1] : 0.f;
+      da[r] = a * acc;
+    }
+  }
+  __syncthreads();
+  const int rows = p.N - n0 < 32 ? (int)(p.N - n0) : 32;
+  for (int j = threadIdx.x; j < Mh; j += 512) {
+    const float wj = p.w[j];
+    float dw = 0.f;
+#pragma unroll 4
+    for (int r = 0; r < rows; ++r) {
+      float* row = TS + (n0 + r) * 2 * Mh;
+      const float t = row[j], s = row[Mh + j], g = da[r];
+      const float dv = g * wj * s * (1.f - t * t);
+      const float du = g * wj * t * s * (1.f - s);
+      row[j] = dv;
+      row[Mh + j] = du;
+      dw += g * t * s;
+    }
+    dwp[(size_t)blockIdx.x * Mh + j] = dw;
+  }
+}
+
+// G[n][d] = alpha_n dz[d] + sum_j dpV[n][j] V[j][d] + dpU[n][j] U[j][d]: 8 rows x 256 features per workgroup
+__global__ void __launch_bounds__(256) pool_wide_g_k(PoolArgs p, const float* __restrict__ Dp) {
+  extern __shared__ float dl[];   // [WR][2 Mh]
+  const int D = p.D, Mh = p.Mh;
+  const long long n0 = (long long)blockIdx.x * WR;
+  for (int i = threadIdx.x; i < WR * 2 * Mh; i += 256) dl[i] = n0 * 2 * Mh + i < p.N * 2 * Mh ? Dp[n0 * 2 * Mh + i] : 0.f;
+  __syncthreads();
+  const int d = blockIdx.y * 256 + threadIdx.x;
+  if (d >= D) return;
+  const float dzd = p.scal[pool_z_off(p.C) + D + d];
+  float acc[WR];
+#pragma unroll
+  for (int r = 0; r < WR; ++r) {
+    const float al = n0 + r < p.N ? __expf(p.a[n0 + r] - p.scal[0]) / p.scal[1] : 0.f;
+    acc[r] = al * dzd;
+  }
+#pragma unroll 8
+  for (int j = 0; j < Mh; ++j) {
+    const float v = p.VW[(size_t)j * D + d], u = p.UW[(size_t)j * D + d];
+#pragma unroll
+    for (int r = 0; r < WR; ++r) acc[r] += dl[r * 2 * Mh + j] * v + dl[r * 2 * Mh + Mh + j] * u;
+  }
+#pragma unroll
+  for (int r = 0; r < WR; ++r)
+    if (n0 + r < p.N) p.G[(n0 + r) * D + d] = acc[r];
+}
+
 // 16-byte accesses to rows of D features and of M_h gate units
 bool vec_ok(const PoolArgs& p) {
   auto al = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
@@ -285,17 +409,40 @@ hipError_t go_gate(const PoolArgs& p, float* out, float* dwp, int parts, hipStre
 }  // namespace
 
 hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
+  if (wide(p)) {
+    if ((size_t)p.N * 2 * p.Mh > p.a_room) return hipErrorInvalidValue;
+    // gate units over as many workgroups as make about four rounds of the chip
+    const long long groups = (p.N + WR - 1) / WR;
+    const int most = (p.Mh + 3) / 4;
+    long long ny = (1024 + groups - 1) / groups;
+    if (ny > most) ny = most;
+    hipLaunchKernelGGL(pool_wide_gate_k, dim3((unsigned)groups, (unsigned)ny), dim3(256), (size_t)WR * p.D * 4, s, p, p.a_tmp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((pool_softmax_part_k<WR, true>), dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, 0);
+    return hipGetLastError();
+  }
   int parts = (p.Mh + 31) / 32;
   if ((size_t)parts * p.N > p.a_room) parts = (int)(p.a_room / p.N);
   if (parts < 1) return hipErrorInvalidValue;
   hipError_t e = vec_ok(p) ? go_gate<true, false>(p, p.a_tmp, nullptr, parts, s) : go_gate<false, false>(p, p.a_tmp, nullptr, parts, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(pool_softmax_part_k, dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, parts);
+  hipLaunchKernelGGL((pool_softmax_part_k<16, false>), dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, parts);
   return hipGetLastError();
 }
 
-// Dp: [N][2 M_h]; dwp: [ceil(N / 32)][M_h] partial sums of dw; writes p.G
+// Dp: [N][2 M_h] (wide rows: [t | s] as the forward left them in a_tmp, the same room); dwp: [ceil(N / 32)][M_h] partial sums
+// of dw; writes p.G
 hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s) {
+  if (wide(p)) {
+    if (Dp != p.a_tmp) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(pool_wide_dgate_k, dim3((unsigned)((p.N + 31) / 32)), dim3(512), 0, s, p, Dp, dwp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(pool_wide_g_k, dim3((unsigned)((p.N + WR - 1) / WR), (p.D + 255) / 256), dim3(256),
+                       (size_t)WR * 2 * p.Mh * 4, s, p, Dp);
+    return hipGetLastError();
+  }
   const int parts = (p.Mh + 31) / 32;
   const bool vec = vec_ok(p);
   hipError_t e = vec ? go_gate<true, true>(p, Dp, dwp, parts, s) : go_gate<false, true>(p, Dp, dwp, parts, s);
