@@ -5,7 +5,8 @@
 // contracted index dealt to the workgroup's wavefronts and their partial blocks added through LDS: a bag of 16 to 1,000
 // rows is a few thousand MFMAs altogether and what bounds it is the serial chain of one wavefront, so the work is cut
 // along all three indices.  (One workgroup per 16 rows with all gate units on the vector units, one dot product per
-// wavefront at a time: 37 x 384 rows, M_h = 128 209 us forward and 279 us backward; 300 x 2048 682 and 1032 us.)
+// wavefront at a time: 37 x 384 rows, M_h = 128 209 us forward and 279 us backward, now 11 and 20.)  Rows wider than 1536
+// features have kernels of their own (below).
 // MFMA operands come straight from global memory: a lane reads four consecutive elements of its row and gives one to each
 // of four MFMAs (which index an MFMA contracts does not matter as long as both operands agree).  Weights are the first
 // operand: a lane then owns one feature row and runs of four neighbouring gate units (features).
@@ -406,18 +407,22 @@ hipError_t go_gate(const PoolArgs& p, float* out, float* dwp, int parts, hipStre
   return hipGetLastError();
 }
 
+hipError_t go_wide_gate(const PoolArgs& p, float* TS, hipStream_t s) {
+  // gate units over as many workgroups as make about four rounds of the chip
+  const long long groups = (p.N + WR - 1) / WR;
+  const int most = (p.Mh + 3) / 4;
+  long long ny = (1024 + groups - 1) / groups;
+  if (ny > most) ny = most;
+  hipLaunchKernelGGL(pool_wide_gate_k, dim3((unsigned)groups, (unsigned)ny), dim3(256), (size_t)WR * p.D * 4, s, p, TS);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
   if (wide(p)) {
     if ((size_t)p.N * 2 * p.Mh > p.a_room) return hipErrorInvalidValue;
-    // gate units over as many workgroups as make about four rounds of the chip
-    const long long groups = (p.N + WR - 1) / WR;
-    const int most = (p.Mh + 3) / 4;
-    long long ny = (1024 + groups - 1) / groups;
-    if (ny > most) ny = most;
-    hipLaunchKernelGGL(pool_wide_gate_k, dim3((unsigned)groups, (unsigned)ny), dim3(256), (size_t)WR * p.D * 4, s, p, p.a_tmp);
-    hipError_t e = hipGetLastError();
+    hipError_t e = go_wide_gate(p, p.a_tmp, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((pool_softmax_part_k<WR, true>), dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, 0);
     return hipGetLastError();
@@ -431,13 +436,14 @@ hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Dp: [N][2 M_h] (wide rows: [t | s] as the forward left them in a_tmp, the same room); dwp: [ceil(N / 32)][M_h] partial sums
-// of dw; writes p.G
+// Dp: [N][2 M_h]; dwp: [ceil(N / 32)][M_h] partial sums of dw; writes p.G
 hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s) {
   if (wide(p)) {
-    if (Dp != p.a_tmp) return hipErrorInvalidValue;
+    // t and s once more: an earlier backward over the same forward has written over them
+    hipError_t e = go_wide_gate(p, Dp, s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pool_wide_dgate_k, dim3((unsigned)((p.N + 31) / 32)), dim3(512), 0, s, p, Dp, dwp);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pool_wide_g_k, dim3((unsigned)((p.N + WR - 1) / WR), (p.D + 255) / 256), dim3(256),
                        (size_t)WR * 2 * p.Mh * 4, s, p, Dp);

@@ -103,6 +103,26 @@ def test_step_is_bitwise_reproducible_and_accumulates():
         np.testing.assert_allclose(c["grads"][k], 2.0 * a["grads"][k], rtol=1e-6, atol=1e-12, err_msg=k)
 
 
+# a backward leaves what a second one over the same forward needs: the float32 aggregator kernels over narrow rows and over
+# 2048-wide ones (9 tiles: one more than a workgroup's rows there)
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("name", ["rn_tiny", "rn_tiny_bneck"])
+def test_second_backward_over_one_forward(name):
+    import torch
+    from resnet_harness import GpuResNet, resnet_inputs
+    cfg, prm, X, label = resnet_inputs(name, n=9)
+    print(f"case {name} n=9 D={cfg.dim}", flush=True)
+    g = GpuResNet(cfg, prm, 9)
+    a = g.step(X, label)
+    g.lib.resnet_slide_step_bwd(False)
+    torch.cuda.synchronize()
+    G = g.view(g.lib.resnet_feature_grads(), (9, cfg.dim))
+    b = g.grads_dict()
+    assert np.array_equal(a["G"], G)
+    for k in a["grads"]:
+        assert np.array_equal(a["grads"][k], b[k]), k
+
+
 @pytest.mark.timeout(300)
 def test_state_and_arena_errors():
     import torch
