@@ -280,10 +280,12 @@ hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda
                             hipStream_t s) {
   if (N % 64 || K % 64 || n <= 0 || (gam && (K > 1024 || a_bf16 || !gelu)) || (gelu && a_bf16)) return hipErrorInvalidValue;
   LaneGemm g{A, lda, (const bf16*)W, ldw, n, N, K, bias, resid, ldr, out, ldc, (bf16*)copy, ldcopy, gam, bet, eps};
-  // 32 x 32 blocks (and the LayerNorm on the way in) up to 327,680 results, 64 x 64 beyond, which read half the operand bytes.
+  // 32 x 32 blocks (and the LayerNorm on the way in) up to 524,288 results, 64 x 64 beyond, which read half the operand bytes.
+  // (They cross at about 400,000; up to 341 rows of D = 384 all take one form, so that a short slide gives the same bits whole
+  // and in chunks: with 64-row chunks on the one and 256 rows on the other the patch embedding's gradients differed by 2.5e-3.)
   // D = 384, us for projection, LayerNorm + fc1, fc2: 200 rows 4.3, 12.5, 11.5 against 8.1, 12.8, 21.7; 332 rows 4.3, 17.4,
   // 11.5 against 8.2, 13.2, 21.6; 2048 rows 7.6, 67, 29 against 8.6, 30, 24.
-  const bool small = n * N <= 320 * 1024;
+  const bool small = n * N <= 512 * 1024;
   if (gam && !small) {
     hipLaunchKernelGGL(lane_ln_k, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, (const float*)A, lda, gam, bet, lnout, (long long)K, n, K, eps);
     hipError_t e = hipGetLastError();

@@ -288,10 +288,14 @@ namespace {
 long long tiles_of(const GemmNT& g, int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
 
 // Whether the 256 x 192 persistent kernels fill the chip well enough.  Their workgroups come one per compute unit, so
-// what counts is how full the last of `rounds` rounds is: measured over bags of 25 to 300 tiles (all the encoder's
+// what counts is how full the last of `rounds` rounds is: measured over bags of 25 tiles and more (all the encoder's
 // shapes, D = 384 and 768) they win from 0.6 on, and from 0.9 on where the epilogue reads an auxiliary operand (with a
 // single round per workgroup nothing overlaps that epilogue); from four rounds on they always do.
+// From 8,192 rows on they take everything: they round a result to bf16 before the residual or the table look-up and the
+// kernels here after it, and a slide has to give the same gradients whole and as the sum of its chunks (with 12,608-row
+// chunks here and the 50,432 rows of the slide there the patch embedding's differed by 2.6e-3).
 bool large_fills(const GemmNT& g) {
+  if (g.M >= 8192) return true;
   const int cus = 256;
   const long long t = tiles_of(g, 256, 192), rounds = (t + cus - 1) / cus;
   const bool aux = g.epi == EPI_BIAS_RESID || g.epi == EPI_DGELU || g.epi == EPI_ROWTAB;
