@@ -241,7 +241,7 @@ bool gemm_nt_f32_ok(const GemmNT& g) {
   if (g.epi == EPI_DGELU) ok = ok && g.ldpre % 4 == 0 && aligned16(g.pre);
   if (g.epi == EPI_PATCH) ok = ok && g.cmap.g2 > 0 && aligned16(g.pos);
   if (g.epi != EPI_PLAIN && g.epi != EPI_DGELU) ok = ok && aligned16(g.bias);
-  return ok && g.epi != EPI_ROWTAB;
+  return ok && g.epi != EPI_ROWTAB && g.epi != EPI_TOKEN;
 }
 
 // 64 x 64 tiles at every size: measured against 64 x 128 and 128 x 128 tiles of the same kernel over M = 68 .. 12,017 (all the

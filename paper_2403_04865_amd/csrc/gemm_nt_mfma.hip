@@ -33,6 +33,7 @@ constexpr int NXCD = 8;
 constexpr int BK = 64;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x8 __attribute__((ext_vector_type(8), aligned(16)));
 
 template <int V> using IC = std::integral_constant<int, V>;
 
@@ -60,8 +61,8 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   constexpr int WBM = BM / 64, WBN = BN / 64;        // 32 x 32 accumulators per wavefront
   constexpr int AG = BM / 32, BG = BN / 32, NLD = AG + BG;   // 8-row groups (load instructions) per wavefront and step
   constexpr int STAGE = (BM + BN) * BK;              // bf16 elements per stage
-  constexpr bool HAS_BIAS = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU;
-  constexpr bool HAS_AUX = MODE == EPI_BIAS_RESID || MODE == EPI_DGELU || MODE == EPI_ROWTAB;
+  constexpr bool HAS_BIAS = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU || MODE == EPI_TOKEN;
+  constexpr bool HAS_AUX = MODE == EPI_BIAS_RESID || MODE == EPI_DGELU || MODE == EPI_ROWTAB || MODE == EPI_TOKEN;
   constexpr int PS = WBN * 32 + 4;                   // patch row stride (floats)
   constexpr int SEG = WBN * 4, RPP = 64 / SEG, NP = 32 / RPP;   // 8-column segments per row, rows per pass, passes per strip
   __shared__ __attribute__((aligned(16))) bf16 st0[STAGE], st1[STAGE];
@@ -84,7 +85,8 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   const int prow = lane / SEG, n = n0 + wn * (WBN * 32) + (lane % SEG) * 8;
   const bool n_ok = n < g.N;
   const long long mw = m0 + wm * (WBM * 32);
-  typedef std::conditional_t<MODE == EPI_DGELU, u32x2, u32x4> aux_t;   // eight one-byte codes / eight bf16
+  // eight one-byte codes / eight bf16 / eight floats
+  typedef std::conditional_t<MODE == EPI_DGELU, u32x2, std::conditional_t<MODE == EPI_TOKEN, f32x8, u32x4>> aux_t;
   aux_t aux[HAS_AUX ? WBM : 1][HAS_AUX ? NP : 1];
   if constexpr (HAS_AUX) {
 #pragma unroll
@@ -95,6 +97,7 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
         if (m > g.M - 1) m = g.M - 1;               // never stored
         const int nn = n_ok ? n : 0;
         if constexpr (MODE == EPI_DGELU) aux[i][ps] = *reinterpret_cast<const aux_t*>((const unsigned char*)g.pre + m * g.ldpre + nn);
+        else if constexpr (MODE == EPI_TOKEN) aux[i][ps] = *reinterpret_cast<const f32x8*>(g.pos + (size_t)((unsigned)m % (unsigned)g.rperiod) * g.N + nn);
         else if constexpr (MODE == EPI_ROWTAB) aux[i][ps] = *reinterpret_cast<const aux_t*>((const bf16*)g.resid + (long long)((unsigned)m % (unsigned)g.rperiod) * g.ldr + nn);
         else aux[i][ps] = *reinterpret_cast<const aux_t*>((const bf16*)g.resid + m * g.ldr + nn);
       }
@@ -191,12 +194,9 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   if constexpr (NST > 3) { if (kt + 2 < nk) step(IC<2>{}, kt + 2); }
 
   // accumulator element r of lane l: row l % 32, column (r / 4) * 8 + (l / 32) * 4 + r % 4 of its block
-  float bias[8];
-  if (HAS_BIAS) {
-    const float4* b4 = reinterpret_cast<const float4*>(g.bias + (n_ok ? n : 0));
-    float4 a = b4[0], b = b4[1];
-    bias[0] = a.x; bias[1] = a.y; bias[2] = a.z; bias[3] = a.w; bias[4] = b.x; bias[5] = b.y; bias[6] = b.z; bias[7] = b.w;
-  }
+  f32x8 bias, cls;
+  if (HAS_BIAS) bias = *reinterpret_cast<const f32x8*>(g.bias + (n_ok ? n : 0));
+  if (MODE == EPI_TOKEN) cls = *reinterpret_cast<const f32x8*>(g.cls + (n_ok ? n : 0));
   __syncthreads();   // every wavefront is done with the stages: they become the patches, each private to its wavefront
   float* patch = reinterpret_cast<float*>(wave < 2 ? st0 : st1) + (wave & 1) * (32 * PS);
 #pragma unroll
@@ -215,7 +215,11 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
       float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
       const long long m = mw + i * 32 + row;
       if (n_ok && m < g.M) {
-        if (HAS_BIAS) {
+        if constexpr (MODE == EPI_TOKEN) {
+          const bool first = (unsigned)m % (unsigned)g.rperiod == 0;   // the class token's row: its product is zero
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = (v[e] + (first ? cls[e] : bias[e])) + aux[i][ps][e];
+        } else if (HAS_BIAS) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] += bias[e];
         }
@@ -260,6 +264,7 @@ hipError_t go(const GemmNT& g, hipStream_t s) {
     case EPI_BIAS_GELU: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_BIAS_GELU>), grid, block, 0, s, g, MT, NTL); break;
     case EPI_DGELU: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_DGELU>), grid, block, 0, s, g, MT, NTL); break;
     case EPI_ROWTAB: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_ROWTAB>), grid, block, 0, s, g, MT, NTL); break;
+    case EPI_TOKEN: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_TOKEN>), grid, block, 0, s, g, MT, NTL); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -274,11 +279,11 @@ bool gemm_nt_mfma_ok(const GemmNT& g) {
   if (g.epi == EPI_BIAS_RESID || g.epi == EPI_ROWTAB) ok = ok && g.ldr % 8 == 0 && aligned16(g.resid);
   if (g.epi == EPI_BIAS_GELU) ok = ok && g.ldc2 % 8 == 0 && ((size_t)g.out2 & 7) == 0;   // 8-byte code segments
   if (g.epi == EPI_DGELU) ok = ok && g.ldpre % 8 == 0 && ((size_t)g.pre & 7) == 0;
-  if (g.epi == EPI_BIAS || g.epi == EPI_BIAS_RESID || g.epi == EPI_BIAS_GELU) ok = ok && aligned16(g.bias);
+  if (g.epi == EPI_BIAS || g.epi == EPI_BIAS_RESID || g.epi == EPI_BIAS_GELU || g.epi == EPI_TOKEN) ok = ok && aligned16(g.bias);
+  if (g.epi == EPI_TOKEN) ok = ok && aligned16(g.pos) && aligned16(g.cls) && g.rperiod > 0;
   return ok && g.epi != EPI_PATCH;
 }
 
-bool gemm_nt_big_ok(const GemmNT& g);
 hipError_t launch_gemm_nt_big(const GemmNT& g, hipStream_t s);
 bool gemm_nt_gelu_ok(const GemmNT& g);
 hipError_t launch_gemm_nt_gelu(const GemmNT& g, hipStream_t s);

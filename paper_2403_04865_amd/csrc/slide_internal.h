@@ -134,6 +134,7 @@ enum {
   EPI_DGELU = 4,       // out(T)  = acc * pre[m][n]   (pre holds the gelu'(m) the forward stored, same format)
   EPI_PATCH = 5,       // out(RS)[rowmap(m)] = acc + bias[n] + pos[1 + m % g2][n]
   EPI_ROWTAB = 6,      // out(RS) = acc + resid(RS)[m % rperiod][n]: a table of rperiod rows added periodically (bf16 matrix-core kernels only)
+  EPI_TOKEN = 7,       // out(RS) = acc + (m % rperiod ? bias : cls)[n] + pos[m % rperiod][n] in float32 (short-bag bf16 kernels only)
 };
 
 struct GemmNT {
@@ -144,11 +145,12 @@ struct GemmNT {
   int epi;
   const float* bias;
   const void* resid; long long ldr;
-  int rperiod;                   // EPI_ROWTAB: rows of the table
+  int rperiod;                   // EPI_ROWTAB, EPI_TOKEN: rows of the table
   void* out; long long ldc;
   void* out2; long long ldc2;          // leading dimensions in elements of the stored-derivative format
   const void* pre; long long ldpre;
-  const float* pos;  // [T, N] position table (EPI_PATCH)
+  const float* pos;  // [T, N] position table (EPI_PATCH, EPI_TOKEN)
+  const float* cls;  // [N] (EPI_TOKEN)
   RowMap cmap;       // EPI_PATCH output rows
 };
 
@@ -191,6 +193,7 @@ hipError_t launch_unpatchify(int dt, const void* dpatches, void* dpix, long long
 hipError_t launch_cls_rows(int dt, void* x, const float* cls, const float* pos, long long n, int T, int D, hipStream_t s);
 hipError_t launch_pos_table(void* tab, const float* cls, const float* pos, const float* bias, int T, int D, hipStream_t s);
 bool gemm_nt_mfma_ok(const GemmNT& g);
+bool gemm_nt_big_ok(const GemmNT& g);   // a shape that the large-M kernel takes
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_calib_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t launch_gelu(int dt, const void* m, void* a, long long count, hipStream_t s);

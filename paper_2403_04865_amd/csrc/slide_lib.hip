@@ -554,18 +554,24 @@ int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool
   launch(r, K_ELEMWISE, 0, 2.0 * n * 3 * c->cfg.tile * c->cfg.tile * elem_size(dt),
          [&] { return launch_patchify(dt, pixels, ar + y.e_patches, n, c->cfg.tile, c->cfg.patch, s, T - c->g2); });
   // the patch matrix has the token matrix's rows (a row of zeros in each tile's CLS slot): its weight gradient is
-  // then a plain product of two row-aligned matrices and runs on the large-M kernel, and so does the forward where
-  // that kernel takes the shape: every token row gets its row of a [T, D] table added (bias + position row; class
-  // token + position row in the CLS slot, where the product is zero)
+  // then a plain product of two row-aligned matrices and runs on the large-M kernel, and so does the forward: every token
+  // row gets bias and position row added (class token and position row in the CLS slot, where the product is zero).  Where
+  // the large-M kernel takes the shape they come as one [T, D] table of the residual stream's type, as that kernel reads
+  // them; the short-bag kernel adds both in float32 and rounds once.
   GemmNT gt{};
   gt.A = ar + y.e_patches; gt.lda = c->Kp; gt.B = weight(c, 0); gt.ldb = c->Kp;
   gt.M = n * T; gt.N = D; gt.K = c->Kp;
   gt.epi = EPI_ROWTAB; gt.resid = ar + y.e_postab; gt.ldr = D; gt.rperiod = T;
   gt.out = ar + y.e_x; gt.ldc = D;
+  const bool large = gemm_nt_mfma_ok(gt) && gemm_nt_big_ok(gt);
+  if (!large) {
+    gt.epi = EPI_TOKEN; gt.bias = c->params + c->o_peb; gt.cls = c->params + c->o_cls; gt.pos = c->params + c->o_pos;
+  }
   if (dt == DT_BF16 && c->use_mfma && gemm_nt_mfma_ok(gt)) {
-    launch(r, K_ELEMWISE, 0, 0, [&] {
-      return launch_pos_table(ar + y.e_postab, c->params + c->o_cls, c->params + c->o_pos, c->params + c->o_peb, T, D, s);
-    });
+    if (large)
+      launch(r, K_ELEMWISE, 0, 0, [&] {
+        return launch_pos_table(ar + y.e_postab, c->params + c->o_cls, c->params + c->o_pos, c->params + c->o_peb, T, D, s);
+      });
     gemm_nt(r, gt);
   } else {
     GemmNT g{};

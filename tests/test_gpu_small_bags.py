@@ -51,3 +51,29 @@ def test_fp32_step_small_bags(name, tiles):
     errs, bad, kappa = compare_step(out, ref, 1e-4, cfg, None, pool_same)   # the bound of every fp32 parity test
     print(f"kappa={kappa:.1f} worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:6], flush=True)
     assert not bad, bad
+
+
+# position rows, class token and patch bias stay float32 on the way into the sum: a patch whose product is -100 plus a little
+# meets a position of 100 plus a little, and only what is left over carries the signal (bf16 numbers near 100 are 0.5 apart)
+@pytest.mark.parametrize("name,tiles", [("tiny", 16), ("tiny", 250), ("small", 5)])
+def test_position_rows_are_added_in_float32(name, tiles):
+    from oracle import slide_oracle as so
+    from slide_harness import GpuSlide, compare_step
+    cfg = replace(gen.CONFIGS[name][0], layers=2)
+    ds, ws, ls = gen.SEEDS[name]
+    prm = {k: gen.to_bf16_grid(v) for k, v in gen.make_params(cfg, ws, perturbed=True).items()}
+    prm["pe.W"][:, 0] = -100.0
+    pos = 25.0 * prm["pos"]
+    pos[1:] += 100.0
+    prm["pos"] = pos.astype(np.float32).astype(np.float64)
+    X = gen.to_bf16_grid(gen.make_pixels(cfg, tiles, ds))
+    X[:, 0, ::cfg.patch, ::cfg.patch] = 1.0
+    lab = gen.make_label(cfg, ls)
+    print(f"case position rows {name} layers=2 n={tiles}", flush=True)
+    # no pixel gradient: that of the pixel with equal weights is -100 times a sum that LayerNorm makes zero
+    out = GpuSlide(cfg, prm, 1, tiles).step(X, lab, want_pixel_grad=False)
+    ref = so.slide_step(prm, X.astype(np.float64), lab, cfg, want_pixel_grad=False)
+    _, pool_same = so.pool_bwd(so.pool_fwd(prm, out["H"], lab, cfg)[4])
+    errs, bad, kappa = compare_step(out, ref, BF16_TOL, cfg, None, pool_same)
+    print(f"kappa={kappa:.1f} worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:6], flush=True)
+    assert not bad, bad
