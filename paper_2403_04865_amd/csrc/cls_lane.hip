@@ -55,9 +55,43 @@ __device__ __forceinline__ Frag split8(f32x4 a, f32x4 b) {
   return f;
 }
 
+// A LayerNorm's statistics and its output have one order of additions, whichever kernel takes them: a lane holds pieces i of 16
+// values starting at (first + 8 i) * 16, half a piece each (x[i][0], x[i][1]: eight neighbours), `row_sum` adds the two halves
+// and then the eight lanes' sums in order.
+constexpr int LANE_WAVES = 8, LN_STEPS = 1024 / 16 / LANE_WAVES;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // a caller's vector: any float's address
+__device__ __forceinline__ f32x4 ld4u(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+
+template <typename F>
+__device__ __forceinline__ void ln_stats(const f32x4 (&x)[LN_STEPS][2], int first, int nk, float eps, F row_sum, float& mu, float& rstd) {
+  const float D = (float)(nk * 16);
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < LN_STEPS; ++i)   // zeros past the row's end
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s += x[i][0][e] + x[i][1][e];
+  mu = row_sum(s, 0) / D;
+  float q = 0.f;
+#pragma unroll
+  for (int i = 0; i < LN_STEPS; ++i)
+    if (first + i * LANE_WAVES < nk) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float c0 = x[i][0][e] - mu, c1 = x[i][1][e] - mu;
+        q += fmaf(c1, c1, c0 * c0);
+      }
+    }
+  rstd = 1.0f / sqrtf(row_sum(q, 1) / D + eps);
+}
+__device__ __forceinline__ f32x4 ln_out(f32x4 x, float mu, float rstd, f32x4 gam, f32x4 bet) {
+  f32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = fmaf((x[e] - mu) * rstd, gam[e], bet[e]);
+  return v;
+}
+
 // MODE 0: out = resid + A W^T + bias (and the optional rounded copy); MODE 1: out = gelu(A W^T + bias).
 // TB x TB blocks of 32 x 32 per workgroup.  LN (TB = 1): A is normalised first; its slices stay in registers (K <= 1024).
-constexpr int LANE_WAVES = 8, LN_STEPS = 1024 / 16 / LANE_WAVES;
 template <int MODE, bool A_BF16, int TB, bool LN>
 __global__ void __launch_bounds__(64 * LANE_WAVES) lane_gemm_k(LaneGemm g) {
   constexpr int U = TB == 1 ? 6 : 3, NR = TB * TB * 16;   // steps whose loads are issued together, accumulators
@@ -91,7 +125,7 @@ __global__ void __launch_bounds__(64 * LANE_WAVES) lane_gemm_k(LaneGemm g) {
     u32x4 w[LN_STEPS];
 #pragma unroll
     for (int i = 0; i < LN_STEPS; ++i) {
-      const int c = wave + i * W;
+      const int c = wave + i * LANE_WAVES;   // with fewer wavefronts (K < 128) each has one piece
       x[i][0] = x[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (c < nk) {
         x[i][0] = ld4(a32[0] + c * 16);
@@ -99,38 +133,22 @@ __global__ void __launch_bounds__(64 * LANE_WAVES) lane_gemm_k(LaneGemm g) {
         w[i] = *reinterpret_cast<const u32x4*>(wr[0] + c * 16);
       }
     }
-    // sum over a row: its pieces in this lane, the other half wavefront's, the other wavefronts'
-    auto row_sum = [&](float v, float* buf) {
+    float mu, rstd;
+    ln_stats(x, wave, nk, g.eps, [&](float v, int which) {
+      float* buf = st + which * (LANE_WAVES * 32);
       v += __shfl_xor(v, 32, 64);
       if (half == 0) buf[wave * 32 + li] = v;
       __syncthreads();
       float t = 0.f;
       for (int k = 0; k < W; ++k) t += buf[k * 32 + li];
       return t;
-    };
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < LN_STEPS; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s += x[i][0][e] + x[i][1][e];
-    const float mu = row_sum(s, st) / (float)g.K;
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < LN_STEPS; ++i)
-      if (wave + i * W < nk) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float c0 = x[i][0][e] - mu, c1 = x[i][1][e] - mu;
-          q += c0 * c0 + c1 * c1;
-        }
-      }
-    const float rstd = 1.0f / sqrtf(row_sum(q, st + LANE_WAVES * 32) / (float)g.K + g.eps);
+    }, mu, rstd);
 #pragma unroll
     for (int i = 0; i < LN_STEPS; ++i) {
-      const int k = (wave + i * W) * 16 + half * 8;
-      if (wave + i * W < nk) {
-        const f32x4 u0 = (x[i][0] - mu) * rstd * ld4(g.gam + k) + ld4(g.bet + k);
-        const f32x4 u1 = (x[i][1] - mu) * rstd * ld4(g.gam + k + 4) + ld4(g.bet + k + 4);
+      const int k = (wave + i * LANE_WAVES) * 16 + half * 8;
+      if (wave + i * LANE_WAVES < nk) {
+        const f32x4 u0 = ln_out(x[i][0], mu, rstd, ld4u(g.gam + k), ld4u(g.bet + k));
+        const f32x4 u1 = ln_out(x[i][1], mu, rstd, ld4u(g.gam + k + 4), ld4u(g.bet + k + 4));
         const Frag f = split8(u0, u1);
         const bf16x8 fb = __builtin_bit_cast(bf16x8, w[i]);
         acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.hi, fb, acc[0][0], 0, 0, 0);
@@ -201,34 +219,41 @@ __global__ void __launch_bounds__(64 * LANE_WAVES) lane_gemm_k(LaneGemm g) {
   }
 }
 
-// LayerNorm of fp32 rows (D <= 1024): one wavefront per row, statistics in two passes over registers.
+// LayerNorm of fp32 rows (D <= 1024, a multiple of 64): 16 lanes per row, two (the halves of a piece) for each wavefront that
+// lane_gemm_k deals a row to, so that a bag gives the same bits with the LayerNorm on the way in and in a launch of its own.
 __global__ void __launch_bounds__(256) lane_ln_k(const float* __restrict__ x, long long xs, const float* __restrict__ gam,
                                                  const float* __restrict__ bet, float* __restrict__ out, long long os,
                                                  long long rows, int D, float eps) {
-  const int lane = threadIdx.x & 63;
-  const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, first = (lane & 15) >> 1, half = lane & 1, nk = D / 16;
+  const long long r = (long long)blockIdx.x * 16 + (threadIdx.x >> 4);
+  const float* row = x + (r < rows ? r : rows - 1) * xs;   // rows past the end re-read the last one and are never stored
+  f32x4 v[LN_STEPS][2];
+#pragma unroll
+  for (int i = 0; i < LN_STEPS; ++i) {
+    const int c = first + i * LANE_WAVES;
+    v[i][0] = v[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (c < nk) {
+      v[i][0] = ld4u(row + c * 16 + half * 8);
+      v[i][1] = ld4u(row + c * 16 + half * 8 + 4);
+    }
+  }
+  float mu, rstd;
+  ln_stats(v, first, nk, eps, [&](float s, int) {
+    s += __shfl_xor(s, 1, 64);
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < LANE_WAVES; ++k) t += __shfl(s, (lane & ~15) + 2 * k, 64);
+    return t;
+  }, mu, rstd);
   if (r >= rows) return;
-  float v[16];
-  float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    int d = lane + 64 * i;
-    v[i] = d < D ? x[r * xs + d] : 0.f;
-    s += v[i];
-  }
-  const float mu = wave_sum(s) / (float)D;
-  float q = 0.f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    int d = lane + 64 * i;
-    float c = d < D ? v[i] - mu : 0.f;
-    q += c * c;
-  }
-  const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    int d = lane + 64 * i;
-    if (d < D) out[r * os + d] = (v[i] - mu) * rstd * gam[d] + bet[d];
+  for (int i = 0; i < LN_STEPS; ++i) {
+    const int k = (first + i * LANE_WAVES) * 16 + half * 8;
+    if (k < D) {
+      float* o = out + r * os + k;
+      *reinterpret_cast<f32x4u*>(o) = ln_out(v[i][0], mu, rstd, ld4u(gam + k), ld4u(bet + k));
+      *reinterpret_cast<f32x4u*>(o + 4) = ln_out(v[i][1], mu, rstd, ld4u(gam + k + 4), ld4u(bet + k + 4));
+    }
   }
 }
 
@@ -251,7 +276,7 @@ hipError_t launch_lane_init(const float* cls, const float* pos, float* xc, long 
 
 hipError_t launch_lane_ln(const float* x, long long xs, const float* gam, const float* bet, float* out, long long os,
                           long long rows, int D, float eps, hipStream_t s) {
-  hipLaunchKernelGGL(lane_ln_k, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, x, xs, gam, bet, out, os, rows, D, eps);
+  hipLaunchKernelGGL(lane_ln_k, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s, x, xs, gam, bet, out, os, rows, D, eps);
   return hipGetLastError();
 }
 
@@ -280,15 +305,13 @@ hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda
                             hipStream_t s) {
   if (N % 64 || K % 64 || n <= 0 || (gam && (K > 1024 || a_bf16 || !gelu)) || (gelu && a_bf16)) return hipErrorInvalidValue;
   LaneGemm g{A, lda, (const bf16*)W, ldw, n, N, K, bias, resid, ldr, out, ldc, (bf16*)copy, ldcopy, gam, bet, eps};
-  // 32 x 32 blocks (and the LayerNorm on the way in) up to 524,288 results, 64 x 64 beyond, which read half the operand bytes.
-  // (They cross at about 400,000; up to 341 rows of D = 384 all take one form, so that a short slide gives the same bits whole
-  // and in chunks: with 64-row chunks on the one and 256 rows on the other the patch embedding's gradients differed by 2.5e-3.)
-  // D = 384, us for projection, LayerNorm + fc1, fc2: 200 rows 4.3, 12.5, 11.5 against 8.1, 12.8, 21.7; 332 rows 4.3, 17.4,
-  // 11.5 against 8.2, 13.2, 21.6; 2048 rows 7.6, 67, 29 against 8.6, 30, 24.
-  const bool small = n * N <= 512 * 1024;
+  // 32 x 32 blocks (and the LayerNorm on the way in) up to 400,000 results, 64 x 64 beyond, which read half the operand bytes;
+  // both give the same bits.  The forward of ViT-S, ms, with the first MLP matrix in the one / in the other form: 200 tiles
+  // (307,200 results) 3.838 / 3.846, 275 4.560 / 4.543, 332 5.228 / 5.171; with all three products in the other form: 200 4.21,
+  // 340 6.30 against 6.11.  512 tiles: 8.14 with fc1 alone in the other form, 8.22 with none, 8.36 with all.
+  const bool small = n * N <= 400000;
   if (gam && !small) {
-    hipLaunchKernelGGL(lane_ln_k, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, (const float*)A, lda, gam, bet, lnout, (long long)K, n, K, eps);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_lane_ln((const float*)A, lda, gam, bet, lnout, K, n, K, eps, s);
     if (e != hipSuccess) return e;
     g.A = lnout; g.lda = K;
   }
