@@ -21,7 +21,10 @@
 // flop through a compute unit's L1, smaller ones reach more compute units.
 // Epilogue: MFMA operands are passed swapped, so a lane holds runs of four neighbouring columns of one row; a wavefront's
 // 32-row strips pass through a private LDS patch and come back as 8-column row segments: 16-byte loads and stores, each
-// result rounded once.
+// result rounded once - except for problems that the large-M kernels take as well (from 4,096 rows on).  Those kernels park
+// a tile's results as bf16 before they add a residual or table row or multiply with the GELU derivative, and start their
+// accumulators from the bias; LARGE does the same in the same order, so that which of the kernels runs does not show
+// in a single bit and a slide gives the same gradients whole and in chunks.
 #include "gemm_epi.h"
 #include <type_traits>
 
@@ -56,19 +59,20 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
   return __builtin_bit_cast(u32x4, t);
 }
 
-template <int BM, int BN, int NST, int MODE>
+template <int BM, int BN, int NST, int MODE, bool LARGE>
 __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + BN == 192 ? 3 : 4) gemm_nt_mid_k(GemmNT g, int MT, int NTL) {
   constexpr int WBM = BM / 64, WBN = BN / 64;        // 32 x 32 accumulators per wavefront
   constexpr int AG = BM / 32, BG = BN / 32, NLD = AG + BG;   // 8-row groups (load instructions) per wavefront and step
   constexpr int STAGE = (BM + BN) * BK;              // bf16 elements per stage
   constexpr bool HAS_BIAS = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU || MODE == EPI_TOKEN;
   constexpr bool HAS_AUX = MODE == EPI_BIAS_RESID || MODE == EPI_DGELU || MODE == EPI_ROWTAB || MODE == EPI_TOKEN;
+  constexpr bool BIAS0 = LARGE && (MODE == EPI_BIAS || MODE == EPI_BIAS_RESID);   // the accumulators start from the bias
   constexpr int PS = WBN * 32 + 4;                   // patch row stride (floats)
   constexpr int SEG = WBN * 4, RPP = 64 / SEG, NP = 32 / RPP;   // 8-column segments per row, rows per pass, passes per strip
   __shared__ __attribute__((aligned(16))) bf16 st0[STAGE], st1[STAGE];
   __shared__ __attribute__((aligned(16))) bf16 st2[NST > 2 ? STAGE : 8];
-  __shared__ __attribute__((aligned(16))) bf16 st3[NST > 3 ? STAGE : 8];
-  static_assert(NST >= 2 && NST <= 4, "stages");
+  __shared__ __attribute__((aligned(16))) bf16 st3[NST > 2 ? STAGE : 8];
+  static_assert(NST == 2 || NST == 4, "stages");
   static_assert(2 * 32 * PS * 4 <= STAGE * 2, "two wavefronts' epilogue patches lie inside a stage");
   // tile id -> (row tile, column tile): ids are dealt round-robin to the XCDs, and the column tiles of one row panel get
   // consecutive slots of one XCD (same L2)
@@ -142,11 +146,19 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
 
   f32x16 acc[WBM][WBN];
 #pragma unroll
-  for (int i = 0; i < WBM; ++i)
+  for (int j = 0; j < WBN; ++j)
 #pragma unroll
-    for (int j = 0; j < WBN; ++j)
+    for (int q = 0; q < 4; ++q) {
+      f32x4 b = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (BIAS0) {   // columns of accumulator elements 4q .. 4q + 3 (past the matrix: never stored)
+        const int c = n0 + wn * (WBN * 32) + j * 32 + q * 8 + (lane >> 5) * 4;
+        b = *reinterpret_cast<const f32x4*>(g.bias + (c < g.N ? c : 0));
+      }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int i = 0; i < WBM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = b[e];
+    }
 
   // fragment addresses: element offset of this lane's row in a stage, and its slot permutation (the same for every
   // 32-row block: 32 rows further leaves (R >> 1) & 7 alone)
@@ -156,8 +168,8 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
     constexpr int S = decltype(sc)::value;
     // this step's operands have landed: at most NST - 2 younger steps are still in flight
     const int younger = nk - 1 - kt;
-    if (NST >= 4 && younger >= 2) wait_vm<2 * NLD>();
-    else if (NST >= 3 && younger >= 1) wait_vm<NLD>();
+    if (NST > 2 && younger >= 2) wait_vm<2 * NLD>();
+    else if (NST > 2 && younger >= 1) wait_vm<NLD>();
     else wait_vm<0>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();   // ... for every wavefront, and the stage of step kt - 1 is free
@@ -181,21 +193,22 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   };
   issue(IC<0>{}, 0);
   if (NST > 2 && nk > 1) issue(IC<1>{}, 1);
-  if (NST > 3 && nk > 2) issue(IC<2>{}, 2);
+  if (NST > 2 && nk > 2) issue(IC<2>{}, 2);
   int kt = 0;
   for (; kt + NST <= nk; kt += NST) {
     step(IC<0>{}, kt);
     step(IC<1>{}, kt + 1);
-    if constexpr (NST > 2) step(IC<2>{}, kt + 2);
-    if constexpr (NST > 3) step(IC<3>{}, kt + 3);
+    if constexpr (NST > 2) { step(IC<2>{}, kt + 2); step(IC<3>{}, kt + 3); }
   }
   if (kt < nk) step(IC<0>{}, kt);
-  if (NST > 2 && kt + 1 < nk) step(IC<1>{}, kt + 1);
-  if constexpr (NST > 3) { if (kt + 2 < nk) step(IC<2>{}, kt + 2); }
+  if constexpr (NST > 2) {
+    if (kt + 1 < nk) step(IC<1>{}, kt + 1);
+    if (kt + 2 < nk) step(IC<2>{}, kt + 2);
+  }
 
   // accumulator element r of lane l: row l % 32, column (r / 4) * 8 + (l / 32) * 4 + r % 4 of its block
   f32x8 bias, cls;
-  if (HAS_BIAS) bias = *reinterpret_cast<const f32x8*>(g.bias + (n_ok ? n : 0));
+  if (HAS_BIAS && !BIAS0) bias = *reinterpret_cast<const f32x8*>(g.bias + (n_ok ? n : 0));
   if (MODE == EPI_TOKEN) cls = *reinterpret_cast<const f32x8*>(g.cls + (n_ok ? n : 0));
   __syncthreads();   // every wavefront is done with the stages: they become the patches, each private to its wavefront
   float* patch = reinterpret_cast<float*>(wave < 2 ? st0 : st1) + (wave & 1) * (32 * PS);
@@ -219,10 +232,11 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
           const bool first = (unsigned)m % (unsigned)g.rperiod == 0;   // the class token's row: its product is zero
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = (v[e] + (first ? cls[e] : bias[e])) + aux[i][ps][e];
-        } else if (HAS_BIAS) {
+        } else if (HAS_BIAS && !BIAS0) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] += bias[e];
         }
+        if constexpr (LARGE && HAS_AUX) unpack8(pack8(v), v);   // to bf16 and back
         if constexpr (MODE == EPI_BIAS_RESID || MODE == EPI_ROWTAB) {
           float t[8];
           unpack8(aux[i][ps], t);
@@ -251,23 +265,26 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-template <int BM, int BN, int NST>
+template <int BM, int BN, int NST, bool LARGE>
 hipError_t go(const GemmNT& g, hipStream_t s) {
   const int MT = (int)((g.M + BM - 1) / BM), NTL = (g.N + BN - 1) / BN;
   const long long wgs = (long long)((MT + NXCD - 1) / NXCD) * NXCD * NTL;
   if (wgs >= (1LL << 31)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)wgs), block(256);
+  auto run = [&](auto mode) {
+    hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, decltype(mode)::value, LARGE>), dim3((unsigned)wgs), dim3(256), 0, s, g, MT, NTL);
+    return hipGetLastError();
+  };
   switch (g.epi) {
-    case EPI_PLAIN: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_PLAIN>), grid, block, 0, s, g, MT, NTL); break;
-    case EPI_BIAS: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_BIAS>), grid, block, 0, s, g, MT, NTL); break;
-    case EPI_BIAS_RESID: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_BIAS_RESID>), grid, block, 0, s, g, MT, NTL); break;
-    case EPI_BIAS_GELU: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_BIAS_GELU>), grid, block, 0, s, g, MT, NTL); break;
-    case EPI_DGELU: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_DGELU>), grid, block, 0, s, g, MT, NTL); break;
-    case EPI_ROWTAB: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_ROWTAB>), grid, block, 0, s, g, MT, NTL); break;
-    case EPI_TOKEN: hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, EPI_TOKEN>), grid, block, 0, s, g, MT, NTL); break;
+    case EPI_PLAIN: return run(IC<EPI_PLAIN>{});
+    case EPI_BIAS: return run(IC<EPI_BIAS>{});
+    case EPI_BIAS_RESID: return run(IC<EPI_BIAS_RESID>{});
+    case EPI_DGELU: return run(IC<EPI_DGELU>{});
+    // the table form only where the large-M kernel has it too, GELU and the float32 token rows only where it does not
+    case EPI_ROWTAB: if constexpr (LARGE) return run(IC<EPI_ROWTAB>{}); else return hipErrorInvalidValue;
+    case EPI_BIAS_GELU: if constexpr (!LARGE) return run(IC<EPI_BIAS_GELU>{}); else return hipErrorInvalidValue;
+    case EPI_TOKEN: if constexpr (!LARGE) return run(IC<EPI_TOKEN>{}); else return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -292,19 +309,28 @@ namespace {
 
 long long tiles_of(const GemmNT& g, int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
 
-// Whether the 256 x 192 persistent kernels fill the chip well enough.  Their workgroups come one per compute unit, so
-// what counts is how full the last of `rounds` rounds is: measured over bags of 25 tiles and more (all the encoder's
-// shapes, D = 384 and 768) they win from 0.6 on, and from 0.9 on where the epilogue reads an auxiliary operand (with a
-// single round per workgroup nothing overlaps that epilogue); from four rounds on they always do.
-// From 8,192 rows on they take everything: they round a result to bf16 before the residual or the table look-up and the
-// kernels here after it, and a slide has to give the same gradients whole and as the sum of its chunks (with 12,608-row
-// chunks here and the 50,432 rows of the slide there the patch embedding's differed by 2.6e-3).
+// Whether the 256 x 192 persistent kernels fill the chip well enough.  Their workgroups come one per compute unit, so what
+// counts is how full the last of `rounds` rounds is: a round takes them the same time however full it is, the kernels here a
+// time in proportion.  us, 256 x 192 / here, M = 18,912 and N = 384 (148 tiles, 0.58 of a round): K = 384 15.3 / 17.0, 1152
+// 29.2 / 32.1, 1536 39.4 / 40.4; M = 9456, N = 768 (0.58 too): K = 768 22.3 / 22.3, 2304 52.6 / 58.4, 3072 68.8 / 84.5.  With an
+// auxiliary operand and a short contraction nothing hides the epilogue of a workgroup's last tile: residual, K = 384
+// 22.8 / 17.2, K = 768 30.1 / 25.0 and at 0.78 of a round 31.8 / 29.2, derivative at 0.77 of three rounds 54.2 / 46.4 (K = 384) and
+// 79 / 74 (768); with a long one it is as without: residual, K = 1536 46.0 / 50.1, 3072 75.9 / 88.5.  From four rounds on the
+// large kernels always win.  (Step of 40 ViT-B tiles with its K = 3072 products at 0.48 of a round there 9.04 ms, here 8.74.)
 bool large_fills(const GemmNT& g) {
-  if (g.M >= 8192) return true;
   const int cus = 256;
   const long long t = tiles_of(g, 256, 192), rounds = (t + cus - 1) / cus;
   const bool aux = g.epi == EPI_BIAS_RESID || g.epi == EPI_DGELU || g.epi == EPI_ROWTAB;
-  return rounds >= 4 || (double)t >= (aux ? 0.9 : 0.6) * (double)(rounds * cus);
+  const double least = aux && g.K <= 768 ? 0.9 : 0.55;
+  return rounds >= 4 || (double)t >= least * (double)(rounds * cus);
+}
+
+template <bool LARGE>
+hipError_t go_mid(const GemmNT& g, hipStream_t s) {
+  if (tiles_of(g, 128, 128) >= 600) return go<128, 128, 2, LARGE>(g, s);
+  if (tiles_of(g, 64, 128) >= 400) return go<64, 128, 2, LARGE>(g, s);
+  if (g.K >= 2048 && tiles_of(g, 64, 64) <= 512) return go<64, 64, 4, LARGE>(g, s);
+  return go<64, 64, 2, LARGE>(g, s);
 }
 
 }  // namespace
@@ -315,13 +341,12 @@ bool large_fills(const GemmNT& g) {
 // projection 16.9 / 8.1 / 7.7 / 6.9, fc2 37.4 / 20.2 / 17.4 / 16.5, fc2 input gradient 20.4 / 17.4 / 17.8 / 19.2.
 // A contraction of thousands of columns on few tiles is a serial chain of K steps: four stages there (K = 3072, one
 // tile of the slide: 17.9 us against 23.8 with two); everywhere else two stages and more workgroups measured faster.
+// The GELU of the large-M kernel comes from a table whose last bits a formula does not give: that kernel has every problem it
+// can take.
 hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s) {
-  if (gemm_nt_gelu_ok(g) && large_fills(g)) return launch_gemm_nt_gelu(g, s);
-  if (g.epi != EPI_BIAS_GELU && gemm_nt_big_ok(g) && large_fills(g)) return launch_gemm_nt_big(g, s);
-  if (tiles_of(g, 128, 128) >= 600) return go<128, 128, 2>(g, s);
-  if (tiles_of(g, 64, 128) >= 400) return go<64, 128, 2>(g, s);
-  if (g.K >= 2048 && tiles_of(g, 64, 64) <= 512) return go<64, 64, 4>(g, s);
-  return go<64, 64, 2>(g, s);
+  if (gemm_nt_gelu_ok(g)) return launch_gemm_nt_gelu(g, s);
+  if (g.epi == EPI_BIAS_GELU || !gemm_nt_big_ok(g)) return go_mid<false>(g, s);
+  return large_fills(g) ? launch_gemm_nt_big(g, s) : go_mid<true>(g, s);
 }
 
 }  // namespace sl

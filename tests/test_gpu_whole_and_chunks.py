@@ -39,3 +39,22 @@ def test_features_by_either_form_of_the_cls_lane():
     assert np.array_equal(whole, np.concatenate([feats(0, 200), feats(200, 400, 1)]))
     assert np.array_equal(feats(400, 433), feats(400, 433, 1))
     assert np.array_equal(feats(433, 436), feats(433, 436, 1))
+
+
+# From 4,096 rows on an encoder GEMM runs on 256 x 192 tiles or on smaller ones, whichever fill the chip, and 21 ViT-S tiles are
+# 4,137 rows: both kernels take part on both sides here (and both forms of the CLS lane at 500).  Features and pixel gradients
+# belong to one tile, so they have to agree to the last bit; the other gradients are the same terms added in another order.
+@pytest.mark.parametrize("tiles,chunk", [(48, 24), (100, 26), (170, 43), (500, 300)])
+def test_step_whole_and_in_chunks(tiles, chunk):
+    from slide_harness import GpuSlide, rel_l2
+    cfg, prm, X, label = _slide(tiles)
+    print(f"case whole {tiles}, chunks of {chunk}", flush=True)
+    g = GpuSlide(cfg, prm, 1, tiles)
+    whole, parts = g.step(X, label), g.step_chunked(X, label, chunk)
+    for k in ("H", "G", "dX"):
+        assert np.isfinite(whole[k]).all() and np.abs(whole[k]).max() > 0
+        assert np.array_equal(whole[k], parts[k]), (k, rel_l2(parts[k], whole[k]))
+    errs = {k: rel_l2(parts["grads"][k], v) for k, v in whole["grads"].items()}
+    print("worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:4], flush=True)
+    # float32 sums of n <= 98,500 terms in two orders: 2 sqrt(n) 2^-24 = 3.7e-5 of the terms' norm
+    assert max(errs.values()) < 4e-5
