@@ -407,7 +407,7 @@ bool red_add(RedList& L, const float* part, int slabs, long long stride, long lo
   if (len <= 0) return true;
   if (L.n >= RED_MAX) return false;
   RedSeg& g = L.seg[L.n];
-  g.part = part; g.out = out; g.stride = stride; g.len = (int)len; g.slabs = slabs; g.accumulate = (short)accumulate;
+  g.part = part; g.out = out; g.stride = stride; g.len = (int)len; g.slabs = slabs; g.accumulate = accumulate != 0;
   if (len < 4096 && slabs >= 64) g.kind = RED_16;
   else if (len >= 4096 && len % 4 == 0 && stride % 4 == 0 && ((uintptr_t)part & 15) == 0 && ((uintptr_t)out & 15) == 0) g.kind = RED_4;
   else g.kind = RED_1;

@@ -164,3 +164,17 @@ def test_pool_over_more_rows_invalidates_a_saved_step():
                                                      ("small", 64, 128, 1), ("full", 300, 256, 0), ("full", 513, 128, 1)])
 def test_pool_f32_blocks(name, N, mil_hidden, dtype):
     _pool_case(name, N, dtype, mil_hidden=mil_hidden)
+
+
+# `accumulate` is any non-zero int, for the sums over slabs as for the head's gradients (65536: its low 16 bits are zero)
+def test_any_nonzero_accumulate_adds():
+    from slide_harness import GpuSlide
+    cfg, n = gen.CONFIGS["tiny"]
+    ds, ws, ls = gen.SEEDS["tiny"]
+    print("case accumulate = 65536 (tiny, fp32)", flush=True)
+    X = gen.make_pixels(cfg, n, ds, kind="uniform")
+    g = GpuSlide(cfg, gen.make_params(cfg, ws, perturbed=True), 0, n)
+    a = g.step(X, 1)["grads"]
+    b = g.step(X, 1, accumulate=65536)["grads"]
+    for k in a:
+        assert np.array_equal(b[k], 2.0 * a[k]), k   # the same bits twice: a doubling is exact
