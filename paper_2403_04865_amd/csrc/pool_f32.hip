@@ -40,7 +40,8 @@ __device__ __forceinline__ f32x4 ld4(const float* row, int k, int n) {
 }
 
 // Pre-activations of 32 rows x 32 gate units of V and of U, K split over the wavefronts, then per element
-//   forward   w t s summed over the gate units: part[blockIdx.y][n] (blockIdx.y walks over blocks of gate units)
+//   forward   w t s summed over a block's gate units: part[blockIdx.y][n], or over all of them, block by block in the order
+//             in which the parts would be added, where there is room for one part only (gridDim.y = 1): the same bits
 //   backward  Dp[n] = [dpV | dpU] (2 M_h), dwp[blockIdx.x][j] = sum over the 32 rows of da t s
 // where t = tanh(V h + b_V), s = sigmoid(U h + b_U), da_n = alpha_n dz . (h_n - z).  All of it stays float32: the column
 // sums of the backward's terms cancel almost completely (the da of a slide add up to zero).
@@ -55,12 +56,12 @@ __global__ void __launch_bounds__(512) pool_gate_f32_k(PoolArgs p, float* __rest
   const float* hrow = p.H + (ok ? n : p.N - 1) * D;
   const float* zv = p.scal + pool_z_off(p.C);
   if (!BWD && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p.ticket = 0;
-  float part = 0.f;
+  float logit = 0.f;   // threads 0 .. 31
   for (int ub = blockIdx.y; ub * 32 < Mh; ub += gridDim.y) {
     const int u = ub * 32 + li < Mh ? ub * 32 + li : Mh - 1;
     const float *vr = p.VW + (size_t)u * D, *ur = p.UW + (size_t)u * D;
     f32x16 av = zero16(), au = zero16();
-    float dot = 0.f;
+    float dot = 0.f, part = 0.f;
     for (int c0 = wave; c0 < nc; c0 += U * W) {   // U steps' loads in flight
       f32x4 h[U], v[U], w[U];
 #pragma unroll
@@ -141,17 +142,21 @@ __global__ void __launch_bounds__(512) pool_gate_f32_k(PoolArgs p, float* __rest
         }
       }
     }
+    if constexpr (!BWD) {
+      if (wave < 4) aux[wave * 64 + lane] = part;
+    }
     __syncthreads();   // the partial blocks have been read
+    if constexpr (!BWD) {   // (aux is next written behind the next block's barrier)
+      if (threadIdx.x < 32) {
+        float a = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a += aux[q * 64 + li] + aux[q * 64 + 32 + li];
+        logit += a;
+      }
+    }
   }
   if constexpr (!BWD) {
-    if (wave < 4) aux[wave * 64 + lane] = part;
-    __syncthreads();
-    if (threadIdx.x < 32 && ok) {
-      float a = 0.f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a += aux[q * 64 + li] + aux[q * 64 + 32 + li];
-      out[blockIdx.y * p.N + n] = a;
-    }
+    if (threadIdx.x < 32 && ok) out[blockIdx.y * p.N + n] = logit;
   }
 }
 
@@ -428,8 +433,8 @@ hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
     return hipGetLastError();
   }
   int parts = (p.Mh + 31) / 32;
-  if ((size_t)parts * p.N > p.a_room) parts = (int)(p.a_room / p.N);
-  if (parts < 1) return hipErrorInvalidValue;
+  if ((size_t)parts * p.N > p.a_room) parts = 1;   // the fixed array of mil_pool_fwd_static, near its limit
+  if ((size_t)p.N > p.a_room) return hipErrorInvalidValue;
   hipError_t e = vec_ok(p) ? go_gate<true, false>(p, p.a_tmp, nullptr, parts, s) : go_gate<false, false>(p, p.a_tmp, nullptr, parts, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((pool_softmax_part_k<16, false>), dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, parts);
