@@ -165,7 +165,7 @@ __device__ __attribute__((aligned(16))) float g_zero4[4];
 // TN: 64 x 64 of the result per workgroup, both operands as [32 rows of m][64 columns] in LDS.  An MFMA operand is one
 // float per lane, 32 consecutive columns of one row of m for each half wavefront: a plain read, nothing is transposed.
 // Rows past the slab's end and columns past the matrix come from a block of zeros.  The column sums of A (bias
-// gradients) ride along in the registers that hold A's operands.
+// gradients) ride along in the registers that hold A's operands: 16 rows of a step first, then the even and the odd steps.
 __global__ void __launch_bounds__(256, 4) gemm_tn_f32_k(GemmTN g, int per) {
   constexpr int STAGE = 2 * BK * 64;
   __shared__ __attribute__((aligned(16))) float st0[STAGE], st1[STAGE];
@@ -194,28 +194,31 @@ __global__ void __launch_bounds__(256, 4) gemm_tn_f32_k(GemmTN g, int per) {
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  float cs = 0.f;
+  float cs0 = 0.f, cs1 = 0.f;
   const int fcol = lane & 31, half = lane >> 5;
-  auto step = [&](const float* s, float* next, int kt) __attribute__((always_inline)) {
+  auto step = [&](const float* s, float* next, int kt, float& cs) __attribute__((always_inline)) {
     step_barrier();
     if (kt + 1 < nk) issue(next, kt + 1);
+    float c16 = 0.f;
     const float* sa = s + half * 64 + wi * 32 + fcol;
     const float* sb = s + BK * 64 + half * 64 + wj * 32 + fcol;
 #pragma unroll
     for (int k = 0; k < BK; k += 2) {
       const float a = sa[k * 64], b = sb[k * 64];
-      cs += a;
+      c16 += a;
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
     }
+    cs += c16;
   };
   if (nk > 0) issue(st0, 0);
   int kt = 0;
   for (; kt + 2 <= nk; kt += 2) {
-    step(st0, st1, kt);
-    step(st1, st0, kt + 1);
+    step(st0, st1, kt, cs0);
+    step(st1, st0, kt + 1, cs1);
   }
-  if (kt < nk) step(st0, st1, kt);
+  if (kt < nk) step(st0, st1, kt, cs0);
   if (g.cs_part && blockIdx.y == 0 && wj == 0) {
+    float cs = cs0 + cs1;
     cs += __shfl_xor(cs, 32, 64);
     const int i = i0 + wi * 32 + fcol;
     if (half == 0 && i < g.N1) g.cs_part[(size_t)slab * g.N1 + i] = cs;
@@ -258,12 +261,16 @@ bool gemm_tn_f32_ok(const GemmTN& g) {
 // slab's result is written and read again - except where few tiles would leave units idle, which 32-row slabs may fill.
 // Measured: M = 12,017, 1536 x 384: 16 slabs 151 us, 9 slabs 165, 4 slabs 191 (258 .. 274 with the vector kernel); 192 x 64: 32
 // slabs 12 us, 8 slabs 39; M = 788, 192 x 64: 32 slabs 3.4 us, 7 slabs 5.6.
+// Never fewer than eight of 512 rows: a slab is one chain of float32 additions, two rows each.
 int gemm_tn_f32_slabs(const GemmTN& g, int max_slabs) {
   const long long tiles = (long long)((g.N1 + 63) / 64) * ((g.N2 + 63) / 64);
   long long s = (2304 + tiles - 1) / tiles, by_rows = (g.M + 127) / 128, idle = 512 / tiles;
   if (idle > (g.M + 31) / 32) idle = (g.M + 31) / 32;
   if (by_rows < idle) by_rows = idle;
   if (s > by_rows) s = by_rows;
+  long long chain = (g.M + 511) / 512;
+  if (chain > 8) chain = 8;
+  if (s < chain) s = chain;
   if (s > max_slabs) s = max_slabs;
   return s < 1 ? 1 : (int)s;
 }

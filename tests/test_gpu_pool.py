@@ -178,3 +178,41 @@ def test_any_nonzero_accumulate_adds():
     b = g.step(X, 1, accumulate=65536)["grads"]
     for k in a:
         assert np.array_equal(b[k], 2.0 * a[k]), k   # the same bits twice: a doubling is exact
+
+
+# Column sums of the gate gradients (db_V, db_U) in short chains of float32 additions: the rows come in two runs whose terms have
+# opposite signs, so that a chain along one run grows to hundreds of terms before the other run takes it back.  Limit: two
+# roundings, 2^-23 (one chain of 512 terms per half wavefront: 1.6e-7 and 1.4e-7; in steps of 16: 1.1e-7 and 0.9e-7)
+def test_pool_fp32_gate_bias_sums():
+    import torch
+    from oracle import slide_oracle as so
+    from paper_2403_04865_amd import SlideLib
+    from slide_harness import lib_config, rel_l2
+    N = 65536
+    cfg = gen.CONFIGS["medium"][0]
+    print(f"case pool gate bias sums N={N} D={cfg.dim} Mh={cfg.mil_hidden} fp32", flush=True)
+    prm = gen.make_params(cfg, gen.SEEDS["medium"][1], perturbed=True)
+    for k in ("mil.V.W", "mil.U.W", "mil.w"):
+        prm[k] = prm[k] * 4.0
+    prm = {k: np.asarray(v, dtype=np.float32).astype(np.float64) for k, v in prm.items()}
+    H = gen.make_features(cfg, N, 5).astype(np.float32)
+    H[N // 2:] += np.float32(0.5) * np.random.default_rng(1).standard_normal(cfg.dim).astype(np.float32)
+    dev = torch.device("cuda:0")
+    lib = SlideLib(lib_config(cfg, 0))
+    flat = np.zeros(lib.slide_param_count(), dtype=np.float32)
+    for nm, off, ln in lib.param_layout():
+        flat[off:off + ln] = np.asarray(prm[nm], dtype=np.float32).reshape(-1)
+    params = torch.from_numpy(flat).to(dev)
+    grads = torch.zeros_like(params)
+    nbytes = lib.slide_pool_arena_bytes(N)
+    arena = torch.empty(nbytes + 256, dtype=torch.uint8, device=dev)
+    o = (-arena.data_ptr()) % 256
+    lib.slide_bind(params, grads, arena[o:o + nbytes])
+    feats = torch.from_numpy(H).to(dev)
+    lib.mil_pool_bwd(feats, N, 1, torch.zeros_like(feats), 0)
+    torch.cuda.synchronize()
+    _, ref = so.pool_bwd(so.pool_fwd(prm, H.astype(np.float64), 1, cfg)[4])
+    g = grads.cpu().numpy().astype(np.float64)
+    errs = {nm: rel_l2(g[off:off + ln], ref[nm].reshape(-1)) for nm, off, ln in lib.param_layout() if nm.startswith("mil.")}
+    print(errs, flush=True)
+    assert errs["mil.V.b"] < 2.0 ** -23 and errs["mil.U.b"] < 2.0 ** -23, errs
