@@ -123,6 +123,38 @@ def test_second_backward_over_one_forward(name):
         assert np.array_equal(a["grads"][k], b[k]), k
 
 
+# the aggregator over 2048-wide rows: 67 rows are three blocks of 32, the last of three rows, and nine groups of eight; 30 gate
+# units are no multiple of four.  Against the oracle on the library's own features, and a second backward
+@pytest.mark.timeout(300)
+def test_wide_aggregator_over_several_blocks():
+    from dataclasses import replace
+    import torch
+    from oracle import resnet_oracle as ro
+    from resnet_harness import GpuResNet, resnet_inputs
+    from slide_harness import rel_l2
+    cfg, _, X, label = resnet_inputs("rn_tiny_bneck", n=67)
+    cfg = replace(cfg, mil_hidden=30)
+    prm = gen.make_resnet_params(cfg, gen.RESNET_SEEDS["rn_tiny_bneck"][1])
+    for k in ("mil.V.W", "mil.U.W", "mil.w"):   # gates beyond their linear range
+        prm[k] = prm[k] * 4.0
+    print(f"case wide aggregator n=67 D={cfg.dim} Mh=30", flush=True)
+    g = GpuResNet(cfg, prm, 67)
+    a = g.step(X, label)
+    prm = {k: np.asarray(v, dtype=np.float32).astype(np.float64) for k, v in prm.items()}
+    loss, y, alpha, _, cache = ro.pool_fwd(prm, a["H"], label, cfg)
+    G, grads = ro.pool_bwd(cache)
+    errs = {"loss": abs(a["loss"] - loss) / abs(loss), "logits": rel_l2(a["logits"], y), "alpha": rel_l2(a["alpha"], alpha),
+            "G": rel_l2(a["G"], G), **{k: rel_l2(a["grads"][k], v) for k, v in grads.items()}}
+    print("worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:5], flush=True)
+    assert max(errs.values()) <= 1e-4, errs   # the bound of the float32 aggregator tests
+    g.lib.resnet_slide_step_bwd(False)
+    torch.cuda.synchronize()
+    b = g.grads_dict()
+    assert np.array_equal(a["G"], g.view(g.lib.resnet_feature_grads(), (67, cfg.dim)))
+    for k in b:
+        assert np.array_equal(a["grads"][k], b[k]), k
+
+
 @pytest.mark.timeout(300)
 def test_state_and_arena_errors():
     import torch
