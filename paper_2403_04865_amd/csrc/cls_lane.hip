@@ -303,7 +303,7 @@ hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda
                             int N, int K, const float* bias, const float* resid, long long ldr, float* out, long long ldc,
                             void* copy, long long ldcopy, const float* gam, const float* bet, float eps, float* lnout,
                             hipStream_t s) {
-  if (N % 64 || K % 64 || n <= 0 || (gam && (K > 1024 || a_bf16 || !gelu)) || (gelu && a_bf16)) return hipErrorInvalidValue;
+  if (N % 64 || K % 64 || n <= 0 || gelu != (gam != nullptr) || (gelu && (K > 1024 || a_bf16))) return hipErrorInvalidValue;
   LaneGemm g{A, lda, (const bf16*)W, ldw, n, N, K, bias, resid, ldr, out, ldc, (bf16*)copy, ldcopy, gam, bet, eps};
   // 32 x 32 blocks (and the LayerNorm on the way in) up to 400,000 results, 64 x 64 beyond, which read half the operand bytes;
   // both give the same bits.  The forward of ViT-S, ms, with the first MLP matrix in the one / in the other form: 200 tiles
@@ -315,7 +315,7 @@ hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda
     if (e != hipSuccess) return e;
     g.A = lnout; g.lda = K;
   }
-  if (gelu) return small ? (gam ? go<1, false, 1, true>(g, s) : go<1, false, 1, false>(g, s)) : go<1, false, 2, false>(g, s);
+  if (gelu) return small ? go<1, false, 1, true>(g, s) : go<1, false, 2, false>(g, s);
   if (a_bf16) return small ? go<0, true, 1, false>(g, s) : go<0, true, 2, false>(g, s);
   return small ? go<0, false, 1, false>(g, s) : go<0, false, 2, false>(g, s);
 }

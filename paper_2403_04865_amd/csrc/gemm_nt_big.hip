@@ -19,12 +19,10 @@
 //     accumulators are free again and the next tile starts at once.  During its steps 1..4 the parked
 //     block goes, one 32-row strip per step, through a wave-private LDS patch (the MFMA operands are
 //     passed swapped, so a lane holds runs of four neighbouring columns of one row and writes 8 bytes;
-//     it reads back 16-byte row segments), is combined with the residual / the stored GELU derivative or
-//     run through the GELU table, and is stored with 16-byte accesses along rows.
+//     it reads back 16-byte row segments), is combined with the residual / the stored GELU derivative, and is
+//     stored with 16-byte accesses along rows.
 //     The sum with the residual and the product with the GELU derivative are formed in fp32 from the
 //     bf16-rounded GEMM result and rounded once more.
-//   * GELU and its derivative come from a table of the normal CDF and of d/dx (x cdf(x)) in LDS, linearly
-//     interpolated at 1/32 steps (error < 1e-4, far below bf16 rounding).
 #include "gemm_epi.h"
 
 #include <type_traits>
@@ -40,7 +38,6 @@ constexpr int WBM = 4, WBN = 3;                    // 32 x 32 accumulators per w
 constexpr int RSTEP = NTH / 8;                     // rows per loader pass
 constexpr int CA = BM / RSTEP, CB = BN / RSTEP;    // 16-byte chunks per thread and K step
 constexpr int STAGE = (BM + BN) * LDT;             // bf16 elements per LDS stage
-constexpr int TAB_N = 448;                         // table over [-7, 7) in steps of 1/32
 constexpr int PSB = 208;                           // patch row stride in bytes (96 bf16 + 16)
 constexpr int PATCH_BYTES = 32 * PSB;              // one 32 x 96 bf16 strip per wavefront
 constexpr int NPASS = 7;                           // 12 lanes per row, 5 rows per pass, lanes 60..63 idle
@@ -73,18 +70,6 @@ __device__ __forceinline__ void unpack8(u32x4 t, float (&v)[8]) {
   }
 }
 
-// table entry k: {cdf(x_k), cdf(x_k+1) - cdf(x_k), c(x_k), c(x_k+1) - c(x_k)}, x_k = -7 + k/32,
-// cdf = standard normal distribution function, dg(x) = cdf(x) + x * pdf(x) = d/dx (x cdf(x)) and c = dg8_code(dg),
-// the derivative in the code space of its one-byte storage
-__device__ __forceinline__ void gelu_both_tab(const float4* tab, float x, float* gl, float* dgc) {
-  float t = __builtin_amdgcn_fmed3f(x * 32.0f + 224.0f, 0.0f, (float)TAB_N - 0.001f);
-  int k = (int)t;                       // t >= 0: truncation is the floor
-  float f = __builtin_amdgcn_fractf(t);
-  float4 e = tab[k];
-  *gl = x * (e.x + f * e.y);
-  *dgc = e.z + f * e.w;
-}
-
 template <class F, int... Is>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
   (f(std::integral_constant<int, Is>{}), ...);
@@ -97,7 +82,7 @@ template <int V> using IC = std::integral_constant<int, V>;
 
 template <int MODE>
 __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) {
-  constexpr bool HAS_BIAS = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU;
+  constexpr bool HAS_BIAS = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID;
   constexpr bool HAS_AUX = MODE == EPI_BIAS_RESID || MODE == EPI_DGELU || MODE == EPI_ROWTAB;
   // stores issued in one burst at the end of a step measured slower than stores spread over the step
   constexpr bool LATE_STORES = false;
@@ -106,7 +91,6 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
   __shared__ __attribute__((aligned(16))) bf16 ring0[STAGE];
   __shared__ __attribute__((aligned(16))) bf16 ring1[STAGE];
   __shared__ __attribute__((aligned(16))) unsigned char patches[(NTH / 64) * PATCH_BYTES];
-  __shared__ float4 tab[MODE == EPI_BIAS_GELU ? TAB_N : 1];
   __shared__ __attribute__((aligned(16))) float lbias_all[BN];  // zeros when there is no bias
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -115,17 +99,6 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
   const int frow = lane & 31, fk = (lane >> 5) * 8;
   const int nk = g.K / BK;
   const int total = (MT + NXCD - 1) / NXCD * NXCD * NTL;
-
-  if (MODE == EPI_BIAS_GELU) {
-    // filled once per workgroup; the K-loop barriers order it before its first use
-    for (int k = tid; k < TAB_N; k += NTH) {
-      float x0 = -7.0f + (float)k * (1.0f / 32.0f), x1 = x0 + (1.0f / 32.0f);
-      float c0 = 0.5f * (1.0f + erff(x0 * 0.70710678118654752f)), c1 = 0.5f * (1.0f + erff(x1 * 0.70710678118654752f));
-      float d0 = c0 + x0 * 0.39894228040143268f * expf(-0.5f * x0 * x0);
-      float d1 = c1 + x1 * 0.39894228040143268f * expf(-0.5f * x1 * x1);
-      tab[k] = make_float4(c0, c1 - c0, dg8_code(d0), dg8_code(d1) - dg8_code(d0));
-    }
-  }
 
   // (every lambda below is forced inline: left to its size heuristics the compiler keeps some of them as calls,
   // and the register arrays they touch would then live in memory)
@@ -245,10 +218,10 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
   const int er = lane < 60 ? lane / 12 : 0;    // row inside a pass (idle lanes: a valid address)
   const int erc = lane < 60 ? lane / 12 : 64;  // the same for comparisons: idle lanes never pass
   const int esg = lane % 12;
-  const unsigned ldc_b = 2u * (unsigned)g.ldc, ldc2_b = (unsigned)g.ldc2;   // bytes (the derivative: one per element)
+  const unsigned ldc_b = 2u * (unsigned)g.ldc;   // bytes
   const unsigned lda_b = MODE == EPI_DGELU ? (unsigned)g.ldpre : 2u * (unsigned)g.ldr;
   constexpr int AUXW = MODE == EPI_DGELU ? 1 : 2;   // bytes per element of the auxiliary operand
-  const unsigned eo_c = (unsigned)er * ldc_b + esg * 16, eo_c2 = (unsigned)er * ldc2_b + esg * 8;
+  const unsigned eo_c = (unsigned)er * ldc_b + esg * 16;
   const unsigned eo_a = (unsigned)er * lda_b + esg * (8 * AUXW);
   unsigned char* const pw = patches + wave * PATCH_BYTES + (lane & 31) * PSB + (lane >> 5) * 8;
   const unsigned char* const pr = patches + wave * PATCH_BYTES + er * PSB + esg * 16;
@@ -292,7 +265,6 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
   };
   // pass p of strip I: combine the row segment with the auxiliary operand (results stay in registers) ...
   u32x4 res[NPASS];
-  u32x2 res2[MODE == EPI_BIAS_GELU ? NPASS : 1];
   auto bg_cmp = [&](auto ic, auto pc) __attribute__((always_inline)) {
     constexpr int I = decltype(ic)::value, p = decltype(pc)::value;
     if constexpr (MODE == EPI_PLAIN || MODE == EPI_BIAS) {
@@ -304,7 +276,7 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] += t[e];
       res[p] = pack8(v);
-    } else if constexpr (MODE == EPI_DGELU) {
+    } else {  // EPI_DGELU
       float v[8], t0[4], t1[4];
       unpack8(rowdat[p], v);
       dg8_unpack4(auxv[I & 1][p][0], t0);
@@ -312,18 +284,6 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
 #pragma unroll
       for (int e = 0; e < 4; ++e) { v[e] *= t0[e]; v[4 + e] *= t1[e]; }
       res[p] = pack8(v);
-    } else {  // EPI_BIAS_GELU: out = gelu(m), out2 = the code of gelu'(m), m the bf16-rounded pre-activation
-      float v[8], t[8];
-      unpack8(rowdat[p], v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float gl, dg;
-        gelu_both_tab(tab, v[e], &gl, &dg);
-        v[e] = gl;
-        t[e] = dg;
-      }
-      res[p] = pack8(v);
-      res2[p] = u32x2{dg8_pack4_code(t[0], t[1], t[2], t[3]), dg8_pack4_code(t[4], t[5], t[6], t[7])};
     }
   };
   // ... and its stores.  They are issued after the step's operand loads: memory operations complete in
@@ -335,10 +295,6 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
       bool ok = p * 5 + erc < lim;
       char* o = (char*)g.out + ((pmw + I * 32 + p * 5) * (long long)ldc_b + 2 * pnw);
       if (ok) __builtin_nontemporal_store(res[p], reinterpret_cast<u32x4*>(o + eo_c));
-      if constexpr (MODE == EPI_BIAS_GELU) {
-        char* o2 = (char*)g.out2 + ((pmw + I * 32 + p * 5) * (long long)ldc2_b + pnw);
-        if (ok) __builtin_nontemporal_store(res2[p], reinterpret_cast<u32x2*>(o2 + eo_c2));
-      }
     }
   };
 
@@ -510,9 +466,9 @@ __global__ void __launch_bounds__(NTH) gemm_nt_big_k(GemmNT g, int MT, int NTL) 
 // of gemm_nt_mfma_ok.  The patch-embedding epilogue (row-mapped output) stays with the small kernel.
 bool gemm_nt_big_ok(const GemmNT& g) {
   bool shape = g.M < (1LL << 31) && g.N % BN == 0 && g.lda < (1 << 20) && g.ldb < (1 << 20) && g.ldc < (1 << 20) &&
-               g.ldc2 < (1 << 20) && g.ldr < (1 << 20) && g.ldpre < (1 << 20) && g.K % (2 * BK) == 0 &&
+               g.ldr < (1 << 20) && g.ldpre < (1 << 20) && g.K % (2 * BK) == 0 &&
                g.K >= MIN_STEPS * BK && g.M >= 4096;
-  bool mode = g.epi == EPI_PLAIN || g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU || g.epi == EPI_DGELU ||
+  bool mode = g.epi == EPI_PLAIN || g.epi == EPI_BIAS || g.epi == EPI_DGELU ||
               (g.epi == EPI_BIAS_RESID && sizeof(rs_bf16path_t) == 2) ||
               (g.epi == EPI_ROWTAB && sizeof(rs_bf16path_t) == 2 && g.rperiod >= 160);
   return shape && mode && g.amap.g2 == 0;
@@ -543,7 +499,6 @@ hipError_t launch_gemm_nt_big(const GemmNT& g, hipStream_t s) {
     case EPI_PLAIN: return launch_big<EPI_PLAIN>(g, s);
     case EPI_BIAS: return launch_big<EPI_BIAS>(g, s);
     case EPI_BIAS_RESID: return launch_big<EPI_BIAS_RESID>(g, s);
-    case EPI_BIAS_GELU: return launch_big<EPI_BIAS_GELU>(g, s);
     case EPI_DGELU: return launch_big<EPI_DGELU>(g, s);
     case EPI_ROWTAB: return launch_big<EPI_ROWTAB>(g, s);
     default: return hipErrorInvalidValue;

@@ -345,7 +345,7 @@ hipError_t go_mid(const GemmNT& g, hipStream_t s) {
 // can take.
 hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s) {
   if (gemm_nt_gelu_ok(g)) return launch_gemm_nt_gelu(g, s);
-  if (g.epi == EPI_BIAS_GELU || !gemm_nt_big_ok(g)) return go_mid<false>(g, s);
+  if (!gemm_nt_big_ok(g)) return go_mid<false>(g, s);
   return large_fills(g) ? launch_gemm_nt_big(g, s) : go_mid<true>(g, s);
 }
 

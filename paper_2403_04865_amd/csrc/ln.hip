@@ -2,9 +2,7 @@
 // row reductions again from the saved layer input.  Three generations of kernels, picked by the launchers at the
 // end of the file: ln_*_row16_k (bf16 path, D = 384 / 768: 16 or 32 lanes per row, 16-byte accesses, several rows
 // per wavefront; the ones the large workloads run), ln_*_fast_k (paired elements, any D up to 1024) and ln_*_k (one
-// wavefront per row, any element types; the fp32 path).  The backward can also write the normalised rows
-// x_hat * gamma + beta next to dx (the operand of the weight gradient behind the LayerNorm) where the forward's own
-// copy was not kept.
+// wavefront per row, any element types; the fp32 path).
 #include "slide_internal.h"
 
 namespace sl {
@@ -316,11 +314,8 @@ __global__ void __launch_bounds__(256) ln_bwd_row16_k(const bf16* __restrict__ x
                                                       const bf16* __restrict__ dy, long long dys,
                                                       const float* __restrict__ gam, const bf16* __restrict__ dres,
                                                       bf16* __restrict__ dxo, long long os, long long rows, float eps,
-                                                      float* __restrict__ part, const float* __restrict__ bet,
-                                                      bf16* __restrict__ uo, long long us, int dres_period) {
+                                                      float* __restrict__ part, int dres_period) {
   // dres_period != 0: dres has a term only for rows r with r % dres_period == 0 (the other rows of it are not read)
-  // uo != nullptr: the normalised rows xh * gamma + beta (the forward output, which the weight gradient of the
-  // following linear map needs and the forward did not keep) are written on the way, [rows][us]
   constexpr int D = 8 * LPR * NP, RPW = 64 / LPR;   // rows per wavefront
   __shared__ float red[4 * 2 * D];
   int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & (LPR - 1), grp = lane / LPR;
@@ -389,17 +384,6 @@ __global__ void __launch_bounds__(256) ln_bwd_row16_k(const bf16* __restrict__ x
       }
     s1 = sum_row<LPR>(s1) * (1.0f / D);
     s2 = sum_row<LPR>(s2) * (1.0f / D);
-    if (uo && ok) {
-#pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        int c = (l16 + LPR * k) * 8;
-        float4 b0 = *reinterpret_cast<const float4*>(bet + c), b1 = *reinterpret_cast<const float4*>(bet + c + 4);
-        float bb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w}, o[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = v[k][e] * g[k][e] + bb[e];
-        ln_st8(uo + r * us + c, o);
-      }
-    }
     if (ok) {
 #pragma unroll
       for (int k = 0; k < NP; ++k) {
@@ -563,15 +547,6 @@ int ln_bwd_slabs(long long rows) {
   return (int)s;
 }
 
-// the backward kernel that can also write the normalised rows is the 16-lanes-per-row one
-bool ln_bwd_emits_u(int dt, const void* x, long long x_stride, const void* dy, long long dy_stride, const float* gam,
-                    const void* dres, const void* dx_out, long long o_stride, int D, bool dy_f32, const float* bet,
-                    const void* u_out, long long u_stride) {
-  return dt == DT_BF16 && !dy_f32 && ln_row16_ok(x, dy, dx_out, x_stride, dy_stride, o_stride, D) &&
-         ((uintptr_t)gam & 15) == 0 && ((uintptr_t)dres & 15) == 0 && ((uintptr_t)bet & 15) == 0 &&
-         ((uintptr_t)u_out & 15) == 0 && u_stride % 8 == 0;
-}
-
 // a residual-gradient term on every dres_period-th row only: the kernel with 16 (32) lanes per row takes it
 bool ln_bwd_periodic_ok(int dt, const void* x, long long x_stride, const void* dy, long long dy_stride, const float* gam,
                         const void* dres, const void* dx_out, long long o_stride, int D, bool dy_f32) {
@@ -581,19 +556,16 @@ bool ln_bwd_periodic_ok(int dt, const void* x, long long x_stride, const void* d
 
 hipError_t launch_ln_bwd(int dt, const void* x, long long x_stride, const void* dy, long long dy_stride,
                          const float* gam, const void* dres, void* dx_out, void* dx_out_t, long long o_stride,
-                         long long rows, int D, float eps, float* part, bool dy_f32, hipStream_t s, const float* bet,
-                         void* u_out, long long u_stride, int dres_period) {
+                         long long rows, int D, float eps, float* part, bool dy_f32, hipStream_t s, int dres_period) {
   if (rows <= 0) return hipSuccess;
   if (dres_period && !ln_bwd_periodic_ok(dt, x, x_stride, dy, dy_stride, gam, dres, dx_out, o_stride, D, dy_f32))
-    return hipErrorInvalidValue;
-  if (u_out && !ln_bwd_emits_u(dt, x, x_stride, dy, dy_stride, gam, dres, dx_out, o_stride, D, dy_f32, bet, u_out, u_stride))
     return hipErrorInvalidValue;
   dim3 grid(ln_bwd_slabs(rows));
   size_t lds = (size_t)4 * 2 * D * sizeof(float);
   if (dt == DT_BF16 && !dy_f32 && ln_row16_ok(x, dy, dx_out, x_stride, dy_stride, o_stride, D) &&
       ((uintptr_t)gam & 15) == 0 && ((uintptr_t)dres & 15) == 0) {
-    if (D == 384) hipLaunchKernelGGL((ln_bwd_row16_k<3, 16>), grid, dim3(256), 0, s, (const bf16*)x, x_stride, (const bf16*)dy, dy_stride, gam, (const bf16*)dres, (bf16*)dx_out, o_stride, rows, eps, part, bet, (bf16*)u_out, u_stride, dres_period);
-    else hipLaunchKernelGGL((ln_bwd_row16_k<3, 32>), grid, dim3(256), 0, s, (const bf16*)x, x_stride, (const bf16*)dy, dy_stride, gam, (const bf16*)dres, (bf16*)dx_out, o_stride, rows, eps, part, bet, (bf16*)u_out, u_stride, dres_period);
+    if (D == 384) hipLaunchKernelGGL((ln_bwd_row16_k<3, 16>), grid, dim3(256), 0, s, (const bf16*)x, x_stride, (const bf16*)dy, dy_stride, gam, (const bf16*)dres, (bf16*)dx_out, o_stride, rows, eps, part, dres_period);
+    else hipLaunchKernelGGL((ln_bwd_row16_k<3, 32>), grid, dim3(256), 0, s, (const bf16*)x, x_stride, (const bf16*)dy, dy_stride, gam, (const bf16*)dres, (bf16*)dx_out, o_stride, rows, eps, part, dres_period);
     return hipGetLastError();
   }
   {

@@ -217,16 +217,11 @@ hipError_t launch_ln_fwd(int dt, const void* x, long long x_stride, const float*
 int ln_bwd_slabs(long long rows);
 hipError_t launch_ln_bwd(int dt, const void* x, long long x_stride, const void* dy, long long dy_stride,
                          const float* gam, const void* dres, void* dx_out, void* dx_out_t, long long o_stride,
-                         long long rows, int D, float eps, float* part, bool dy_f32, hipStream_t s,
-                         const float* bet = nullptr, void* u_out = nullptr, long long u_stride = 0, int dres_period = 0);
+                         long long rows, int D, float eps, float* part, bool dy_f32, hipStream_t s, int dres_period);
 // dres_period != 0: dres contributes on rows r % dres_period == 0 only (its other rows are not read); only where
 // ln_bwd_periodic_ok says so
 bool ln_bwd_periodic_ok(int dt, const void* x, long long x_stride, const void* dy, long long dy_stride, const float* gam,
                         const void* dres, const void* dx_out, long long o_stride, int D, bool dy_f32);
-// u_out: also write the normalised rows x_hat * gamma + beta (bf16 [rows][u_stride]); only where ln_bwd_emits_u says so
-bool ln_bwd_emits_u(int dt, const void* x, long long x_stride, const void* dy, long long dy_stride, const float* gam,
-                    const void* dres, const void* dx_out, long long o_stride, int D, bool dy_f32, const float* bet,
-                    const void* u_out, long long u_stride);
 
 // Attention over qkv [n*T, 3D] (T): O [n*T, D] (T), lse [n,H,T] fp32.
 // cls_only (matrix-core kernels only, see attn_cls_only_ok): only query 0 of every tile is wanted (forward: the rest

@@ -392,7 +392,7 @@ void ln_bwd(Sums& q, const void* x, long long xs, const void* dy, long long dys,
   float* part = q.room((size_t)slabs * 2 * c->D);
   launch(r, K_LN_BWD, 0, bytes, [&] {
     return launch_ln_bwd(c->dt, x, xs, dy, dys, c->params + o_gam, dres, dxo, dxo_t, os, rows, c->D, c->cfg.ln_eps, part,
-                         dy_f32, r.s, nullptr, nullptr, 0, dres_period);
+                         dy_f32, r.s, dres_period);
   });
   if (o_bet == o_gam + (size_t)c->D) {   // gain and shift are neighbours in the parameter vector, as in a slab's partials
     q.add(part, slabs, 2LL * c->D, 2LL * c->D, c->grads + o_gam, accumulate);
