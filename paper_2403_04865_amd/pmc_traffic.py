@@ -23,7 +23,9 @@ import sys
 
 FAMILIES = [("gemm_nt", ("gemm_nt_",)), ("gemm_tn", ("gemm_tn_",)), ("attn_fwd", ("attn_fwd",)),
             ("attn_bwd", ("attn_bwd",)), ("ln_fwd", ("ln_fwd",)), ("ln_bwd", ("ln_bwd",)),
-            ("pool_fwd", ("pool_gate", "pool_combine", "pool_alpha", "pool_cast")), ("pool_bwd", ("pool_bwd",)),
+            # (the float32 gate kernels, pool_gate_f32_k and pool_wide_gate_k, run in both directions)
+            ("pool_fwd", ("pool_gate", "pool_combine", "pool_cast", "pool_softmax", "pool_wide_gate")),
+            ("pool_bwd", ("pool_bwd", "pool_g_f32", "pool_wide")),
             ("cls_lane", ("lane_",)),
             # convolutional encoders: forward and input gradient are launches of one kernel (family conv_nt)
             ("conv_nt", ("conv_nt_",)), ("conv_wgrad", ("conv_wgrad_",)), ("bn_stats", ("bn_stats_",)),
