@@ -209,6 +209,22 @@ struct RedList { int n = 0, blocks = 0; RedSeg seg[RED_MAX]; };
 bool red_add(RedList& L, const float* part, int slabs, long long stride, long long len, float* out, int accumulate);   // false: full
 hipError_t launch_reduce_partials(const RedList& L, hipStream_t s);
 
+// MLP half of a block in one kernel (mlp_fused.hip).  Forward: out = resid + gelu(A W1^T + b1) W2^T + b2 (h, code unused).
+// Backward (grad): h = (A W1^T) * derivative, out = h W2^T, with W1, W2 the transposed copies of fc2, fc1 and code the one-byte
+// codes of the derivative; no biases, no residual.  Row strides D and F.  out may be resid, neither may be A.
+struct MlpArgs {
+  const void* A;           // bf16 [M][D]
+  const void *W1, *W2;     // bf16 [F][D], [D][F]
+  const float *b1, *b2;
+  const void* resid;       // bf16 [M][D]
+  void* out;               // bf16 [M][D]
+  void* h;                 // bf16 [M][F]
+  const void* code;        // [M][F]
+  long long M; int F;
+};
+bool mlp_ok(const MlpArgs& g, int D, bool grad);
+hipError_t launch_mlp(const MlpArgs& g, bool grad, hipStream_t s);
+
 // LayerNorm.  x rows at x + r*x_stride (RS), out rows at out + r*out_stride (T, or fp32 when out_f32).
 hipError_t launch_ln_fwd(int dt, const void* x, long long x_stride, const float* gam, const float* bet, void* out,
                          long long out_stride, long long rows, int D, float eps, bool out_f32, hipStream_t s);

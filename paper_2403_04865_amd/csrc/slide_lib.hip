@@ -408,6 +408,16 @@ int check_bound(const slide_ctx* c) {
   return SLIDE_OK;
 }
 
+// MLP half of a block in one kernel where there is one for the shape.  false: not taken
+bool mlp_fused(Run& r, const MlpArgs& g, bool grad) {
+  slide_ctx* c = r.c;
+  if (c->dt != DT_BF16 || !c->use_mfma || !mlp_ok(g, c->D, grad)) return false;
+  const double hidden = grad ? 3 : 0, rows = grad ? 2 : 3;   // bytes per hidden element (gradient, code), rows moved
+  launch(r, K_GEMM_NT, 4.0 * g.M * c->D * g.F, (double)g.M * (g.F * hidden + c->D * rows * 2) + 4.0 * c->D * g.F,
+         [&] { return launch_mlp(g, grad, r.s); });
+  return true;
+}
+
 // One transformer block forward: x_in(l) -> x_in(l+1), leaving qkv, O, lse, x_mid, the MLP activation
 // a = gelu(m) and gelu'(m) of block l in their (per-block or shared) arena slots.  `replay` (backward of the
 // block-inputs-only policy): x_in(l+1) is already stored, so the fc2 GEMM is skipped.
@@ -519,6 +529,15 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
   }
   lane_attn_half(r, y, l, n, O, xmid);
   ln_fwd(r, xmid, D, c->params + o.ln2g, c->params + o.ln2b, u2, D, M);
+  if (!replay && !dg) {   // no backward reads the activations of this pass
+    MlpArgs g{};
+    g.A = u2; g.W1 = weight(c, wi + 2); g.W2 = weight(c, wi + 3); g.b1 = c->params + o.fc1b; g.b2 = c->params + o.fc2b;
+    g.resid = xmid; g.out = xout; g.M = M; g.F = F;
+    if (mlp_fused(r, g, false)) {
+      lane_mlp_half(r, y, l, n, xout);
+      return;
+    }
+  }
   {
     GemmNT g{};
     g.A = u2; g.lda = D; g.B = weight(c, wi + 2); g.ldb = D; g.M = M; g.N = F; g.K = D;
@@ -690,14 +709,18 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       continue;
     }
     // ---- MLP half: x_out = x_mid + gelu(LN2(x_mid) W1^T + b1) W2^T + b2
-    {  // dm = (dx W2) * gelu'(m), gelu'(m) as stored by the forward
+    // dm = (dx W2) * gelu'(m), gelu'(m) as stored by the forward;  du = dm W1
+    MlpArgs mg{};
+    mg.A = dxAt; mg.W1 = weight_t(c, wi + 3); mg.W2 = weight_t(c, wi + 2); mg.out = du; mg.h = dm; mg.code = m; mg.M = M; mg.F = F;
+    const bool fused = mlp_fused(r, mg, true);
+    if (!fused) {
       GemmNT g{};
       g.A = dxAt; g.lda = D; g.B = weight_t(c, wi + 3); g.ldb = D; g.M = M; g.N = F; g.K = D;
       g.epi = EPI_DGELU; g.pre = m; g.ldpre = F; g.out = dm; g.ldc = F;
       gemm_nt(r, g);
     }
     gemm_tn(q, dxAt, D, a, F, M, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, nullptr, nullptr, true);
-    {
+    if (!fused) {
       GemmNT g{};
       g.A = dm; g.lda = F; g.B = weight_t(c, wi + 2); g.ldb = F; g.M = M; g.N = D; g.K = F;
       g.epi = EPI_PLAIN; g.out = du; g.ldc = D;

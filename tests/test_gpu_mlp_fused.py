@@ -1,0 +1,48 @@
+"""MLP half of a block as one kernel: the same bits as the two GEMM launches, on both sides of the line that picks it.
+
+The kernel is taken from 0.58 rounds of 128-row workgroups on (149 of them on 256 compute units, 18,945 rows), backward and in
+forwards that no backward follows; a step's own forward and fewer rows take two GEMMs.  A step in chunks runs both kinds of
+forward, so what belongs to one tile has to agree with the whole step to the last bit; parameter gradients are the same
+terms added in another order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2403_04865_amd import SlideConfig, SlideLib
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(n, chunk, recompute, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    lib = SlideLib(SlideConfig(224, 16, 384, 2, 6, 4, 128, 1, dtype=1, recompute=recompute))
+    p = torch.randn(lib.slide_param_count(), device="cuda", generator=g).clamp_(-2, 2).mul_(0.05)
+    for name, off, length in lib.param_layout():
+        if name.endswith(".g"):
+            p[off:off + length] += 1.0
+    x = torch.randn((n, 3, 224, 224), device="cuda", generator=g).to(torch.bfloat16)
+    grads, dpix = torch.zeros_like(p), torch.zeros_like(x)
+    loss, logits, alpha = (torch.zeros(k, device="cuda") for k in (1, 1, n))
+    nbytes = lib.slide_chunked_arena_bytes(n, chunk) if chunk else lib.slide_arena_bytes(n)
+    arena = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    lib.slide_bind(p, grads, arena)
+    if chunk:
+        lib.slide_step_chunked(x, n, chunk, 1, 0, loss, logits, alpha, dpix)
+    else:
+        lib.slide_step_fwd(x, n, 1, loss, logits, alpha)
+        lib.slide_step_bwd(0, dpix)
+    torch.cuda.synchronize()
+    return [t.float().cpu().numpy() for t in (loss, logits, alpha, dpix, grads)]
+
+
+# tiles x 197 rows: 97 = 19,109 rows, the first count above the line (a ragged last workgroup); 130 = 25,610 with chunks below
+# the line; 167 = 32,899 rows, two workgroups more than a round; 333 = a round and chunks of 33 rows less and more than it
+@pytest.mark.parametrize("n,chunk,recompute", [(97, 49, 0), (130, 65, 1), (167, 84, 0), (167, 97, 1), (333, 167, 1)])
+def test_same_bits_as_two_launches(n, chunk, recompute):
+    print(f"case {n} tiles, chunks of {chunk}, recompute {recompute}", flush=True)
+    whole, parts = _run(n, 0, recompute, n), _run(n, chunk, recompute, n)
+    for a, b in zip(whole[:4], parts[:4]):
+        assert np.isfinite(a).all() and np.abs(a).max() > 0
+        np.testing.assert_array_equal(a, b)
+    # float32 sums of at most 66,000 terms in two orders: 2 sqrt(n) 2^-24 = 3.1e-5 of the terms' norm
+    assert np.linalg.norm(whole[4] - parts[4]) <= 3.1e-5 * np.linalg.norm(whole[4])
