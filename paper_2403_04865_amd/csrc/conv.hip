@@ -16,6 +16,7 @@
 //                  a fixed order by wgrad_reduce_k (no atomics: run-to-run identical), which also turns the
 //                  [co][tap][ci] order of the kernels into the parameter's [co][ci][kh][kw].
 #include "resnet_internal.h"
+#include "lds_dma.h"
 #include <type_traits>
 
 namespace sl {
@@ -76,29 +77,20 @@ __device__ __forceinline__ void launch_pos(long long m, long long M, const ConvG
   }
 }
 
-// stem geometry: element offset in the padded image of the 8 columns at contraction column k for produced row (n, y, x)
-__device__ __forceinline__ long long stem_off(const ConvGeom& g, int n, int y, int x, int k) {
-  int kh = k >> 5;
-  kh = kh > 6 ? 6 : kh;   // the eighth kernel row has zero weights: read the seventh again
-  return (((long long)n * g.YS + 2 * y + kh) * g.XS + 2 * x) * 4 + (k & 31);
-}
-
 constexpr int CBK = 64;   // channels of one tap per K step
 
 // ---------------------------------------------------------------------------------------------------------------
 // forward / input gradient
 // ---------------------------------------------------------------------------------------------------------------
-// The same contraction with global_load_lds_dwordx4: a wavefront instruction moves 64 x 16 bytes from 64 independent
-// global addresses to 1 KB of consecutive LDS (lane l -> bytes 16 l ..), without passing through registers, so three
+// Operands straight into LDS (lds_dma.h): a wavefront instruction moves 64 x 16 bytes from 64 independent
+// offsets to 1 KB of consecutive LDS (lane l -> bytes 16 l ..), without passing through registers, so three
 // K steps of operands are in flight per workgroup at no register cost and the loop waits only for the oldest.
 //   * One instruction fills 8 rows x 128 bytes (8 lanes per row).  Rows are unpadded; the 16-byte pieces of a row are
 //     stored permuted (piece c of row R sits in slot c ^ ((R >> 1) & 7)), which the loading lane realises by choosing
 //     its global address, so that the 16-byte fragment reads of 16 consecutive rows fall on 64 different banks.
-//   * A row in the zero padding reads a row of zeros in global memory instead (no branch, every lane loads).
+//   * A row in the zero padding is an offset outside of the buffer, which loads zeros (no branch, every lane loads).
 //   * Every wavefront owns a 64 x 64 block of the tile: 256 x 64 tiles (4 x 1 wavefronts) where the output has 64
 //     channels, 128 x 128 (2 x 2) otherwise.
-__device__ __attribute__((aligned(128))) bf16 g_zero_row[64];
-
 // LDS stages.  Two (64 / 80 KB per workgroup, two workgroups per compute unit, loads one step ahead) measured 22 %
 // faster over the ResNet18 step than three (one workgroup per compute unit, loads two steps ahead): the second
 // workgroup hides more than the deeper queue.
@@ -266,60 +258,92 @@ __global__ void __launch_bounds__(256) conv_nt_dl_k(ConvNT p, int row_tiles, int
   const int nky = p.g.KH > kh0 ? (p.g.KH - kh0 + tstep - 1) / tstep : 0, nkx = p.g.KW > kw0 ? (p.g.KW - kw0 + tstep - 1) / tstep : 0;
   const int nk = nky * nkx * cpt;
 
-  // Per row of the tile, once: the position, the address of its source row for tap offset zero and which of the
-  // launch's taps exist for it.  A K step then costs a mask test and the step's uniform offset per row.
-  int pn[AG], py[AG], px[AG], pc[AG];
-  const bf16* rb[AG];
-  unsigned rm[AG];
+  // Per row of the tile, once: the byte offset of its source row for tap offset zero, from the source row of the tile's
+  // first row on, and which of the launch's taps exist for it.  A K step then costs a mask test per row and the step's
+  // uniform offset.  `lead`: room in front, so that no offset is negative (rows above the first one's, taps that count
+  // backwards); nothing is read there.
   const int sh = p.g.stride >> 1;
+  const int rowb = 2 * p.Cs;   // bytes of a source row
+  const int lead = PW || STEM ? 0 : ((2 * p.g.pad + p.g.KH + 2) * p.g.XS) * rowb;
+  const int back = p.g.transposed ? (((p.g.KH - 1) >> sh) * p.g.XS + ((p.g.KW - 1) >> sh)) * rowb : 0;   // no uniform offset is, either
+  int vo[AG];
+  unsigned rm[AG];
+  __amdgpu_buffer_rsrc_t ra;
+  if (PW) {
+    ra = dma_buffer(p.src + m0 * p.Cs, (p.M - m0) * rowb);
 #pragma unroll
-  for (int j = 0; j < AG; ++j) {
-    const int R = (j * 4 + wave) * 8 + lr;
-    pc[j] = (ls ^ ((R >> 1) & 7)) * 8;
-    if (PW) {
-      rb[j] = p.src + (m0 + R) * p.Cs + pc[j];
-      rm[j] = m0 + R < p.M ? 1u : 0u;
-      continue;
+    for (int j = 0; j < AG; ++j) {
+      const int R = (j * 4 + wave) * 8 + lr;
+      vo[j] = R * rowb + (ls ^ ((R >> 1) & 7)) * 16;
     }
-    launch_pos(m0 + R, p.M, p.g, pn[j], py[j], px[j]);
-    if (!STEM) {
-      const int yb = p.g.transposed ? (py[j] + p.g.pad) >> sh : py[j] * p.g.stride - p.g.pad;
-      const int xb = p.g.transposed ? (px[j] + p.g.pad) >> sh : px[j] * p.g.stride - p.g.pad;
-      rb[j] = p.src + (((long long)pn[j] * p.g.YS + yb) * p.g.XS + xb) * p.Cs + pc[j];
-      unsigned m = 0;
-      for (int t = 0; t < nky * nkx; ++t) {
-        const int ty = t / nkx;
-        m |= (src_row(p.g, pn[j], py[j], px[j], kh0 + tstep * ty, kw0 + tstep * (t - ty * nkx)) >= 0 ? 1u : 0u) << t;
+  } else {
+    int fn, fy, fx;
+    launch_pos(m0, p.M, p.g, fn, fy, fx);
+    const int yf = STEM ? 2 * fy : p.g.transposed ? (fy + p.g.pad) >> sh : fy * p.g.stride - p.g.pad;
+    const long long first = ((long long)fn * p.g.YS + yf) * p.g.XS;   // source row (stem: pixel) the offsets count from
+    const int unit = STEM ? 8 : rowb;
+    const long long images = p.M / (p.g.cls ? (p.g.YO >> 1) * (p.g.XO >> 1) : p.g.YO * p.g.XO);
+    ra = dma_buffer((const char*)p.src + first * unit - lead, (images * p.g.YS * p.g.XS - first) * unit + lead);
+#pragma unroll
+    for (int j = 0; j < AG; ++j) {
+      const int R = (j * 4 + wave) * 8 + lr;
+      const int pc = (ls ^ ((R >> 1) & 7)) * 16;
+      int n, y, x;
+      launch_pos(m0 + R, p.M, p.g, n, y, x);
+      const bool ok = y != ROW_ABSENT;
+      if (STEM) {   // chunk pc of a step's 64 columns: kernel row pc / 64 of its two, 16-byte piece of that row
+        vo[j] = ok ? (((n - fn) * p.g.YS + 2 * y - yf) * p.g.XS + 2 * x) * 8 + (pc & 63) : DMA_ABSENT;
+        rm[j] = pc >> 6;
+        continue;
       }
-      rm[j] = m;
+      const int yb = p.g.transposed ? (y + p.g.pad) >> sh : y * p.g.stride - p.g.pad;
+      const int xb = p.g.transposed ? (x + p.g.pad) >> sh : x * p.g.stride - p.g.pad;
+      vo[j] = ok ? (((n - fn) * p.g.YS + yb - yf) * p.g.XS + xb) * rowb + pc + lead - back : DMA_ABSENT;
+      const int sm = p.g.stride - 1;   // a tap exists where both of its coordinates do
+      unsigned my = 0, m = 0;
+      for (int t = 0; t < nkx; ++t) {
+        const int k = kw0 + tstep * t, tx = x + p.g.pad - k;
+        const bool in = p.g.transposed ? (tx >= 0) & ((tx & sm) == 0) & ((tx >> sh) < p.g.XS) : (unsigned)(xb + k) < (unsigned)p.g.XS;
+        my |= (in ? 1u : 0u) << t;
+      }
+      for (int t = 0; t < nky; ++t) {
+        const int k = kh0 + tstep * t, ty = y + p.g.pad - k;
+        const bool in = p.g.transposed ? (ty >= 0) & ((ty & sm) == 0) & ((ty >> sh) < p.g.YS) : (unsigned)(yb + k) < (unsigned)p.g.YS;
+        m |= (in ? my : 0u) << (t * nkx);
+      }
+      rm[j] = ok ? m : 0u;
     }
   }
-  const bf16* wb[BG];
+  const __amdgpu_buffer_rsrc_t rw = dma_buffer(p.W + (long long)n0 * ldw, 2 * BN * ldw);
+  int wo[BG];
 #pragma unroll
   for (int j = 0; j < BG; ++j) {
     const int R = (j * 4 + wave) * 8 + lr;
-    wb[j] = p.W + (long long)(n0 + R) * ldw + (ls ^ ((R >> 1) & 7)) * 8;
+    wo[j] = R * 2 * (int)ldw + (ls ^ ((R >> 1) & 7)) * 16;
   }
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
   auto issue = [&](int kt, int st) {
     const int tap = kt / cpt, c0 = (kt - tap * cpt) * CBK;
     const int ty = tap / nkx;
     const int kh = kh0 + tstep * ty, kw = kw0 + tstep * (tap - ty * nkx);
-    const long long wcol = (long long)(kh * p.g.KW + kw) * p.Cs + c0;   // column of this step in the weight rows
-    // the tap's offset from a row's base address (input gradient: taps count backwards, in source steps)
-    const long long soff = (p.g.transposed ? -(long long)((kh >> sh) * p.g.XS + (kw >> sh)) : (long long)(kh * p.g.XS + kw)) * p.Cs + c0;
+    const int wcol = 2 * ((kh * p.g.KW + kw) * p.Cs + c0);   // this step's bytes in the weight rows
+    // the tap's offset from a row's (input gradient: taps count backwards, in source steps)
+    const int soff = (p.g.transposed ? -((kh >> sh) * p.g.XS + (kw >> sh)) : kh * p.g.XS + kw) * rowb + back + 2 * c0;
     bf16* sa = S + st * STAGE;
 #pragma unroll
     for (int j = 0; j < AG; ++j) {
-      const bf16* gp;
-      if (STEM) gp = py[j] != ROW_ABSENT ? p.src + stem_off(p.g, pn[j], py[j], px[j], c0 + pc[j]) : g_zero_row + pc[j];
-      else gp = (rm[j] >> tap) & 1u ? rb[j] + soff : g_zero_row + pc[j];
-      __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)(sa + (j * 4 + wave) * 8 * CBK), 16, 0, 0);
+      bf16* dst = sa + (j * 4 + wave) * 8 * CBK;
+      if (PW) {
+        dma16(ra, dst, vo[j], 2 * c0);
+      } else if (STEM) {
+        int r = (c0 >> 5) + (int)rm[j];
+        r = r > 6 ? 6 : r;   // the eighth kernel row has zero weights: read the seventh again
+        dma16(ra, dst, vo[j] + r * p.g.XS * 8, 0);
+      } else {
+        dma16(ra, dst, (rm[j] >> tap) & 1u ? vo[j] : DMA_ABSENT, soff);
+      }
     }
 #pragma unroll
-    for (int j = 0; j < BG; ++j)
-      __builtin_amdgcn_global_load_lds((gptr_t)(wb[j] + wcol), (lptr_t)(sa + BM * CBK + (j * 4 + wave) * 8 * CBK), 16, 0, 0);
+    for (int j = 0; j < BG; ++j) dma16(rw, sa + BM * CBK + (j * 4 + wave) * 8 * CBK, wo[j], wcol);
   };
 
   f32x16 acc[2][2];
@@ -411,19 +435,16 @@ __global__ void __launch_bounds__(256) conv_nt_halo_k(ConvNT p, int row_tiles, i
   const int nk = 9 * cpt;                            // a multiple of 3
   const int halo = p.g.XO + 1;
   const int sg = p.g.transposed ? -1 : 1;
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
 
   // the window: instruction q of this wavefront fills pieces [(q * 4 + wave) * 64, + 64) in row-major order
   const int ninst = wrows * cpr / 256;
+  const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + (m0 - halo) * p.Cs, (p.M - m0 + halo) * 2 * p.Cs);   // rows past the end: zeros
+  const int jlo = m0 < halo ? (int)(halo - m0) : 0, jhi = BM + 2 * halo;   // rows in front of the first one and behind the window too
   for (int q = 0; q < ninst; ++q) {
     const int gidx = (q * 4 + wave) * 64 + lane;
     const int j = gidx / cpr, sl = gidx - j * cpr;
     const int piece = (sl & ~7) | ((sl ^ (j >> 1)) & 7);
-    const long long f = m0 - halo + j;
-    const bool ok = (f >= 0) & (f < p.M) & (j < BM + 2 * halo);
-    const bf16* gp = ok ? p.src + f * p.Cs + piece * 8 : g_zero_row + (piece & 7) * 8;
-    __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)(Wd + (long long)(q * 4 + wave) * 64 * 8), 16, 0, 0);
+    dma16(rs, Wd + (q * 4 + wave) * 64 * 8, ((j >= jlo) & (j < jhi)) ? (j * p.Cs + piece * 8) * 2 : DMA_ABSENT, 0);
   }
 
   // weights: operand (j, ks) of K step kt is the 1 KB at slice (block of 32 channels, 16 columns) of the fragment-order copy
@@ -553,22 +574,15 @@ __global__ void __launch_bounds__(256, 2) stem_fwd_k(ConvNT p, int tiles, int wb
   const unsigned char* const wl = wsm + li * STEM_WROW + h2 * 16;   // this lane's row of column block 0
 
   // the window of tile tt, straight into LDS (a wavefront instruction copies 1 KB): wbytes from image row 2 y0 of its
-  // image on; pieces past the end of the whole image buffer (only ever the unused tail of the last tiles' windows)
-  // read its last piece instead
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
+  // image on; past the end of the whole image buffer (only ever the unused tail of the last tiles' windows) come zeros
   auto fetch = [&](int tt) __attribute__((always_inline)) {
     const int m0 = tt * 256, n = m0 / plane, y0 = (m0 - n * plane) / XO;
     const long long woff = ((long long)(n * YS + 2 * y0) * XS) * 8;
-    const char* src = reinterpret_cast<const char*>(p.src);
+    const __amdgpu_buffer_rsrc_t rs = dma_buffer((const char*)p.src + woff, img_bytes - woff);
 #pragma unroll
     for (int i = 0; i < STEM_WPT; ++i) {
       const int c = i * 4 + wave;   // 1 KB chunk of the window
-      if (c * 1024 < wbytes) {      // uniform
-        long long o = woff + c * 1024 + lane * 16;
-        o = o > img_bytes - 16 ? img_bytes - 16 : o;
-        __builtin_amdgcn_global_load_lds((gptr_t)(src + o), (lptr_t)(win + c * 1024), 16, 0, 0);
-      }
+      if (c * 1024 < wbytes) dma16(rs, win + c * 1024, lane * 16, c * 1024);   // uniform
     }
   };
   fetch(t);
@@ -658,34 +672,45 @@ __global__ void __launch_bounds__(256) conv_wgrad_k(ConvWG p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qa = wave >> 1, qb = wave & 1;
   const int r = wave * 8 + (lane >> 3);                          // this lane's row of every slice
-  const int cl = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 8;       // the piece it fetches (its slot holds piece slot ^ ...)
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
+  const int cl = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 16;      // the piece it fetches, in bytes (its slot holds piece slot ^ ...)
+  const int rowb = 2 * p.Cs, lead = STEM || PW ? 0 : ((2 * p.g.pad + p.g.KH + 2) * p.g.XS) * rowb;   // as in the forward kernel
+  const int dvo = r * 2 * p.Co + cl, svo = r * rowb + cl;
+  const float invXO = 1.0f / (float)p.g.XO;
+  int in, iy, ix;   // position of the first row of the step to be fetched (uniform)
+  row_pos(lo < p.M ? lo : p.M - 1, p.M, p.g, in, iy, ix);
 
   auto issue = [&](long long mstep, int st) {   // only called with mstep < hi
-    const long long m = mstep + r;
-    const bool ok = m < hi;
     bf16* sa = S + st * STAGE + wave * 8 * 64;
-    const bf16* gd = ok ? p.dout + m * p.Co + co0 + cl : g_zero_row + cl;
-    __builtin_amdgcn_global_load_lds((gptr_t)gd, (lptr_t)sa, 16, 0, 0);
+    dma16(dma_buffer(p.dout + mstep * p.Co + co0, ((hi - mstep) * p.Co - co0) * 2), sa, dvo, 0);   // rows past the slab: zeros
     if (PW) {
-      const bf16* gp = ok ? p.src + m * p.Cs + ci0 + cl : g_zero_row + cl;
-      __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)(sa + SLICE), 16, 0, 0);
+      dma16(dma_buffer(p.src + mstep * p.Cs + ci0, ((hi - mstep) * p.Cs - ci0) * 2), sa + SLICE, svo, 0);
       return;
     }
-    int n, y, x;
-    row_pos(ok ? m : hi - 1, p.M, p.g, n, y, x);
+    // this lane's row r positions behind (in, iy, ix)
+    const int xr = ix + r;
+    const int w = (int)(((float)xr + 0.5f) * invXO);   // image rows further: exact, the half keeps multiples of XO off the edge
+    const int x = xr - w * p.g.XO;
+    int y = iy + w, dn = 0;
+    while (y >= p.g.YO) { y -= p.g.YO; ++dn; }
+    const bool ok = r < hi - mstep;
+    const int yf = STEM ? 2 * iy : iy * p.g.stride - p.g.pad;
+    const long long first = ((long long)in * p.g.YS + yf) * p.g.XS;
+    const long long rows = p.M / (p.g.YO * p.g.XO) * (long long)p.g.YS * p.g.XS;
     if (STEM) {   // the four 64-column groups of the stem's 256 contraction columns stand where the taps stand
+      const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + first * 4, (rows - first) * 8);
+      const int base = ((dn * p.g.YS + 2 * y - yf) * p.g.XS + 2 * x) * 8 + (cl & 63);
 #pragma unroll
       for (int t = 0; t < TAPS; ++t) {
-        const bf16* gp = ok ? p.src + stem_off(p.g, n, y, x, t * 64 + cl) : g_zero_row + cl;
-        __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)(sa + (1 + t) * SLICE), 16, 0, 0);
+        int k = t * 2 + (cl >> 6);
+        k = k > 6 ? 6 : k;   // the eighth kernel row has zero weights: read the seventh again
+        dma16(rs, sa + (1 + t) * SLICE, ok ? base + k * p.g.XS * 8 : DMA_ABSENT, 0);
       }
     } else {
       // the row's source position for tap (0, 0), once; a tap adds a uniform offset, and exists where both of its
       // coordinates fall inside the source grid
+      const __amdgpu_buffer_rsrc_t rs = dma_buffer((const char*)(p.src + first * p.Cs + ci0) - lead, ((rows - first) * p.Cs - ci0) * 2 + lead);
       const int ys0 = y * p.g.stride - p.g.pad, xs0 = x * p.g.stride - p.g.pad;
-      const bf16* base = p.src + (((long long)n * p.g.YS + ys0) * p.g.XS + xs0) * p.Cs + ci0 + cl;
+      const int base = ((dn * p.g.YS + ys0 - yf) * p.g.XS + xs0) * rowb + cl + lead;
       bool oky[3], okx[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -695,9 +720,13 @@ __global__ void __launch_bounds__(256) conv_wgrad_k(ConvWG p) {
 #pragma unroll
       for (int t = 0; t < TAPS; ++t) {
         const int kh = TAPS == 1 ? 0 : t / 3, kw = TAPS == 1 ? 0 : t % 3;
-        const bf16* gp = (oky[kh] & okx[kw]) ? base + (long long)(kh * p.g.XS + kw) * p.Cs : g_zero_row + cl;
-        __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)(sa + (1 + t) * SLICE), 16, 0, 0);
+        dma16(rs, sa + (1 + t) * SLICE, (oky[kh] & okx[kw]) ? base : DMA_ABSENT, (kh * p.g.XS + kw) * rowb);
       }
+    }
+    ix += WBK;
+    while (ix >= p.g.XO) {
+      ix -= p.g.XO;
+      if (++iy == p.g.YO) { iy = 0; ++in; }
     }
   };
 
@@ -762,22 +791,18 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_pw_k(ConvWG p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = wave % WI, wo = wave / WI;
   const int r = wave * 8 + (lane >> 3);                          // this lane's row of every slice
-  const int cl = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 8;       // the piece it fetches (its slot holds piece slot ^ ...)
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
+  const int cl = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 16;      // the piece it fetches, in bytes (its slot holds piece slot ^ ...)
+  const int dvo = r * 2 * p.Co + cl, svo = r * 2 * p.Cs + cl;
 
   auto issue = [&](long long mstep, auto stc) __attribute__((always_inline)) {   // only called with mstep < hi
     constexpr int ST = decltype(stc)::value;
     bf16* sa = (ST == 0 ? sg0 : ST == 1 ? sg1 : sg2) + wave * 8 * 64;
-    const long long m = mstep + r;
-    const bool ok = m < hi;
-    const bf16* gd = ok ? p.dout + m * p.Co + co0 + cl : g_zero_row + cl;
-    const bf16* gs = ok ? p.src + m * p.Cs + ci0 + cl : g_zero_row + cl;
-    const int so = ok ? 64 : 0;   // the zero row has one slice
+    const __amdgpu_buffer_rsrc_t rd = dma_buffer(p.dout + mstep * p.Co + co0, ((hi - mstep) * p.Co - co0) * 2);
+    const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + mstep * p.Cs + ci0, ((hi - mstep) * p.Cs - ci0) * 2);
 #pragma unroll
-    for (int sl = 0; sl < SA; ++sl) __builtin_amdgcn_global_load_lds((gptr_t)(gd + sl * so), (lptr_t)(sa + sl * SLICE), 16, 0, 0);
+    for (int sl = 0; sl < SA; ++sl) dma16(rd, sa + sl * SLICE, dvo, sl * 128);
 #pragma unroll
-    for (int sl = 0; sl < SB; ++sl) __builtin_amdgcn_global_load_lds((gptr_t)(gs + sl * so), (lptr_t)(sa + (SA + sl) * SLICE), 16, 0, 0);
+    for (int sl = 0; sl < SB; ++sl) dma16(rs, sa + (SA + sl) * SLICE, svo, sl * 128);
   };
 
   f32x16 acc[2][2];
@@ -872,24 +897,22 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_win_k(ConvWG p) {
   const int qa = wave >> 1, qb = wave & 1;
   const int XO = p.g.XO, YO = p.g.YO, P1 = XO + 1;
   const float invP1 = 1.0f / (float)P1, invXO = 1.0f / (float)XO;
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
-
   // (y0, x0): position of row mstep
   // Load instructions of a step (1 KB each): wavefront w takes rows 8 w .. of the output gradient, band rows 8 w .. of
   // all three bands (what decides a band row -- gap, image row, source row -- is the same in the three, only the
   // image-row test and the base differ) and, w < 3, band rows 32 .. 39 of band w: five instructions (wavefront 3: four).
   const int lr = lane >> 3;
   const int rA = wave * 8 + lr, rB = 32 + lr;                       // band rows of the two row groups of this lane
-  const int clA = ((lane & 7) ^ (((rA >> 1) & 1) << 2)) * 8, clB = ((lane & 7) ^ (((rB >> 1) & 1) << 2)) * 8;
+  const int clA = ((lane & 7) ^ (((rA >> 1) & 1) << 2)) * 16, clB = ((lane & 7) ^ (((rB >> 1) & 1) << 2)) * 16;   // bytes
+  const int rowb = 2 * p.Cs, dvo = rA * 2 * p.Co + clA;
   auto issue = [&](long long mstep, auto stc, int y0, int x0) __attribute__((always_inline)) {   // only called with mstep < hi
     constexpr int ST = decltype(stc)::value;
     bf16* sa = ST == 0 ? sg0 : ST == 1 ? sg1 : ST == 2 ? sg2 : sg3;
-    {
-      const long long m = mstep + rA;   // (rA is also this lane's output-gradient row)
-      const bf16* gp = m < hi ? p.dout + m * p.Co + co0 + clA : g_zero_row + clA;
-      __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)(sa + wave * 8 * 64), 16, 0, 0);
-    }
+    // (rA is also this lane's output-gradient row)
+    dma16(dma_buffer(p.dout + mstep * p.Co + co0, ((hi - mstep) * p.Co - co0) * 2), sa + wave * 8 * 64, dvo, 0);
+    // source rows from one image row and one position in front of row mstep on (nothing in front of the first row is read:
+    // a row with an image row above it has one in memory)
+    const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + (mstep - P1) * p.Cs + ci0, ((p.M - mstep + P1) * p.Cs - ci0) * 2);
     // band row r of band b: padded column (one padded image row ahead so that it is not negative), image rows after
     // the step's first one (-1 only for a gap), source row relative to the row in the column of row mstep
     auto band_row = [&](int r, int cl, auto bc) __attribute__((always_inline)) {
@@ -899,12 +922,10 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_win_k(ConvWG p) {
       int yo = y0 + w;
       yo = yo >= YO ? yo - YO : yo;                        // the image row of the output rows this source row serves
       const bool okx = rem != XO;
-      const int rel = r - 1 - w;
+      const int vo = (r - w) * rowb + cl;   // source row r - 1 - w of the band's first one, counted from P1 rows in front
       auto one = [&](int b, bf16* dst) __attribute__((always_inline)) {
-        const long long f = mstep + (long long)((b - 1) * XO + rel);
-        const bool ok = okx & ((unsigned)(yo + b - 1) < (unsigned)YO) & (f >= 0) & (f < p.M);
-        const bf16* gp = ok ? p.src + f * p.Cs + ci0 + cl : g_zero_row + cl;
-        __builtin_amdgcn_global_load_lds((gptr_t)gp, (lptr_t)dst, 16, 0, 0);
+        const bool ok = okx & ((unsigned)(yo + b - 1) < (unsigned)YO);
+        dma16(rs, dst, ok ? vo : DMA_ABSENT, b * XO * rowb);
       };
       constexpr int B = decltype(bc)::value;
       if constexpr (B < 0) {
