@@ -6,9 +6,10 @@
 // What bounds them is the matrix pipe: 256 flops a clock and compute unit, a sixteenth of the bf16 rate, so that a
 // 64 x 64 x 32 step lasts 1024 clocks against 16 KB of operands.  Hence small tiles (a bag of a few dozen tiles gives
 // several workgroups to every compute unit, and the last wave of workgroups is short), operands straight from global
-// memory into LDS one step ahead (global_load_lds_dwordx4, no registers), one barrier per step, and an epilogue that
+// memory into LDS one step ahead (lds_dma.h, no registers), one barrier per step, and an epilogue that
 // stores from the accumulators.
 #include "gemm_epi.h"
+#include "lds_dma.h"
 #include <type_traits>
 
 namespace sl {
@@ -19,8 +20,6 @@ constexpr int NXCD = 8;
 constexpr int BK = 32;   // floats of K (NT) / rows of m (TN) per step
 
 template <int V> using IC = std::integral_constant<int, V>;
-typedef const void __attribute__((address_space(1)))* gptr_t;
-typedef void __attribute__((address_space(3)))* lptr_t;
 
 __device__ __forceinline__ void step_barrier() {
   __builtin_amdgcn_s_waitcnt(0x0070);   // this wavefront's loads into LDS have landed, its LDS reads are done
@@ -50,28 +49,27 @@ __global__ void __launch_bounds__(256, BM + BN == 256 ? 2 : BM + BN == 192 ? 3 :
   const int nk = g.K / BK;
 
   const int lr = lane >> 3, ls = lane & 7;
-  const float *ap[AG], *bp[BG];
+  const long long row0 = g.amap.map32((unsigned)m0);
+  const __amdgpu_buffer_rsrc_t ra = dma_buffer((const float*)g.A + row0 * g.lda, DMA_MAX);   // (no row past the last one is asked for)
+  const __amdgpu_buffer_rsrc_t rb = dma_rows((const float*)g.B + (long long)n0 * g.ldb, g.N - n0 < BN ? g.N - n0 : BN, (int)g.ldb, g.K);
+  int ao[AG], bo[BG];
 #pragma unroll
   for (int j = 0; j < AG; ++j) {
     const int R = (j * 4 + wave) * 8 + lr;
     long long m = m0 + R;
     if (m > g.M - 1) m = g.M - 1;   // rows past the end re-read the last one and are never stored
-    ap[j] = (const float*)g.A + g.amap.map32((unsigned)m) * g.lda + (ls ^ ((R >> 1) & 7)) * 4;
+    ao[j] = ((int)(g.amap.map32((unsigned)m) - row0) * (int)g.lda + (ls ^ ((R >> 1) & 7)) * 4) * 4;
   }
 #pragma unroll
   for (int j = 0; j < BG; ++j) {
     const int R = (j * 4 + wave) * 8 + lr;
-    int b = n0 + R;
-    if (b > g.N - 1) b = g.N - 1;
-    bp[j] = (const float*)g.B + (long long)b * g.ldb + (ls ^ ((R >> 1) & 7)) * 4;
+    bo[j] = (R * (int)g.ldb + (ls ^ ((R >> 1) & 7)) * 4) * 4;
   }
   auto issue = [&](float* s, int kt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < AG; ++j)
-      __builtin_amdgcn_global_load_lds((gptr_t)(ap[j] + kt * BK), (lptr_t)(s + (j * 4 + wave) * 8 * BK), 16, 0, 0);
+    for (int j = 0; j < AG; ++j) dma16(ra, s + (j * 4 + wave) * 8 * BK, ao[j], kt * BK * 4);
 #pragma unroll
-    for (int j = 0; j < BG; ++j)
-      __builtin_amdgcn_global_load_lds((gptr_t)(bp[j] + kt * BK), (lptr_t)(s + BM * BK + (j * 4 + wave) * 8 * BK), 16, 0, 0);
+    for (int j = 0; j < BG; ++j) dma16(rb, s + BM * BK + (j * 4 + wave) * 8 * BK, bo[j], kt * BK * 4);
   };
 
   f32x16 acc[WBM][WBN];
@@ -160,11 +158,9 @@ hipError_t go_nt(const GemmNT& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-__device__ __attribute__((aligned(16))) float g_zero4[4];
-
 // TN: 64 x 64 of the result per workgroup, both operands as [32 rows of m][64 columns] in LDS.  An MFMA operand is one
 // float per lane, 32 consecutive columns of one row of m for each half wavefront: a plain read, nothing is transposed.
-// Rows past the slab's end and columns past the matrix come from a block of zeros.  The column sums of A (bias
+// Rows past the slab's end and columns past the matrix lie outside of the buffers: zeros.  The column sums of A (bias
 // gradients) ride along in the registers that hold A's operands: 16 rows of a step first, then the even and the odd steps.
 __global__ void __launch_bounds__(256, 4) gemm_tn_f32_k(GemmTN g, int per) {
   constexpr int STAGE = 2 * BK * 64;
@@ -177,18 +173,18 @@ __global__ void __launch_bounds__(256, 4) gemm_tn_f32_k(GemmTN g, int per) {
 
   // a load instruction fills 4 rows of 64 floats: instruction j of a wavefront rows (j * 4 + wave) * 4 .. + 3
   const int lr = lane >> 4, lc = (lane & 15) * 4;
-  const bool a_ok = i0 + lc < g.N1, b_ok = j0 + lc < g.N2;
-  const float* A = (const float*)g.A + i0 + lc;
-  const float* B = (const float*)g.B + j0 + lc;
+  const int ao = i0 + lc < g.N1 ? ((wave * 4 + lr) * (int)g.lda + lc) * 4 : DMA_ABSENT;
+  const int bo = j0 + lc < g.N2 ? ((wave * 4 + lr) * (int)g.ldb + lc) * 4 : DMA_ABSENT;
   auto issue = [&](float* s, int kt) __attribute__((always_inline)) {
+    const long long m = lo + (long long)kt * BK;
+    const int rows = hi - m < BK ? (int)(hi - m) : BK;
+    const __amdgpu_buffer_rsrc_t ra = dma_rows((const float*)g.A + m * g.lda + i0, rows, (int)g.lda, g.N1 - i0);
+    const __amdgpu_buffer_rsrc_t rb = dma_rows((const float*)g.B + m * g.ldb + j0, rows, (int)g.ldb, g.N2 - j0);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int R = (j * 4 + wave) * 4;
-      const long long m = lo + (long long)kt * BK + R + lr;
-      const float* pa = a_ok && m < hi ? A + m * g.lda : g_zero4;
-      const float* pb = b_ok && m < hi ? B + m * g.ldb : g_zero4;
-      __builtin_amdgcn_global_load_lds((gptr_t)pa, (lptr_t)(s + R * 64), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((gptr_t)pb, (lptr_t)(s + BK * 64 + R * 64), 16, 0, 0);
+      dma16(ra, s + R * 64, ao, j * 64 * (int)g.lda);
+      dma16(rb, s + BK * 64 + R * 64, bo, j * 64 * (int)g.ldb);
     }
   };
   f32x16 acc;
@@ -237,7 +233,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
 bool gemm_nt_f32_ok(const GemmNT& g) {
-  bool ok = g.K % BK == 0 && g.N % 4 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.ldc % 4 == 0 && aligned16(g.A) &&
+  bool ok = g.K % BK == 0 && g.N % 4 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.lda <= DMA_LD && g.ldb <= DMA_LD && g.ldc % 4 == 0 && aligned16(g.A) &&
             aligned16(g.B) && aligned16(g.out) && g.M < (1LL << 31);
   if (g.epi == EPI_BIAS_RESID) ok = ok && g.ldr % 4 == 0 && aligned16(g.resid);
   if (g.epi == EPI_BIAS_GELU) ok = ok && g.ldc2 % 4 == 0 && aligned16(g.out2);
@@ -253,7 +249,7 @@ bool gemm_nt_f32_ok(const GemmNT& g) {
 hipError_t launch_gemm_nt_f32(const GemmNT& g, hipStream_t s) { return go_nt<64, 64>(g, s); }
 
 bool gemm_tn_f32_ok(const GemmTN& g) {
-  return g.N1 % 4 == 0 && g.N2 % 4 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && aligned16(g.A) && aligned16(g.B) &&
+  return g.N1 % 4 == 0 && g.N2 % 4 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.lda <= DMA_LD && g.ldb <= DMA_LD && aligned16(g.A) && aligned16(g.B) &&
          g.amap.g2 == 0 && g.bmap.g2 == 0 && g.M < (1LL << 31);
 }
 

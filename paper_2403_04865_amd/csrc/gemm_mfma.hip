@@ -4,7 +4,7 @@
 // last block, narrow encoders and the aggregator.  128 x 128 of the result per workgroup (4 wavefronts as 2 x 2), M split
 // into slabs.  A 32-row step moves 16 KB for 256 clocks of MFMAs, the 64 bytes a clock that a compute unit gets from its
 // L2, and one trip there takes thousands of clocks: what bounds the kernel is how much a compute unit keeps in flight.
-//   * operands go straight from global memory into LDS (global_load_lds_dwordx4: a wavefront instruction moves 4 rows x 256
+//   * operands go straight from global memory into LDS (lds_dma.h: a wavefront instruction moves 4 rows x 256
 //     bytes) one step ahead at no register cost; three workgroups share a compute unit (deeper rings with fewer workgroups
 //     measured 5 to 20 % slower at every size, as did 64-row steps);
 //   * rows stay row-major; the MFMA operands, eight consecutive rows of one column per lane, are LDS transpose reads
@@ -12,12 +12,13 @@
 //     32-byte pieces of a row are slot-permuted by the loading lane's choice of address (piece p of row r in slot
 //     p ^ 2 (r % 4)): the eight pieces that are served together fall on 64 different banks;
 //   * the stages are separate arrays: the compiler waits for every load into an LDS array before any read of that array;
-//   * rows past the slab's end and columns past the matrix come from a block of zeros.
+//   * rows past the slab's end and columns past the matrix lie outside of the buffers: zeros.
 // Column sums of A (bias gradients) are taken from the operand registers by the workgroups of the first tile column: the 16
 // rows a lane sees in a step first, then the even and the odd steps.
 // Measured, M = 7289 (37 tiles of 197 tokens), against the kernel that transposed 8 x 8 blocks in registers on the way into
 // LDS: 384 x 1536 34.9 -> 22.4 us, 1536 x 384 35.9 -> 19.5, 1152 x 384 31.9 -> 19.4, 384 x 384 14.6 -> 10.7.
 #include "slide_internal.h"
+#include "lds_dma.h"
 
 namespace sl {
 
@@ -27,10 +28,6 @@ constexpr int BT = 128, BK = 32, STAGE = BK * 2 * BT;   // bf16 elements: [32 ro
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef const void __attribute__((address_space(1)))* gptr_t;
-typedef void __attribute__((address_space(3)))* lptr_t;
-
-__device__ __attribute__((aligned(16))) unsigned int g_zero16[4];
 
 // problems of one launch: workgroups block0 .. of problem i, row tiles of the result innermost, then column tiles, then slabs
 struct TnGroup {
@@ -58,19 +55,16 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(TnGroup G) {
 
   // loads: instruction j of a wavefront fills rows (j * 4 + wave) * 4 .. + 3 of a stage; lane: row lane / 16, slot lane % 16
   const int lr = lane >> 4, lc = (((lane & 15) >> 1) ^ (2 * lr)) * 16 + (lane & 1) * 8;   // column of this lane's slot
-  const bool a_ok = i0 + lc < g.N1, b_ok = j0 + lc < g.N2;   // N1, N2 are multiples of 8
-  const bf16* zero = reinterpret_cast<const bf16*>(g_zero16);
-  const bf16* ap = g.A + (lo + wave * 4 + lr) * g.lda + i0 + lc;
-  const bf16* bp = g.B + (lo + wave * 4 + lr) * g.ldb + j0 + lc;
+  const int ao = i0 + lc < g.N1 ? ((wave * 4 + lr) * (int)g.lda + lc) * 2 : DMA_ABSENT;   // N1, N2 are multiples of 8
+  const int bo = j0 + lc < g.N2 ? ((wave * 4 + lr) * (int)g.ldb + lc) * 2 : DMA_ABSENT;
   auto issue = [&](bf16* s, int kt) __attribute__((always_inline)) {
+    const int rows = span - kt * BK < BK ? span - kt * BK : BK;
+    const __amdgpu_buffer_rsrc_t ra = dma_rows(g.A + (lo + kt * BK) * g.lda + i0, rows, (int)g.lda, g.N1 - i0);
+    const __amdgpu_buffer_rsrc_t rb = dma_rows(g.B + (lo + kt * BK) * g.ldb + j0, rows, (int)g.ldb, g.N2 - j0);
 #pragma unroll
     for (int j = 0; j < BK / 16; ++j) {
-      const int row = kt * BK + j * 16;   // + wave * 4 + lr
-      const bool ok = row + wave * 4 + lr < span;
-      const bf16* pa = ok && a_ok ? ap + (long long)row * g.lda : zero;
-      const bf16* pb = ok && b_ok ? bp + (long long)row * g.ldb : zero;
-      __builtin_amdgcn_global_load_lds((gptr_t)pa, (lptr_t)(s + (j * 4 + wave) * 4 * BT), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((gptr_t)pb, (lptr_t)(s + BK * BT + (j * 4 + wave) * 4 * BT), 16, 0, 0);
+      dma16(ra, s + (j * 4 + wave) * 4 * BT, ao, j * 32 * (int)g.lda);
+      dma16(rb, s + BK * BT + (j * 4 + wave) * 4 * BT, bo, j * 32 * (int)g.ldb);
     }
   };
 
@@ -172,7 +166,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
 bool gemm_tn_mfma_ok(const GemmTN& g) {
-  return g.N1 % 8 == 0 && g.N2 % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && aligned16(g.A) && aligned16(g.B) &&
+  return g.N1 % 8 == 0 && g.N2 % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.lda <= DMA_LD && g.ldb <= DMA_LD && aligned16(g.A) && aligned16(g.B) &&
          g.amap.g2 == 0 && g.bmap.g2 == 0 && g.M < (1LL << 31);
 }
 

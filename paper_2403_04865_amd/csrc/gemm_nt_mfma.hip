@@ -7,7 +7,7 @@
 //
 // What bounds such a problem is latency, not bandwidth or the matrix pipe: one or two tiles per compute unit, 1 to 48
 // K steps each, and a step's MFMAs (128 to 512 clocks) are shorter than a trip to L2.  So
-//   * operands go straight from global memory into LDS (global_load_lds_dwordx4: a wavefront instruction moves 64 x 16
+//   * operands go straight from global memory into LDS (lds_dma.h: a wavefront instruction moves 64 x 16
 //     bytes to 1 KB of consecutive LDS), NST - 1 K steps ahead, at no register cost; two stages (two to five workgroups per
 //     compute unit) hide more than deeper ones;
 //   * a K step is 64 wide; rows are unpadded (128 bytes) and their 16-byte pieces slot-permuted by the loading lane's
@@ -26,6 +26,7 @@
 // accumulators from the bias; LARGE does the same in the same order, so that which of the kernels runs does not show
 // in a single bit and a slide gives the same gradients whole and in chunks.
 #include "gemm_epi.h"
+#include "lds_dma.h"
 #include <type_traits>
 
 namespace sl {
@@ -107,26 +108,22 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
       }
   }
 
-  // loads: instruction j of a wavefront fills rows (j * 4 + wave) * 8 .. + 7 of the tile; rows past the end re-read the
-  // last one (valid memory, never stored)
+  // loads: instruction j of a wavefront fills rows (j * 4 + wave) * 8 .. + 7 of the tile; rows past the end lie outside of
+  // the buffer (zeros, never stored)
   const int lr = lane >> 3, ls = lane & 7;
-  const bf16 *ap[AG], *bp[BG];
+  const __amdgpu_buffer_rsrc_t ra = dma_rows((const bf16*)g.A + m0 * g.lda, (int)(g.M - m0 < BM ? g.M - m0 : BM), (int)g.lda, g.K);
+  const __amdgpu_buffer_rsrc_t rb = dma_rows((const bf16*)g.B + (long long)n0 * g.ldb, g.N - n0 < BN ? g.N - n0 : BN, (int)g.ldb, g.K);
+  int ao[AG], bo[BG];
 #pragma unroll
   for (int j = 0; j < AG; ++j) {
     const int R = (j * 4 + wave) * 8 + lr;
-    long long m = m0 + R;
-    if (m > g.M - 1) m = g.M - 1;
-    ap[j] = (const bf16*)g.A + m * g.lda + (ls ^ ((R >> 1) & 7)) * 8;
+    ao[j] = (R * (int)g.lda + (ls ^ ((R >> 1) & 7)) * 8) * 2;
   }
 #pragma unroll
   for (int j = 0; j < BG; ++j) {
     const int R = (j * 4 + wave) * 8 + lr;
-    int b = n0 + R;
-    if (b > g.N - 1) b = g.N - 1;
-    bp[j] = (const bf16*)g.B + (long long)b * g.ldb + (ls ^ ((R >> 1) & 7)) * 8;
+    bo[j] = (R * (int)g.ldb + (ls ^ ((R >> 1) & 7)) * 8) * 2;
   }
-  typedef const void __attribute__((address_space(1)))* gptr_t;
-  typedef void __attribute__((address_space(3)))* lptr_t;
   auto stage = [&](auto sc) __attribute__((always_inline)) -> bf16* {
     constexpr int S = decltype(sc)::value;
     if constexpr (S == 0) return st0;
@@ -137,11 +134,9 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   auto issue = [&](auto sc, int kt) __attribute__((always_inline)) {
     bf16* s = stage(sc);
 #pragma unroll
-    for (int j = 0; j < AG; ++j)
-      __builtin_amdgcn_global_load_lds((gptr_t)(ap[j] + kt * BK), (lptr_t)(s + (j * 4 + wave) * 8 * BK), 16, 0, 0);
+    for (int j = 0; j < AG; ++j) dma16(ra, s + (j * 4 + wave) * 8 * BK, ao[j], kt * BK * 2);
 #pragma unroll
-    for (int j = 0; j < BG; ++j)
-      __builtin_amdgcn_global_load_lds((gptr_t)(bp[j] + kt * BK), (lptr_t)(s + BM * BK + (j * 4 + wave) * 8 * BK), 16, 0, 0);
+    for (int j = 0; j < BG; ++j) dma16(rb, s + BM * BK + (j * 4 + wave) * 8 * BK, bo[j], kt * BK * 2);
   };
 
   f32x16 acc[WBM][WBN];
@@ -290,7 +285,7 @@ hipError_t go(const GemmNT& g, hipStream_t s) {
 }  // namespace
 
 bool gemm_nt_mfma_ok(const GemmNT& g) {
-  bool ok = g.K % 64 == 0 && g.N % 16 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && aligned16(g.A) && aligned16(g.B) &&
+  bool ok = g.K % 64 == 0 && g.N % 16 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.lda <= DMA_LD && g.ldb <= DMA_LD && aligned16(g.A) && aligned16(g.B) &&
             g.M > 0 && g.M < (1LL << 31) && g.ldc % 8 == 0 && aligned16(g.out) && g.amap.g2 == 0 &&
             sizeof(rs_bf16path_t) == 2;
   if (g.epi == EPI_BIAS_RESID || g.epi == EPI_ROWTAB) ok = ok && g.ldr % 8 == 0 && aligned16(g.resid);
