@@ -202,7 +202,7 @@ int colsum_slabs(long long M);
 hipError_t launch_colsum_part(int elem, const void* A, long long lda, RowMap map, long long M, int N, float* part,
                               int slabs, hipStream_t s);
 // out[i] = (accumulate ? out[i] : 0) + sum_s part[s*stride + i], i < len, for a list of results in one launch
-enum { RED_1 = 0, RED_4 = 1, RED_16 = 2 };
+enum { RED_1 = 0, RED_4 = 1, RED_16 = 2, RED_F = 3 };
 struct RedSeg { const float* part; float* out; long long stride; int len, slabs, block0; short kind, accumulate; };
 constexpr int RED_MAX = 64;
 struct RedList { int n = 0, blocks = 0; RedSeg seg[RED_MAX]; };
