@@ -67,6 +67,27 @@ __global__ void __launch_bounds__(256) pool_combine_k(PoolArgs p, int nz) {
   float* zlo = dz + D;
   float m;
   double Z;
+  // a chain of trips to memory bounds this kernel, so what it will need is asked for at its start: this thread's partials (up to 256
+  // workgroups: 16 of them) and, for whoever comes last, this wavefront's first class of the head
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c16 = threadIdx.x & 15, sl = threadIdx.x >> 4;
+  const int d16 = (int)blockIdx.x * 16 + c16, dc = d16 < D ? d16 : D - 1;
+  double pv[16];
+  float cw[8];
+  float cb0 = 0.f;
+  if ((int)blockIdx.x < nz) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int b = sl + 16 * i;
+      pv[i] = p.part[(size_t)(b < B ? b : 0) * (2 + D) + 2 + dc];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int d = lane + 64 * i;
+      cw[i] = p.cW[(size_t)(w < C ? w : 0) * D + (d < D ? d : 0)];
+    }
+    cb0 = p.cb[w < C ? w : 0];
+  }
   pool_partial_stats(p, sm, smd, wts, m, Z);
   if ((int)blockIdx.x >= nz) {
     const float Zf = (float)Z;
@@ -75,11 +96,13 @@ __global__ void __launch_bounds__(256) pool_combine_k(PoolArgs p, int nz) {
     return;
   }
   {
-    const int c = threadIdx.x & 15, sl = threadIdx.x >> 4;
-    const int d = blockIdx.x * 16 + c, dc = d < D ? d : D - 1;
+    const int c = c16, d = d16;
     double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (sl + 16 * i < B) acc += pv[i] * (double)wts[sl + 16 * i];
 #pragma unroll 8
-    for (int b = sl; b < B; b += 16) acc += p.part[(size_t)b * (2 + D) + 2 + dc] * (double)wts[b];
+    for (int b = sl + 256; b < B; b += 16) acc += p.part[(size_t)b * (2 + D) + 2 + dc] * (double)wts[b];
     red[sl][c] = acc;
     __syncthreads();
     if (threadIdx.x < 16 && d < D) {
@@ -103,12 +126,16 @@ __global__ void __launch_bounds__(256) pool_combine_k(PoolArgs p, int nz) {
     __syncthreads();
   }
   // logits: one wave per class round-robin
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int c = w; c < C; c += 4) {
     float acc = 0.f;
-    for (int d = lane; d < D; d += 64) acc += p.cW[(size_t)c * D + d] * zs[d];
+    if (c == w) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (lane + 64 * i < D) acc += cw[i] * zs[lane + 64 * i];
+    }
+    for (int d = c == w ? lane + 512 : lane; d < D; d += 64) acc += p.cW[(size_t)c * D + d] * zs[d];
     acc = wave_sum(acc);
-    if (lane == 0) y[c] = acc + p.cb[c];
+    if (lane == 0) y[c] = acc + (c == w ? cb0 : p.cb[c]);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -130,6 +157,7 @@ __global__ void __launch_bounds__(256) pool_combine_k(PoolArgs p, int nz) {
     if (p.loss) p.loss[0] = loss;
     if (p.logits) for (int c = 0; c < C; ++c) p.logits[c] = y[c];
   }
+  if (p.fwd_only) return;
   __syncthreads();
   float part = 0.f;
   for (int d = threadIdx.x; d < D; d += 256) {

@@ -39,26 +39,10 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
 }
 
-// out[d][u] (bf16, [D][2 Mh]) = u < Mh ? V[u][d] : U[u - Mh][d]
-__global__ void __launch_bounds__(256) pool_cast_vut_k(const float* __restrict__ V, const float* __restrict__ U,
-                                                       bf16* __restrict__ out, int Mh, int D) {
-  long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)D * 2 * Mh) return;
-  int d = (int)(i / (2 * Mh)), u = (int)(i % (2 * Mh));
-  out[i] = (bf16)(u < Mh ? V[(size_t)u * D + d] : U[(size_t)(u - Mh) * D + d]);
-}
-
-// out (bf16, [2 Mh][D]) = [V; U]
-__global__ void __launch_bounds__(256) pool_cast_vu2_k(const float* __restrict__ V, const float* __restrict__ U,
-                                                       bf16* __restrict__ out, long long n) {
-  long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) { out[i] = (bf16)V[i]; out[n + i] = (bf16)U[i]; }
-}
-
 // Pass 1.  Same skeleton as the forward kernel with register-resident weights: persistent workgroups of 4
 // wavefronts over blocks of 32 rows, a wavefront owns 32 gate units, a thread owns 4 rows x 12 columns of every block
 // in fp32 registers (two sets), LDS holds the bf16 image of the block for the MFMA fragments.
-//   Dp  [N][2 Mh] bf16: dpV | dpU     Hb16 [N][D] bf16: the features
+//   Dp  [N][2 Mh] bf16: dpV | dpU     Hb16 [N][D] bf16: the features (may be null: another half of the gate units has written them)
 //   csp [gridDim.x][Mh] fp32: this workgroup's sum of da t s (dw)
 template <int D, int MH>
 __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* __restrict__ VU, bf16* __restrict__ Dp,
@@ -81,17 +65,6 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
 
   for (int j = tid; j < MH; j += 256) { gb[j] = C1 * p.Vb[j]; gb[MH + j] = C2 * p.Ub[j]; gb[2 * MH + j] = p.w[j]; }
   bf16x8 wv[KS], wu[KS];
-  {
-    const bf16* wr = VU + (size_t)(32 * wave + li) * D + h2 * 8;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 a = *reinterpret_cast<const u32x4*>(wr + ks * 16);
-      u32x4 b = *reinterpret_cast<const u32x4*>(wr + (size_t)MH * D + ks * 16);
-      asm volatile("" : "+a"(a), "+a"(b));   // accumulation half of the register file, read by the MFMA directly
-      wv[ks] = __builtin_bit_cast(bf16x8, a);
-      wu[ks] = __builtin_bit_cast(bf16x8, b);
-    }
-  }
   // z = zv + zlo to fp64 accuracy; the zlo part of the dot product is a constant of the thread's 12 columns
   float kz = 0.f;
   {
@@ -142,7 +115,7 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
         w2.x = pack_bf16(v.x, v.y);
         w2.y = pack_bf16(v.z, v.w);
         *reinterpret_cast<uint2*>(Hb + (buf * RB + 4 * rgrp + k) * LDB + (cl + 32 * j) * 4) = w2;
-        if (row < p.N) *reinterpret_cast<uint2*>(Hb16 + row * D + (cl + 32 * j) * 4) = w2;
+        if (Hb16 && row < p.N) *reinterpret_cast<uint2*>(Hb16 + row * D + (cl + 32 * j) * 4) = w2;
       }
     }
   };
@@ -242,6 +215,18 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
   long long gi = blockIdx.x;
   const long long st = gridDim.x;
   issue_h(ra, gi);
+  // the weights, while the rows come from memory
+  {
+    const u32x4* wr = reinterpret_cast<const u32x4*>(VU) + (size_t)wave * KS * 2 * 64 + lane;   // fragment order (pool_cast_frag_k)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      u32x4 a = wr[(ks * 2 + 0) * 64];
+      u32x4 b = wr[(ks * 2 + 1) * 64];
+      asm volatile("" : "+a"(a), "+a"(b));   // accumulation half of the register file, read by the MFMA directly
+      wv[ks] = __builtin_bit_cast(bf16x8, a);
+      wu[ks] = __builtin_bit_cast(bf16x8, b);
+    }
+  }
   stash_h(ra, 0, gi);
   __syncthreads();
   while (true) {
@@ -266,12 +251,11 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
   }
 }
 
-// Pass 2.  G[n][d] = alpha_n dz[d] + sum_u Dp[n][u] VUT[d][u]; with ADD the first term is what G already holds (the
-// second half of the gate units when M_h = 256 is taken as two halves).  A wavefront holds the transposed weights of its
+// Pass 2.  G[n][d] = alpha_n dz[d] + sum_u Dp[n][u] VUT[d][u].  A wavefront holds the transposed weights of its
 // D / 4 columns (3 tiles of 32 x 256: 192 registers); the block's gradient rows go through LDS (double buffered, the
 // next block in flight in registers).  Rows are the M index: accumulator register r of a lane is row
 // (r / 4) * 8 + h2 * 4 + r % 4, the lane is the column, so a store instruction writes two 128-byte lines.
-template <int D, int MH, bool ADD>
+template <int D, int MH>
 __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __restrict__ VUT,
                                                     const bf16* __restrict__ Dp) {
   constexpr int RB = 32, KU = 2 * MH, KS = KU / 16, LDP = KU + 8, NT = D / 128, CH = RB * KU / 8 / 256, LDG = 2 * MH;
@@ -286,20 +270,6 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
   const int dcol = (D / 4) * wave + li;   // + 32 t
   bf16x8 wt[NT][KS];
   float dzr[NT];
-  {
-    const float* dz = p.scal + pool_z_off(p.C) + D;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      dzr[t] = dz[dcol + 32 * t];
-      const bf16* wr = VUT + (size_t)(dcol + 32 * t) * KU + h2 * 8;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        u32x4 a = *reinterpret_cast<const u32x4*>(wr + ks * 16);
-        asm volatile("" : "+a"(a));   // accumulation half of the register file, read by the MFMA directly
-        wt[t][ks] = __builtin_bit_cast(bf16x8, a);
-      }
-    }
-  }
   u32x4 rp[CH];
   float ra = 0.f;
   auto issue_one = [&](long long g, auto ic) __attribute__((always_inline)) {
@@ -329,6 +299,20 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
   long long gi = blockIdx.x;
   const long long st = gridDim.x;
   issue(gi);
+  {
+    const float* dz = p.scal + pool_z_off(p.C) + D;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      dzr[t] = dz[dcol + 32 * t];
+      const u32x4* wr = reinterpret_cast<const u32x4*>(VUT) + (size_t)(NT * wave + t) * KS * 64 + lane;   // fragment order
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        u32x4 a = wr[ks * 64];
+        asm volatile("" : "+a"(a));   // accumulation half of the register file, read by the MFMA directly
+        wt[t][ks] = __builtin_bit_cast(bf16x8, a);
+      }
+    }
+  }
   stash(0, gi);
   __syncthreads();
   for (int buf = 0; gi < groups; gi += st, buf ^= 1) {
@@ -366,7 +350,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           float* o = gout + (size_t)((r / 4) * 8 + h2 * 4 + r % 4) * D + 32 * t;
-          *o = ADD ? *o + acc[t][r] : fmaf(al[r], dzr[t], acc[t][r]);
+          *o = fmaf(al[r], dzr[t], acc[t][r]);
         }
     } else {
 #pragma unroll
@@ -375,11 +359,121 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
         for (int r = 0; r < 16; ++r) {
           int row = (r / 4) * 8 + h2 * 4 + r % 4;
           float* o = gout + (size_t)row * D + 32 * t;
-          if (n0 + row < p.N) *o = ADD ? *o + acc[t][r] : fmaf(al[r], dzr[t], acc[t][r]);
+          if (n0 + row < p.N) *o = fmaf(al[r], dzr[t], acc[t][r]);
         }
     }
     stash(buf ^ 1, gi + st);     // the next block (loaded during this one)
     __syncthreads();             // the next gradient image and its alpha are visible
+  }
+}
+
+// Pass 2 at M_h = 256.  The transposed weights, 384 KB, are twice what the accumulation halves of a compute unit's registers hold,
+// so a workgroup takes half of the columns (workgroups 2 i and 2 i + 1 the same rows): two wavefronts per 96 columns, one for each half
+// of the gate units, exchange half of a block's rows through LDS and finish 16 of them each, in the order alpha dz + first half +
+// second half.  Both halves in one pass: G is written once and never read (as two passes over all columns, the second adding to the
+// first's G, 65 us at 45,056 rows; this way 50).
+template <int D, int MH>
+__global__ void __launch_bounds__(256) pool_bwd_g2_k(PoolArgs p, const bf16* __restrict__ VU, const bf16* __restrict__ Dp) {
+  constexpr int RB = 32, KU = 2 * MH, KS = KU / 16, LDP = KU + 8, NT = D / 128, CH = 2 * RB * KU / 8 / 256, FR = KU * D;
+  static_assert(MH == 128 && D % 128 == 0, "shape");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  bf16* Dps = reinterpret_cast<bf16*>(smem);                           // [2][2 halves][RB][LDP]
+  float* als = reinterpret_cast<float*>(Dps + 2 * 2 * RB * LDP);       // [2][RB] alpha
+  float* ex = als + 2 * RB;                                            // [4][NT * 8][64] sums on their way to the other wavefront
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, h2 = lane >> 5, kh = wave & 1, cg = wave >> 1;
+  const long long groups = (p.N + RB - 1) / RB;
+  const float m = p.scal[0], Zinv = 1.0f / p.scal[1];
+  const int blk0 = (int)(blockIdx.x & 1) * 2 * NT + cg * NT, dcol = blk0 * 32 + li;   // + 32 t
+  u32x4 rp[CH];
+  float ra = 0.f;
+  auto issue_one = [&](long long g, auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < CH) {
+      const int ch = tid + 256 * (i % (CH / 2)), row = ch / (KU / 8), c16 = ch % (KU / 8);
+      long long gr = g * RB + row;   // past the end: the last row again (never stored)
+      gr = gr < p.N ? gr : p.N - 1;
+      rp[i] = *reinterpret_cast<const u32x4*>(Dp + ((i / (CH / 2)) * p.N + gr) * KU + c16 * 8);
+    } else if (tid < RB) {
+      const long long gr = g * RB + tid;
+      ra = p.a[gr < p.N ? gr : p.N - 1];
+    }
+  };
+  auto stash = [&](int buf, long long g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int ch = tid + 256 * (i % (CH / 2)), row = ch / (KU / 8), c16 = ch % (KU / 8);
+      *reinterpret_cast<u32x4*>(Dps + ((buf * 2 + i / (CH / 2)) * RB + row) * LDP + c16 * 8) = rp[i];
+    }
+    if (tid < RB) als[buf * RB + tid] = g * RB + tid < p.N ? __expf(ra - m) * Zinv : 0.f;
+  };
+  long long gi = blockIdx.x >> 1;
+  const long long st = gridDim.x >> 1;
+  static_for<0, CH + 1>([&](auto ic) __attribute__((always_inline)) { issue_one(gi, ic); });
+  bf16x8 wt[NT][KS];
+  float dzr[NT];
+  {
+    const float* dz = p.scal + pool_z_off(p.C) + D;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      dzr[t] = dz[dcol + 32 * t];
+      const u32x4* wr = reinterpret_cast<const u32x4*>(VU + (2 * kh + 1) * FR) + (size_t)(blk0 + t) * KS * 64 + lane;   // fragment order
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        u32x4 a = wr[ks * 64];
+        asm volatile("" : "+a"(a));   // accumulation half of the register file, read by the MFMA directly
+        wt[t][ks] = __builtin_bit_cast(bf16x8, a);
+      }
+    }
+  }
+  stash(0, gi);
+  __syncthreads();
+  for (int buf = 0; gi < groups; gi += st, buf ^= 1) {
+    const long long n0 = gi * RB;
+    f32x16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    const bf16* prow = Dps + ((buf * 2 + kh) * RB + li) * LDP + h2 * 8;
+    constexpr int PF = 4;
+    u32x4 pf[PF];
+#pragma unroll
+    for (int ks = 0; ks < PF; ++ks) pf[ks] = *reinterpret_cast<const u32x4*>(prow + ks * 16);
+    static_for<0, KS>([&](auto kc) __attribute__((always_inline)) {
+      constexpr int ks = decltype(kc)::value;
+      bf16x8 f = __builtin_bit_cast(bf16x8, pf[ks % PF]);
+      if constexpr (ks + PF < KS) pf[ks % PF] = *reinterpret_cast<const u32x4*>(prow + (ks + PF) * 16);
+      if constexpr (ks < CH + 1) issue_one(gi + st, IC<ks>{});   // the next block's loads, spread over the loop
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, wt[t][ks], acc[t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // registers 0 .. 7 of an accumulator are rows 0 .. 15, finished by the first half's wavefront
+    float* ew = ex + (size_t)wave * NT * 8 * 64 + lane;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) ew[(t * 8 + r) * 64] = kh ? acc[t][r] : acc[t][8 + r];
+    __syncthreads();   // the sums are visible
+    const float* er = ex + (size_t)(wave ^ 1) * NT * 8 * 64 + lane;
+    float al[8];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float4 v = *reinterpret_cast<const float4*>(als + buf * RB + 16 * kh + q * 8 + h2 * 4);
+      al[4 * q + 0] = v.x; al[4 * q + 1] = v.y; al[4 * q + 2] = v.z; al[4 * q + 3] = v.w;
+    }
+    float* gout = p.G + (n0 + 16 * kh) * D + dcol;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const int row = (r / 4) * 8 + h2 * 4 + r % 4;
+        const float o = er[(t * 8 + r) * 64], s0 = kh ? o : acc[t][r], s1 = kh ? acc[t][8 + r] : o;
+        if (n0 + 16 * kh + row < p.N) gout[(size_t)row * D + 32 * t] = fmaf(al[r], dzr[t], s0) + s1;
+      }
+    stash(buf ^ 1, gi + st);     // the next block (loaded during this one)
+    __syncthreads();             // the next gradient image and its alpha are visible, the sums have been taken
   }
 }
 
@@ -403,7 +497,7 @@ int pool_bwd_mfma_blocks(const PoolArgs& p) {
 }
 
 // Dp: [N][2 Mh] bf16, Hb16: [N][D] bf16, csp: [pool_bwd_mfma_blocks][Mh] fp32 partial sums of dw.  p.vub has room for two
-// bf16 copies of [V;U] (plain and transposed).
+// bf16 copies of [V;U] (in fragment order, and transposed); p.copies: they are there already.
 // M_h = 256 does not fit the register file (2 M_h D bf16 = 384 KB) and is taken as two halves of 128 gate units, which
 // are independent given the softmax gradient of the row: each half is the M_h = 128 problem on its rows of V, U, b_V, b_U
 // and w; the second half adds its part of G to the first's.  Then Dp is [2][N][256] (half h: dpV | dpU of its units),
@@ -414,39 +508,38 @@ hipError_t launch_pool_bwd_mfma(const PoolArgs& p0, void* Dp, void* Hb16, float*
   const int blocks = pool_bwd_mfma_blocks(p0);
   const int halves = p0.Mh / MH;
   hipError_t e;
+  if (!p0.copies && (e = launch_pool_cast_frag(p0, true, nullptr, s)) != hipSuccess) return e;
   for (int h = 0; h < halves; ++h) {
     PoolArgs p = p0;
     p.Mh = MH;
     p.VW = p0.VW + (size_t)h * MH * D; p.UW = p0.UW + (size_t)h * MH * D;
     p.Vb = p0.Vb + h * MH; p.Ub = p0.Ub + h * MH; p.w = p0.w + h * MH;
     bf16* vu = (bf16*)p0.vub + (size_t)h * 2 * (2 * MH * D);
-    bf16* vut = vu + (size_t)2 * MH * D;
     bf16* dp = (bf16*)Dp + (size_t)h * p0.N * 2 * MH;
-    const long long n = (long long)MH * D;
-    hipLaunchKernelGGL(pool_cast_vu2_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, vu, n);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(pool_cast_vut_k, dim3((unsigned)((2 * MH * D + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, vut, MH, D);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     {
       auto kern = pool_bwd_gate_k<D, MH>;
       size_t lds = (size_t)2 * 32 * (D + 8) * 2 + (size_t)32 * (2 * MH + 8) * 2 + (size_t)3 * MH * 4 + 32 * 4 + 2 * D * 4;
       if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
         return e;
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, p, (const bf16*)vu, dp, (bf16*)Hb16,
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, p, (const bf16*)vu, dp, h == 0 ? (bf16*)Hb16 : nullptr,
                          csp + (size_t)h * blocks * MH);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    {
-      size_t lds = (size_t)2 * 32 * (2 * MH + 8) * 2 + (size_t)2 * 32 * 4;
-      auto k0 = pool_bwd_g_k<D, MH, false>;
-      auto k1 = pool_bwd_g_k<D, MH, true>;
-      auto kern = h == 0 ? k0 : k1;
-      if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
-        return e;
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, p, (const bf16*)vut, (const bf16*)dp);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
   }
+  if (halves == 1) {
+    const size_t lds = (size_t)2 * 32 * (2 * MH + 8) * 2 + (size_t)2 * 32 * 4;
+    auto kern = pool_bwd_g_k<D, MH>;
+    if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, p0, (const bf16*)p0.vub + 2 * MH * D, (const bf16*)Dp);
+  } else {
+    const size_t lds = (size_t)2 * 2 * 32 * (2 * MH + 8) * 2 + (size_t)2 * 32 * 4 + (size_t)4 * (D / 128) * 8 * 64 * 4;
+    auto kern = pool_bwd_g2_k<D, MH>;
+    if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
+    const long long groups = (p0.N + 31) / 32;
+    const int pairs = groups < (blocks + 1) / 2 ? (int)groups : (blocks + 1) / 2;
+    hipLaunchKernelGGL(kern, dim3(2 * pairs), dim3(256), lds, s, p0, (const bf16*)p0.vub, (const bf16*)Dp);
+  }
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   return hipSuccess;
 }
 

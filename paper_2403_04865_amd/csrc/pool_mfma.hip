@@ -53,6 +53,39 @@ __global__ void __launch_bounds__(256) pool_cast_vu_k(const float* __restrict__ 
   if (i < n) { out[i] = (bf16)V[i]; out[n + i] = (bf16)U[i]; }
 }
 
+// [V;U] of 128 gate units x 384 as the register-resident kernels hold them: every wavefront load of a fragment is 1 KB in a row
+// (row-major, the lanes of a load touch 32 rows, which fills a compute unit's L1 at a third of the rate: 192 KB in 5 us
+// against 2).  Half h of the gate units (units 128 h .. + 127) at out + h * 2 * FRAG: FRAG elements of [V;U], for wavefront w,
+// slice ks, matrix m the 64 lanes' eight values (unit 32 w + l % 32, column 16 ks + 8 (l / 32) ..); then, if transposed, FRAG
+// elements of its transpose (column 32 b + l % 32, unit 16 ks + 8 (l / 32) .. of V's 128 and U's 128).
+constexpr int FRAG_D = 384, FRAG_MH = 128, FRAG = 2 * FRAG_MH * FRAG_D;
+__global__ void __launch_bounds__(256) pool_cast_frag_k(const float* __restrict__ V, const float* __restrict__ U, bf16* __restrict__ out,
+                                                        int transposed, unsigned* __restrict__ ticket) {
+  if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
+  constexpr int PIECES = FRAG / 8;
+  const int per = transposed ? 2 * PIECES : PIECES, i = blockIdx.x * 256 + threadIdx.x;   // a whole number of workgroups
+  const int h = i / per, r = i - h * per, l = r & 63;
+  V += (size_t)h * FRAG_MH * FRAG_D;
+  U += (size_t)h * FRAG_MH * FRAG_D;
+  float v[8];
+  if (r < PIECES) {
+    const int q = r >> 6, m = q & 1, ks = (q >> 1) % (FRAG_D / 16), w = (q >> 1) / (FRAG_D / 16);
+    const float* src = (m ? U : V) + (size_t)(32 * w + (l & 31)) * FRAG_D + ks * 16 + (l >> 5) * 8;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = src[e];
+  } else {
+    const int q = (r - PIECES) >> 6, ks = q % (2 * FRAG_MH / 16), b = q / (2 * FRAG_MH / 16);
+    const int u = ks * 16 + (l >> 5) * 8, d = 32 * b + (l & 31);
+    const float* src = (u < FRAG_MH ? V + (size_t)u * FRAG_D : U + (size_t)(u - FRAG_MH) * FRAG_D) + d;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = src[(size_t)e * FRAG_D];
+  }
+  bf16x8 t;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) t[e] = (bf16)v[e];
+  *reinterpret_cast<bf16x8*>(out + (size_t)h * 2 * FRAG + (size_t)r * 8) = t;
+}
+
 template <int RB, int MH, int BK>
 struct PoolCfg {
   static constexpr int RG = RB / 32;          // row groups of 32 (wavefronts along the rows)
@@ -269,22 +302,6 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   // to the last register and the allocator spills
   bf16x8 wv[KR], wu[KR];
   u32x4* wl = Wl + (size_t)wave * NL * 2 * 64 + lane;
-  {
-    const bf16* wr = VU + (size_t)(32 * wave + li) * D + h2 * 8;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 a = *reinterpret_cast<const u32x4*>(wr + ks * 16);
-      u32x4 b = *reinterpret_cast<const u32x4*>(wr + (size_t)MH * D + ks * 16);
-      if (ks < KR) {
-        asm volatile("" : "+a"(a), "+a"(b));
-        wv[ks] = __builtin_bit_cast(bf16x8, a);
-        wu[ks] = __builtin_bit_cast(bf16x8, b);
-      } else {
-        wl[((ks - KR) * 2 + 0) * 64] = a;
-        wl[((ks - KR) * 2 + 1) * 64] = b;
-      }
-    }
-  }
   float4 rs[3][NR];
   f32x16 acc[2][2];
   // The blocks of a workgroup are loaded strictly one after the other (load 0 .. NR - 1 of a block, then the next
@@ -487,6 +504,23 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   // prologue: block 0 of this workgroup, and the first loads of block 1
   static_for<0, NR>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[0], ic); });
   static_for<0, EARLY>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[1], ic); });
+  // the weights, while the rows come from memory
+  {
+    const u32x4* wr = reinterpret_cast<const u32x4*>(VU) + (size_t)wave * KS * 2 * 64 + lane;   // fragment order
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      u32x4 a = wr[(ks * 2 + 0) * 64];
+      u32x4 b = wr[(ks * 2 + 1) * 64];
+      if (ks < KR) {
+        asm volatile("" : "+a"(a), "+a"(b));
+        wv[ks] = __builtin_bit_cast(bf16x8, a);
+        wu[ks] = __builtin_bit_cast(bf16x8, b);
+      } else {
+        wl[((ks - KR) * 2 + 0) * 64] = a;
+        wl[((ks - KR) * 2 + 1) * 64] = b;
+      }
+    }
+  }
   stash_h(rs[0], 0);
   // iteration 0 has no previous block: its gate reads zeros and its weighted sum adds zero times zero
 #pragma unroll
@@ -522,16 +556,13 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   }
 }
 
-template <int D, int MH>
-hipError_t go_reg(const PoolArgs& p, hipStream_t s) {
+hipError_t go_reg(const PoolArgs& p, const bf16* vu, hipStream_t s) {
+  constexpr int D = FRAG_D, MH = FRAG_MH;
   auto kern = pool_gate_part_reg_k<D, MH>;
   size_t lds = (size_t)2 * 32 * (D + 8) * 2 + (size_t)4 * POOL_REG_NL * 2 * 64 * 16 + (size_t)3 * MH * 4 + 4 * 32 * 4;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  long long n = (long long)MH * p.D;
-  hipLaunchKernelGGL(pool_cast_vu_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, n, p.ticket);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(256), lds, s, p, (const bf16*)p.vub);
+  hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(256), lds, s, p, vu);
   return hipGetLastError();
 }
 
@@ -539,17 +570,17 @@ hipError_t go_reg(const PoolArgs& p, hipStream_t s) {
 // streaming from L2 for every block of rows in the one-pass kernel): pass 1 leaves the partial logits of gate units
 // 0..127 in a_tmp, pass 2 adds those of units 128..255 and does the softmax partials.
 hipError_t go_reg_halves(const PoolArgs& p0, hipStream_t s) {
-  constexpr int MH = 128;
+  constexpr int MH = FRAG_MH;
   if (!p0.a_tmp) return hipErrorInvalidValue;
   PoolArgs p = p0;
   p.Mh = MH; p.partial = 1; p.a_in = nullptr; p.w_other = nullptr; p.a = p0.a_tmp;
-  hipError_t e = go_reg<384, MH>(p, s);
+  hipError_t e = go_reg(p, (const bf16*)p0.vub, s);
   if (e != hipSuccess) return e;
   p = p0;
   p.Mh = MH; p.partial = 0; p.a_in = p0.a_tmp; p.w_other = p0.w;
   p.VW = p0.VW + (size_t)MH * p0.D; p.UW = p0.UW + (size_t)MH * p0.D;
   p.Vb = p0.Vb + MH; p.Ub = p0.Ub + MH; p.w = p0.w + MH;
-  return go_reg<384, MH>(p, s);
+  return go_reg(p, (const bf16*)p0.vub + 2 * FRAG, s);
 }
 
 template <int RB, int MH, int BK, int HCH>
@@ -580,9 +611,23 @@ static bool pool_two_pass(const PoolArgs& p) { return p.D == 384 && p.Mh == 256 
 
 int pool_mfma_rows(const PoolArgs& p) { return (p.D == 384 && p.Mh == 256 && !pool_two_pass(p)) ? 64 : 32; }
 
+// whether the forward leaves the weights in fragment order in p.vub (with their transposes if p.G is set)
+bool pool_frag_fwd(const PoolArgs& p) {
+  return p.use_mfma && pool_mfma_ok(p) && p.D == FRAG_D && (p.Mh == FRAG_MH || pool_two_pass(p));
+}
+
+hipError_t launch_pool_cast_frag(const PoolArgs& p, bool transposed, unsigned* ticket, hipStream_t s) {
+  const int pieces = p.Mh / FRAG_MH * (FRAG / 8) * (transposed ? 2 : 1);
+  hipLaunchKernelGGL(pool_cast_frag_k, dim3(pieces / 256), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, (int)transposed, ticket);
+  return hipGetLastError();
+}
+
 hipError_t launch_pool_gate_part_mfma(const PoolArgs& p, hipStream_t s) {
-  if (p.D == 384 && p.Mh == 128) return go_reg<384, 128>(p, s);
-  if (pool_two_pass(p)) return go_reg_halves(p, s);
+  if (pool_frag_fwd(p)) {
+    hipError_t e = launch_pool_cast_frag(p, p.G != nullptr, p.ticket, s);
+    if (e != hipSuccess) return e;
+    return p.Mh == FRAG_MH ? go_reg(p, (const bf16*)p.vub, s) : go_reg_halves(p, s);
+  }
   if (p.D == 384 && p.Mh == 256) return go<64, 256, 16, 24>(p, s);
   if (p.D == 768 && p.Mh == 128) return go<32, 128, 32, 24>(p, s);
   if (p.D == 768 && p.Mh == 256) return go<32, 256, 16, 24>(p, s);

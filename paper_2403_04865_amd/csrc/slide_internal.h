@@ -273,10 +273,14 @@ struct PoolArgs {
   // (the softmax shift is a bound over all gate units).  a_tmp: [N] floats of scratch for the partial logits.
   const float* a_in; int partial; const float* w_other; float* a_tmp;
   size_t a_room;      // floats behind a_tmp (the float32 kernels keep partial logits of blocks of gate units there)
+  int copies;         // the forward of this call has left the weights and their transposes in vub (pool_frag_fwd)
+  int fwd_only;       // no backward will read the scalars behind the logits
   unsigned* ticket;   // arrival counter of the combine kernel's workgroups, cleared by the kernels of stage 1
 };
 int pool_blocks(long long N);
 bool pool_mfma_ok(const PoolArgs& p);
+bool pool_frag_fwd(const PoolArgs& p);
+hipError_t launch_pool_cast_frag(const PoolArgs& p, bool transposed, unsigned* ticket, hipStream_t s);
 int pool_mfma_rows(const PoolArgs& p);
 hipError_t launch_pool_gate_part_mfma(const PoolArgs& p, hipStream_t s);
 hipError_t launch_pool_fwd(const PoolArgs& p, hipStream_t s);

@@ -818,8 +818,10 @@ int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
   PoolArgs p = pool_args(c, y, feats, N, label);
   p.G = (float*)G; p.accumulate = accumulate;
   int D = c->D, Mh = c->Mh;
-  if (!fwd_done)
+  if (!fwd_done) {
     launch(r, K_POOL_FWD, 4.0 * N * D * Mh, (double)N * D * 4, [&] { return launch_pool_fwd(p, s); });
+    p.copies = pool_frag_fwd(p);
+  }
   char* Dp = ar + y.p_Dp;
   Sums q(r, (float*)(ar + y.p_tn), (size_t)((y.p_cs - y.p_tn) / 4 + (size_t)1024 * 3 * Mh));
   // the matrix-core path keeps [dpV dpU] and a feature copy as bf16 in the room of the fp32 [N, 3 Mh] array; db_V and
@@ -1085,7 +1087,7 @@ int mil_pool_fwd_static(const slide_ctx* c, const float* params, const void* fea
   p.a_tmp = (float*)(ws + o_tmp);   // the last piece: it may use what is left of the array
   p.a_room = (sizeof(scratch) - o_tmp) / 4;
   p.ticket = (unsigned*)(p.scal + pool_scal_floats(C, D) - 1);
-  p.loss = loss; p.logits = logits; p.alpha = alpha;
+  p.loss = loss; p.logits = logits; p.alpha = alpha; p.fwd_only = 1;
   (void)hipGetLastError();
   e = launch_pool_fwd(p, (hipStream_t)stream);
   if (e != hipSuccess) { g_last_hip = (int)e; return SLIDE_EHIP; }
