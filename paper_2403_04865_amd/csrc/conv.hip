@@ -772,7 +772,8 @@ __global__ void __launch_bounds__(256) conv_wgrad_k(ConvWG p) {
 // again.  Here a workgroup owns BO x BI = 128 x 128, 256 x 64 or 64 x 256 of (c_out, c_in), a wavefront 64 x 64 of it
 // (eight MFMAs per step), the source row of output row m is row m, three stages in separate LDS arrays, loads two
 // steps ahead.
-template <int BO, int BI>
+// STRIDED: the 1x1 stride-2 projections, whose source row is that of position (2 y, 2 x)
+template <int BO, int BI, bool STRIDED>
 __global__ void __launch_bounds__(256, 2) conv_wgrad_pw_k(ConvWG p) {
   constexpr int SA = BO / 64, SB = BI / 64, SL = SA + SB, SLICE = WBK * 64, STAGE = SL * SLICE;   // bf16 elements
   constexpr int WI = SB >= 4 ? 4 : SB >= 2 ? 2 : 1;   // wavefronts along c_in, the others along c_out
@@ -793,16 +794,37 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_pw_k(ConvWG p) {
   const int r = wave * 8 + (lane >> 3);                          // this lane's row of every slice
   const int cl = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 16;      // the piece it fetches, in bytes (its slot holds piece slot ^ ...)
   const int dvo = r * 2 * p.Co + cl, svo = r * 2 * p.Cs + cl;
+  const float invXO = 1.0f / (float)p.g.XO;
+  const long long images = p.M / (p.g.YO * p.g.XO);
+  int in = 0, iy = 0, ix = 0;   // position of the first row of the step to be fetched (uniform)
+  if (STRIDED) row_pos(lo < p.M ? lo : p.M - 1, p.M, p.g, in, iy, ix);
 
   auto issue = [&](long long mstep, auto stc) __attribute__((always_inline)) {   // only called with mstep < hi
     constexpr int ST = decltype(stc)::value;
     bf16* sa = (ST == 0 ? sg0 : ST == 1 ? sg1 : sg2) + wave * 8 * 64;
     const __amdgpu_buffer_rsrc_t rd = dma_buffer(p.dout + mstep * p.Co + co0, ((hi - mstep) * p.Co - co0) * 2);
-    const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + mstep * p.Cs + ci0, ((hi - mstep) * p.Cs - ci0) * 2);
 #pragma unroll
     for (int sl = 0; sl < SA; ++sl) dma16(rd, sa + sl * SLICE, dvo, sl * 128);
+    if constexpr (!STRIDED) {
+      const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + mstep * p.Cs + ci0, ((hi - mstep) * p.Cs - ci0) * 2);
 #pragma unroll
-    for (int sl = 0; sl < SB; ++sl) dma16(rs, sa + (SA + sl) * SLICE, svo, sl * 128);
+      for (int sl = 0; sl < SB; ++sl) dma16(rs, sa + (SA + sl) * SLICE, svo, sl * 128);
+    } else {   // this lane's row r positions behind (in, iy, ix), counted from that position's source row
+      const int xr = ix + r;
+      const int w = (int)(((float)xr + 0.5f) * invXO);   // exact: the half keeps multiples of XO off the edge
+      int y = iy + w, dn = 0;
+      while (y >= p.g.YO) { y -= p.g.YO; ++dn; }
+      const long long first = ((long long)in * p.g.YS + 2 * iy) * p.g.XS + 2 * ix;
+      const __amdgpu_buffer_rsrc_t rs = dma_buffer(p.src + first * p.Cs + ci0, ((images * p.g.YS * p.g.XS - first) * p.Cs - ci0) * 2);
+      const int vo = r < hi - mstep ? ((dn * p.g.YS + 2 * (y - iy)) * p.g.XS + 2 * (xr - w * p.g.XO - ix)) * 2 * p.Cs + cl : DMA_ABSENT;
+#pragma unroll
+      for (int sl = 0; sl < SB; ++sl) dma16(rs, sa + (SA + sl) * SLICE, vo, sl * 128);
+      ix += WBK;
+      while (ix >= p.g.XO) {
+        ix -= p.g.XO;
+        if (++iy == p.g.YO) { iy = 0; ++in; }
+      }
+    }
   };
 
   f32x16 acc[2][2];
@@ -869,11 +891,11 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_pw_k(ConvWG p) {
 //   * a source row whose output row would need an image row above the first or below the last (kh = 0 with y = 0,
 //     kh = 2 with y = YO - 1; also the neighbouring image in the flattened order) is fetched as zeros: within band
 //     kh every source row serves output rows of one image row only.
-// The loading lane decides per band row what to fetch (row, gap, or zeros); the K loop has no masks.  Needs XO >= 8.
+// The loading lane decides per band row what to fetch (row, gap, or zeros); the K loop has no masks.  Needs XO >= 7.
 // The stages being half the size, four of them fit (two workgroups per compute unit): a step's rows are requested three
 // steps ahead.  With one step of lead a step cannot be shorter than a memory latency, which, not the bytes, is what
 // the two-stage kernels of this file wait for (measured: the halved traffic alone changed nothing).
-constexpr int WBAND = 40;   // band rows per step: 32 + 2 neighbours + at most 4 gap rows, rounded to the 8 of an instruction
+constexpr int WBAND = 40;   // band rows per step: 32 + 2 neighbours + at most 5 gap rows, rounded to the 8 of an instruction
 constexpr int WSTAGES = 4;
 
 __global__ void __launch_bounds__(256, 2) conv_wgrad_win_k(ConvWG p) {
@@ -1243,6 +1265,11 @@ namespace {
 bool wgrad_pointwise(const ConvWG& p) {
   return !p.g.stem && p.g.KH == 1 && p.g.KW == 1 && p.g.stride == 1 && p.g.pad == 0 && p.g.YS == p.g.YO && p.g.XS == p.g.XO;
 }
+// 1x1 stride 2 (a projection on the way into a stage): 64 x 64 blocks fetched every operand slice up to 32 times and had two MFMAs
+// between barriers (ResNet50's three, 300 tiles, 212 us each)
+bool wgrad_projection(const ConvWG& p) {
+  return !p.g.stem && p.g.KH == 1 && p.g.KW == 1 && p.g.stride == 2 && p.g.pad == 0 && p.g.YS == 2 * p.g.YO && p.g.XS == 2 * p.g.XO;
+}
 
 }  // namespace
 
@@ -1254,7 +1281,7 @@ int conv_wgrad_slabs(const ConvWG& p) {
   const int blocks = (p.Co / 64) * (p.Cs / 64);
   if (p.g.stem) return (1024 + blocks - 1) / blocks;
   if (p.g.KH == 3) return (512 + blocks - 1) / blocks;
-  const bool big = wgrad_pointwise(p) && ((p.Co % 128 == 0 && p.Cs % 128 == 0) || p.Co % 256 == 0 || p.Cs % 256 == 0);
+  const bool big = (wgrad_pointwise(p) || wgrad_projection(p)) && ((p.Co % 128 == 0 && p.Cs % 128 == 0) || p.Co % 256 == 0 || p.Cs % 256 == 0);
   return big ? (4 * 768 + blocks - 1) / blocks : (2048 + blocks - 1) / blocks;
 }
 
@@ -1279,23 +1306,26 @@ hipError_t launch_conv_wgrad(const ConvWG& p, hipStream_t s) {
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  // 3x3 stride-1 pad-1 layers on a grid at least 8 wide: the kernel that fetches a step's source rows once
-  if (!p.g.stem && taps == 9 && p.g.stride == 1 && p.g.pad == 1 && p.g.YS == p.g.YO && p.g.XS == p.g.XO && p.g.XO >= 8) {
+  // 3x3 stride-1 pad-1 layers on a grid at least 7 wide: the kernel that fetches a step's source rows once
+  if (!p.g.stem && taps == 9 && p.g.stride == 1 && p.g.pad == 1 && p.g.YS == p.g.YO && p.g.XS == p.g.XO && p.g.XO >= 7) {
     hipLaunchKernelGGL(conv_wgrad_win_k, grid, dim3(256), 0, s, p);   // (its stages are static LDS arrays)
     return hipGetLastError();
   }
+  const bool pw = wgrad_pointwise(p), proj = wgrad_projection(p);
   if (p.g.stem) hipLaunchKernelGGL((conv_wgrad_k<4, true>), grid, dim3(256), lds_of(4), s, p);
-  else if (wgrad_pointwise(p)) {
+  else if ((pw || proj) && ((p.Co % 128 == 0 && p.Cs % 128 == 0) || p.Co % 256 == 0 || p.Cs % 256 == 0)) {
     const unsigned g8 = (unsigned)((p.slabs + 7) / 8 * 8);
-    if (p.Co % 128 == 0 && p.Cs % 128 == 0)
-      hipLaunchKernelGGL((conv_wgrad_pw_k<128, 128>), dim3(g8 * (p.Co / 128) * (p.Cs / 128)), dim3(256), 0, s, p);
-    else if (p.Co % 256 == 0)
-      hipLaunchKernelGGL((conv_wgrad_pw_k<256, 64>), dim3(g8 * (p.Co / 256) * (p.Cs / 64)), dim3(256), 0, s, p);
-    else if (p.Cs % 256 == 0)
-      hipLaunchKernelGGL((conv_wgrad_pw_k<64, 256>), dim3(g8 * (p.Co / 64) * (p.Cs / 256)), dim3(256), 0, s, p);
-    else
-      hipLaunchKernelGGL((conv_wgrad_k<1, false, true>), grid, dim3(256), lds_of(1), s, p);
+    auto go = [&](auto bo, auto bi) {
+      constexpr int BO = decltype(bo)::value, BI = decltype(bi)::value;
+      const dim3 gr(g8 * (p.Co / BO) * (p.Cs / BI));
+      if (pw) hipLaunchKernelGGL((conv_wgrad_pw_k<BO, BI, false>), gr, dim3(256), 0, s, p);
+      else hipLaunchKernelGGL((conv_wgrad_pw_k<BO, BI, true>), gr, dim3(256), 0, s, p);
+    };
+    if (p.Co % 128 == 0 && p.Cs % 128 == 0) go(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{});
+    else if (p.Co % 256 == 0) go(std::integral_constant<int, 256>{}, std::integral_constant<int, 64>{});
+    else go(std::integral_constant<int, 64>{}, std::integral_constant<int, 256>{});
   }
+  else if (pw) hipLaunchKernelGGL((conv_wgrad_k<1, false, true>), grid, dim3(256), lds_of(1), s, p);
   else if (taps == 1) hipLaunchKernelGGL((conv_wgrad_k<1, false>), grid, dim3(256), lds_of(1), s, p);
   else hipLaunchKernelGGL((conv_wgrad_k<9, false>), grid, dim3(256), lds_of(9), s, p);
   return hipGetLastError();
