@@ -104,7 +104,8 @@ __device__ __forceinline__ void wait_vm() {   // until at most N vector-memory o
 // The accumulators of a tile (one 64 x 64 block per wavefront) to memory: through LDS in fp32, then whole row segments;
 // what is added on the way (the output's old value, the shortcut's gradient) is added to the unrounded sums, so every
 // stored element is rounded once; optionally the tile's channel sums for the batch statistics.
-template <int BM, int BN>
+// ADD: something may be added
+template <int BM, int BN, bool ADD = true>
 __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&acc)[2][2], unsigned char* smem, long long m0,
                                               int n0, int rt, int tid, int lane, int wm, int wn) {
   __syncthreads();   // every operand read is done: the stages become the copy of the tile
@@ -113,7 +114,7 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
   float ss[8], qq[8];   // this thread's 8 channels (the same in every iteration: 256 % CH == 0) summed over its rows
 #pragma unroll
   for (int e = 0; e < 8; ++e) ss[e] = qq[e] = 0.f;
-  if (!p.add && !p.extra) {   // uniform: nothing is added on the way, the tile can cross LDS as bf16 (half the LDS traffic)
+  if (!ADD || (!p.add && !p.extra)) {   // uniform: nothing is added on the way, the tile can cross LDS as bf16 (half the LDS traffic)
     constexpr int CLDB = BN + 8;
     bf16* Cb = reinterpret_cast<bf16*>(smem);
 #pragma unroll
@@ -152,7 +153,7 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
         __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.out + orow * p.N + n0 + ch * 8));
       }
     }
-  } else {
+  } else if constexpr (ADD) {
   constexpr int CLDC = BN + 4, NIT = BM * CH / 256;
   float* Cs = reinterpret_cast<float*>(smem);
   // what is added, for all of this thread's pieces before the tile crosses LDS: asked for one piece at a time behind it, a piece
@@ -242,8 +243,11 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
 // PW: a pointwise (1x1, stride 1) layer: produced row m reads source row m, so none of the position arithmetic below
 // is needed (a tile of such a layer is one to eight K steps long, and what a wavefront spends per tile outside the
 // MFMAs -- some 1000 vector instructions in the general form -- is what bounds it)
-template <int BM, int BN, int NST, bool STEM, bool PW = false>
-__global__ void __launch_bounds__(256, 2) conv_nt_dl_k(ConvNT p, int row_tiles, int col_tiles) {
+// ADD = false: nothing is added on the way out.  Such a pointwise launch (the forward) has one stage: its tile then needs 35 KB of LDS
+// (the bf16 copy) and 168 registers, and three workgroups share a compute unit; a tile is one to eight K steps behind a prologue
+// and in front of a write-out that nothing else of its workgroup overlaps.
+template <int BM, int BN, int NST, bool STEM, bool PW = false, bool ADD = true>
+__global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, int row_tiles, int col_tiles) {
   constexpr int STAGE = (BM + BN) * CBK;   // bf16 elements per stage
   constexpr int WN = BN / 64, WM = 4 / WN;
   static_assert(WM * 64 == BM && (BN == 64 || BN == 128), "one 64 x 64 block per wavefront");
@@ -378,17 +382,21 @@ __global__ void __launch_bounds__(256, 2) conv_nt_dl_k(ConvNT p, int row_tiles, 
     offB[i] = BM * CBK + Rb * CBK; swB[i] = (Rb >> 1) & 7;
   }
 
-  if (nk > 0) issue(0, 0);   // a parity class may have no tap at all (1x1 kernels): its positions get zeros
+  if (NST > 1 && nk > 0) issue(0, 0);   // a parity class may have no tap at all (1x1 kernels): its positions get zeros
   if (NST == 3 && nk > 1) issue(1, 1);
   int st = 0;
   for (int kt = 0; kt < nk; ++kt) {
+    if (NST == 1) {
+      if (kt > 0) __builtin_amdgcn_s_barrier();   // the step before is done with the stage
+      issue(kt, 0);
+    }
     // this step's operands have landed (with three stages the next step's may be pending)
     if (NST == 3 && kt + 1 < nk) wait_vm<AG + BG>(); else wait_vm<0>();
     // ... for every wavefront, and the stage of step kt - 1 is free (its fragment reads were waited for before the
     // MFMAs that used them).  A bare barrier: the fence of __syncthreads would wait for every pending load.
     __builtin_amdgcn_s_barrier();
     if (NST == 3) { if (kt + 2 < nk) issue(kt + 2, st >= 1 ? st - 1 : 2); }   // (kt + 2) % 3
-    else if (kt + 1 < nk) issue(kt + 1, st ^ 1);
+    else if (NST == 2 && kt + 1 < nk) issue(kt + 1, st ^ 1);
     const bf16* sb = S + st * STAGE;
 #pragma unroll
     for (int ks = 0; ks < CBK / 16; ++ks) {
@@ -407,7 +415,7 @@ __global__ void __launch_bounds__(256, 2) conv_nt_dl_k(ConvNT p, int row_tiles, 
     }
     st = st == NST - 1 ? 0 : st + 1;
   }
-  conv_tile_out<BM, BN>(p, acc, smem, m0, n0, rt, tid, lane, wm, wn);
+  conv_tile_out<BM, BN, ADD>(p, acc, smem, m0, n0, rt, tid, lane, wm, wn);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1262,6 +1270,16 @@ hipError_t launch_conv_nt(const ConvNT& p, hipStream_t s) {
   // pointwise layers (and their input gradients): produced row m reads source row m
   const bool pw = !p.g.stem && !p.g.cls && p.g.KH == 1 && p.g.KW == 1 && p.g.stride == 1 && p.g.pad == 0 && p.g.YS == p.g.YO &&
                   p.g.XS == p.g.XO;
+  if (pw && !p.add && !p.extra) {
+    // one stage, or the bf16 copy of the tile, or the statistics' scratch
+    auto lds_1 = [](size_t BM, size_t BN) {
+      const size_t st = (BM + BN) * CBK * sizeof(bf16), ep = BM * (BN + 8) * sizeof(bf16);
+      return st > ep ? st : ep;
+    };
+    if (wide) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, 1, false, true, false>), dim3(grid), dim3(256), lds_1(128, 128), s, p, row_tiles, col_tiles);
+    else hipLaunchKernelGGL((conv_nt_dl_k<256, 64, 1, false, true, false>), dim3(grid), dim3(256), lds_1(256, 64), s, p, row_tiles, col_tiles);
+    return hipGetLastError();
+  }
   if (pw) {
     if (wide) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, NST, false, true>), dim3(grid), dim3(256), lds_w, s, p, row_tiles, col_tiles);
     else hipLaunchKernelGGL((conv_nt_dl_k<256, 64, NST, false, true>), dim3(grid), dim3(256), lds_n, s, p, row_tiles, col_tiles);
