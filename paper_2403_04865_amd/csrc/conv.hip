@@ -83,8 +83,8 @@ constexpr int CBK = 64;   // channels of one tap per K step
 // forward / input gradient
 // ---------------------------------------------------------------------------------------------------------------
 // Operands straight into LDS (lds_dma.h): a wavefront instruction moves 64 x 16 bytes from 64 independent
-// offsets to 1 KB of consecutive LDS (lane l -> bytes 16 l ..), without passing through registers, so three
-// K steps of operands are in flight per workgroup at no register cost and the loop waits only for the oldest.
+// offsets to 1 KB of consecutive LDS (lane l -> bytes 16 l ..), without passing through registers, so what a
+// workgroup has in flight costs none.
 //   * One instruction fills 8 rows x 128 bytes (8 lanes per row).  Rows are unpadded; the 16-byte pieces of a row are
 //     stored permuted (piece c of row R sits in slot c ^ ((R >> 1) & 7)), which the loading lane realises by choosing
 //     its global address, so that the 16-byte fragment reads of 16 consecutive rows fall on 64 different banks.
@@ -244,9 +244,10 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
 // is needed (a tile of such a layer is one to eight K steps long, and what a wavefront spends per tile outside the
 // MFMAs -- some 1000 vector instructions in the general form -- is what bounds it)
 // ADD = false: nothing is added on the way out.  Such a launch (the forwards, most input gradients) has one stage: its tile then
-// needs 35 KB of LDS (the bf16 copy) and 104 registers, and four workgroups share a compute unit, which hide more of each other's
-// prologue, loads and write-out than a second stage does of a workgroup's own (ResNet18, 1024 tiles, its 23 launches of this kind 3.45
-// ms with two stages and two workgroups, 2.43 this way).
+// needs 40 KB of LDS at most and 104 to 114 registers, and four workgroups share a compute unit, which hide more of each other's
+// prologue, loads and write-out than a second stage does of a workgroup's own (ResNet18, 1024 tiles, its 27 launches that are not
+// pointwise: 3.44 ms with two stages, 2.93 this way).  Launches that add something keep two: what they add takes 166 registers, so
+// three workgroups at most, and one stage measured the same over both ResNet steps.
 template <int BM, int BN, int NST, bool STEM, bool PW = false, bool ADD = true>
 __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, int row_tiles, int col_tiles) {
   constexpr int STAGE = (BM + BN) * CBK;   // bf16 elements per stage
@@ -388,7 +389,12 @@ __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, 
   int st = 0;
   for (int kt = 0; kt < nk; ++kt) {
     if (NST == 1) {
-      if (kt > 0) __builtin_amdgcn_s_barrier();   // the step before is done with the stage
+      if (kt > 0) {   // every wavefront has read the step before
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
       issue(kt, 0);
     }
     // this step's operands have landed (with three stages the next step's may be pending)
