@@ -21,7 +21,7 @@ import json
 import os
 import sys
 
-FAMILIES = [("gemm_nt", ("gemm_nt_",)), ("gemm_tn", ("gemm_tn_",)), ("attn_fwd", ("attn_fwd",)),
+FAMILIES = [("gemm_nt", ("gemm_nt_", "mlp_k")), ("gemm_tn", ("gemm_tn_",)), ("attn_fwd", ("attn_fwd",)),
             ("attn_bwd", ("attn_bwd",)), ("ln_fwd", ("ln_fwd",)), ("ln_bwd", ("ln_bwd",)),
             # (the float32 gate kernels, pool_gate_f32_k and pool_wide_gate_k, run in both directions)
             ("pool_fwd", ("pool_gate", "pool_combine", "pool_cast", "pool_softmax", "pool_wide_gate")),
