@@ -504,20 +504,23 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   // prologue: block 0 of this workgroup, and the first loads of block 1
   static_for<0, NR>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[0], ic); });
   static_for<0, EARLY>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[1], ic); });
-  // the weights, while the rows come from memory
+  // the weights, while the rows come from memory; all of them are requested before the first is waited for (one at a time, each
+  // a trip to L2, 1,037 rows take 11.7 us instead of 8.9 and 45,056 rows 22.3 instead of 19.2)
   {
     const u32x4* wr = reinterpret_cast<const u32x4*>(VU) + (size_t)wave * KS * 2 * 64 + lane;   // fragment order
+    u32x4 a[2 * KS];
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i) a[i] = wr[i * 64];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      u32x4 a = wr[(ks * 2 + 0) * 64];
-      u32x4 b = wr[(ks * 2 + 1) * 64];
       if (ks < KR) {
-        asm volatile("" : "+a"(a), "+a"(b));
-        wv[ks] = __builtin_bit_cast(bf16x8, a);
-        wu[ks] = __builtin_bit_cast(bf16x8, b);
+        asm volatile("" : "+a"(a[2 * ks]), "+a"(a[2 * ks + 1]));
+        wv[ks] = __builtin_bit_cast(bf16x8, a[2 * ks]);
+        wu[ks] = __builtin_bit_cast(bf16x8, a[2 * ks + 1]);
       } else {
-        wl[((ks - KR) * 2 + 0) * 64] = a;
-        wl[((ks - KR) * 2 + 1) * 64] = b;
+        wl[((ks - KR) * 2 + 0) * 64] = a[2 * ks];
+        wl[((ks - KR) * 2 + 1) * 64] = a[2 * ks + 1];
       }
     }
   }
