@@ -101,6 +101,16 @@ __device__ __forceinline__ void wait_vm() {   // until at most N vector-memory o
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070 | 0x0f00);
 }
 
+// Between two uses of a stage: this wavefront's LDS reads are done, and no access to memory moves across in the program either (the
+// barrier alone orders only the wavefronts, and a read of what another wavefront has loaded may not be moved in front of it).  The
+// fence of __syncthreads would wait for every pending load.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // The accumulators of a tile (one 64 x 64 block per wavefront) to memory: through LDS in fp32, then whole row segments;
 // what is added on the way (the output's old value, the shortcut's gradient) is added to the unrounded sums, so every
 // stored element is rounded once; optionally the tile's channel sums for the batch statistics.
@@ -188,10 +198,7 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
         *reinterpret_cast<float4*>(&Cs[row * CLDC + col]) =
             make_float4(acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]);
       }
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);   // the tile is in LDS (a fence would wait for the loads as well)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  lds_barrier();   // the tile is in LDS (a __syncthreads would wait for the loads as well)
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int idx = tid + 256 * it;
@@ -389,19 +396,12 @@ __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, 
   int st = 0;
   for (int kt = 0; kt < nk; ++kt) {
     if (NST == 1) {
-      if (kt > 0) {   // every wavefront has read the step before
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-      }
+      if (kt > 0) lds_barrier();   // every wavefront has read the step before
       issue(kt, 0);
     }
     // this step's operands have landed (with three stages the next step's may be pending)
     if (NST == 3 && kt + 1 < nk) wait_vm<AG + BG>(); else wait_vm<0>();
-    // ... for every wavefront, and the stage of step kt - 1 is free (its fragment reads were waited for before the
-    // MFMAs that used them).  A bare barrier: the fence of __syncthreads would wait for every pending load.
-    __builtin_amdgcn_s_barrier();
+    lds_barrier();   // ... for every wavefront, and the stage of step kt - 1 is free
     if (NST == 3) { if (kt + 2 < nk) issue(kt + 2, st >= 1 ? st - 1 : 2); }   // (kt + 2) % 3
     else if (NST == 2 && kt + 1 < nk) issue(kt + 1, st ^ 1);
     const bf16* sb = S + st * STAGE;
@@ -769,7 +769,7 @@ __global__ void __launch_bounds__(256) conv_wgrad_k(ConvWG p) {
   int st = 0;
   for (long long mstep = lo; mstep < hi; mstep += WBK) {
     wait_vm<0>();                     // this step's rows have landed ...
-    __builtin_amdgcn_s_barrier();     // ... for every wavefront, and the other stage is no longer read
+    lds_barrier();                    // ... for every wavefront, and the other stage is no longer read
     if (mstep + WBK < hi) issue(mstep + WBK, st ^ 1);
     const bf16* sb = S + st * STAGE;
 #pragma unroll
@@ -870,7 +870,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_pw_k(ConvWG p) {
     constexpr int ST = decltype(stc)::value;
     // this step's rows have landed (the next step's SL requests may be pending) ...
     if (mstep + WBK < hi) wait_vm<SL>(); else wait_vm<0>();
-    __builtin_amdgcn_s_barrier();     // ... for every wavefront, and the stage of the previous step is no longer read
+    lds_barrier();                    // ... for every wavefront, and the stage of the previous step is no longer read
     if (mstep + 2 * WBK < hi) issue(mstep + 2 * WBK, std::integral_constant<int, (ST + 2) % 3>{});
     const bf16* sb = ST == 0 ? sg0 : ST == 1 ? sg1 : sg2;
 #pragma unroll
@@ -1026,7 +1026,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_win_k(ConvWG p) {
     if (later >= WSTAGES - 2) { if (wave < 3) wait_vm<10>(); else wait_vm<8>(); }
     else if (later == 1) { if (wave < 3) wait_vm<5>(); else wait_vm<4>(); }
     else wait_vm<0>();
-    __builtin_amdgcn_s_barrier();     // ... for every wavefront, and the stage of the previous step is no longer read
+    lds_barrier();                    // ... for every wavefront, and the stage of the previous step is no longer read
     if (mstep + (WSTAGES - 1) * WBK < hi) {
       issue(mstep + (WSTAGES - 1) * WBK, std::integral_constant<int, (ST + WSTAGES - 1) % WSTAGES>{}, iy, ix);
       adv32(iy, ix);
