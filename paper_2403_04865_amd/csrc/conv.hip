@@ -91,10 +91,9 @@ constexpr int CBK = 64;   // channels of one tap per K step
 //   * A row in the zero padding is an offset outside of the buffer, which loads zeros (no branch, every lane loads).
 //   * Every wavefront owns a 64 x 64 block of the tile: 256 x 64 tiles (4 x 1 wavefronts) where the output has 64
 //     channels, 128 x 128 (2 x 2) otherwise.
-// LDS stages.  Two (64 / 80 KB per workgroup, two workgroups per compute unit, loads one step ahead) measured 22 %
-// faster over the ResNet18 step than three (one workgroup per compute unit, loads two steps ahead): the second
+// LDS stages, one or two (conv_one_stage).  Two (64 / 80 KB per workgroup, two workgroups per compute unit, loads one step ahead)
+// measured 22 % faster over the ResNet18 step than three (one workgroup per compute unit, loads two steps ahead): the second
 // workgroup hides more than the deeper queue.
-constexpr int CONV_STAGES = 2;
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {   // until at most N vector-memory operations of this wavefront are pending
@@ -250,11 +249,11 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
 // PW: a pointwise (1x1, stride 1) layer: produced row m reads source row m, so none of the position arithmetic below
 // is needed (a tile of such a layer is one to eight K steps long, and what a wavefront spends per tile outside the
 // MFMAs -- some 1000 vector instructions in the general form -- is what bounds it)
-// ADD = false: nothing is added on the way out.  Such a launch (the forwards, most input gradients) has one stage: its tile then
-// needs 40 KB of LDS at most and 104 to 114 registers, and four workgroups share a compute unit, which hide more of each other's
-// prologue, loads and write-out than a second stage does of a workgroup's own (ResNet18, 1024 tiles, its 27 launches that are not
-// pointwise: 3.44 ms with two stages, 2.93 this way).  Launches that add something keep two: what they add takes 166 registers, so
-// three workgroups at most, and one stage measured the same over both ResNet steps.
+// ADD = false: nothing is added on the way out.  Where such a launch (the forwards, most input gradients) has workgroups enough it
+// has one stage: its tile then needs 40 KB of LDS at most and 104 to 114 registers, and four workgroups share a compute unit, which
+// hide more of each other's prologue, loads and write-out than a second stage does of a workgroup's own (ResNet18, 1024 tiles, its
+// 27 launches that are not pointwise: 3.44 ms with two stages, 2.93 this way; conv_one_stage).  Launches that add something
+// have two: what they add takes 166 registers, so three workgroups at most, and one stage measured the same over both ResNet steps.
 template <int BM, int BN, int NST, bool STEM, bool PW = false, bool ADD = true>
 __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, int row_tiles, int col_tiles) {
   constexpr int STAGE = (BM + BN) * CBK;   // bf16 elements per stage
@@ -1177,6 +1176,43 @@ bool geom_ok(const ConvGeom& g) {
          g.pad >= 0 && g.pad < (1 << 10) && g.KH < (1 << 10) && g.KW < (1 << 10);
 }
 
+template <int BM, int BN, int NST, bool STEM, bool PW, bool ADD>
+hipError_t launch_conv_dl(const ConvNT& p, unsigned grid, int row_tiles, int col_tiles, hipStream_t s) {
+  // the operand stages, or the copy of the tile that takes their place at the end, whichever is larger
+  constexpr size_t st = (size_t)NST * (BM + BN) * CBK * sizeof(bf16);
+  constexpr size_t ep = ADD ? (size_t)BM * (BN + 4) * sizeof(float) : (size_t)BM * (BN + 8) * sizeof(bf16);
+  constexpr size_t lds = st > ep ? st : ep;
+  auto kern = conv_nt_dl_k<BM, BN, NST, STEM, PW, ADD>;
+  if constexpr (lds > 65536) {
+    static bool attr_done = false;
+    if (!attr_done) {
+      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      attr_done = true;
+    }
+  }
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, p, row_tiles, col_tiles);
+  return hipGetLastError();
+}
+
+int compute_units() {
+  static const int cus = [] {
+    int dev = 0;
+    hipDeviceProp_t prop;
+    return hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0
+               ? prop.multiProcessorCount : 256;
+  }();
+  return cus;
+}
+
+// One stage or two where nothing is added.  Up to two workgroups per compute unit are there all at once either way, so a second
+// stage is what hides a step's loads; beyond, four workgroups of one stage take the place of two.  Time with two stages over that
+// with one, 256 compute units, all such launches of ResNet18 (8 to 1024 tiles) and ResNet50 (4 to 300), pointwise / general:
+// 16 to 256 workgroups 0.78-0.84 / 0.78-0.87, 320 0.84 / 0.79, 400 0.89 / 0.86, 512 0.89 / 0.89, 592 1.11 / 1.26, 624 1.15 / 1.23,
+// 784 1.03 / 1.12, 1232 1.04 / 1.12, 1568 1.13 / 1.19, 3136 1.15 / 1.22, 7360 1.26 / 1.34; 256 x 64 tiles 392 0.96 / 0.92,
+// 784 1.03 / 1.06, 3136 - / 1.24, 3680 1.01 / -.
+bool conv_one_stage(int tiles) { return tiles > 2 * compute_units(); }
+
 }  // namespace
 
 int conv_nt_row_tiles(const ConvNT& p) {
@@ -1188,7 +1224,7 @@ hipError_t launch_conv_nt(const ConvNT& p, hipStream_t s) {
   if (!geom_ok(p.g) || p.M <= 0 || p.M >= (1LL << 31) - 256 || p.Cs <= 0 || p.Cs % CBK || p.N <= 0 || p.N % 64 ||
       !al16(p.src) || !al16(p.W) || !al16(p.out) || !al16(p.extra) || (p.extra && !p.mask))
     return hipErrorInvalidValue;
-  if (p.g.stem && p.Cs != 256) return hipErrorInvalidValue;
+  if (p.g.stem && (p.Cs != 256 || p.add || p.extra)) return hipErrorInvalidValue;
   if (p.stat_part && (p.add || p.extra || p.g.cls)) return hipErrorInvalidValue;   // sums of a whole, fresh output only
   if (p.g.cls && (p.g.cls < 1 || p.g.cls > 4 || !p.g.transposed || p.g.stride != 2 || p.g.YO % 2 || p.g.XO % 2))
     return hipErrorInvalidValue;
@@ -1230,15 +1266,6 @@ hipError_t launch_conv_nt(const ConvNT& p, hipStream_t s) {
     const long long wbytes = (long long)(2 * (rows_out - 1) + 7) * p.g.XS * 8;
     const long long img_bytes = n * p.g.YS * p.g.XS * 8;
     if (wbytes <= STEM_WIN && img_bytes >= 16) {
-      static int cus = 0;
-      if (!cus) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        hipError_t e;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-        if ((e = hipGetDeviceProperties(&prop, dev)) != hipSuccess) return e;
-        cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
-      }
       const int tiles = (int)(p.M / 256);
       static bool stem_attr = false;
       if (!stem_attr) {
@@ -1246,59 +1273,27 @@ hipError_t launch_conv_nt(const ConvNT& p, hipStream_t s) {
         if (e != hipSuccess) return e;
         stem_attr = true;
       }
-      const int g = tiles < 2 * cus ? tiles : 2 * cus;   // two workgroups per compute unit
+      const int cus = compute_units(), g = tiles < 2 * cus ? tiles : 2 * cus;   // two workgroups per compute unit
       hipLaunchKernelGGL(stem_fwd_k, dim3((unsigned)g), dim3(256), STEM_LDS, s, p, tiles, (int)wbytes, img_bytes);
       return hipGetLastError();
     }
   }
-  static bool attr_done = false;
-  constexpr int NST = CONV_STAGES;
-  // the operand stages, or the fp32 copy of the tile that takes their place at the end, whichever is larger
-  auto lds_of = [](size_t BM, size_t BN) {
-    const size_t st = (size_t)NST * (BM + BN) * CBK * sizeof(bf16), ep = BM * (BN + 4) * sizeof(float);
-    return st > ep ? st : ep;
-  };
-  const size_t lds_w = lds_of(128, 128), lds_n = lds_of(256, 64);
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)conv_nt_dl_k<128, 128, NST, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_w);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)conv_nt_dl_k<256, 64, NST, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_n);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)conv_nt_dl_k<128, 128, NST, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_w);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)conv_nt_dl_k<256, 64, NST, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_n);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)conv_nt_dl_k<128, 128, NST, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_w);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)conv_nt_dl_k<256, 64, NST, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_n);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
   // pointwise layers (and their input gradients): produced row m reads source row m
   const bool pw = !p.g.stem && !p.g.cls && p.g.KH == 1 && p.g.KW == 1 && p.g.stride == 1 && p.g.pad == 0 && p.g.YS == p.g.YO &&
                   p.g.XS == p.g.XO;
-  if (!p.add && !p.extra && !p.g.stem) {
-    // one stage, or the bf16 copy of the tile, or the statistics' scratch
-    auto lds_1 = [](size_t BM, size_t BN) {
-      const size_t st = (BM + BN) * CBK * sizeof(bf16), ep = BM * (BN + 8) * sizeof(bf16);
-      return st > ep ? st : ep;
-    };
-    if (pw && wide) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, 1, false, true, false>), dim3(grid), dim3(256), lds_1(128, 128), s, p, row_tiles, col_tiles);
-    else if (pw) hipLaunchKernelGGL((conv_nt_dl_k<256, 64, 1, false, true, false>), dim3(grid), dim3(256), lds_1(256, 64), s, p, row_tiles, col_tiles);
-    else if (wide) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, 1, false, false, false>), dim3(grid), dim3(256), lds_1(128, 128), s, p, row_tiles, col_tiles);
-    else hipLaunchKernelGGL((conv_nt_dl_k<256, 64, 1, false, false, false>), dim3(grid), dim3(256), lds_1(256, 64), s, p, row_tiles, col_tiles);
-    return hipGetLastError();
-  }
-  if (pw) {
-    if (wide) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, NST, false, true>), dim3(grid), dim3(256), lds_w, s, p, row_tiles, col_tiles);
-    else hipLaunchKernelGGL((conv_nt_dl_k<256, 64, NST, false, true>), dim3(grid), dim3(256), lds_n, s, p, row_tiles, col_tiles);
-    return hipGetLastError();
-  }
-  if (wide && p.g.stem) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, NST, true>), dim3(grid), dim3(256), lds_w, s, p, row_tiles, col_tiles);
-  else if (wide) hipLaunchKernelGGL((conv_nt_dl_k<128, 128, NST, false>), dim3(grid), dim3(256), lds_w, s, p, row_tiles, col_tiles);
-  else if (p.g.stem) hipLaunchKernelGGL((conv_nt_dl_k<256, 64, NST, true>), dim3(grid), dim3(256), lds_n, s, p, row_tiles, col_tiles);
-  else hipLaunchKernelGGL((conv_nt_dl_k<256, 64, NST, false>), dim3(grid), dim3(256), lds_n, s, p, row_tiles, col_tiles);
-  return hipGetLastError();
+  const bool add = p.add || p.extra, one = conv_one_stage(row_tiles * col_tiles);
+  auto go = [&](auto bm, auto bn) {
+    constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
+    if (p.g.stem) return launch_conv_dl<BM, BN, 2, true, false, false>(p, grid, row_tiles, col_tiles, s);
+    if (pw) return add ? launch_conv_dl<BM, BN, 2, false, true, true>(p, grid, row_tiles, col_tiles, s)
+                 : one ? launch_conv_dl<BM, BN, 1, false, true, false>(p, grid, row_tiles, col_tiles, s)
+                       : launch_conv_dl<BM, BN, 2, false, true, false>(p, grid, row_tiles, col_tiles, s);
+    return add ? launch_conv_dl<BM, BN, 2, false, false, true>(p, grid, row_tiles, col_tiles, s)
+         : one ? launch_conv_dl<BM, BN, 1, false, false, false>(p, grid, row_tiles, col_tiles, s)
+               : launch_conv_dl<BM, BN, 2, false, false, false>(p, grid, row_tiles, col_tiles, s);
+  };
+  return wide ? go(std::integral_constant<int, 128>{}, std::integral_constant<int, 128>{})
+              : go(std::integral_constant<int, 256>{}, std::integral_constant<int, 64>{});
 }
 
 namespace {
