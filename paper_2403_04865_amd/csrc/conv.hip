@@ -112,18 +112,18 @@ __device__ __forceinline__ void lds_barrier() {
 
 // The accumulators of a tile (one 64 x 64 block per wavefront) to memory: through LDS in fp32, then whole row segments;
 // what is added on the way (the output's old value, the shortcut's gradient) is added to the unrounded sums, so every
-// stored element is rounded once; optionally the tile's channel sums for the batch statistics.
-// ADD: something may be added
-template <int BM, int BN, bool ADD = true>
+// stored element is rounded once; or (ADD = false) nothing is added and, optionally, the tile's channel sums are left for the
+// batch statistics.
+template <int BM, int BN, bool ADD>
 __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&acc)[2][2], unsigned char* smem, long long m0,
                                               int n0, int rt, int tid, int lane, int wm, int wn) {
   __syncthreads();   // every operand read is done: the stages become the copy of the tile
 
   constexpr int CH = BN / 8;
-  float ss[8], qq[8];   // this thread's 8 channels (the same in every iteration: 256 % CH == 0) summed over its rows
+  if constexpr (!ADD) {   // the tile can cross LDS as bf16 (half the LDS traffic)
+    float ss[8], qq[8];   // this thread's 8 channels (the same in every iteration: 256 % CH == 0) summed over its rows
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ss[e] = qq[e] = 0.f;
-  if (!ADD || (!p.add && !p.extra)) {   // uniform: nothing is added on the way, the tile can cross LDS as bf16 (half the LDS traffic)
+    for (int e = 0; e < 8; ++e) ss[e] = qq[e] = 0.f;
     constexpr int CLDB = BN + 8;
     bf16* Cb = reinterpret_cast<bf16*>(smem);
 #pragma unroll
@@ -162,7 +162,21 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
         __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.out + orow * p.N + n0 + ch * 8));
       }
     }
-  } else if constexpr (ADD) {
+    if (p.stat_part) {   // uniform
+      __syncthreads();   // the tile has been read out
+      float* red = reinterpret_cast<float*>(smem);   // [2][256][8]
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { red[tid * 8 + e] = ss[e]; red[2048 + tid * 8 + e] = qq[e]; }
+      __syncthreads();
+      if (tid < BN) {   // channel tid of the tile: threads ch + CH j hold its pieces, added in order
+        const int ch = tid >> 3, e = tid & 7;
+        float a = 0.f, b = 0.f;
+        for (int j = 0; j < 256 / CH; ++j) { a += red[(ch + CH * j) * 8 + e]; b += red[2048 + (ch + CH * j) * 8 + e]; }
+        p.stat_part[((long long)rt * 2) * p.N + n0 + tid] = a;
+        p.stat_part[((long long)rt * 2 + 1) * p.N + n0 + tid] = b;
+      }
+    }
+  } else {
   constexpr int CLDC = BN + 4, NIT = BM * CH / 256;
   float* Cs = reinterpret_cast<float*>(smem);
   // what is added, for all of this thread's pieces before the tile crosses LDS: asked for one piece at a time behind it, a piece
@@ -220,29 +234,10 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
       }
       bf16x8 t;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        t[e] = (bf16)f[e];
-        const float v = (float)t[e];   // the statistics are those of the stored values
-        ss[e] += v;
-        qq[e] += v * v;
-      }
+      for (int e = 0; e < 8; ++e) t[e] = (bf16)f[e];
       __builtin_nontemporal_store(t, reinterpret_cast<bf16x8*>(p.out + at));
     }
   }
-  }
-  if (p.stat_part) {   // uniform
-    __syncthreads();   // the tile has been read out
-    float* red = reinterpret_cast<float*>(smem);   // [2][256][8]
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { red[tid * 8 + e] = ss[e]; red[2048 + tid * 8 + e] = qq[e]; }
-    __syncthreads();
-    if (tid < BN) {   // channel tid of the tile: threads ch + CH j hold its pieces, added in order
-      const int ch = tid >> 3, e = tid & 7;
-      float a = 0.f, b = 0.f;
-      for (int j = 0; j < 256 / CH; ++j) { a += red[(ch + CH * j) * 8 + e]; b += red[2048 + (ch + CH * j) * 8 + e]; }
-      p.stat_part[((long long)rt * 2) * p.N + n0 + tid] = a;
-      p.stat_part[((long long)rt * 2 + 1) * p.N + n0 + tid] = b;
-    }
   }
 }
 
@@ -250,11 +245,11 @@ __device__ __forceinline__ void conv_tile_out(const ConvNT& p, const f32x16 (&ac
 // is needed (a tile of such a layer is one to eight K steps long, and what a wavefront spends per tile outside the
 // MFMAs -- some 1000 vector instructions in the general form -- is what bounds it)
 // ADD = false: nothing is added on the way out.  Where such a launch (the forwards, most input gradients) has workgroups enough it
-// has one stage: its tile then needs 40 KB of LDS at most and 104 to 114 registers, and four workgroups share a compute unit, which
+// has one stage: its tile then needs 40 KB of LDS at most and 104 to 112 registers, and four workgroups share a compute unit, which
 // hide more of each other's prologue, loads and write-out than a second stage does of a workgroup's own (ResNet18, 1024 tiles, its
 // 27 launches that are not pointwise: 3.44 ms with two stages, 2.93 this way; conv_one_stage).  Launches that add something
-// have two: what they add takes 166 registers, so three workgroups at most, and one stage measured the same over both ResNet steps.
-template <int BM, int BN, int NST, bool STEM, bool PW = false, bool ADD = true>
+// have two: what they add takes 161 registers, so three workgroups at most, and one stage measured the same over both ResNet steps.
+template <int BM, int BN, int NST, bool STEM, bool PW, bool ADD>
 __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, int row_tiles, int col_tiles) {
   constexpr int STAGE = (BM + BN) * CBK;   // bf16 elements per stage
   constexpr int WN = BN / 64, WM = 4 / WN;
@@ -391,18 +386,15 @@ __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, 
   }
 
   if (NST > 1 && nk > 0) issue(0, 0);   // a parity class may have no tap at all (1x1 kernels): its positions get zeros
-  if (NST == 3 && nk > 1) issue(1, 1);
   int st = 0;
   for (int kt = 0; kt < nk; ++kt) {
     if (NST == 1) {
       if (kt > 0) lds_barrier();   // every wavefront has read the step before
       issue(kt, 0);
     }
-    // this step's operands have landed (with three stages the next step's may be pending)
-    if (NST == 3 && kt + 1 < nk) wait_vm<AG + BG>(); else wait_vm<0>();
+    wait_vm<0>();    // this step's operands have landed ...
     lds_barrier();   // ... for every wavefront, and the stage of step kt - 1 is free
-    if (NST == 3) { if (kt + 2 < nk) issue(kt + 2, st >= 1 ? st - 1 : 2); }   // (kt + 2) % 3
-    else if (NST == 2 && kt + 1 < nk) issue(kt + 1, st ^ 1);
+    if (NST == 2 && kt + 1 < nk) issue(kt + 1, st ^ 1);
     const bf16* sb = S + st * STAGE;
 #pragma unroll
     for (int ks = 0; ks < CBK / 16; ++ks) {
@@ -419,7 +411,7 @@ __global__ void __launch_bounds__(256, NST == 1 ? 3 : 2) conv_nt_dl_k(ConvNT p, 
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
-    st = st == NST - 1 ? 0 : st + 1;
+    if (NST == 2) st ^= 1;
   }
   conv_tile_out<BM, BN, ADD>(p, acc, smem, m0, n0, rt, tid, lane, wm, wn);
 }
@@ -558,7 +550,8 @@ __global__ void __launch_bounds__(256, 2) conv_nt_halo_k(ConvNT p, int row_tiles
     step(std::integral_constant<int, 1>{}, kt + 1);
     step(std::integral_constant<int, 2>{}, kt + 2);
   }
-  conv_tile_out<BM, BN>(p, acc, smem, m0, n0, rt, tid, lane, wm, wn);
+  if (p.add || p.extra) conv_tile_out<BM, BN, true>(p, acc, smem, m0, n0, rt, tid, lane, wm, wn);
+  else conv_tile_out<BM, BN, false>(p, acc, smem, m0, n0, rt, tid, lane, wm, wn);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -647,7 +640,7 @@ __global__ void __launch_bounds__(256, 2) stem_fwd_k(ConvNT p, int tiles, int wb
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
     // (starts with a barrier: every wavefront is done with the window before the tile's copy overwrites it)
-    conv_tile_out<256, 64>(p, acc, smem, (long long)m0, 0, t, tid, lane, wave, 0);
+    conv_tile_out<256, 64, false>(p, acc, smem, (long long)m0, 0, t, tid, lane, wave, 0);
     if (!more) break;
     __syncthreads();   // the copy and the statistics have been read out
     fetch(nt);
