@@ -327,15 +327,13 @@ int colsum_slabs(long long M) {
 // Sums over slab partials, any number of results in one launch (a launch per weight, bias, gain and shift gradient is nine
 // per block of the encoder, most of them shorter than a launch).  The additions of a result have a fixed order that does not
 // depend on scheduling.  A result's kind says how its outputs and slabs are dealt to a workgroup:
-//   RED_F   1024 outputs, four neighbours per thread, which adds up to 16 slabs itself, eight loads in flight: long results of
-//           few slabs, 35,000 workgroups for three blocks of ViT-S as RED_4, whose launch alone takes 90 us (35 this way)
+//   RED_F   1024 outputs, four neighbours per thread, which adds the slabs itself: long results of up to 8 slabs, which are all in
+//           flight together.  As RED_4 five blocks' weights of ViT-S are 35,262 workgroups, 94 us at 5 slabs (9,342 and 48 this way);
+//           with 16 slabs (fc1 and fc2 of 16 tiles in float32) a RED_4 workgroup has work enough, and the two measured the same
 //   RED_4   256 outputs, four neighbours per thread (16-byte accesses), slabs dealt to 4 quarter groups, in the same order
 //   RED_1   64 outputs, otherwise the same
 //   RED_16  16 outputs, slabs dealt to 16 groups of lanes (short results of up to a thousand slabs), the 16 group sums added
 //           as a binary tree
-// FEW: some result is of kind RED_F (without that branch the others come out faster: 27.5 against 33 us per launch of the
-// 2048-tile ViT-S step, whose results have 40 slabs)
-template <bool FEW>
 __global__ void __launch_bounds__(256) reduce_partials_k(RedList L) {
   __shared__ float4 red4[4][64];
   int i = 0;
@@ -343,7 +341,7 @@ __global__ void __launch_bounds__(256) reduce_partials_k(RedList L) {
   const RedSeg sg = L.seg[i];
   const float* __restrict__ part = sg.part;
   const long long b = blockIdx.x - sg.block0;
-  if (FEW && sg.kind == RED_F) {
+  if (sg.kind == RED_F) {
     const long long o = (b * 256 + threadIdx.x) * 4;
     if (o >= sg.len) return;
     const f32x4* p = reinterpret_cast<const f32x4*>(part + o);
@@ -352,7 +350,7 @@ __global__ void __launch_bounds__(256) reduce_partials_k(RedList L) {
     f32x4 a[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < sg.slabs; s0 += 8) {   // uniform
+    for (int s0 = 0; s0 < sg.slabs; s0 += 8) {   // uniform; once (without the loop the compiler takes 202 registers)
       f32x4 v[8];
 #pragma unroll
       for (int s = 0; s < 8; ++s)
@@ -436,7 +434,7 @@ bool red_add(RedList& L, const float* part, int slabs, long long stride, long lo
   g.part = part; g.out = out; g.stride = stride; g.len = (int)len; g.slabs = slabs; g.accumulate = accumulate != 0;
   if (len < 4096 && slabs >= 64) g.kind = RED_16;
   else if (len >= 4096 && len % 4 == 0 && stride % 4 == 0 && ((uintptr_t)part & 15) == 0 && ((uintptr_t)out & 15) == 0)
-    g.kind = slabs <= 16 && len >= 65536 ? RED_F : RED_4;
+    g.kind = slabs <= 8 && len >= 65536 ? RED_F : RED_4;
   else g.kind = RED_1;
   g.block0 = L.blocks;
   const int per = g.kind == RED_16 ? 16 : g.kind == RED_F ? 1024 : g.kind == RED_4 ? 256 : 64;
@@ -447,10 +445,7 @@ bool red_add(RedList& L, const float* part, int slabs, long long stride, long lo
 
 hipError_t launch_reduce_partials(const RedList& L, hipStream_t s) {
   if (L.n == 0) return hipSuccess;
-  bool few = false;
-  for (int i = 0; i < L.n; ++i) few |= L.seg[i].kind == RED_F;
-  if (few) hipLaunchKernelGGL(reduce_partials_k<true>, dim3((unsigned)L.blocks), dim3(256), 0, s, L);
-  else hipLaunchKernelGGL(reduce_partials_k<false>, dim3((unsigned)L.blocks), dim3(256), 0, s, L);
+  hipLaunchKernelGGL(reduce_partials_k, dim3((unsigned)L.blocks), dim3(256), 0, s, L);
   return hipGetLastError();
 }
 
