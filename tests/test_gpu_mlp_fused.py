@@ -13,9 +13,9 @@ from paper_2403_04865_amd import SlideConfig, SlideLib
 pytestmark = pytest.mark.gpu
 
 
-def _run(n, chunk, recompute, seed):
+def _run(n, chunk, recompute, ratio, seed):
     g = torch.Generator(device="cuda").manual_seed(seed)
-    lib = SlideLib(SlideConfig(224, 16, 384, 2, 6, 4, 128, 1, dtype=1, recompute=recompute))
+    lib = SlideLib(SlideConfig(224, 16, 384, 2, 6, ratio, 128, 1, dtype=1, recompute=recompute))
     p = torch.randn(lib.slide_param_count(), device="cuda", generator=g).clamp_(-2, 2).mul_(0.05)
     for name, off, length in lib.param_layout():
         if name.endswith(".g"):
@@ -36,11 +36,15 @@ def _run(n, chunk, recompute, seed):
 
 
 # tiles x 197 rows: 97 = 19,109 rows, the first count above the line (a ragged last workgroup); 130 = 25,610 with chunks below
-# the line; 167 = 32,899 rows, two workgroups more than a round; 333 = a round and chunks of 33 rows less and more than it
-@pytest.mark.parametrize("n,chunk,recompute", [(97, 49, 0), (130, 65, 1), (167, 84, 0), (167, 97, 1), (333, 167, 1)])
-def test_same_bits_as_two_launches(n, chunk, recompute):
-    print(f"case {n} tiles, chunks of {chunk}, recompute {recompute}", flush=True)
-    whole, parts = _run(n, 0, recompute, n), _run(n, chunk, recompute, n)
+# the line; 167 = 32,899 rows, 131 more than a round; 333 = 65,601, two rounds and 65 rows (workgroups of three tiles), in chunks
+# of 167 and 166 tiles, 131 rows above and 66 below a round, which the kernel takes too, and of 84 and 81, which it does not.
+# MLP ratios 1, 2 and 3: 6, 12 and 18 steps of 64 hidden columns instead of 24.
+@pytest.mark.parametrize("n,chunk,recompute,ratio", [
+    (97, 49, 0, 4), (130, 65, 1, 4), (167, 84, 0, 4), (167, 97, 1, 4), (333, 167, 1, 4), (333, 84, 1, 4),
+    (97, 49, 1, 1), (333, 84, 0, 1), (333, 84, 1, 2), (167, 84, 1, 3)])
+def test_same_bits_as_two_launches(n, chunk, recompute, ratio):
+    print(f"case {n} tiles, chunks of {chunk}, recompute {recompute}, ratio {ratio}", flush=True)
+    whole, parts = _run(n, 0, recompute, ratio, n), _run(n, chunk, recompute, ratio, n)
     for a, b in zip(whole[:4], parts[:4]):
         assert np.isfinite(a).all() and np.abs(a).max() > 0
         np.testing.assert_array_equal(a, b)
