@@ -421,10 +421,14 @@ bool mlp_ok(const MlpArgs& g, int width, bool grad) {
   if (!(width == D && g.F % FS == 0 && g.F >= 3 * FS && g.F <= F_MAX && g.M > 0 && g.M < (1LL << 31))) return false;
   if (!(aligned16(g.A) && aligned16(g.W1) && aligned16(g.W2) && aligned16(g.out) && aligned16(g.h) && aligned16(g.code))) return false;
   if (!grad && !(aligned16(g.b1) && aligned16(g.b2) && aligned16(g.resid))) return false;
-  // A workgroup takes 128 rows, so this kernel pays from somewhat more than half a round of workgroups on.  us, two launches /
-  // here, forward: 0.5 rounds 60 / 72, 0.6 82 / 71, 1.1 146 / 140, 2.1 262 / 217; backward: 63 / 71, 75 / 71, 139 / 135, 224 / 225,
-  // from 3 rounds on 0.97 to 0.87 of the time.
-  return (g.M + RB - 1) / RB * 100 >= 58LL * compute_units();
+  // A workgroup takes 128 rows and comes once per compute unit, so what counts is how full the last round of them is.  Two launches /
+  // here, by rounds, us forward: 0.50 60 / 72, 0.59 85 / 71, 0.84 103 / 80, 1.00 108 / 89, 1.01 130 / 140, 1.09 136 / 143, 1.15
+  // 150 / 145, 1.20 152 / 145, 1.45 169 / 149, 2.00 205 / 167, 2.01 245 / 219, 3.01 332 / 290, 6.0 600 / 522; backward: 0.59 82 / 80,
+  // 0.63 81 / 82, 0.68 94 / 85, 1.00 116 / 96, 1.01 143 / 157, 1.15 153 / 153, 1.27 164 / 156, 1.45 172 / 162, 2.01 244 / 235,
+  // 3.01 330 / 312, 6.0 616 / 556.  The weight gradient behind the backward form takes 1 to 2 us longer than behind two launches, hence
+  // its higher line: steps of 1.2 and 1.27 rounds measured the same either way, of 1.02 and less slower here.
+  const long long tiles = (g.M + RB - 1) / RB, cus = compute_units(), rounds = (tiles + cus - 1) / cus;
+  return tiles * 100 >= (grad ? 65 : 58) * rounds * cus;
 }
 
 hipError_t launch_mlp(const MlpArgs& g, bool grad, hipStream_t s) {

@@ -1,9 +1,10 @@
-"""MLP half of a block as one kernel: the same bits as the two GEMM launches, on both sides of the line that picks it.
+"""MLP half of a block as one kernel: the same bits as the two GEMM launches, on both sides of the lines that pick it.
 
-The kernel is taken from 0.58 rounds of 128-row workgroups on (149 of them on 256 compute units, 18,945 rows), backward and in
-forwards that no backward follows; a step's own forward and fewer rows take two GEMMs.  A step in chunks runs both kinds of
-forward, so what belongs to one tile has to agree with the whole step to the last bit; parameter gradients are the same
-terms added in another order."""
+On 256 compute units its 128-row workgroups come in rounds of 256.  The kernel is taken where the last round leaves at most 0.42
+of the units idle over all rounds (backward 0.35): forwards that no backward follows from 149 workgroups on but for 257 to 296, backwards
+from 167 on but for 257 to 332.  Otherwise, and in a step's own forward, two GEMMs run.  A step in chunks runs both kinds of forward, so
+what belongs to one tile has to agree with the whole step to the last bit; parameter gradients are the same terms added in another
+order."""
 import numpy as np
 import pytest
 import torch
@@ -35,13 +36,15 @@ def _run(n, chunk, recompute, ratio, seed):
     return [t.float().cpu().numpy() for t in (loss, logits, alpha, dpix, grads)]
 
 
-# tiles x 197 rows: 97 = 19,109 rows, the first count above the line (a ragged last workgroup); 130 = 25,610 with chunks below
-# the line; 167 = 32,899 rows, 131 more than a round; 333 = 65,601, two rounds and 65 rows (workgroups of three tiles), in chunks
-# of 167 and 166 tiles, 131 rows above and 66 below a round, which the kernel takes too, and of 84 and 81, which it does not.
+# 197 rows per tile.  97 tiles: 150 workgroups, the first count above the forward's line (a ragged last one); 109: 168, above the
+# backward's; 130: 201, with chunks below both lines; 167: 258, a round and two, where neither takes it, in chunks of which it takes
+# some; 193 and 217: 298 and 334, the second round full enough for the forward and for both; 333: 513, a third round of one workgroup,
+# in chunks of 167 and 166 tiles (258 and 256 workgroups) and of 84 and 81, which it does not take.
 # MLP ratios 1, 2 and 3: 6, 12 and 18 steps of 64 hidden columns instead of 24.
 @pytest.mark.parametrize("n,chunk,recompute,ratio", [
-    (97, 49, 0, 4), (130, 65, 1, 4), (167, 84, 0, 4), (167, 97, 1, 4), (333, 167, 1, 4), (333, 84, 1, 4),
-    (97, 49, 1, 1), (333, 84, 0, 1), (333, 84, 1, 2), (167, 84, 1, 3)])
+    (97, 49, 0, 4), (109, 55, 0, 4), (130, 65, 1, 4), (167, 84, 0, 4), (167, 97, 1, 4), (193, 97, 1, 4), (217, 109, 1, 4),
+    (333, 167, 1, 4), (333, 84, 1, 4),
+    (97, 49, 1, 1), (333, 84, 0, 1), (333, 84, 1, 2), (217, 109, 1, 3)])
 def test_same_bits_as_two_launches(n, chunk, recompute, ratio):
     print(f"case {n} tiles, chunks of {chunk}, recompute {recompute}, ratio {ratio}", flush=True)
     whole, parts = _run(n, 0, recompute, ratio, n), _run(n, chunk, recompute, ratio, n)
