@@ -304,36 +304,46 @@ namespace {
 
 long long tiles_of(const GemmNT& g, int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
 
-// Whether the 256 x 192 persistent kernels fill the chip well enough.  Their workgroups come one per compute unit, so what
-// counts is how full the last of `rounds` rounds is: a round takes them the same time however full it is, the kernels here a
-// time in proportion.  us, 256 x 192 / here, M = 18,912 and N = 384 (148 tiles, 0.58 of a round): K = 384 15.3 / 17.0, 1152
-// 29.2 / 32.1, 1536 39.4 / 40.4; M = 9456, N = 768 (0.58 too): K = 768 22.3 / 22.3, 2304 52.6 / 58.4, 3072 68.8 / 84.5.  With an
-// auxiliary operand and a short contraction nothing hides the epilogue of a workgroup's last tile: residual, K = 384
-// 22.8 / 17.2, K = 768 30.1 / 25.0 and at 0.78 of a round 31.8 / 29.2, derivative at 0.77 of three rounds 54.2 / 46.4 (K = 384) and
-// 79 / 74 (768); with a long one it is as without: residual, K = 1536 46.0 / 50.1, 3072 75.9 / 88.5.  From four rounds on the
-// large kernels always win.  (Step of 40 ViT-B tiles with its K = 3072 products at 0.48 of a round there 9.04 ms, here 8.74.)
+constexpr int CUS = 256, XCU = CUS / NXCD;   // compute units, of the chip and of an XCD
+
+// Whether the 256 x 192 persistent kernels are the faster ones.  Their workgroups come one per compute unit, and an XCD takes whole
+// row tiles, so what counts is how full the last of the rounds is that the fullest XCD needs.  us, 128 x 128 here / 256 x 192:
+//   * up to 512 tiles of 128 x 128, which is one round of two per unit, those always win: QKV of 32 ViT-S tiles 12.7 / 14.1, fc2 of 96
+//     32.3 / 40.8, of 48 ViT-B tiles 53.2 / 67.2;
+//   * beyond, without an operand for the epilogue or with a long contraction, by the fill: QKV 0.59 21.9 / 23.7, 0.66 22.9 / 24.3, 0.69
+//     equal, 0.73 28.4 / 25.4, of three rounds and more 0.64 1.03 times, 0.97 1.25 times; fc2 of ViT-B 0.60 0.81 times, 0.66 1.04, 0.69 1.27;
+//   * with an operand for the epilogue (residual, derivative, table row) and K <= 768 nothing hides the epilogue of a workgroup's last
+//     tile: projection of ViT-B 0.60 of two rounds 36.3 / 50.5, 0.91 of two 51.0 / 54.0, 0.80 of three 69.0 / 76.5, 0.90 of four
+//     96.3 / 95.7, 0.96 of five 133 / 121, of ViT-S 0.84 of five 76.7 / 81.0, 0.90 of six 102.4 / 97.4, 0.96 of ten 177 / 157.
 bool large_fills(const GemmNT& g) {
-  const int cus = 256;
-  const long long t = tiles_of(g, 256, 192), rounds = (t + cus - 1) / cus;
+  if (tiles_of(g, 128, 128) <= 2 * CUS) return false;
+  const long long mt = (g.M + 255) / 256, nt = (g.N + 191) / 192, rounds = ((mt + NXCD - 1) / NXCD * nt + XCU - 1) / XCU;
+  const long long fill = mt * nt * 100 / (rounds * CUS);   // per cent
   const bool aux = g.epi == EPI_BIAS_RESID || g.epi == EPI_DGELU || g.epi == EPI_ROWTAB;
-  const double least = aux && g.K <= 768 ? 0.9 : 0.55;
-  return rounds >= 4 || (double)t >= least * (double)(rounds * cus);
+  if (aux && g.K <= 768) return rounds >= 6 || (rounds >= 4 && fill >= 95);
+  return rounds >= 3 || fill >= 67;
 }
 
+// The largest tile that gives every compute unit work, by what a unit gets: 128 x 128 from the second per unit on but for a
+// nearly empty second round (two fit a unit), 64 x 128 from the fourth 64 x 64 per unit on.  us, 64 x 64 / 64 x 128 / 128 x 128,
+// fc2 of 41 ViT-S tiles (762 of 64 x 64) 21.8 / 23.1 / 24.6, 42 (780) 28.8 / 23.2 / 24.9, 52 (243 of 128 x 128) 30.2 / 24.0 / 25.4, 56
+// (261) 33.5 / 29.0 / 26.7, 80 (372) 42.8 / 37.1 / 30.5, 88 (408) 46.2 / 46.5 / 31.7; projection of ViT-B 444 23.5 (64 x 128) / 19.1,
+// 522 25.1 / 27.8, 594 26.6 / 27.9, 744 32.0 / 29.6.  The GELU by formula keeps a workgroup's vector unit busy: 300 tiles 13.9 (64 x 128) / 15.5, 600
+// 33.1 / 34.0, 744 the same.
 template <bool LARGE>
 hipError_t go_mid(const GemmNT& g, hipStream_t s) {
-  if (tiles_of(g, 128, 128) >= 600) return go<128, 128, 2, LARGE>(g, s);
-  if (tiles_of(g, 64, 128) >= 400) return go<64, 128, 2, LARGE>(g, s);
+  const long long t = tiles_of(g, 128, 128);
+  const bool big = g.epi == EPI_BIAS_GELU ? t >= 740 : t > CUS && (t <= 2 * CUS || t >= 5 * CUS / 2);
+  if (big) return go<128, 128, 2, LARGE>(g, s);
+  if (tiles_of(g, 64, 64) > 3 * CUS) return go<64, 128, 2, LARGE>(g, s);
   if (g.K >= 2048 && tiles_of(g, 64, 64) <= 512) return go<64, 64, 4, LARGE>(g, s);
   return go<64, 64, 2, LARGE>(g, s);
 }
 
 }  // namespace
 
-// Which kernel takes a problem: the large-M kernels where their tiles fill the chip, else the largest tile that still
-// gives every compute unit work (two workgroups of 128 x 128 fit a unit, three of 64 x 128, five of 64 x 64).  Times in
-// us, 37 tiles of 197 tokens (M = 7289), 256 x 192 / 128 x 128 / 64 x 128 / 64 x 64: QKV 13.0 / 15.4 / 14.4 / 15.3,
-// projection 16.9 / 8.1 / 7.7 / 6.9, fc2 37.4 / 20.2 / 17.4 / 16.5, fc2 input gradient 20.4 / 17.4 / 17.8 / 19.2.
+// Which kernel takes a problem: the large-M kernels where they are the faster ones, else the largest tile that gives every compute
+// unit work (two workgroups of 128 x 128 fit a unit, three of 64 x 128, five of 64 x 64).
 // A contraction of thousands of columns on few tiles is a serial chain of K steps: four stages there (K = 3072, one
 // tile of the slide: 17.9 us against 23.8 with two); everywhere else two stages and more workgroups measured faster.
 // The GELU of the large-M kernel comes from a table whose last bits a formula does not give: that kernel has every problem it
