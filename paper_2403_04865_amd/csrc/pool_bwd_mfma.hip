@@ -512,10 +512,10 @@ int pool_bwd_mfma_blocks(const PoolArgs& p) {
 
 // Dp: [N][2 Mh] bf16, Hb16: [N][D] bf16, csp: [pool_bwd_mfma_blocks][Mh] fp32 partial sums of dw.  p.vub has room for two
 // bf16 copies of [V;U] (in fragment order, and transposed); p.copies: they are there already.
-// M_h = 256 does not fit the register file (2 M_h D bf16 = 384 KB) and is taken as two halves of 128 gate units, which
-// are independent given the softmax gradient of the row: each half is the M_h = 128 problem on its rows of V, U, b_V, b_U
-// and w; the second half adds its part of G to the first's.  Then Dp is [2][N][256] (half h: dpV | dpU of its units),
-// csp [2][blocks][128], and the feature copy is written twice.
+// M_h = 256 does not fit the register file (2 M_h D bf16 = 384 KB).  The gate pass takes it as two halves of 128 gate units, which
+// are independent given the softmax gradient of the row: each half is the M_h = 128 problem on its rows of V, U, b_V, b_U and w, and the
+// first writes the feature copy.  Dp is then [2][N][256] (half h: dpV | dpU of its units), csp [2][blocks][128].  G comes from one
+// pass over both halves (pool_bwd_g2_k).
 hipError_t launch_pool_bwd_mfma(const PoolArgs& p0, void* Dp, void* Hb16, float* csp, hipStream_t s) {
   constexpr int D = 384, MH = 128;
   if (!pool_bwd_mfma_ok(p0)) return hipErrorInvalidValue;

@@ -57,7 +57,8 @@ __global__ void __launch_bounds__(256) pool_cast_vu_k(const float* __restrict__ 
 // (row-major, the lanes of a load touch 32 rows, which fills a compute unit's L1 at a third of the rate: 192 KB in 5 us
 // against 2).  Half h of the gate units (units 128 h .. + 127) at out + h * 2 * FRAG: FRAG elements of [V;U], for wavefront w,
 // slice ks, matrix m the 64 lanes' eight values (unit 32 w + l % 32, column 16 ks + 8 (l / 32) ..); then, if transposed, FRAG
-// elements of its transpose (column 32 b + l % 32, unit 16 ks + 8 (l / 32) .. of V's 128 and U's 128).
+// elements of its transpose (column 32 b + l % 32, unit 16 ks + 8 (l / 32) .. of V's 128 and U's 128).  The second half starts at the same
+// place without transposes, so `out` has room for both copies in every call.
 constexpr int FRAG_D = 384, FRAG_MH = 128, FRAG = 2 * FRAG_MH * FRAG_D;
 __global__ void __launch_bounds__(256) pool_cast_frag_k(const float* __restrict__ V, const float* __restrict__ U, bf16* __restrict__ out,
                                                         int transposed, unsigned* __restrict__ ticket) {

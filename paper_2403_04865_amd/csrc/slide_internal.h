@@ -266,7 +266,10 @@ struct PoolArgs {
   float* grads;                  // flat gradient vector
   size_t ocW, ocb;               // offsets of head.W / head.b in it
   int accumulate;
-  void* vub;     // 2 x [2 Mh][D] bf16: copy of [V;U] and room for its transpose (scratch of the matrix-core kernels), may be null
+  // room for 2 x [2 Mh][D] bf16, in every call, may be null: copies of [V;U] for the matrix-core kernels.  D = 384 and M_h = 128 or two halves of
+  // 128: in fragment order, half h (copy, transpose) from element h * 2 * 256 * 384 on, the transposes only where G is wanted
+  // (pool_cast_frag_k); otherwise one row-major copy
+  void* vub;
   int use_mfma;  // bf16 path: gate projections on the matrix cores where the shape is built
   // M_h = 256 taken as two halves of 128 gate units by the register-resident forward kernel: the first half only writes
   // its partial logits (partial = 1), the second adds them (a_in) and does everything else; w_other = the other half's w
@@ -305,8 +308,7 @@ hipError_t launch_adamw(float* theta, const float* g, float* m, float* v, size_t
                         float b2, float eps, float wd, hipStream_t s);
 // matrix-core backward over the rows (bf16 path, D = 384, M_h = 128 or 256 = two halves of 128 gate units): per half
 // Dp [N][256] bf16 (dpV | dpU of its units) and csp [pool_bwd_mfma_blocks][128] partial sums of da t s (dw), half after
-// half; Hb16 [N][D] bf16 feature copy; writes p.G.  p.vub must have room for two bf16 copies of [V;U] (plain and
-// transposed).
+// half; Hb16 [N][D] bf16 feature copy; writes p.G.  p.vub: copies and transposes in fragment order, made here unless p.copies.
 bool pool_bwd_mfma_ok(const PoolArgs& p);
 int pool_bwd_mfma_blocks(const PoolArgs& p);
 hipError_t launch_pool_bwd_mfma(const PoolArgs& p, void* Dp, void* Hb16, float* csp, hipStream_t s);
