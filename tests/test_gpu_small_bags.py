@@ -15,8 +15,8 @@ BF16_TOL = 2e-2   # the bound of every bf16 parity test of the step (test_gpu_pa
 # token rows = 197 x tiles (of two tiles the gate gradients are one difference of two feature rows, no sum to average
 # its rounding).  5: every GEMM on 64 x 64 tiles, a last tile of 25 rows; 13: 64 x 64 and 64 x 128 tiles,
 # 2561 = 40 * 64 + 1 rows; 20: 3940 rows, below the 4096 from which biases start the accumulators, QKV (279 tiles of 128 x 128) and the
-# GELU derivative on 128 x 128; 33: 6501 rows, QKV on 128 x 128, GELU on 256 x 192, the others on 64 x 64.  ViT-B width: contractions
-# of 3072.
+# GELU derivative on 128 x 128, GELU on 64 x 128; 33: 6501 rows, QKV on 128 x 128, GELU on 256 x 192, its derivative on 64 x 128, the others
+# on 64 x 64.  ViT-B width: contractions of 3072.
 @pytest.mark.parametrize("name,tiles", [("small", 5), ("small", 13), ("small", 20), ("small", 33), ("full", 4)])
 def test_bf16_step_small_bags(name, tiles):
     from oracle import slide_oracle as so
