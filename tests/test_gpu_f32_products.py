@@ -1,0 +1,69 @@
+"""float32 products as bf16 terms (gemm_f32.hip) at the sizes where the kernel changes, and operands that have no such terms
+(needs an MI355X)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import gen
+
+pytestmark = pytest.mark.gpu
+
+
+# token rows = 197 x tiles, two blocks of ViT-S width.  1: 32 x 32 blocks with K over eight wavefronts (N = 384), K over four groups (N = 1152,
+# 1536), a last tile of 5 rows, and the CLS rows alone; 13: two groups for QKV (738 workgroups) and the first MLP matrix's one group (984); 18: 64 x 128
+# for the first MLP matrix (672), 128 x 128 weight gradients in 14 slabs whose last is short.
+@pytest.mark.parametrize("tiles", [1, 13, 18])
+def test_fp32_step_where_the_kernel_changes(tiles):
+    from oracle import slide_oracle as so
+    from slide_harness import GpuSlide, compare_step
+    cfg = replace(gen.CONFIGS["small"][0], layers=2)
+    ds, ws, ls = gen.SEEDS["small"]
+    prm = gen.make_params(cfg, ws, perturbed=True)
+    X = gen.make_pixels(cfg, tiles, ds)
+    lab = gen.make_label(cfg, ls)
+    print(f"case f32 products layers=2 n={tiles} dtype=0 label={lab}", flush=True)
+    out = GpuSlide(cfg, prm, 0, tiles).step(X, lab)
+    ref = so.slide_step(prm, X.astype(np.float64), lab, cfg)
+    _, pool_same = so.pool_bwd(so.pool_fwd(prm, out["H"], lab, cfg)[4])
+    errs, bad, kappa = compare_step(out, ref, 1e-4, cfg, None, pool_same)   # the bound of every fp32 parity test
+    print(f"kappa={kappa:.1f} worst:", sorted(errs.items(), key=lambda kv: -kv[1])[:6], flush=True)
+    assert not bad, bad
+
+
+# Weights near the largest float: a pixel of 2 times 3e38 is infinite (no number where two such meet with other signs), as in
+# float32 products, and is so in the rows of its tile only.  The others' products are finite: pixels that meet a zero weight stay.
+@pytest.mark.parametrize("tiles", [1, 40])
+def test_products_that_are_infinite(tiles):
+    from slide_harness import GpuSlide
+    cfg = replace(gen.CONFIGS["small"][0], layers=0)
+    ds, ws, _ = gen.SEEDS["small"]
+    prm = gen.make_params(cfg, ws, perturbed=True)
+    prm["pe.W"] = np.zeros_like(prm["pe.W"])
+    prm["pe.W"][:, 0] = 3e38     # the first channel's first pixel of every patch
+    prm["pe.W"][:, 1] = np.where(np.arange(cfg.dim) % 2, 1e-3, -2e-3)
+    prm["pos"] *= 0.0
+    prm["pe.b"] *= 0.0
+    X = np.zeros((tiles, 3, cfg.tile, cfg.tile), np.float32)
+    X[:, 0, ::cfg.patch, 1::cfg.patch] = 1.5          # finite products everywhere
+    X[0, 0, 0, 0] = 2.0                               # 6e38 in the first patch of the first tile
+    X[0, 0, 0, cfg.patch] = np.inf
+    X[0, 0, 0, 2 * cfg.patch] = np.nan
+    g = GpuSlide(cfg, prm, 0, tiles)
+    g.lib.encoder_fwd_tiles(g.to_dev(X), tiles, g.torch.zeros((tiles, cfg.dim), device=g.dev), 1)
+    g.torch.cuda.synchronize()
+    # the stream behind the patch embedding is the arena's tensor of n T rows that holds 1.5 W[:, 1] on its patch rows
+    rows = g.arena[: g.arena.numel() // 4 * 4].view(g.torch.float32)
+    want = (np.float32(1.5) * prm["pe.W"][:, 1].astype(np.float32))
+    T = cfg.tokens
+    key = g.torch.from_numpy(want).to(g.dev)
+    last = None
+    for off in range(0, rows.numel() - cfg.dim, 64):   # allocations are aligned to 64 floats, rows are 384 of them
+        if bool((rows[off:off + cfg.dim] == key).all()):
+            last = off
+            break
+    assert last is not None
+    x = rows[last:last + cfg.dim * (T - 4)].reshape(-1, cfg.dim)   # the fourth patch row of the first tile and on
+    assert bool((x == key).all())
+    first = rows[last - 3 * cfg.dim:last].reshape(3, cfg.dim).cpu().numpy()
+    assert np.isposinf(first[0]).all() and np.isposinf(first[1]).all() and np.isnan(first[2]).all()
