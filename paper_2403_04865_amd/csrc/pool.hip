@@ -180,23 +180,6 @@ __global__ void __launch_bounds__(256) pool_combine_k(PoolArgs p, int nz) {
   if (threadIdx.x == 0) scal[3] = sm[0];
 }
 
-// head.W grad = dy z^T, head.b grad = dy
-__global__ void __launch_bounds__(256) pool_head_grads_k(PoolArgs p) {
-  int D = p.D, C = p.C;
-  const float* dy = p.scal + 4 + C;
-  const float* z = p.scal + pool_z_off(C);
-  float* gW = p.grads + p.ocW;
-  float* gb = p.grads + p.ocb;
-  for (int i = threadIdx.x + blockIdx.x * 256; i < C * D; i += 256 * gridDim.x) {
-    float v = dy[i / D] * z[i % D];
-    gW[i] = p.accumulate ? gW[i] + v : v;
-  }
-  if (blockIdx.x == 0 && threadIdx.x < C) {
-    float v = dy[threadIdx.x];
-    gb[threadIdx.x] = p.accumulate ? gb[threadIdx.x] + v : v;
-  }
-}
-
 int pool_blocks(long long N) {
   long long g = (N + 15) / 16;
   if (g > 1024) g = 1024;
@@ -217,8 +200,7 @@ hipError_t launch_pool_fwd(const PoolArgs& p0, hipStream_t s) {
       if ((e = hipGetDeviceProperties(&prop, dev)) != hipSuccess) return e;
       cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
     }
-    int rb = pool_mfma_rows(p);
-    long long groups = (p.N + rb - 1) / rb;
+    long long groups = (p.N + 31) / 32;
     p.blocks = (int)(groups < cus ? groups : cus);
     if (p.blocks > 1024) p.blocks = 1024;
     e = launch_pool_gate_part_mfma(p, s);
@@ -230,11 +212,6 @@ hipError_t launch_pool_fwd(const PoolArgs& p0, hipStream_t s) {
   const int nz = (p.D + 15) / 16;
   const long long na = p.alpha ? (p.N + 1023) / 1024 : 0;
   hipLaunchKernelGGL(pool_combine_k, dim3((unsigned)(nz + na)), dim3(256), 0, s, p, nz);
-  return hipGetLastError();
-}
-
-hipError_t launch_pool_head_grads(const PoolArgs& p, hipStream_t s) {
-  hipLaunchKernelGGL(pool_head_grads_k, dim3(4), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

@@ -42,8 +42,11 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
 // Pass 1.  Same skeleton as the forward kernel with register-resident weights: persistent workgroups of 4
 // wavefronts over blocks of 32 rows, a wavefront owns 32 gate units, a thread owns 4 rows x 12 columns of every block
 // in fp32 registers (two sets), LDS holds the bf16 image of the block for the MFMA fragments.
-//   Dp  [N][2 Mh] bf16: dpV | dpU     Hb16 [N][D] bf16: the features (may be null: another half of the gate units has written them)
-//   csp [gridDim.x][Mh] fp32: this workgroup's sum of da t s (dw)
+//   Dp  [N][gridDim.y][2 Mh] bf16: dpV | dpU of each half     Hb16 [N][D] bf16: the features
+//   csp [gridDim.y][gridDim.x][Mh] fp32: this workgroup's sum of da t s (dw)
+// gridDim.y halves of Mh gate units each, which are independent given the rows' softmax gradients: the problem of Mh units on their rows of
+// V, U, b_V, b_U and w; the first writes the feature copy.  (In one launch: a bag of up to 128 blocks of rows has compute units left
+// for the second half, and a longer one no drained chip between them.)
 template <int D, int MH>
 __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* __restrict__ VU, bf16* __restrict__ Dp,
                                                        bf16* __restrict__ Hb16, float* __restrict__ csp) {
@@ -62,6 +65,12 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
   const long long groups = (p.N + RB - 1) / RB;
   constexpr float C1 = -2.0f * 1.44269504088896f, C2 = -1.44269504088896f;   // exp(-2x) and exp(-x) as exp2
   const float m = p.scal[0], Zinv = 1.0f / p.scal[1];
+  const int hf = blockIdx.y, ldp = gridDim.y * KU;
+  VU += (size_t)hf * 2 * KU * D;   // copies and transposes of a half
+  Dp += hf * KU;
+  csp += (size_t)hf * gridDim.x * MH;
+  if (hf) Hb16 = nullptr;
+  p.Vb += hf * MH; p.Ub += hf * MH; p.w += hf * MH;
 
   for (int j = tid; j < MH; j += 256) { gb[j] = C1 * p.Vb[j]; gb[MH + j] = C2 * p.Ub[j]; gb[2 * MH + j] = p.w[j]; }
   bf16x8 wv[KS], wu[KS];
@@ -207,7 +216,7 @@ __global__ void __launch_bounds__(256) pool_bwd_gate_k(PoolArgs p, const bf16* _
     for (int i = 0; i < RB * KU / 8 / 256; ++i) {
       int ch = tid + 256 * i, row = ch / (KU / 8), c16 = ch % (KU / 8);
       if (n0 + row < p.N)
-        *reinterpret_cast<u32x4*>(Dp + (n0 + row) * KU + c16 * 8) =
+        *reinterpret_cast<u32x4*>(Dp + (n0 + row) * ldp + c16 * 8) =
             *reinterpret_cast<const u32x4*>(Dps + row * LDP + c16 * 8);
     }
   };
@@ -303,6 +312,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
   long long gi = blockIdx.x;
   const long long st = gridDim.x;
   issue(gi);
+  pool_head_grads(p, (gridDim.x - 1 - blockIdx.x) * 256 + tid, gridDim.x * 256);
   {
     const float* dz = p.scal + pool_z_off(p.C) + D;
     u32x4 a[NT][KS];   // all requested before the first is waited for
@@ -402,7 +412,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g2_k(PoolArgs p, const bf16* __r
       const int ch = tid + 256 * (i % (CH / 2)), row = ch / (KU / 8), c16 = ch % (KU / 8);
       long long gr = g * RB + row;   // past the end: the last row again (never stored)
       gr = gr < p.N ? gr : p.N - 1;
-      rp[i] = *reinterpret_cast<const u32x4*>(Dp + ((i / (CH / 2)) * p.N + gr) * KU + c16 * 8);
+      rp[i] = *reinterpret_cast<const u32x4*>(Dp + gr * (2 * KU) + (i / (CH / 2)) * KU + c16 * 8);
     } else if (tid < RB) {
       const long long gr = g * RB + tid;
       ra = p.a[gr < p.N ? gr : p.N - 1];
@@ -419,6 +429,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g2_k(PoolArgs p, const bf16* __r
   long long gi = blockIdx.x >> 1;
   const long long st = gridDim.x >> 1;
   static_for<0, CH + 1>([&](auto ic) __attribute__((always_inline)) { issue_one(gi, ic); });
+  pool_head_grads(p, (gridDim.x - 1 - blockIdx.x) * 256 + tid, gridDim.x * 256);
   bf16x8 wt[NT][KS];
   float dzr[NT];
   {
@@ -512,10 +523,8 @@ int pool_bwd_mfma_blocks(const PoolArgs& p) {
 
 // Dp: [N][2 Mh] bf16, Hb16: [N][D] bf16, csp: [pool_bwd_mfma_blocks][Mh] fp32 partial sums of dw.  p.vub has room for two
 // bf16 copies of [V;U] (in fragment order, and transposed); p.copies: they are there already.
-// M_h = 256 does not fit the register file (2 M_h D bf16 = 384 KB).  The gate pass takes it as two halves of 128 gate units, which
-// are independent given the softmax gradient of the row: each half is the M_h = 128 problem on its rows of V, U, b_V, b_U and w, and the
-// first writes the feature copy.  Dp is then [2][N][256] (half h: dpV | dpU of its units), csp [2][blocks][128].  G comes from one
-// pass over both halves (pool_bwd_g2_k).
+// M_h = 256 does not fit the register file (2 M_h D bf16 = 384 KB): the gate pass takes two halves of 128 gate units, Dp is [N][2][256] (dpV |
+// dpU of a half's units), csp [2][blocks][128].  G comes from one pass over both halves (pool_bwd_g2_k).
 hipError_t launch_pool_bwd_mfma(const PoolArgs& p0, void* Dp, void* Hb16, float* csp, hipStream_t s) {
   constexpr int D = 384, MH = 128;
   if (!pool_bwd_mfma_ok(p0)) return hipErrorInvalidValue;
@@ -523,22 +532,13 @@ hipError_t launch_pool_bwd_mfma(const PoolArgs& p0, void* Dp, void* Hb16, float*
   const int halves = p0.Mh / MH;
   hipError_t e;
   if (!p0.copies && (e = launch_pool_cast_frag(p0, true, nullptr, s)) != hipSuccess) return e;
-  for (int h = 0; h < halves; ++h) {
-    PoolArgs p = p0;
-    p.Mh = MH;
-    p.VW = p0.VW + (size_t)h * MH * D; p.UW = p0.UW + (size_t)h * MH * D;
-    p.Vb = p0.Vb + h * MH; p.Ub = p0.Ub + h * MH; p.w = p0.w + h * MH;
-    bf16* vu = (bf16*)p0.vub + (size_t)h * 2 * (2 * MH * D);
-    bf16* dp = (bf16*)Dp + (size_t)h * p0.N * 2 * MH;
-    {
-      auto kern = pool_bwd_gate_k<D, MH>;
-      size_t lds = (size_t)2 * 32 * (D + 8) * 2 + (size_t)32 * (2 * MH + 8) * 2 + (size_t)3 * MH * 4 + 32 * 4 + 2 * D * 4;
-      if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
-        return e;
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, p, (const bf16*)vu, dp, h == 0 ? (bf16*)Hb16 : nullptr,
-                         csp + (size_t)h * blocks * MH);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+  {
+    auto kern = pool_bwd_gate_k<D, MH>;
+    size_t lds = (size_t)2 * 32 * (D + 8) * 2 + (size_t)32 * (2 * MH + 8) * 2 + (size_t)3 * MH * 4 + 32 * 4 + 2 * D * 4;
+    if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
+      return e;
+    hipLaunchKernelGGL(kern, dim3(blocks, halves), dim3(256), lds, s, p0, (const bf16*)p0.vub, (bf16*)Dp, (bf16*)Hb16, csp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (halves == 1) {
     const size_t lds = (size_t)2 * 32 * (2 * MH + 8) * 2 + (size_t)2 * 32 * 4;

@@ -249,6 +249,7 @@ __global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __r
   const bool ok = n < p.N;
   const int d = blockIdx.y * 32 + li, dc = d < D ? d : D - 1;
   const float* drow = Dp + (ok ? n : p.N - 1) * K;
+  pool_head_grads(p, ((gridDim.x - 1 - blockIdx.x) * gridDim.y + blockIdx.y) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
   f32x16 acc = zero16();
   for (int c0 = wave; c0 < nc; c0 += 4 * UG) {
     f32x4 g[UG];
@@ -384,6 +385,7 @@ __global__ void __launch_bounds__(256) pool_wide_g_k(PoolArgs p, const float* __
   extern __shared__ float dl[];   // [WR][2 Mh]
   const int D = p.D, Mh = p.Mh;
   const long long n0 = (long long)blockIdx.x * WR;
+  pool_head_grads(p, ((gridDim.x - 1 - blockIdx.x) * gridDim.y + blockIdx.y) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
   for (int i = threadIdx.x; i < WR * 2 * Mh; i += 256) dl[i] = n0 * 2 * Mh + i < p.N * 2 * Mh ? Dp[n0 * 2 * Mh + i] : 0.f;
   __syncthreads();
   const int d = blockIdx.y * 256 + threadIdx.x;
@@ -440,6 +442,11 @@ hipError_t go_wide_gate(const PoolArgs& p, float* TS, hipStream_t s) {
 
 }  // namespace
 
+hipError_t launch_pool_softmax_part(const PoolArgs& p, const float* part, int parts, hipStream_t s) {
+  hipLaunchKernelGGL((pool_softmax_part_k<16, false>), dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, part, parts);
+  return hipGetLastError();
+}
+
 hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
   if (wide(p)) {
     if ((size_t)p.N * 2 * p.Mh > p.a_room) return hipErrorInvalidValue;
@@ -453,11 +460,10 @@ hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
   if ((size_t)p.N > p.a_room) return hipErrorInvalidValue;
   hipError_t e = vec_ok(p) ? go_gate<true, false>(p, p.a_tmp, nullptr, parts, s) : go_gate<false, false>(p, p.a_tmp, nullptr, parts, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((pool_softmax_part_k<16, false>), dim3(p.blocks), dim3(256), (size_t)p.D * 8, s, p, p.a_tmp, parts);
-  return hipGetLastError();
+  return launch_pool_softmax_part(p, p.a_tmp, parts, s);
 }
 
-// Dp: [N][2 M_h]; dwp: [ceil(N / 32)][M_h] partial sums of dw; writes p.G
+// Dp: [N][2 M_h]; dwp: [ceil(N / 32)][M_h] partial sums of dw; writes p.G and the head's gradients
 hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s) {
   if (wide(p)) {
     // t and s once more: an earlier backward over the same forward has written over them

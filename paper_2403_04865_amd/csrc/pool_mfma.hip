@@ -6,15 +6,13 @@
 // unrounded features: the softmax over tiles is a two-level online reduction (every workgroup keeps a running
 // max, sum and weighted feature sum over its row blocks; one workgroup combines them afterwards).
 // Two kernels:
-//   * pool_gate_part_reg_k (D = 384, M_h = 128; M_h = 256 as two passes over halves of the gate units above
-//     32768 rows): the main one.  One persistent workgroup (4 wavefronts) per compute unit; the bf16 copy of
+//   * pool_gate_part_reg_k (D = 384, M_h = 128; M_h = 256 as two halves of the gate units): the main one.  One persistent workgroup (4 wavefronts) per compute unit; the bf16 copy of
 //     [V;U] is 192 kB, which is what the accumulation half of a compute unit's register file holds, so every
 //     wavefront keeps the fragments of its 32 gate units in registers for the whole kernel and the only traffic is
 //     the feature rows, each read from HBM exactly once into fp32 registers (a bf16 image in LDS feeds the MFMAs;
 //     the weighted feature sum is taken from the unrounded registers).  The gate arithmetic of block i - 1 is
 //     issued between the MFMAs of block i.
-//   * pool_gate_part_mfma_k (the other built shapes: M_h = 256 below 32768 rows, D = 768): rows in LDS as fp32,
-//     [V;U] streams from L2 through a double-buffered LDS ring, BK columns per step.
+//   * pool_gate_part_mfma_k (the other built shapes, D = 768): rows in LDS as fp32, [V;U] streams from L2 through a double-buffered LDS ring, BK columns per step.
 //   Operands are passed swapped (weights first): a lane then owns one feature row and 16 gate units per
 //   accumulator, so the sum over gate units is in-lane plus one exchange between the lane halves.
 #include "slide_internal.h"
@@ -87,10 +85,10 @@ __global__ void __launch_bounds__(256) pool_cast_frag_k(const float* __restrict_
   *reinterpret_cast<bf16x8*>(out + (size_t)h * 2 * FRAG + (size_t)r * 8) = t;
 }
 
-template <int RB, int MH, int BK>
+constexpr int RB = 32;   // rows per block
+template <int MH, int BK>
 struct PoolCfg {
-  static constexpr int RG = RB / 32;          // row groups of 32 (wavefronts along the rows)
-  static constexpr int JG = 4 / RG;           // wavefronts along the gate units
+  static constexpr int JG = 4;                // wavefronts along the gate units
   static constexpr int JW = MH / JG;          // gate units per wavefront
   static constexpr int NBK = JW / 32;         // 32 x 32 accumulators per wavefront for V (and as many for U)
   static constexpr int LDW = BK + 8;          // LDS row stride of the weight ring (bf16)
@@ -102,9 +100,9 @@ struct PoolCfg {
   }
 };
 
-template <int RB, int MH, int BK, int HCH>   // HCH: float4 chunks of the row block per thread (RB * D / 1024)
+template <int MH, int BK, int HCH>   // HCH: float4 chunks of the row block per thread (RB * D / 1024)
 __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const bf16* __restrict__ VU) {
-  using C = PoolCfg<RB, MH, BK>;
+  using C = PoolCfg<MH, BK>;
   constexpr int LDW = C::LDW, NBK = C::NBK, JW = C::JW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int D = p.D, LDH = D + 4;
@@ -118,7 +116,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const b
   double* run_l = reinterpret_cast<double*>(misc + 2);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = wave % C::RG, jg = wave / C::RG;
+  const int jg = wave;
   const int li = lane & 31, h2 = lane >> 5;
   const int nk = D / BK;
   const float* H = p.H;
@@ -188,7 +186,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const b
       stash_w(buf);
       issue_w(kt + 1 < nk ? kt + 1 : 0);
       __syncthreads();   // ring stage (and, at kt == 0, the feature block) visible; the other stage is free
-      const float* hrow = Hs + (rg * 32 + li) * LDH + kt * BK + h2 * 8;
+      const float* hrow = Hs + li * LDH + kt * BK + h2 * 8;
       const bf16* wbase = Ws + (size_t)buf * 2 * MH * LDW + h2 * 8;
 #pragma unroll
       for (int ks = 0; ks < BK / 16; ++ks) {
@@ -203,7 +201,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const b
         }
       }
     }
-    // gate: lane = feature row rg * 32 + li; accumulator register r = gate unit (r / 4) * 8 + h2 * 4 + r % 4 of its block
+    // gate: lane = feature row li; accumulator register r = gate unit (r / 4) * 8 + h2 * 4 + r % 4 of its block
     float part = 0.f;
 #pragma unroll
     for (int b = 0; b < NBK; ++b)
@@ -223,7 +221,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const b
         }
       }
     part += __shfl_xor(part, 32, 64);
-    if (h2 == 0) apart[jg * RB + rg * 32 + li] = part;
+    if (h2 == 0) apart[jg * RB + li] = part;
     __syncthreads();
     if (tid < 64) {   // wavefront 0: logits of the block, online softmax state
       float a = 0.f;
@@ -281,7 +279,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const b
 constexpr int POOL_REG_NL = 4;   // weight slices read from LDS (the rest stay in registers)
 template <int D, int MH>
 __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf16* __restrict__ VU) {
-  constexpr int RB = 32, LDB = D + 8, KS = D / 16, CJ = D / 128, NR = 4 * CJ, EARLY = CJ;
+  constexpr int LDB = D + 8, KS = D / 16, CJ = D / 128, NR = 4 * CJ, EARLY = CJ;
   constexpr int NL = POOL_REG_NL, KR = KS - NL;   // the last NL slices of the weights are read from LDS
   static_assert(MH == 128 && D % 128 == 0 && KS % 3 == 0 && KS / 3 * 2 == 16 && NR - EARLY <= KS && EARLY % CJ == 0, "shape");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -295,6 +293,11 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   const float* H = p.H;
   const long long groups = (p.N + RB - 1) / RB;
   constexpr float C1 = -2.0f * 1.44269504088896f, C2 = -1.44269504088896f;   // exp(-2x) and exp(-x) as exp2
+  if (const int hf = blockIdx.y) {   // the second half of the gate units beside the first
+    VU += (size_t)hf * 2 * FRAG;
+    p.Vb += hf * MH; p.Ub += hf * MH; p.w += hf * MH;
+    p.a += hf * p.N;
+  }
 
   for (int j = tid; j < MH; j += 256) { gb[j] = C1 * p.Vb[j]; gb[MH + j] = C2 * p.Ub[j]; gb[2 * MH + j] = p.w[j]; }
   // this wavefront's gate units 32 wave .. + 31 of V and of U: slices 0 .. KR - 1 of their weights stay in the
@@ -540,6 +543,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
     iter(IC<4>{}, it); if (++it > nblk) break;
     iter(IC<5>{}, it); if (++it > nblk) break;
   }
+  if (p.partial) return;
   // column sums over the 8 row groups (the bf16 images are dead: every wavefront is past the last barrier (B))
   double* zred = reinterpret_cast<double*>(smem);   // [8][D]
   static_assert(8 * D * 8 <= 2 * RB * LDB * 2, "reduction buffer");
@@ -560,24 +564,31 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   }
 }
 
-hipError_t go_reg(const PoolArgs& p, const bf16* vu, hipStream_t s) {
+hipError_t go_reg(const PoolArgs& p, const bf16* vu, hipStream_t s, int halves = 1) {
   constexpr int D = FRAG_D, MH = FRAG_MH;
   auto kern = pool_gate_part_reg_k<D, MH>;
   size_t lds = (size_t)2 * 32 * (D + 8) * 2 + (size_t)4 * POOL_REG_NL * 2 * 64 * 16 + (size_t)3 * MH * 4 + 4 * 32 * 4;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(256), lds, s, p, vu);
+  hipLaunchKernelGGL(kern, dim3(p.blocks, halves), dim3(256), lds, s, p, vu);
   return hipGetLastError();
 }
 
 // M_h = 256 as two passes of the M_h = 128 kernel over the rows (the features are read twice, against the weights
-// streaming from L2 for every block of rows in the one-pass kernel): pass 1 leaves the partial logits of gate units
-// 0..127 in a_tmp, pass 2 adds those of units 128..255 and does the softmax partials.
-hipError_t go_reg_halves(const PoolArgs& p0, hipStream_t s) {
+// streaming from L2 for every block of rows in a one-pass kernel, which took the calls below 32,768 rows before: serving 16,384 rows 36.8
+// us, this way 31.0): pass 1 leaves the partial logits of gate units 0..127 in a_tmp, pass 2 adds those of units 128..255 and does the
+// softmax partials.  Where both fit the chip side by side (up to 4,096 rows) they are one launch that leaves both halves' partial
+// logits, and the softmax partials one of their own: serving 1,037 rows 29.6 -> 21.9 us, 4,096 28.9 -> 23.0.
+hipError_t go_reg_halves(PoolArgs& p0, hipStream_t s) {
   constexpr int MH = FRAG_MH;
-  if (!p0.a_tmp) return hipErrorInvalidValue;
   PoolArgs p = p0;
   p.Mh = MH; p.partial = 1; p.a_in = nullptr; p.w_other = nullptr; p.a = p0.a_tmp;
+  if (p.N <= 4096 && (size_t)p.N * 2 <= p.a_room) {
+    hipError_t e = go_reg(p, (const bf16*)p0.vub, s, 2);
+    if (e != hipSuccess) return e;
+    p0.blocks = pool_blocks(p0.N);
+    return launch_pool_softmax_part(p0, p0.a_tmp, 2, s);
+  }
   hipError_t e = go_reg(p, (const bf16*)p0.vub, s);
   if (e != hipSuccess) return e;
   p = p0;
@@ -587,10 +598,10 @@ hipError_t go_reg_halves(const PoolArgs& p0, hipStream_t s) {
   return go_reg(p, (const bf16*)p0.vub + 2 * FRAG, s);
 }
 
-template <int RB, int MH, int BK, int HCH>
+template <int MH, int BK, int HCH>
 hipError_t go(const PoolArgs& p, hipStream_t s) {
-  using C = PoolCfg<RB, MH, BK>;
-  auto kern = pool_gate_part_mfma_k<RB, MH, BK, HCH>;
+  using C = PoolCfg<MH, BK>;
+  auto kern = pool_gate_part_mfma_k<MH, BK, HCH>;
   size_t lds = C::lds_bytes(p.D);
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -609,15 +620,9 @@ bool pool_mfma_ok(const PoolArgs& p) {
          ((uintptr_t)p.H & 15) == 0 && ((uintptr_t)p.vub & 15) == 0;
 }
 
-// above this many rows M_h = 256 goes through the register-resident kernel in two passes (below it the launches cost
-// more than the weights streaming from L2)
-static bool pool_two_pass(const PoolArgs& p) { return p.D == 384 && p.Mh == 256 && p.N >= 32768 && p.a_tmp != nullptr; }
-
-int pool_mfma_rows(const PoolArgs& p) { return (p.D == 384 && p.Mh == 256 && !pool_two_pass(p)) ? 64 : 32; }
-
 // whether the forward leaves the weights in fragment order in p.vub (with their transposes if p.G is set)
 bool pool_frag_fwd(const PoolArgs& p) {
-  return p.use_mfma && pool_mfma_ok(p) && p.D == FRAG_D && (p.Mh == FRAG_MH || pool_two_pass(p));
+  return p.use_mfma && pool_mfma_ok(p) && p.D == FRAG_D;
 }
 
 hipError_t launch_pool_cast_frag(const PoolArgs& p, bool transposed, unsigned* ticket, hipStream_t s) {
@@ -626,15 +631,14 @@ hipError_t launch_pool_cast_frag(const PoolArgs& p, bool transposed, unsigned* t
   return hipGetLastError();
 }
 
-hipError_t launch_pool_gate_part_mfma(const PoolArgs& p, hipStream_t s) {
+hipError_t launch_pool_gate_part_mfma(PoolArgs& p, hipStream_t s) {
   if (pool_frag_fwd(p)) {
     hipError_t e = launch_pool_cast_frag(p, p.G != nullptr, p.ticket, s);
     if (e != hipSuccess) return e;
     return p.Mh == FRAG_MH ? go_reg(p, (const bf16*)p.vub, s) : go_reg_halves(p, s);
   }
-  if (p.D == 384 && p.Mh == 256) return go<64, 256, 16, 24>(p, s);
-  if (p.D == 768 && p.Mh == 128) return go<32, 128, 32, 24>(p, s);
-  if (p.D == 768 && p.Mh == 256) return go<32, 256, 16, 24>(p, s);
+  if (p.D == 768 && p.Mh == 128) return go<128, 32, 24>(p, s);
+  if (p.D == 768 && p.Mh == 256) return go<256, 16, 24>(p, s);
   return hipErrorInvalidValue;
 }
 

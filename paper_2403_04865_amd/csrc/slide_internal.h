@@ -280,16 +280,29 @@ struct PoolArgs {
   int fwd_only;       // no backward will read the scalars behind the logits
   unsigned* ticket;   // arrival counter of the combine kernel's workgroups, cleared by the kernels of stage 1
 };
+// head.W grad = dy z^T, head.b grad = dy: elements i, i + stride, ...; rides in the kernels that write G (as a launch of its own 4.5 us of
+// 262 at 45,056 rows)
+__device__ __forceinline__ void pool_head_grads(const PoolArgs& p, int i, int stride) {
+  const int D = p.D, C = p.C;
+  const float* dy = p.scal + 4 + C;
+  const float* z = p.scal + pool_z_off(C);
+  for (; i < C * (D + 1); i += stride) {
+    const bool w = i < C * D;
+    const float v = w ? dy[i / D] * z[i % D] : dy[i - C * D];
+    float* g = p.grads + (w ? p.ocW + i : p.ocb + (i - C * D));
+    *g = p.accumulate ? *g + v : v;
+  }
+}
 int pool_blocks(long long N);
 bool pool_mfma_ok(const PoolArgs& p);
 bool pool_frag_fwd(const PoolArgs& p);
 hipError_t launch_pool_cast_frag(const PoolArgs& p, bool transposed, unsigned* ticket, hipStream_t s);
-int pool_mfma_rows(const PoolArgs& p);
-hipError_t launch_pool_gate_part_mfma(const PoolArgs& p, hipStream_t s);
+hipError_t launch_pool_gate_part_mfma(PoolArgs& p, hipStream_t s);   // may set p.blocks
+// softmax partials (p.blocks of them) from `parts` partial logits of every row, part[i][n]
+hipError_t launch_pool_softmax_part(const PoolArgs& p, const float* part, int parts, hipStream_t s);
 hipError_t launch_pool_fwd(const PoolArgs& p, hipStream_t s);
 hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s);
 hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s);
-hipError_t launch_pool_head_grads(const PoolArgs& p, hipStream_t s);
 
 // fp32 lane of the CLS rows (bf16 path, cls_lane.hip)
 bool cls_lane_ok(int D, int F);
@@ -306,9 +319,9 @@ hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda
 // theta, m, v updated in place (fp32, n elements); step counts from 1
 hipError_t launch_adamw(float* theta, const float* g, float* m, float* v, size_t n, long long step, float lr, float b1,
                         float b2, float eps, float wd, hipStream_t s);
-// matrix-core backward over the rows (bf16 path, D = 384, M_h = 128 or 256 = two halves of 128 gate units): per half
-// Dp [N][256] bf16 (dpV | dpU of its units) and csp [pool_bwd_mfma_blocks][128] partial sums of da t s (dw), half after
-// half; Hb16 [N][D] bf16 feature copy; writes p.G.  p.vub: copies and transposes in fragment order, made here unless p.copies.
+// matrix-core backward over the rows (bf16 path, D = 384, M_h = 128 or 256 = two halves of 128 gate units): Dp [N][halves][256] bf16
+// (dpV | dpU of a half's units), per half csp [pool_bwd_mfma_blocks][128] partial sums of da t s (dw); Hb16 [N][D] bf16 feature
+// copy; writes p.G and the head's gradients.  p.vub: copies and transposes in fragment order, made here unless p.copies.
 bool pool_bwd_mfma_ok(const PoolArgs& p);
 int pool_bwd_mfma_blocks(const PoolArgs& p);
 hipError_t launch_pool_bwd_mfma(const PoolArgs& p, void* Dp, void* Hb16, float* csp, hipStream_t s);

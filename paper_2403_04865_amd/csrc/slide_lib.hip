@@ -323,12 +323,13 @@ void run_group(Sums& q) {
   }
 }
 
+struct TnOut { float *out, *bias; };
+
 // dW (+)= A^T B through split partials; optionally also db (+)= column sums of A
 void gemm_tn(Sums& q, const void* A, long long lda, const void* B, long long ldb, long long M, int N1, int N2, float* out,
-             int accumulate, float* bias_out = nullptr, int dt_override = -1, float* out2 = nullptr, float* bias_out2 = nullptr,
-             bool wait = false) {
-  // wait: may run together with others of its kind at run_group (no out2 then)
-  // out2 / bias_out2: the result rows N1/2 .. N1-1 (and their column sums) belong to a second tensor
+             int accumulate, float* bias_out = nullptr, int dt_override = -1, bool wait = false, const TnOut* outs = nullptr, int nout = 1) {
+  // wait: may run together with others of its kind at run_group
+  // outs (then neither out, bias_out nor wait): the result's rows belong to nout tensors of N1 / nout rows each
   Run& r = q.r;
   GemmTN g;
   int dt = dt_override >= 0 ? dt_override : r.c->dt;
@@ -349,28 +350,22 @@ void gemm_tn(Sums& q, const void* A, long long lda, const void* B, long long ldb
   int bs = (dt == DT_BF16 && r.c->use_mfma) ? gemm_tn_big_slabs(g, fit > 256 ? 256 : (int)fit) : 0;
   if (bs) { g.slabs = bs; g.big = 1; }
   else g.slabs = gemm_tn_pick_slabs(dt, g, r.c->use_mfma, fit > 64 ? 64 : (int)fit);
-  bool fused = bias_out && gemm_tn_fuses_colsum(dt, g, r.c->use_mfma);
-  if (bias_out && !fused) {
-    if (bias_out2) {
-      colsum(q, dt, A, lda, id, M, N1 / 2, bias_out, accumulate);
-      colsum(q, dt, (const char*)A + (size_t)(N1 / 2) * elem_size(dt), lda, id, M, N1 / 2, bias_out2, accumulate);
-    } else {
-      colsum(q, dt, A, lda, id, M, N1, bias_out, accumulate);
-    }
-  }
-  const long long len = (long long)N1 * N2, len1 = out2 ? len / 2 : len;
+  const TnOut one{out, bias_out};
+  if (!outs) { outs = &one; nout = 1; }
+  const int n1 = N1 / nout;
+  const bool bias = outs[0].bias != nullptr, fused = bias && gemm_tn_fuses_colsum(dt, g, r.c->use_mfma);
+  for (int i = 0; bias && !fused && i < nout; ++i)
+    colsum(q, dt, (const char*)A + (size_t)i * n1 * elem_size(dt), lda, id, M, n1, outs[i].bias, accumulate);
+  const long long len = (long long)N1 * N2, len1 = (long long)n1 * N2;
   float* part = q.room((size_t)g.slabs * (len + (fused ? N1 : 0)));
   g.part = part;
   if (fused) g.cs_part = part + (size_t)g.slabs * len;
   size_t e = elem_size(dt);
   launch(r, K_GEMM_TN, 2.0 * M * N1 * N2, (double)M * (N1 + N2) * e + (double)g.slabs * N1 * N2 * 4,
          [&] { return launch_gemm_tn(dt, g, r.c->use_mfma, r.s); });
-  q.add(part, g.slabs, len, len1, out, accumulate);
-  if (out2) q.add(part + len1, g.slabs, len, len1, out2, accumulate);
-  if (fused) {
-    const int n1 = bias_out2 ? N1 / 2 : N1;
-    q.add(g.cs_part, g.slabs, N1, n1, bias_out, accumulate);
-    if (bias_out2) q.add(g.cs_part + n1, g.slabs, N1, n1, bias_out2, accumulate);
+  for (int i = 0; i < nout; ++i) {
+    q.add(part + i * len1, g.slabs, len, len1, outs[i].out, accumulate);
+    if (fused) q.add(g.cs_part + i * n1, g.slabs, N1, n1, outs[i].bias, accumulate);
   }
 }
 
@@ -679,8 +674,8 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
         g.epi = EPI_DGELU; g.pre = m; g.ldpre = F; g.out = dm; g.ldc = F;
         gemm_nt(r, g);
       }
-      gemm_tn(q, dxAt, TD, a, F, n, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, nullptr, nullptr, true);
-      gemm_tn(q, dm, F, u2, D, n, F, D, G + o.fc1W, accumulate, G + o.fc1b, -1, nullptr, nullptr, true);
+      gemm_tn(q, dxAt, TD, a, F, n, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, true);
+      gemm_tn(q, dm, F, u2, D, n, F, D, G + o.fc1W, accumulate, G + o.fc1b, -1, true);
       {
         GemmNT g{};
         g.A = dm; g.lda = F; g.B = weight_t(c, wi + 2); g.ldb = F; g.M = n; g.N = D; g.K = F;
@@ -688,7 +683,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
         gemm_nt(r, g);
       }
       ln_bwd(q, xmid, TD, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, TD, n, accumulate);
-      gemm_tn(q, dxBt, TD, O, TD, n, D, D, G + o.projW, accumulate, G + o.projb, -1, nullptr, nullptr, true);
+      gemm_tn(q, dxBt, TD, O, TD, n, D, D, G + o.projW, accumulate, G + o.projb, -1, true);
       {
         GemmNT g{};
         g.A = dxBt; g.lda = TD; g.B = weight_t(c, wi + 1); g.ldb = D; g.M = n; g.N = D; g.K = D;
@@ -697,7 +692,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       }
       launch(r, K_ATTN_BWD, 10.0 * n * c->H * (double)T * c->dh, (double)M * 7 * D * e,
              [&] { return launch_attn_bwd(dt, qkv, O, lse, du, dqkv, n, T, c->H, c->dh, c->use_mfma, s, true, (float*)(ar + y.e_dl)); });
-      gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb, -1, nullptr, nullptr, true);
+      gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb, -1, true);
       {
         GemmNT g{};
         g.A = dqkv; g.lda = 3 * D; g.B = weight_t(c, wi + 0); g.ldb = 3 * D; g.M = M; g.N = D; g.K = 3 * D;
@@ -714,7 +709,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
     mg.A = dxAt; mg.W1 = weight_t(c, wi + 3); mg.W2 = weight_t(c, wi + 2); mg.out = du; mg.h = dm; mg.code = m; mg.M = M; mg.F = F;
     // fc2's weight gradient first: where the partial sums that wait leave it no room they are added up before its launch, and behind
     // the 2.5 GB that the fused kernel moves they would come from memory (2048 ViT-S tiles: 41 us a launch instead of 28)
-    gemm_tn(q, dxAt, D, a, F, M, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, nullptr, nullptr, true);
+    gemm_tn(q, dxAt, D, a, F, M, D, F, G + o.fc2W, accumulate, G + o.fc2b, -1, true);
     if (!mlp_fused(r, mg, true)) {
       GemmNT g{};
       g.A = dxAt; g.lda = D; g.B = weight_t(c, wi + 3); g.ldb = D; g.M = M; g.N = F; g.K = D;
@@ -726,9 +721,9 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       gemm_nt(r, g);
     }
     ln_bwd(q, xmid, D, du, D, o.ln2g, o.ln2b, dxA, dxB, dxBt, D, M, accumulate);
-    gemm_tn(q, dm, F, u2, D, M, F, D, G + o.fc1W, accumulate, G + o.fc1b, -1, nullptr, nullptr, true);
+    gemm_tn(q, dm, F, u2, D, M, F, D, G + o.fc1W, accumulate, G + o.fc1b, -1, true);
     // ---- attention half: x_mid = x_in + attn(LN1(x_in)) Wo^T + bo
-    gemm_tn(q, dxBt, D, O, D, M, D, D, G + o.projW, accumulate, G + o.projb, -1, nullptr, nullptr, true);
+    gemm_tn(q, dxBt, D, O, D, M, D, D, G + o.projW, accumulate, G + o.projb, -1, true);
     {
       GemmNT g{};
       g.A = dxBt; g.lda = D; g.B = weight_t(c, wi + 1); g.ldb = D; g.M = M; g.N = D; g.K = D;
@@ -743,7 +738,7 @@ int enc_bwd(slide_ctx* c, const void* dfeats, long long n, int accumulate, void*
       g.epi = EPI_PLAIN; g.out = du; g.ldc = D;
       gemm_nt(r, g);
     }
-    gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb, -1, nullptr, nullptr, true);
+    gemm_tn(q, dqkv, 3 * D, u1, D, M, 3 * D, D, G + o.qkvW, accumulate, G + o.qkvb, -1, true);
     run_group(q);   // LN1's backward overwrites dxA
     ln_bwd(q, xin, D, du, D, o.ln1g, o.ln1b, dxB, dxA, dxAt, D, M, accumulate);
   }
@@ -826,20 +821,20 @@ int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
   // the matrix-core path keeps [dpV dpU] and a feature copy as bf16 in the room of the fp32 [N, 3 Mh] array; db_V and
   // db_U come out of the weight-gradient GEMM as column sums of its first operand
   if (pool_bwd_mfma_ok(p) && (size_t)(2 * Mh + D) * 2 <= (size_t)3 * Mh * 4) {
-    // M_h = 256 runs as two halves of 128 gate units: Dp is then [2][N][256], the dw partials [2][blocks][128]
+    // M_h = 256 runs as two halves of 128 gate units: Dp is [N][2][dpV dpU], the dw partials [2][blocks][128]
     const int MHK = 128, halves = Mh / MHK;
     char* Hb16 = Dp + (size_t)N * 2 * Mh * 2;
     int blocks = pool_bwd_mfma_blocks(p);
     float* csw = q.room((size_t)blocks * Mh);
     launch(r, K_POOL_BWD, 12.0 * N * D * Mh, 2.0 * N * D * 4, [&] { return launch_pool_bwd_mfma(p, Dp, Hb16, csw, s); });
-    launch(r, K_ELEMWISE, 0, 0, [&] { return launch_pool_head_grads(p, s); });
-    for (int h = 0; h < halves; ++h)
-      q.add(csw + (size_t)h * blocks * MHK, blocks, MHK, MHK, c->grads + c->o_w + h * MHK, accumulate);
+    TnOut outs[4];
     for (int h = 0; h < halves; ++h) {
+      q.add(csw + (size_t)h * blocks * MHK, blocks, MHK, MHK, c->grads + c->o_w + h * MHK, accumulate);
       const size_t ow = (size_t)h * MHK * D;
-      gemm_tn(q, Dp + (size_t)h * N * 2 * MHK * 2, 2 * MHK, Hb16, D, N, 2 * MHK, D, c->grads + c->o_VW + ow, accumulate,
-              c->grads + c->o_Vb + h * MHK, DT_BF16, c->grads + c->o_UW + ow, c->grads + c->o_Ub + h * MHK);
+      outs[2 * h] = {c->grads + c->o_VW + ow, c->grads + c->o_Vb + h * MHK};
+      outs[2 * h + 1] = {c->grads + c->o_UW + ow, c->grads + c->o_Ub + h * MHK};
     }
+    gemm_tn(q, Dp, 2 * Mh, Hb16, D, N, 2 * Mh, D, nullptr, accumulate, nullptr, DT_BF16, false, outs, 2 * halves);
     q.flush();
     return finish(r);
   }
@@ -847,10 +842,9 @@ int pool_bwd(slide_ctx* c, const Layout& y, const void* feats, long long N, int 
   float* dwp = (float*)Dp + (size_t)N * 2 * Mh;
   const int rblocks = (int)((N + 31) / 32);
   launch(r, K_POOL_BWD, 8.0 * N * D * Mh, 2.0 * N * D * 4, [&] { return launch_pool_bwd_f32(p, (float*)Dp, dwp, s); });
-  launch(r, K_ELEMWISE, 0, 0, [&] { return launch_pool_head_grads(p, s); });
   q.add(dwp, rblocks, Mh, Mh, c->grads + c->o_w, accumulate);
-  gemm_tn(q, Dp, 2 * Mh, feats, D, N, 2 * Mh, D, c->grads + c->o_VW, accumulate, c->grads + c->o_Vb, DT_F32,
-          c->grads + c->o_UW, c->grads + c->o_Ub);
+  const TnOut outs[2] = {{c->grads + c->o_VW, c->grads + c->o_Vb}, {c->grads + c->o_UW, c->grads + c->o_Ub}};
+  gemm_tn(q, Dp, 2 * Mh, feats, D, N, 2 * Mh, D, nullptr, accumulate, nullptr, DT_F32, false, outs, 2);
   q.flush();
   return finish(r);
 }
