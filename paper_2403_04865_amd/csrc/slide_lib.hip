@@ -491,21 +491,23 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
     long long TD = (long long)T * D;
     launch(r, K_ATTN_FWD, 4.0 * n * c->H * (double)T * c->dh, (double)M * 2 * D * elem_size(dt),
            [&] { return launch_attn_fwd(dt, qkv, O, lse, n, T, c->H, c->dh, c->use_mfma, s, true); });
-    {
+    // Here the lane has every row, and what it leaves in the stream is all that is read of it: the projection and fc2 on the rounded rows
+    // run without a lane only, LayerNorm and fc1 for the backward of their weights (a forward alone needs none of the four).
+    if (!c->use_lane) {
       GemmNT g{};
       g.A = O; g.lda = TD; g.B = weight(c, wi + 1); g.ldb = D; g.M = n; g.N = D; g.K = D;
       g.epi = EPI_BIAS_RESID; g.bias = c->params + o.projb; g.resid = xin; g.ldr = TD; g.out = xmid; g.ldc = TD;
       gemm_nt(r, g);
     }
     lane_attn_half(r, y, l, n, O, xmid);
-    ln_fwd(r, xmid, TD, c->params + o.ln2g, c->params + o.ln2b, u2, D, n);   // compact [n, D]
-    {
+    if (!c->use_lane || dg) {
+      ln_fwd(r, xmid, TD, c->params + o.ln2g, c->params + o.ln2b, u2, D, n);   // compact [n, D]
       GemmNT g{};
       g.A = u2; g.lda = D; g.B = weight(c, wi + 2); g.ldb = D; g.M = n; g.N = F; g.K = D;
       g.epi = EPI_BIAS_GELU; g.bias = c->params + o.fc1b; g.out = a; g.ldc = F; g.out2 = dg ? m : nullptr; g.ldc2 = F;
       gemm_nt(r, g);
     }
-    {
+    if (!c->use_lane) {
       GemmNT g{};
       g.A = a; g.lda = F; g.B = weight(c, wi + 3); g.ldb = F; g.M = n; g.N = D; g.K = F;
       g.epi = EPI_BIAS_RESID; g.bias = c->params + o.fc2b; g.resid = xmid; g.ldr = TD; g.out = xout; g.ldc = TD;
