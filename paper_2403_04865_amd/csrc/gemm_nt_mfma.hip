@@ -25,6 +25,7 @@
 // a tile's results as bf16 before they add a residual or table row or multiply with the GELU derivative, and start their
 // accumulators from the bias; LARGE does the same in the same order, so that which of the kernels runs does not show
 // in a single bit and a slide gives the same gradients whole and in chunks.
+#include "cls_lane.h"
 #include "gemm_epi.h"
 #include "lds_dma.h"
 #include <type_traits>
@@ -35,7 +36,6 @@ namespace {
 
 constexpr int NXCD = 8;
 constexpr int BK = 64;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x8 __attribute__((ext_vector_type(8), aligned(16)));
 
@@ -60,8 +60,12 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
   return __builtin_bit_cast(u32x4, t);
 }
 
-template <int BM, int BN, int NST, int MODE, bool LARGE>
-__global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + BN == 192 ? 3 : 4) gemm_nt_mid_k(GemmNT g, int MT, int NTL) {
+constexpr int mid_wgs(int bm, int bn, int nst) { return nst > 2 ? 1 : bm + bn == 256 ? 2 : bm + bn == 192 ? 3 : 4; }   // per compute unit
+
+// Tile `id` of the problem.  LANE: 0, or the kernel carries a product of the CLS lane as well (1: its A is bf16, 2: float32), in its first
+// workgroups; the rows of the CLS tokens are the lane's then
+template <int BM, int BN, int NST, int MODE, bool LARGE, int LANE>
+__device__ __forceinline__ void mid_tile(const GemmNT& g, int MT, int NTL, int id, const LaneGemm* lg, int lane_wgs, int lane_nt) {
   constexpr int WBM = BM / 64, WBN = BN / 64;        // 32 x 32 accumulators per wavefront
   constexpr int AG = BM / 32, BG = BN / 32, NLD = AG + BG;   // 8-row groups (load instructions) per wavefront and step
   constexpr int STAGE = (BM + BN) * BK;              // bf16 elements per stage
@@ -77,7 +81,16 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   static_assert(2 * 32 * PS * 4 <= STAGE * 2, "two wavefronts' epilogue patches lie inside a stage");
   // tile id -> (row tile, column tile): ids are dealt round-robin to the XCDs, and the column tiles of one row panel get
   // consecutive slots of one XCD (same L2)
-  const int xcd = blockIdx.x % NXCD, slot = blockIdx.x / NXCD;
+  if constexpr (LANE != 0) {
+    static_assert(STAGE * 2 >= 4 * 16 * 64 * 4, "a stage holds four wavefronts' partial blocks");
+    if (id < lane_wgs) {
+      const int mb = id / lane_nt;
+      if (mb * 32LL < lg->n) lane_block4<LANE == 1>(*lg, mb, id % lane_nt, reinterpret_cast<float*>(st0), reinterpret_cast<float*>(st1));
+      return;
+    }
+    id -= lane_wgs;
+  }
+  const int xcd = id % NXCD, slot = id / NXCD;
   const int mt = (slot / NTL) * NXCD + xcd;
   if (mt >= MT) return;
   const long long m0 = (long long)mt * BM;
@@ -222,7 +235,7 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
       float4 a = src[0], b = src[1];
       float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
       const long long m = mw + i * 32 + row;
-      if (n_ok && m < g.M) {
+      if (n_ok && m < g.M && !(LANE != 0 && (unsigned)m % (unsigned)g.rperiod == 0)) {
         if constexpr (MODE == EPI_TOKEN) {
           const bool first = (unsigned)m % (unsigned)g.rperiod == 0;   // the class token's row: its product is zero
 #pragma unroll
@@ -258,13 +271,31 @@ __global__ void __launch_bounds__(256, NST > 2 ? 1 : BM + BN == 256 ? 2 : BM + B
   }
 }
 
+template <int BM, int BN, int NST, int MODE, bool LARGE>
+__global__ void __launch_bounds__(256, mid_wgs(BM, BN, NST)) gemm_nt_mid_k(GemmNT g, int MT, int NTL) {
+  mid_tile<BM, BN, NST, MODE, LARGE, 0>(g, MT, NTL, blockIdx.x, nullptr, 0, 1);
+}
+template <int BM, int BN, int NST, bool LARGE, int LANE>
+__global__ void __launch_bounds__(256, mid_wgs(BM, BN, NST)) gemm_nt_mid_lane_k(GemmNT g, int MT, int NTL, LaneGemm lg, int lane_wgs, int lane_nt) {
+  mid_tile<BM, BN, NST, EPI_BIAS_RESID, LARGE, LANE>(g, MT, NTL, blockIdx.x, &lg, lane_wgs, lane_nt);
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// a product of the lane that rides along
+struct Beside { const LaneGemm* lg; bool a_bf16; };
+
 template <int BM, int BN, int NST, bool LARGE>
-hipError_t go(const GemmNT& g, hipStream_t s) {
+hipError_t go(const GemmNT& g, hipStream_t s, Beside b) {
   const int MT = (int)((g.M + BM - 1) / BM), NTL = (g.N + BN - 1) / BN;
   const long long wgs = (long long)((MT + NXCD - 1) / NXCD) * NXCD * NTL;
   if (wgs >= (1LL << 31)) return hipErrorInvalidValue;
+  if (b.lg) {   // its workgroups first, and a whole number for every XCD
+    const int nt = b.lg->N / 32, lw = ((int)((b.lg->n + 31) / 32) * nt + NXCD - 1) / NXCD * NXCD;
+    if (b.a_bf16) hipLaunchKernelGGL((gemm_nt_mid_lane_k<BM, BN, NST, LARGE, 1>), dim3((unsigned)(wgs + lw)), dim3(256), 0, s, g, MT, NTL, *b.lg, lw, nt);
+    else hipLaunchKernelGGL((gemm_nt_mid_lane_k<BM, BN, NST, LARGE, 2>), dim3((unsigned)(wgs + lw)), dim3(256), 0, s, g, MT, NTL, *b.lg, lw, nt);
+    return hipGetLastError();
+  }
   auto run = [&](auto mode) {
     hipLaunchKernelGGL((gemm_nt_mid_k<BM, BN, NST, decltype(mode)::value, LARGE>), dim3((unsigned)wgs), dim3(256), 0, s, g, MT, NTL);
     return hipGetLastError();
@@ -331,13 +362,13 @@ bool large_fills(const GemmNT& g) {
 // 522 25.1 / 27.8, 594 26.6 / 27.9, 744 32.0 / 29.6.  The GELU by formula keeps a workgroup's vector unit busy: 300 tiles 13.9 (64 x 128) / 15.5, 600
 // 33.1 / 34.0, 744 the same.
 template <bool LARGE>
-hipError_t go_mid(const GemmNT& g, hipStream_t s) {
+hipError_t go_mid(const GemmNT& g, hipStream_t s, Beside b = {}) {
   const long long t = tiles_of(g, 128, 128);
   const bool big = g.epi == EPI_BIAS_GELU ? t >= 740 : t > CUS && (t <= 2 * CUS || t >= 5 * CUS / 2);
-  if (big) return go<128, 128, 2, LARGE>(g, s);
-  if (tiles_of(g, 64, 64) > 3 * CUS) return go<64, 128, 2, LARGE>(g, s);
-  if (g.K >= 2048 && tiles_of(g, 64, 64) <= 512) return go<64, 64, 4, LARGE>(g, s);
-  return go<64, 64, 2, LARGE>(g, s);
+  if (big) return go<128, 128, 2, LARGE>(g, s, b);
+  if (tiles_of(g, 64, 64) > 3 * CUS) return go<64, 128, 2, LARGE>(g, s, b);
+  if (g.K >= 2048 && tiles_of(g, 64, 64) <= 512) return go<64, 64, 4, LARGE>(g, s, b);
+  return go<64, 64, 2, LARGE>(g, s, b);
 }
 
 }  // namespace
@@ -352,6 +383,15 @@ hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s) {
   if (gemm_nt_gelu_ok(g)) return launch_gemm_nt_gelu(g, s);
   if (!gemm_nt_big_ok(g)) return go_mid<false>(g, s);
   return large_fills(g) ? launch_gemm_nt_big(g, s) : go_mid<true>(g, s);
+}
+
+// Whether the product would run here, and not on the large-M kernels, with the lane's in its 32 x 32 form.
+bool gemm_nt_lane_ok(const GemmNT& g, const LaneGemm& lg, bool a_bf16) {
+  return g.epi == EPI_BIAS_RESID && g.rperiod > 0 && g.M <= LANE_BESIDE_ROWS && gemm_nt_mfma_ok(g) && !(gemm_nt_big_ok(g) && large_fills(g)) && lane_small(lg) &&
+         lane_gemm_ok(lg, false, a_bf16);
+}
+hipError_t launch_gemm_nt_lane(const GemmNT& g, const LaneGemm& lg, bool a_bf16, hipStream_t s) {
+  return gemm_nt_big_ok(g) ? go_mid<true>(g, s, {&lg, a_bf16}) : go_mid<false>(g, s, {&lg, a_bf16});
 }
 
 }  // namespace sl

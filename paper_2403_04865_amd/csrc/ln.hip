@@ -3,18 +3,20 @@
 // end of the file: ln_*_row16_k (bf16 path, D = 384 / 768: 16 or 32 lanes per row, 16-byte accesses, several rows
 // per wavefront; the ones the large workloads run), ln_*_fast_k (paired elements, any D up to 1024) and ln_*_k (one
 // wavefront per row, any element types; the fp32 path).
-#include "slide_internal.h"
+#include "cls_lane.h"
+
+#include <type_traits>
 
 namespace sl {
 
 constexpr int LN_MAXV = 16;  // D <= 64 * LN_MAXV
 
+// row r by a wavefront
 template <typename RS, typename T>
-__global__ void __launch_bounds__(256) ln_fwd_k(const RS* __restrict__ x, long long xs, const float* __restrict__ gam,
-                                                const float* __restrict__ bet, T* __restrict__ out, long long os,
-                                                long long rows, int D, float eps) {
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  long long r = (long long)blockIdx.x * 4 + w;
+__device__ __forceinline__ void ln_fwd_row(const RS* __restrict__ x, long long xs, const float* __restrict__ gam,
+                                           const float* __restrict__ bet, T* __restrict__ out, long long os,
+                                           long long rows, int D, float eps, long long r) {
+  const int lane = threadIdx.x & 63;
   if (r >= rows) return;
   const RS* xr = x + r * xs;
   float v[LN_MAXV];
@@ -41,7 +43,12 @@ __global__ void __launch_bounds__(256) ln_fwd_k(const RS* __restrict__ x, long l
     if (c < D) o[c] = from_f<T>((v[i] - mean) * rstd * gam[c] + bet[c]);
   }
 }
-
+template <typename RS, typename T>
+__global__ void __launch_bounds__(256) ln_fwd_k(const RS* __restrict__ x, long long xs, const float* __restrict__ gam,
+                                                const float* __restrict__ bet, T* __restrict__ out, long long os,
+                                                long long rows, int D, float eps) {
+  ln_fwd_row(x, xs, gam, bet, out, os, rows, D, eps, (long long)blockIdx.x * 4 + (threadIdx.x >> 6));
+}
 
 // ---- fast path: D == 128 * NP, each lane owns NP column pairs {2*(lane + 64*i), +1} -----------
 template <typename E> struct Pair;
@@ -247,13 +254,14 @@ __device__ __forceinline__ float sum16(float v) {   // over the 16 lanes of a ro
 // shift are fetched once for them (two rows at 384 columns: 0.40 -> 0.37 ms per launch, four no better; at 768
 // columns the gain and shift alone are 96 registers, one row).
 constexpr int ln_fwd_rpg(int np) { return np <= 3 ? 2 : 1; }
+// (wave: the wavefront's number in the launch)
 template <int NP>
-__global__ void __launch_bounds__(256) ln_fwd_row16_k(const bf16* __restrict__ x, long long xs,
-                                                      const float* __restrict__ gam, const float* __restrict__ bet,
-                                                      bf16* __restrict__ out, long long os, long long rows, float eps) {
+__device__ __forceinline__ void ln_fwd_rows16(const bf16* __restrict__ x, long long xs,
+                                              const float* __restrict__ gam, const float* __restrict__ bet,
+                                              bf16* __restrict__ out, long long os, long long rows, float eps, long long wave) {
   constexpr int D = 128 * NP, RPG = ln_fwd_rpg(NP);
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, grp = lane >> 4;
-  const long long r0 = ((long long)blockIdx.x * 4 + w) * (4 * RPG) + grp;
+  int lane = threadIdx.x & 63, l16 = lane & 15, grp = lane >> 4;
+  const long long r0 = wave * (4 * RPG) + grp;
   lnu4 raw[RPG][NP];
 #pragma unroll
   for (int j = 0; j < RPG; ++j) {
@@ -303,6 +311,30 @@ __global__ void __launch_bounds__(256) ln_fwd_row16_k(const bf16* __restrict__ x
       }
     }
   }
+}
+
+template <int NP>
+__global__ void __launch_bounds__(256) ln_fwd_row16_k(const bf16* __restrict__ x, long long xs,
+                                                      const float* __restrict__ gam, const float* __restrict__ bet,
+                                                      bf16* __restrict__ out, long long os, long long rows, float eps) {
+  ln_fwd_rows16<NP>(x, xs, gam, bet, out, os, rows, eps, (long long)blockIdx.x * 4 + (threadIdx.x >> 6));
+}
+
+// The same (NP = 0: any width, a row per wavefront) with the CLS lane's LayerNorm and first MLP matrix in the first lane_wgs workgroups:
+// neither reads what the other writes, and on a short bag each is a launch of a few microseconds that leaves the chip mostly idle
+template <int NP>
+__global__ void __launch_bounds__(64 * LANE_WAVES) ln_fwd_lane_k(const bf16* __restrict__ x, long long xs,
+                                                                 const float* __restrict__ gam, const float* __restrict__ bet,
+                                                                 bf16* __restrict__ out, long long os, long long rows, int D, float eps,
+                                                                 LaneGemm lg, int lane_wgs, int lane_nt) {
+  __shared__ float red[LANE_WAVES * 16 * 64], st[2 * LANE_WAVES * 32];
+  if ((int)blockIdx.x < lane_wgs) {
+    lane_block<1, false, 1, true>(lg, blockIdx.x / lane_nt, blockIdx.x % lane_nt, red, st);
+    return;
+  }
+  const long long wave = (long long)(blockIdx.x - lane_wgs) * LANE_WAVES + (threadIdx.x >> 6);
+  if constexpr (NP == 0) ln_fwd_row(x, xs, gam, bet, out, os, rows, D, eps, wave);
+  else ln_fwd_rows16<NP>(x, xs, gam, bet, out, os, rows, eps, wave);
 }
 
 // dx = (dres ? dres : 0) + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)), dxh = dy * gamma;
@@ -461,6 +493,29 @@ hipError_t launch_ln_fwd(int dt, const void* x, long long x_stride, const float*
     hipLaunchKernelGGL((ln_fwd_k<rs_bf16path_t, bf16>), grid, dim3(256), 0, s, (const rs_bf16path_t*)x, x_stride, gam,
                        bet, (bf16*)out, out_stride, rows, D, eps);
   return hipGetLastError();
+}
+
+// Up to 16,384 rows: beyond, the kernels beside the lane fill the chip, and the lane's registers leave the LayerNorm twelve wavefronts on
+// a compute unit.  Features of ViT-S, us, apart / beside: 1 tile 806 / 636, 20 1016 / 854, 64 1776 / 1566, 83 (16,351 rows) 2000 / 1781,
+// and of 100 with the products beside and the LayerNorm apart 2175 / 2200.
+bool ln_fwd_lane_ok(int dt, const void* x, long long x_stride, const float* gam, const float* bet, const void* out, long long out_stride, long long rows,
+                    int D, const LaneGemm& lg) {
+  if (dt != DT_BF16 || sizeof(rs_bf16path_t) != 2 || rows <= 0 || rows > LANE_BESIDE_ROWS || !lane_small(lg) || !lane_gemm_ok(lg, true, false)) return false;
+  return (ln_row16_ok(x, out, gam, x_stride, out_stride, 0, D) && ((uintptr_t)bet & 15) == 0) || (D < 128 && D != 384 && D != 768);
+}
+hipError_t launch_ln_fwd_lane(const void* x, long long x_stride, const float* gam, const float* bet, void* out, long long out_stride, long long rows, int D,
+                              float eps, const LaneGemm& lg, hipStream_t s) {
+  const int nt = lg.N / 32, lw = (int)((lg.n + 31) / 32) * nt;
+  auto run = [&](auto np) {
+    constexpr int NP = decltype(np)::value;
+    const int rpw = LANE_WAVES * (NP == 0 ? 1 : 4 * ln_fwd_rpg(NP));   // rows per workgroup
+    hipLaunchKernelGGL(ln_fwd_lane_k<NP>, dim3((unsigned)(lw + (rows + rpw - 1) / rpw)), dim3(64 * LANE_WAVES), 0, s, (const bf16*)x, x_stride, gam, bet,
+                       (bf16*)out, out_stride, rows, D, eps, lg, lw, nt);
+    return hipGetLastError();
+  };
+  if (D == 384) return run(std::integral_constant<int, 3>{});
+  if (D == 768) return run(std::integral_constant<int, 6>{});
+  return run(std::integral_constant<int, 0>{});
 }
 
 // dx = rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)),  dxh = dy * gamma

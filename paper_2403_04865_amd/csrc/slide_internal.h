@@ -309,12 +309,29 @@ bool cls_lane_ok(int D, int F);
 hipError_t launch_lane_init(const float* cls, const float* pos, float* xc, long long n, int D, hipStream_t s);
 hipError_t launch_lane_ln(const float* x, long long xs, const float* gam, const float* bet, float* out, long long os,
                           long long rows, int D, float eps, hipStream_t s);
-// out[n,N] (fp32) = A[n,K] W[N,K]^T + bias, then + resid (fp32) or, with gelu, gelu(.).  A: fp32, or bf16 with a_bf16;
-// W: bf16.  gam, bet (may be null, gelu only): A goes through a LayerNorm first (lnout: room for [n,K]).  copy (may be null): bf16 copy of the result rows (row stride ldcopy), residual mode only.
-hipError_t launch_lane_gemm(bool gelu, bool a_bf16, const void* A, long long lda, const void* W, long long ldw, long long n,
-                            int N, int K, const float* bias, const float* resid, long long ldr, float* out, long long ldc,
-                            void* copy, long long ldcopy, const float* gam, const float* bet, float eps, float* lnout,
-                            hipStream_t s);
+// out[n,N] (fp32) = A[n,K] W[N,K]^T + bias, then + resid (fp32) or, with gelu, gelu(.).  A: fp32, or bf16 with a_bf16.
+// gelu: A goes through a LayerNorm first (gam, bet, eps; lnout: room for [n,K]).
+struct LaneGemm {
+  const void* A; long long lda;       // fp32 or bf16 [n][K]
+  const bf16* W; long long ldw;     // [N][K]
+  long long n; int N, K;
+  const float* bias;                // [N]
+  const float* resid; long long ldr;  // residual form
+  float* out; long long ldc;
+  bf16* copy; long long ldcopy;     // bf16 copy of the result rows, may be null (residual form)
+  const float *gam, *bet; float eps;   // gelu form
+};
+bool lane_small(const LaneGemm& g);   // the forms that the launches below carry, up to this many token rows:
+constexpr long long LANE_BESIDE_ROWS = 16384;
+bool lane_gemm_ok(const LaneGemm& g, bool gelu, bool a_bf16);
+hipError_t launch_lane_gemm(bool gelu, bool a_bf16, LaneGemm g, float* lnout, hipStream_t s);
+// A product of the lane in the launch of the short bag's GEMM beside it (EPI_BIAS_RESID; of its rows, those with m % rperiod == 0 are the
+// lane's and are not stored), and the lane's LayerNorm and first MLP matrix in the launch of a LayerNorm.  false: not taken
+bool gemm_nt_lane_ok(const GemmNT& g, const LaneGemm& lg, bool a_bf16);
+hipError_t launch_gemm_nt_lane(const GemmNT& g, const LaneGemm& lg, bool a_bf16, hipStream_t s);
+bool ln_fwd_lane_ok(int dt, const void* x, long long x_stride, const float* gam, const float* bet, const void* out, long long out_stride, long long rows, int D, const LaneGemm& lg);
+hipError_t launch_ln_fwd_lane(const void* x, long long x_stride, const float* gam, const float* bet, void* out, long long out_stride, long long rows, int D,
+                              float eps, const LaneGemm& lg, hipStream_t s);
 
 // theta, m, v updated in place (fp32, n elements); step counts from 1
 hipError_t launch_adamw(float* theta, const float* g, float* m, float* v, size_t n, long long step, float lr, float b1,

@@ -428,37 +428,57 @@ bool prune_last_block(const slide_ctx* c) {
 float* lane_xc(const slide_ctx* c, const Layout& y, int l) { return (float*)(c->arena + y.l_xc + (size_t)l * y.s_xc); }
 
 // attention half: xcm = xc(l) + O[cls rows] Wo^T + bo, and its rounded copy over the CLS rows of x_mid
-void lane_attn_half(Run& r, const Layout& y, int l, long long n, const void* O, void* xmid) {
-  slide_ctx* c = r.c;
-  if (!c->use_lane) return;
+LaneGemm lane_proj(const slide_ctx* c, const Layout& y, int l, long long n, const void* O, void* xmid) {
   const int D = c->D;
   const long long TD = (long long)c->T * D;
-  const LayerOff& o = c->lo[l];
-  float* xcm = (float*)(c->arena + y.l_xcm);
-  launch(r, K_CLS_LANE, 2.0 * n * D * D, (double)n * D * 14, [&] {
-    return launch_lane_gemm(false, true, O, TD, weight(c, 2 + 4 * l), D, n, D, D, c->params + o.projb, lane_xc(c, y, l), D,
-                            xcm, D, xmid, TD, nullptr, nullptr, 0.f, nullptr, r.s);
-  });
+  return LaneGemm{O, TD, (const bf16*)weight(c, 2 + 4 * l), D, n, D, D, c->params + c->lo[l].projb, lane_xc(c, y, l), D,
+                  (float*)(c->arena + y.l_xcm), D, (bf16*)xmid, TD, nullptr, nullptr, 0.f};
 }
-
 // MLP half: xc(l+1) = xcm + gelu(LN2(xcm) W1^T + b1) W2^T + b2, and its rounded copy over the CLS rows of x_out
-void lane_mlp_half(Run& r, const Layout& y, int l, long long n, void* xout) {
+LaneGemm lane_fc1(const slide_ctx* c, const Layout& y, int l, long long n) {
+  const int D = c->D, F = c->F;
+  const LayerOff& o = c->lo[l];
+  return LaneGemm{c->arena + y.l_xcm, D, (const bf16*)weight(c, 3 + 4 * l), D, n, F, D, c->params + o.fc1b, nullptr, 0,
+                  (float*)(c->arena + y.l_ac), F, nullptr, 0, c->params + o.ln2g, c->params + o.ln2b, c->cfg.ln_eps};
+}
+LaneGemm lane_fc2(const slide_ctx* c, const Layout& y, int l, long long n, void* xout) {
+  const int D = c->D, F = c->F;
+  return LaneGemm{c->arena + y.l_ac, F, (const bf16*)weight(c, 4 + 4 * l), F, n, D, F, c->params + c->lo[l].fc2b,
+                  (const float*)(c->arena + y.l_xcm), D, lane_xc(c, y, l + 1), D, (bf16*)xout, (long long)c->T * D, nullptr, nullptr, 0.f};
+}
+double lane_bytes(const LaneGemm& g, bool a_bf16) { return (double)g.n * (g.K * (a_bf16 ? 2.0 : 4.0) + g.N * (g.copy ? 10.0 : 4.0)); }
+void lane_gemm(Run& r, const Layout& y, const LaneGemm& g, bool gelu, bool a_bf16) {
   slide_ctx* c = r.c;
   if (!c->use_lane) return;
-  const int D = c->D, F = c->F;
-  const long long TD = (long long)c->T * D;
-  const LayerOff& o = c->lo[l];
-  float* xcm = (float*)(c->arena + y.l_xcm);
-  float* u2c = (float*)(c->arena + y.l_u2c);
-  float* ac = (float*)(c->arena + y.l_ac);
-  launch(r, K_CLS_LANE, 4.0 * n * D * F, (double)n * (D + F) * 4, [&] {
-    return launch_lane_gemm(true, false, xcm, D, weight(c, 3 + 4 * l), D, n, F, D, c->params + o.fc1b, nullptr, 0, ac, F,
-                            nullptr, 0, c->params + o.ln2g, c->params + o.ln2b, c->cfg.ln_eps, u2c, r.s);
-  });
-  launch(r, K_CLS_LANE, 4.0 * n * D * F, (double)n * (F * 4 + D * 10), [&] {
-    return launch_lane_gemm(false, false, ac, F, weight(c, 4 + 4 * l), F, n, D, F, c->params + o.fc2b, xcm, D,
-                            lane_xc(c, y, l + 1), D, xout, TD, nullptr, nullptr, 0.f, nullptr, r.s);
-  });
+  launch(r, K_CLS_LANE, (a_bf16 ? 2.0 : 4.0) * g.n * g.N * g.K, lane_bytes(g, a_bf16),
+         [&] { return launch_lane_gemm(gelu, a_bf16, g, (float*)(c->arena + y.l_u2c), r.s); });
+}
+// a residual product and the lane's for its CLS rows, in one launch where the bag is short
+void gemm_nt_lane(Run& r, const Layout& y, GemmNT g, const LaneGemm& lg, bool a_bf16) {
+  slide_ctx* c = r.c;
+  g.rperiod = c->T;
+  if (!c->use_lane || c->dt != DT_BF16 || !c->use_mfma || !gemm_nt_lane_ok(g, lg, a_bf16)) {
+    gemm_nt(r, g);
+    lane_gemm(r, y, lg, false, a_bf16);
+    return;
+  }
+  launch(r, K_GEMM_NT, 2.0 * g.M * g.N * g.K + (a_bf16 ? 2.0 : 4.0) * lg.n * lg.N * lg.K,
+         ((double)g.M * g.K + (double)g.N * g.K + 2.0 * g.M * g.N) * 2 + lane_bytes(lg, a_bf16),
+         [&] { return launch_gemm_nt_lane(g, lg, a_bf16, r.s); });
+}
+
+// LayerNorm of the token rows and, with mlp, the lane's LayerNorm and first MLP matrix, in one launch where the bag is short
+void ln_fwd_lane(Run& r, const Layout& y, const void* x, const float* gam, const float* bet, void* out, long long rows, const LaneGemm& lg, bool mlp) {
+  slide_ctx* c = r.c;
+  const int D = c->D;
+  mlp = mlp && c->use_lane;
+  if (!mlp || !ln_fwd_lane_ok(c->dt, x, D, gam, bet, out, D, rows, D, lg)) {
+    ln_fwd(r, x, D, gam, bet, out, D, rows);
+    if (mlp) lane_gemm(r, y, lg, true, false);
+    return;
+  }
+  launch(r, K_LN_FWD, 4.0 * lg.n * lg.N * lg.K, (double)rows * D * 4 + lane_bytes(lg, false),
+         [&] { return launch_ln_fwd_lane(x, D, gam, bet, out, D, rows, D, c->cfg.ln_eps, lg, r.s); });
 }
 
 // dg: the derivative of the activation is kept for the backward
@@ -499,7 +519,7 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
       g.epi = EPI_BIAS_RESID; g.bias = c->params + o.projb; g.resid = xin; g.ldr = TD; g.out = xmid; g.ldc = TD;
       gemm_nt(r, g);
     }
-    lane_attn_half(r, y, l, n, O, xmid);
+    lane_gemm(r, y, lane_proj(c, y, l, n, O, xmid), false, true);
     if (!c->use_lane || dg) {
       ln_fwd(r, xmid, TD, c->params + o.ln2g, c->params + o.ln2b, u2, D, n);   // compact [n, D]
       GemmNT g{};
@@ -513,7 +533,8 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
       g.epi = EPI_BIAS_RESID; g.bias = c->params + o.fc2b; g.resid = xmid; g.ldr = TD; g.out = xout; g.ldc = TD;
       gemm_nt(r, g);
     }
-    lane_mlp_half(r, y, l, n, xout);
+    lane_gemm(r, y, lane_fc1(c, y, l, n), true, false);
+    lane_gemm(r, y, lane_fc2(c, y, l, n, xout), false, false);
     return;
   }
   launch(r, K_ATTN_FWD, 4.0 * n * c->H * (double)T * T * c->dh, (double)M * 4 * D * elem_size(dt),
@@ -522,16 +543,16 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
     GemmNT g{};
     g.A = O; g.lda = D; g.B = weight(c, wi + 1); g.ldb = D; g.M = M; g.N = D; g.K = D;
     g.epi = EPI_BIAS_RESID; g.bias = c->params + o.projb; g.resid = xin; g.ldr = D; g.out = xmid; g.ldc = D;
-    gemm_nt(r, g);
+    gemm_nt_lane(r, y, g, lane_proj(c, y, l, n, O, xmid), true);
   }
-  lane_attn_half(r, y, l, n, O, xmid);
-  ln_fwd(r, xmid, D, c->params + o.ln2g, c->params + o.ln2b, u2, D, M);
+  // (a replay only re-creates x_mid: x_in(l + 1) is stored with the lane's row in it)
+  ln_fwd_lane(r, y, xmid, c->params + o.ln2g, c->params + o.ln2b, u2, M, lane_fc1(c, y, l, n), !replay);
   if (!replay && !dg) {   // no backward reads the activations of this pass
     MlpArgs g{};
     g.A = u2; g.W1 = weight(c, wi + 2); g.W2 = weight(c, wi + 3); g.b1 = c->params + o.fc1b; g.b2 = c->params + o.fc2b;
     g.resid = xmid; g.out = xout; g.M = M; g.F = F;
     if (mlp_fused(r, g, false)) {
-      lane_mlp_half(r, y, l, n, xout);
+      lane_gemm(r, y, lane_fc2(c, y, l, n, xout), false, false);
       return;
     }
   }
@@ -546,8 +567,7 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
     GemmNT g{};
     g.A = a; g.lda = F; g.B = weight(c, wi + 3); g.ldb = F; g.M = M; g.N = D; g.K = F;
     g.epi = EPI_BIAS_RESID; g.bias = c->params + o.fc2b; g.resid = xmid; g.ldr = D; g.out = xout; g.ldc = D;
-    gemm_nt(r, g);
-    lane_mlp_half(r, y, l, n, xout);   // a replay only re-creates x_mid: x_in(l + 1) is stored with the lane's row in it
+    gemm_nt_lane(r, y, g, lane_fc2(c, y, l, n, xout), false);
   }
 }
 
