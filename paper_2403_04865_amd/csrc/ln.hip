@@ -290,23 +290,23 @@ __device__ __forceinline__ void ln_fwd_rows16(const bf16* __restrict__ x, long l
 #pragma unroll
       for (int e = 0; e < 8; ++e) sum += v[k][e];
     }
-    float mean = sum16(sum) * (1.0f / D);
+    const float mean = ln_mean(sum16(sum), D);
     float sq = 0.f;
 #pragma unroll
     for (int k = 0; k < NP; ++k)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         v[k][e] -= mean;
-        sq += v[k][e] * v[k][e];
+        sq = fmaf(v[k][e], v[k][e], sq);
       }
-    float rstd = 1.0f / sqrtf(sum16(sq) * (1.0f / D) + eps);
+    const float rstd = ln_rstd(sum16(sq), D, eps);
     if (r < rows) {
       bf16* o = out + r * os;
 #pragma unroll
       for (int k = 0; k < NP; ++k) {
         float y[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] = v[k][e] * rstd * gg[k][e] + bb[k][e];
+        for (int e = 0; e < 8; ++e) y[e] = fmaf(v[k][e] * rstd, gg[k][e], bb[k][e]);
         ln_st8(o + (l16 + 16 * k) * 8, y);
       }
     }

@@ -1,4 +1,4 @@
-// The MLP half of a transformer block in one kernel (bf16, D = 384): out = resid + gelu(A W1^T + b1) W2^T + b2, and its
+// The MLP half of a transformer block in one kernel (bf16, D = 384): out = x + gelu(LN(x) W1^T + b1) W2^T + b2, and its
 // backward h = (A W1^T) * gelu', out = h W2^T (W1, W2 then the transposed copies of fc2 and fc1).
 //
 // As two GEMMs the hidden layer goes through memory: 3072 bytes a row out and in again beside 768 in and 768 out, and the
@@ -15,8 +15,11 @@
 //     128 bytes of rows are slot-permuted as in gemm_nt_mfma.hip.
 //   * The activation of step s runs between the MFMAs of the second product of step s - 1 and the first of step s + 1, one
 //     element per three MFMAs, in explicit order (a fence per MFMA).
-// K order, initial bias, table and every rounding are those of the large-M GEMM kernels, so the results are theirs bit for
-// bit (whole slides and chunks take different kernels).
+//   * The forward's LayerNorm is taken on the rows in their registers (a row is two lanes'), at a tile's end for the next one, while
+//     the tile's results are on their way out.  As a launch of its own it read and wrote every row once more: features of 3001 ViT-S
+//     tiles 38.8 -> 37.9 ms.
+// K order, initial bias, table, the LayerNorm's order of additions and every rounding are those of the large-M GEMM and the LayerNorm
+// kernels, so the results are theirs bit for bit (whole slides and chunks take different kernels).
 //
 // What bounds it: the matrix pipe is busy half of the clocks (49 % forward, 46 % backward at 2.0 GHz); each MFMA takes one
 // fragment from LDS (fragments for every second one only: -14 % of the loop), the activation's instructions share the issue
@@ -93,6 +96,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
   __shared__ __attribute__((aligned(16))) bf16 st0[UNIT], st1[UNIT], st2[UNIT], st3[UNIT];
   __shared__ __attribute__((aligned(16))) unsigned char patches[NW * RW * PB];
   __shared__ __attribute__((aligned(16))) float lb1[GRAD ? 4 : F_MAX], lb2[GRAD ? 4 : D];
+  __shared__ __attribute__((aligned(16))) float lgam[GRAD ? 4 : D], lbet[GRAD ? 4 : D];
   __shared__ h16x2 tab[GRAD ? 1 : TAB_N];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, frow = lane & 31, sw = (frow >> 1) & 7;
@@ -106,7 +110,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
       tab[k] = h16x2{(_Float16)c0, (_Float16)(c1 - c0)};
     }
     for (int k = tid; k < g.F; k += NTH) lb1[k] = g.b1[k];
-    for (int k = tid; k < D; k += NTH) lb2[k] = g.b2[k];
+    for (int k = tid; k < D; k += NTH) { lb2[k] = g.b2[k]; lgam[k] = g.gam[k]; lbet[k] = g.bet[k]; }
   }
 
   auto stage = [&](auto sc) __attribute__((always_inline)) -> bf16* {
@@ -306,6 +310,73 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
     for (int k = 0; k < 24; ++k) U[k] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ru, uoff, k * 32, 0));
   };
 
+  // LayerNorm of the rows in U, in the order of ln_fwd_row16_k: there 16 lanes share a row, lane l with its pieces l, l + 16, l + 32 of
+  // eight columns; here lane half h has pieces 2 k + h, so that lane's sum is the one over k = l / 2, + 8, + 16, and the exchanges over
+  // eight, four and two lanes are sums of registers
+  auto norm_u = [&]() __attribute__((always_inline)) {
+    auto un = [&](int k, float (&v)[8]) __attribute__((always_inline)) {
+      const u32x4 t = __builtin_bit_cast(u32x4, U[k]);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        v[2 * w] = __uint_as_float(t[w] << 16);
+        v[2 * w + 1] = __uint_as_float(t[w] & 0xffff0000u);
+      }
+    };
+    auto total = [&](float (&s)[8]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+        for (int j = 0; j < o; ++j) s[j] += s[j + o];
+      return s[0] + __shfl_xor(s[0], 32, 64);
+    };
+    // the rows are unpacked anew by every pass over them: kept unpacked they would take 192 registers
+    auto again = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < 24; ++k) asm volatile("" : "+v"(U[k]));
+    };
+    float s[8], v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      s[j] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        un(j + 8 * i, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[j] += v[e];
+      }
+    }
+    const float mean = ln_mean(total(s), D);
+    again();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      s[j] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        un(j + 8 * i, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float d = v[e] - mean;
+          s[j] = fmaf(d, d, s[j]);
+        }
+      }
+    }
+    const float rstd = ln_rstd(total(s), D, g.eps);
+    again();
+#pragma unroll
+    for (int k = 0; k < 24; ++k) {
+      un(k, v);
+      float gb[16];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        *reinterpret_cast<f32x4*>(gb + 4 * q) = *reinterpret_cast<const f32x4*>(lgam + k * 16 + half * 8 + 4 * q);
+        *reinterpret_cast<f32x4*>(gb + 8 + 4 * q) = *reinterpret_cast<const f32x4*>(lbet + k * 16 + half * 8 + 4 * q);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) U[k][e] = (bf16)fmaf((v[e] - mean) * rstd, gb[e], gb[8 + e]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
   load_u(tile);
 #pragma unroll
   for (int j = 0; j < 6; ++j) dma(c0, A, c0, 0, j);
@@ -315,6 +386,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
   for (int j = 0; j < 6; ++j) dma(c2, A, c0, 1, j);
   wait_vm<0>();   // the first stages count no younger operations
   __syncthreads();
+  if constexpr (!GRAD) norm_u();
 #pragma unroll
   for (int n = 0; n < AHEAD; ++n) rd(c0, A, n);
 
@@ -364,7 +436,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
     const __amdgpu_buffer_rsrc_t ro = rows_of(g.out, tile, 2 * D);
     u32x4 rs[2][12];
     auto load_r = [&](int h) __attribute__((always_inline)) {
-      const __amdgpu_buffer_rsrc_t rr = rows_of(g.resid, tile, 2 * D);
+      const __amdgpu_buffer_rsrc_t rr = rows_of(g.A, tile, 2 * D);
 #pragma unroll
       for (int p = 0; p < 12; ++p) rs[h][p] = __builtin_amdgcn_raw_buffer_load_b128(rr, qoff[p % 3], (p / 3) * 8 * 2 * D + h * 384, 0);
     };
@@ -396,6 +468,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
     }
     if (next >= tiles) break;
     tile = next;
+    if constexpr (!GRAD) norm_u();
   }
   wait_vm<0>();   // the ring's last loads land before the workgroup's LDS is given back
 }
@@ -420,7 +493,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 bool mlp_ok(const MlpArgs& g, int width, bool grad) {
   if (!(width == D && g.F % FS == 0 && g.F >= 3 * FS && g.F <= F_MAX && g.M > 0 && g.M < (1LL << 31))) return false;
   if (!(aligned16(g.A) && aligned16(g.W1) && aligned16(g.W2) && aligned16(g.out) && aligned16(g.h) && aligned16(g.code))) return false;
-  if (!grad && !(aligned16(g.b1) && aligned16(g.b2) && aligned16(g.resid))) return false;
+  if (!grad && !(aligned16(g.b1) && aligned16(g.b2) && aligned16(g.gam) && aligned16(g.bet))) return false;
   // A workgroup takes 128 rows and comes once per compute unit, so what counts is how full the last round of them is.  Two launches /
   // here, by rounds, us forward: 0.50 60 / 72, 0.59 85 / 71, 0.84 103 / 80, 1.00 108 / 89, 1.01 130 / 140, 1.09 136 / 143, 1.15
   // 150 / 145, 1.20 152 / 145, 1.45 169 / 149, 2.00 205 / 167, 2.01 245 / 219, 3.01 332 / 290, 6.0 600 / 522; backward: 0.59 82 / 80,

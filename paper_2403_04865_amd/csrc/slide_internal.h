@@ -209,14 +209,14 @@ struct RedList { int n = 0, blocks = 0; RedSeg seg[RED_MAX]; };
 bool red_add(RedList& L, const float* part, int slabs, long long stride, long long len, float* out, int accumulate);   // false: full
 hipError_t launch_reduce_partials(const RedList& L, hipStream_t s);
 
-// MLP half of a block in one kernel (mlp_fused.hip).  Forward: out = resid + gelu(A W1^T + b1) W2^T + b2 (h, code unused).
+// MLP half of a block in one kernel (mlp_fused.hip).  Forward: out = A + gelu(LN(A) W1^T + b1) W2^T + b2 (h, code unused; out may be A).
 // Backward (grad): h = (A W1^T) * derivative, out = h W2^T, with W1, W2 the transposed copies of fc2, fc1 and code the one-byte
-// codes of the derivative; no biases, no residual.  Row strides D and F.  out may be resid, neither may be A.
+// codes of the derivative; no LayerNorm, biases or residual.  Row strides D and F.  out may not be A then.
 struct MlpArgs {
   const void* A;           // bf16 [M][D]
   const void *W1, *W2;     // bf16 [F][D], [D][F]
   const float *b1, *b2;
-  const void* resid;       // bf16 [M][D]
+  const float *gam, *bet; float eps;   // the LayerNorm
   void* out;               // bf16 [M][D]
   void* h;                 // bf16 [M][F]
   const void* code;        // [M][F]
@@ -224,6 +224,19 @@ struct MlpArgs {
 };
 bool mlp_ok(const MlpArgs& g, int D, bool grad);
 hipError_t launch_mlp(const MlpArgs& g, bool grad, hipStream_t s);
+
+// mean and 1 / deviation from a row's sums, in one form wherever a forward LayerNorm is taken: results are made opaque, so that no
+// caller's next operation swallows a rounding
+__device__ __forceinline__ float ln_mean(float sum, int D) {
+  float m = sum * (1.0f / (float)D);
+  asm volatile("" : "+v"(m));
+  return m;
+}
+__device__ __forceinline__ float ln_rstd(float sq, int D, float eps) {
+  float r = 1.0f / sqrtf(fmaf(sq, 1.0f / (float)D, eps));
+  asm volatile("" : "+v"(r));
+  return r;
+}
 
 // LayerNorm.  x rows at x + r*x_stride (RS), out rows at out + r*out_stride (T, or fp32 when out_f32).
 hipError_t launch_ln_fwd(int dt, const void* x, long long x_stride, const float* gam, const float* bet, void* out,

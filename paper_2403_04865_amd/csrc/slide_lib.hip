@@ -407,7 +407,7 @@ int check_bound(const slide_ctx* c) {
 bool mlp_fused(Run& r, const MlpArgs& g, bool grad) {
   slide_ctx* c = r.c;
   if (c->dt != DT_BF16 || !c->use_mfma || !mlp_ok(g, c->D, grad)) return false;
-  const double hidden = grad ? 3 : 0, rows = grad ? 2 : 3;   // bytes per hidden element (gradient, code), rows moved
+  const double hidden = grad ? 3 : 0, rows = 2;   // bytes per hidden element (gradient, code), rows moved
   launch(r, K_GEMM_NT, 4.0 * g.M * c->D * g.F, (double)g.M * (g.F * hidden + c->D * rows * 2) + 4.0 * c->D * g.F,
          [&] { return launch_mlp(g, grad, r.s); });
   return true;
@@ -545,17 +545,18 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
     g.epi = EPI_BIAS_RESID; g.bias = c->params + o.projb; g.resid = xin; g.ldr = D; g.out = xmid; g.ldc = D;
     gemm_nt_lane(r, y, g, lane_proj(c, y, l, n, O, xmid), true);
   }
-  // (a replay only re-creates x_mid: x_in(l + 1) is stored with the lane's row in it)
-  ln_fwd_lane(r, y, xmid, c->params + o.ln2g, c->params + o.ln2b, u2, M, lane_fc1(c, y, l, n), !replay);
   if (!replay && !dg) {   // no backward reads the activations of this pass
     MlpArgs g{};
-    g.A = u2; g.W1 = weight(c, wi + 2); g.W2 = weight(c, wi + 3); g.b1 = c->params + o.fc1b; g.b2 = c->params + o.fc2b;
-    g.resid = xmid; g.out = xout; g.M = M; g.F = F;
+    g.A = xmid; g.W1 = weight(c, wi + 2); g.W2 = weight(c, wi + 3); g.b1 = c->params + o.fc1b; g.b2 = c->params + o.fc2b;
+    g.gam = c->params + o.ln2g; g.bet = c->params + o.ln2b; g.eps = c->cfg.ln_eps; g.out = xout; g.M = M; g.F = F;
     if (mlp_fused(r, g, false)) {
+      lane_gemm(r, y, lane_fc1(c, y, l, n), true, false);
       lane_gemm(r, y, lane_fc2(c, y, l, n, xout), false, false);
       return;
     }
   }
+  // (a replay only re-creates x_mid: x_in(l + 1) is stored with the lane's row in it)
+  ln_fwd_lane(r, y, xmid, c->params + o.ln2g, c->params + o.ln2b, u2, M, lane_fc1(c, y, l, n), !replay);
   {
     GemmNT g{};
     g.A = u2; g.lda = D; g.B = weight(c, wi + 2); g.ldb = D; g.M = M; g.N = F; g.K = D;
