@@ -400,15 +400,23 @@ __global__ void __launch_bounds__(256) maxpool_bwd_k(const unsigned char* __rest
   st8(o1 + C, g11);
 }
 
-// one workgroup per tile; thread t sums channels t, t + 256, ... over the positions (neighbouring threads read
-// neighbouring channels)
+// 512 channels of a tile per workgroup, two neighbouring channels per thread, many positions in flight (a channel's additions run
+// in the order of the positions).  (One workgroup per tile, one load at a time: 16 tiles of ResNet50 151 us, this way 4.7.)
 __global__ void __launch_bounds__(256) avgpool_fwd_k(const bf16* __restrict__ x, float* __restrict__ feats, int HW, int C) {
   const long long n = blockIdx.x;
-  for (int ch = threadIdx.x; ch < C; ch += 256) {
-    float a = 0.f;
-    for (int p = 0; p < HW; ++p) a += (float)x[(n * HW + p) * C + ch];
-    feats[n * C + ch] = a / (float)HW;
+  const int ch = (blockIdx.y * 256 + threadIdx.x) * 2;
+  if (ch >= C) return;
+  const unsigned* px = reinterpret_cast<const unsigned*>(x + n * HW * C + ch);
+  const int st = C / 2;
+  float a = 0.f, b = 0.f;
+#pragma unroll 16
+  for (int p = 0; p < HW; ++p) {
+    const unsigned u = px[(long long)p * st];
+    a += __uint_as_float(u << 16);
+    b += __uint_as_float(u & 0xffff0000u);
   }
+  feats[n * C + ch] = a / (float)HW;
+  feats[n * C + ch + 1] = b / (float)HW;
 }
 
 __global__ void __launch_bounds__(256) avgpool_bwd_k(const float* __restrict__ df, bf16* __restrict__ dx, long long chunks,
@@ -521,8 +529,8 @@ hipError_t launch_maxpool_bwd(const unsigned char* arg, const bf16* dy, bf16* dx
 }
 
 hipError_t launch_avgpool_fwd(const bf16* x, float* feats, long long n, int HW, int C, hipStream_t s) {
-  if (!x || !feats || n <= 0 || n >= (1LL << 31) || HW <= 0 || !chan_ok(C)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(avgpool_fwd_k, dim3((unsigned)n), dim3(256), 0, s, x, feats, HW, C);
+  if (!x || !feats || n <= 0 || n >= (1LL << 31) || HW <= 0 || !chan_ok(C) || !al16(x)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(avgpool_fwd_k, dim3((unsigned)n, (C + 511) / 512), dim3(256), 0, s, x, feats, HW, C);
   return hipGetLastError();
 }
 

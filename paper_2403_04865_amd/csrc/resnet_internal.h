@@ -66,16 +66,16 @@ struct ConvWG {
 int conv_wgrad_slabs(const ConvWG& p);   // before any limit of rows or room
 hipError_t launch_conv_wgrad(const ConvWG& p, hipStream_t s);
 
-// dW[co][ci][kh][kw] (fp32, the parameter's own layout) = (accumulate ? dW : 0) + sum_s part[s][co][tap * Cin + ci],
-// part row stride ldk (>= taps * Cin)
-hipError_t launch_wgrad_reduce(const float* part, int slabs, int Co, int Cin, int taps, int ldk, float* dW, int accumulate,
-                               hipStream_t s);
-// fp32 W[co][ci][kh][kw] -> bf16 Wk[co][ldk] (column tap * Cin + ci, zero beyond taps * Cin) and, if Wt is not null,
-// Wt[ci][tap * Co + co]; Wf / Wtf (optional): the same two matrices in fragment order: for every block of 32 rows and
+// dW[co][ci][kh][kw] (fp32, the parameter's own layout) = (accumulate ? dW : 0) + sum_s part[s][co][tap * Cin + ci]
+struct WgradSum { const float* part; float* dW; int slabs, Co, Cin, taps, accumulate, block0; };   // part: [slabs][Co][taps Cin]
+constexpr int WGRAD_SUM_MAX = 32;   // layers of one launch
+struct WgradSumList { int n; WgradSum m[WGRAD_SUM_MAX]; };
+hipError_t launch_wgrad_reduce(WgradSumList& L, hipStream_t s);
+// fp32 W[co][ci][kh][kw] (multiples of 32 channels, up to nine taps) -> bf16 Wk[co][tap * Cin + ci] and, if Wt is not null, Wt[ci][tap * Co + co]; Wf / Wtf (optional): the same two matrices in fragment order: for every block of 32 rows and
 // 16 columns, the 64 MFMA lanes' operands (row l % 32, columns 8 (l / 32) .. + 7) back to back
 struct ConvCast {
   const float* W;
-  int Co, Cin, taps, ldk, block0;
+  int Co, Cin, taps, block0;
   bf16 *Wk, *Wt, *Wf, *Wtf;   // all but Wk may be null
 };
 constexpr int CONV_CAST_MAX = 48;   // matrices of one launch

@@ -196,7 +196,7 @@ void cast_weights(Run& r) {
   for (const ConvL& L : c->convs) {
     if (is_stem(L)) continue;
     ConvCast& e = list.m[list.n++];
-    e = ConvCast{c->params + L.oW, L.Cout, L.kCs, L.kK * L.kK, L.ldk(), 0, (bf16*)(c->arena + L.w),
+    e = ConvCast{c->params + L.oW, L.Cout, L.kCs, L.kK * L.kK, 0, (bf16*)(c->arena + L.w),
                  L.need_wt ? (bf16*)(c->arena + L.wt) : nullptr, L.wf ? (bf16*)(c->arena + L.wf) : nullptr,
                  L.wtf ? (bf16*)(c->arena + L.wtf) : nullptr};
     if (list.n == CONV_CAST_MAX) flush();
@@ -246,13 +246,26 @@ void bn_bwd(Run& r, int id, long long n, const bf16* dy, const unsigned char* ma
   });
 }
 
-void conv_wgrad(Run& r, int id, long long n, const bf16* dout, int accumulate) {
+// Weight gradients whose slab partials wait for their sum: they lie one behind the other in the room for them, and the sums of up to 32 MB
+// (beyond, they would have left the caches before they are read) run as one launch: ResNet50 of 16 tiles has 52 of 8 us.
+struct WgradSums {
+  Run& r;
+  WgradSumList list{};
+  size_t used = 0;
+  void flush() {
+    if (list.n) launch(r, RK_ELEMWISE, 0, 0, [&] { return launch_wgrad_reduce(list, r.s); });
+    list.n = 0;
+    used = 0;
+  }
+};
+
+void conv_wgrad(WgradSums& q, int id, long long n, const bf16* dout, int accumulate) {
+  Run& r = q.r;
   resnet_ctx* c = r.c;
   const ConvL& L = c->convs[id];
   ConvWG p{};
   p.dout = dout; p.Co = L.Cout; p.src = conv_src(c, L);
   p.Cs = is_stem(L) ? 64 : L.kCs;   // the stem's 256 columns are four groups of 64 handled like taps
-  p.part = (float*)(c->arena + c->lay.wpart);
   p.M = rows_of(c, L.t_conv, n); p.g = geom_fwd(L);
   long long slabs = conv_wgrad_slabs(p);
   const long long by_rows = (p.M + 255) / 256;
@@ -263,13 +276,19 @@ void conv_wgrad(Run& r, int id, long long n, const bf16* dout, int accumulate) {
   if (slabs < 1) slabs = 1;
   p.slabs = (int)slabs;
   p.per = ((p.M + slabs - 1) / slabs + 31) / 32 * 32;
+  const size_t bytes = ((size_t)slabs * L.Cout * L.ldk() * 4 + 255) & ~(size_t)255;
+  if (is_stem(L) || q.used + bytes > c->lay.wpart_bytes || q.list.n == WGRAD_SUM_MAX) q.flush();
+  p.part = (float*)(c->arena + c->lay.wpart + q.used);
   const double K = (double)L.Cin * L.K * L.K;
   launch(r, RK_CONV_WGRAD, 2.0 * p.M * L.Cout * K, conv_bytes(c, L, p.M, n),
          [&] { return launch_conv_wgrad(p, r.s); });
-  launch(r, RK_ELEMWISE, 0, 0, [&] {
-    if (is_stem(L)) return launch_stem_wgrad_reduce(p.part, p.slabs, L.Cout, c->grads + L.oW, accumulate, r.s);
-    return launch_wgrad_reduce(p.part, p.slabs, L.Cout, L.kCs, L.kK * L.kK, L.ldk(), c->grads + L.oW, accumulate, r.s);
-  });
+  if (is_stem(L)) {
+    launch(r, RK_ELEMWISE, 0, 0, [&] { return launch_stem_wgrad_reduce(p.part, p.slabs, L.Cout, c->grads + L.oW, accumulate, r.s); });
+    return;
+  }
+  q.list.m[q.list.n++] = WgradSum{p.part, c->grads + L.oW, p.slabs, L.Cout, L.kCs, L.kK * L.kK, accumulate, 0};
+  q.used += bytes;
+  if (q.used > (32u << 20)) q.flush();
 }
 
 // gradient with respect to the convolution's source rows; add != 0 adds to what dsrc holds; extra (with mask): also
@@ -350,6 +369,7 @@ int enc_fwd(resnet_ctx* c, const void* pixels, long long n, void* feats_out, hip
 int enc_bwd(resnet_ctx* c, const void* dfeats, long long n, int accumulate, hipStream_t s) {
   if (!c->enc_saved || c->enc_n != n) return SLIDE_ESTATE;
   Run r{c, s};
+  WgradSums sums{r};
   bf16* gA = (bf16*)(c->arena + c->lay.gA);
   bf16* gB = (bf16*)(c->arena + c->lay.gB);
   bf16* gC = (bf16*)(c->arena + c->lay.gC);
@@ -365,7 +385,7 @@ int enc_bwd(resnet_ctx* c, const void* dfeats, long long n, int accumulate, hipS
     // gA: gradient at the block's output (behind the ReLU)
     bn_bwd(r, b.conv[b.nconv - 1], n, gA, out, gB, accumulate);
     for (int k = b.nconv - 1; k >= 0; --k) {
-      conv_wgrad(r, b.conv[k], n, gB, accumulate);
+      conv_wgrad(sums, b.conv[k], n, gB, accumulate);
       // the last input gradient of a block with an identity shortcut takes the shortcut's gradient along (one rounding
       // of the sum, no pass of its own)
       if (k == 0 && b.down < 0) conv_dgrad(r, b.conv[k], n, gB, gC, 0, gA, out);
@@ -375,7 +395,7 @@ int enc_bwd(resnet_ctx* c, const void* dfeats, long long n, int accumulate, hipS
     // gC: gradient at the block's input through the residual branch; add the shortcut's
     if (b.down >= 0) {
       bn_bwd(r, b.down, n, gA, out, gB, accumulate);
-      conv_wgrad(r, b.down, n, gB, accumulate);
+      conv_wgrad(sums, b.down, n, gB, accumulate);
       conv_dgrad(r, b.down, n, gB, gC, 1);
     }
     bf16* t = gA; gA = gC; gC = t;
@@ -387,7 +407,7 @@ int enc_bwd(resnet_ctx* c, const void* dfeats, long long n, int accumulate, hipS
       return launch_maxpool_bwd((const unsigned char*)(c->arena + c->lay.parg), gA, gB, n, a.H, a.H, a.C, s);
     });
     bn_bwd(r, 0, n, gB, act_bits(c, c->t_r0), gC, accumulate);
-    conv_wgrad(r, 0, n, gC, accumulate);
+    conv_wgrad(sums, 0, n, gC, accumulate);
   }
   return finish(r);
 }
