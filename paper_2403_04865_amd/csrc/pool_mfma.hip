@@ -276,8 +276,11 @@ __global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const b
 //     of block i + 2 at once.  The roles repeat every 6 iterations (2 images x 3 row sets), which are written out.
 //   * Every wavefront computes the block's softmax terms itself from the four partial logits (no serial section).
 //   * Two barriers per block: partial logits visible; next bf16 image visible.
+//   * NH = 2: two such sets of gate units one after the other, each a pass over the workgroup's blocks: the first leaves its partial
+//     logits in a_tmp, the second adds them and does everything else.  A launch for each paid for ramp and drain twice:
+//     45,056 rows, two of a training step 77 us, this way 74 (a step 223 -> 219).
 constexpr int POOL_REG_NL = 4;   // weight slices read from LDS (the rest stay in registers)
-template <int D, int MH>
+template <int D, int MH, int NH>
 __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf16* __restrict__ VU) {
   constexpr int LDB = D + 8, KS = D / 16, CJ = D / 128, NR = 4 * CJ, EARLY = CJ;
   constexpr int NL = POOL_REG_NL, KR = KS - NL;   // the last NL slices of the weights are read from LDS
@@ -299,7 +302,6 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
     p.a += hf * p.N;
   }
 
-  for (int j = tid; j < MH; j += 256) { gb[j] = C1 * p.Vb[j]; gb[MH + j] = C2 * p.Ub[j]; gb[2 * MH + j] = p.w[j]; }
   // this wavefront's gate units 32 wave .. + 31 of V and of U: slices 0 .. KR - 1 of their weights stay in the
   // accumulation half of the register file (the MFMA reads them there), the last NL go to LDS in fragment order
   // (each lane reads back what it wrote): with all of them in registers the two accumulator sets fill that half
@@ -351,16 +353,15 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   // fp32 partial sums: a lane adds 4 rows per block, a few thousand terms at most (N < 2^31, 256 workgroups x 8 row
   // groups), before the fp64 reduction over row groups and workgroups
   float z[4 * CJ];
-#pragma unroll
-  for (int i = 0; i < 4 * CJ; ++i) z[i] = 0.f;
   float wabs = 0.f;
-  for (int j = lane; j < MH; j += 64) wabs += fabsf(p.w[j]) + (p.w_other ? fabsf(p.w_other[j]) : 0.f);
+  for (int j = lane; j < NH * MH; j += 64) wabs += fabsf(p.w[j]);
   wabs = wave_sum(wabs);
   const bool fixed = wabs <= 40.f;   // a bound of every logit serves as the softmax shift
   float run_m = fixed ? wabs : -INFINITY;
   double lsum = 0.0;
   const int st = gridDim.x;
   const int nblk = (int)((groups - blockIdx.x + st - 1) / st);   // blocks of this workgroup (>= 1)
+  int pass = 0;
 
   // iteration `it` (role phase ph = it mod 6): MFMAs of block it (on the last image again when it == nblk: unused),
   // gate, softmax terms and weighted sum of block it - 1, loads of block it + 1 (and the first of block it + 2)
@@ -425,8 +426,8 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
     static_assert(GA + CJ + 1 < KS && NR % SP == 0, "tail schedule");
     const long long n0 = ((long long)blockIdx.x + (long long)(it - 1) * st) * RB;   // first row of block it - 1
     float a_out = 0.f, sc = 1.0f, ek[4] = {0.f, 0.f, 0.f, 0.f};
-    float a_prev = 0.f;   // the other half's partial logit of this lane's row (two-pass use)
-    if (p.a_in != nullptr && it >= 1) a_prev = p.a_in[n0 + li < p.N ? n0 + li : p.N - 1];   // uniform
+    float a_prev = 0.f;   // the first pass's partial logit of this lane's row
+    if (NH > 1 && pass > 0 && it >= 1) a_prev = p.a_tmp[n0 + li < p.N ? n0 + li : p.N - 1];   // uniform
     static_for<0, KS>([&](auto kc) __attribute__((always_inline)) {
       constexpr int ks = decltype(kc)::value;
       bf16x8 f = __builtin_bit_cast(bf16x8, hf[ks % PF]);
@@ -458,7 +459,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
           const bool ok = n0 + li < p.N;
           a_out = a;
           float e;
-          if (p.partial) {   // uniform: only the partial logits are wanted
+          if (NH > 1 ? pass + 1 < NH : p.partial != 0) {   // uniform: only the partial logits are wanted
             e = 0.f;
           } else if (fixed) {   // uniform
             e = ok ? __expf(a - run_m) : 0.f;
@@ -501,47 +502,54 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
     // both accumulator sets stay in the accumulation half of the register file (left to itself the allocator moves
     // the finished one to 32 ordinary registers, which the three row sets need)
     asm volatile("" : "+a"(ac[0]), "+a"(ac[1]));
-    if (it >= 1 && wave == 0 && h2 == 0 && n0 + li < p.N) p.a[n0 + li] = a_out;   // kept for the backward
+    if (it >= 1 && wave == 0 && h2 == 0 && n0 + li < p.N) (pass + 1 < NH ? p.a_tmp : p.a)[n0 + li] = a_out;   // kept for the backward
     __syncthreads();   // (B) the next bf16 image is visible; apart is free again
   };
 
-  // prologue: block 0 of this workgroup, and the first loads of block 1
-  static_for<0, NR>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[0], ic); });
-  static_for<0, EARLY>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[1], ic); });
-  // the weights, while the rows come from memory; all of them are requested before the first is waited for (one at a time, each
-  // a trip to L2, 1,037 rows take 11.7 us instead of 8.9 and 45,056 rows 22.3 instead of 19.2)
-  {
-    const u32x4* wr = reinterpret_cast<const u32x4*>(VU) + (size_t)wave * KS * 2 * 64 + lane;   // fragment order
-    u32x4 a[2 * KS];
+  for (;; ++pass) {
+    // prologue: block 0 of this workgroup, and the first loads of block 1 (every wavefront is past the last barrier (B) of the pass before)
+    lrow = blockIdx.x * RB + 4 * rgrp;
 #pragma unroll
-    for (int i = 0; i < 2 * KS; ++i) a[i] = wr[i * 64];
-    __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < 4 * CJ; ++i) z[i] = 0.f;
+    for (int j = tid; j < MH; j += 256) { gb[j] = C1 * p.Vb[pass * MH + j]; gb[MH + j] = C2 * p.Ub[pass * MH + j]; gb[2 * MH + j] = p.w[pass * MH + j]; }
+    static_for<0, NR>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[0], ic); });
+    static_for<0, EARLY>([&](auto ic) __attribute__((always_inline)) { issue_one(rs[1], ic); });
+    // the weights, while the rows come from memory; all of them are requested before the first is waited for (one at a time, each
+    // a trip to L2, 1,037 rows take 11.7 us instead of 8.9 and 45,056 rows 22.3 instead of 19.2)
+    {
+      const u32x4* wr = reinterpret_cast<const u32x4*>(VU + (size_t)pass * 2 * FRAG) + (size_t)wave * KS * 2 * 64 + lane;   // fragment order
+      u32x4 a[2 * KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks < KR) {
-        asm volatile("" : "+a"(a[2 * ks]), "+a"(a[2 * ks + 1]));
-        wv[ks] = __builtin_bit_cast(bf16x8, a[2 * ks]);
-        wu[ks] = __builtin_bit_cast(bf16x8, a[2 * ks + 1]);
-      } else {
-        wl[((ks - KR) * 2 + 0) * 64] = a[2 * ks];
-        wl[((ks - KR) * 2 + 1) * 64] = a[2 * ks + 1];
+      for (int i = 0; i < 2 * KS; ++i) a[i] = wr[i * 64];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks < KR) {
+          asm volatile("" : "+a"(a[2 * ks]), "+a"(a[2 * ks + 1]));
+          wv[ks] = __builtin_bit_cast(bf16x8, a[2 * ks]);
+          wu[ks] = __builtin_bit_cast(bf16x8, a[2 * ks + 1]);
+        } else {
+          wl[((ks - KR) * 2 + 0) * 64] = a[2 * ks];
+          wl[((ks - KR) * 2 + 1) * 64] = a[2 * ks + 1];
+        }
       }
     }
-  }
-  stash_h(rs[0], 0);
-  // iteration 0 has no previous block: its gate reads zeros and its weighted sum adds zero times zero
+    stash_h(rs[0], 0);
+    // iteration 0 has no previous block: its gate reads zeros and its weighted sum adds zero times zero
 #pragma unroll
-  for (int i = 0; i < NR; ++i) rs[2][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < NR; ++i) rs[2][i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[1][0][r] = 0.f; acc[1][1][r] = 0.f; }
-  __syncthreads();
-  for (int it = 0;;) {
-    iter(IC<0>{}, it); if (++it > nblk) break;
-    iter(IC<1>{}, it); if (++it > nblk) break;
-    iter(IC<2>{}, it); if (++it > nblk) break;
-    iter(IC<3>{}, it); if (++it > nblk) break;
-    iter(IC<4>{}, it); if (++it > nblk) break;
-    iter(IC<5>{}, it); if (++it > nblk) break;
+    for (int r = 0; r < 16; ++r) { acc[1][0][r] = 0.f; acc[1][1][r] = 0.f; }
+    __syncthreads();
+    for (int it = 0;;) {
+      iter(IC<0>{}, it); if (++it > nblk) break;
+      iter(IC<1>{}, it); if (++it > nblk) break;
+      iter(IC<2>{}, it); if (++it > nblk) break;
+      iter(IC<3>{}, it); if (++it > nblk) break;
+      iter(IC<4>{}, it); if (++it > nblk) break;
+      iter(IC<5>{}, it); if (++it > nblk) break;
+    }
+    if (pass + 1 == NH) break;
   }
   if (p.partial) return;
   // column sums over the 8 row groups (the bf16 images are dead: every wavefront is past the last barrier (B))
@@ -564,9 +572,11 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   }
 }
 
+// NH passes in a workgroup, or `halves` sets of gate units side by side
+template <int NH>
 hipError_t go_reg(const PoolArgs& p, const bf16* vu, hipStream_t s, int halves = 1) {
   constexpr int D = FRAG_D, MH = FRAG_MH;
-  auto kern = pool_gate_part_reg_k<D, MH>;
+  auto kern = pool_gate_part_reg_k<D, MH, NH>;
   size_t lds = (size_t)2 * 32 * (D + 8) * 2 + (size_t)4 * POOL_REG_NL * 2 * 64 * 16 + (size_t)3 * MH * 4 + 4 * 32 * 4;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -574,28 +584,22 @@ hipError_t go_reg(const PoolArgs& p, const bf16* vu, hipStream_t s, int halves =
   return hipGetLastError();
 }
 
-// M_h = 256 as two passes of the M_h = 128 kernel over the rows (the features are read twice, against the weights
-// streaming from L2 for every block of rows in a one-pass kernel, which took the calls below 32,768 rows before: serving 16,384 rows 36.8
-// us, this way 31.0): pass 1 leaves the partial logits of gate units 0..127 in a_tmp, pass 2 adds those of units 128..255 and does the
-// softmax partials.  Where both fit the chip side by side (up to 4,096 rows) they are one launch that leaves both halves' partial
-// logits, and the softmax partials one of their own: serving 1,037 rows 29.6 -> 21.9 us, 4,096 28.9 -> 23.0.
+// M_h = 256 as two passes over the rows (the features are read twice, against the weights streaming from L2 for every block of rows in
+// a one-pass kernel, which took the calls below 32,768 rows before: serving 16,384 rows 36.8 us, as two launches 31.0).  Where both halves
+// fit the chip side by side (up to 4,096 rows) they run so and leave their partial logits, and the softmax partials are a launch
+// of their own: serving 1,037 rows 29.6 -> 21.9 us, 4,096 28.9 -> 23.0.
 hipError_t go_reg_halves(PoolArgs& p0, hipStream_t s) {
-  constexpr int MH = FRAG_MH;
   PoolArgs p = p0;
-  p.Mh = MH; p.partial = 1; p.a_in = nullptr; p.w_other = nullptr; p.a = p0.a_tmp;
+  p.Mh = FRAG_MH;
   if (p.N <= 4096 && (size_t)p.N * 2 <= p.a_room) {
-    hipError_t e = go_reg(p, (const bf16*)p0.vub, s, 2);
+    p.partial = 1;
+    p.a = p0.a_tmp;
+    hipError_t e = go_reg<1>(p, (const bf16*)p0.vub, s, 2);
     if (e != hipSuccess) return e;
     p0.blocks = pool_blocks(p0.N);
     return launch_pool_softmax_part(p0, p0.a_tmp, 2, s);
   }
-  hipError_t e = go_reg(p, (const bf16*)p0.vub, s);
-  if (e != hipSuccess) return e;
-  p = p0;
-  p.Mh = MH; p.partial = 0; p.a_in = p0.a_tmp; p.w_other = p0.w;
-  p.VW = p0.VW + (size_t)MH * p0.D; p.UW = p0.UW + (size_t)MH * p0.D;
-  p.Vb = p0.Vb + MH; p.Ub = p0.Ub + MH; p.w = p0.w + MH;
-  return go_reg(p, (const bf16*)p0.vub + 2 * FRAG, s);
+  return go_reg<2>(p, (const bf16*)p0.vub, s);
 }
 
 template <int MH, int BK, int HCH>
@@ -635,7 +639,7 @@ hipError_t launch_pool_gate_part_mfma(PoolArgs& p, hipStream_t s) {
   if (pool_frag_fwd(p)) {
     hipError_t e = launch_pool_cast_frag(p, p.G != nullptr, p.ticket, s);
     if (e != hipSuccess) return e;
-    return p.Mh == FRAG_MH ? go_reg(p, (const bf16*)p.vub, s) : go_reg_halves(p, s);
+    return p.Mh == FRAG_MH ? go_reg<1>(p, (const bf16*)p.vub, s) : go_reg_halves(p, s);
   }
   if (p.D == 768 && p.Mh == 128) return go<128, 32, 24>(p, s);
   if (p.D == 768 && p.Mh == 256) return go<256, 16, 24>(p, s);

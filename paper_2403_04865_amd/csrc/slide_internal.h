@@ -284,10 +284,8 @@ struct PoolArgs {
   // (pool_cast_frag_k); otherwise one row-major copy
   void* vub;
   int use_mfma;  // bf16 path: gate projections on the matrix cores where the shape is built
-  // M_h = 256 taken as two halves of 128 gate units by the register-resident forward kernel: the first half only writes
-  // its partial logits (partial = 1), the second adds them (a_in) and does everything else; w_other = the other half's w
-  // (the softmax shift is a bound over all gate units).  a_tmp: [N] floats of scratch for the partial logits.
-  const float* a_in; int partial; const float* w_other; float* a_tmp;
+  int partial;        // only the partial logits of these gate units are wanted
+  float* a_tmp;       // partial logits
   size_t a_room;      // floats behind a_tmp (the float32 kernels keep partial logits of blocks of gate units there)
   int copies;         // the forward of this call has left the weights and their transposes in vub (pool_frag_fwd)
   int fwd_only;       // no backward will read the scalars behind the logits
