@@ -366,8 +366,9 @@ hipError_t go_mid(const GemmNT& g, hipStream_t s, Beside b = {}) {
   const long long t = tiles_of(g, 128, 128);
   const bool big = g.epi == EPI_BIAS_GELU ? t >= 740 : t > CUS && (t <= 2 * CUS || t >= 5 * CUS / 2);
   if (big) return go<128, 128, 2, LARGE>(g, s, b);
-  if (tiles_of(g, 64, 64) > 3 * CUS) return go<64, 128, 2, LARGE>(g, s, b);
-  if (g.K >= 2048 && tiles_of(g, 64, 64) <= 512) return go<64, 64, 4, LARGE>(g, s, b);
+  const long long t64 = tiles_of(g, 64, 64);
+  if (t64 > 3 * CUS) return go<64, 128, 2, LARGE>(g, s, b);
+  if (t64 <= 2 * CUS && g.K >= (t64 <= CUS ? 256 : 2048)) return go<64, 64, 4, LARGE>(g, s, b);
   return go<64, 64, 2, LARGE>(g, s, b);
 }
 
@@ -375,8 +376,10 @@ hipError_t go_mid(const GemmNT& g, hipStream_t s, Beside b = {}) {
 
 // Which kernel takes a problem: the large-M kernels where they are the faster ones, else the largest tile that gives every compute
 // unit work (two workgroups of 128 x 128 fit a unit, three of 64 x 128, five of 64 x 64).
-// A contraction of thousands of columns on few tiles is a serial chain of K steps: four stages there (K = 3072, one
-// tile of the slide: 17.9 us against 23.8 with two); everywhere else two stages and more workgroups measured faster.
+// Where there is no more than one tile a unit the chain of K steps is all that counts: four stages there (1,576 rows (150 workgroups): the
+// products over K = 384, 1152 and 1536 13.0 -> 9.2 us on average; ViT-S step of 8 tiles 2174 -> 1996 us, ViT-B features of one 1117 ->
+// 1043), and up to two tiles a unit if it is long (K = 3072: 17.9 us against 23.8 with two).  Elsewhere two stages and more workgroups
+// measured faster.
 // The GELU of the large-M kernel comes from a table whose last bits a formula does not give: that kernel has every problem it
 // can take.
 hipError_t launch_gemm_nt_mfma(const GemmNT& g, hipStream_t s) {
