@@ -11,6 +11,7 @@
 // of four MFMAs (which index an MFMA contracts does not matter as long as both operands agree).  Weights are the first
 // operand: a lane then owns one feature row and runs of four neighbouring gate units (features).
 #include "slide_internal.h"
+#include "split_f32.h"
 
 namespace sl {
 
@@ -292,6 +293,233 @@ __global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __r
   }
 }
 
+// ---- backward of long bags ----
+// The same two products on the bf16 matrix cores, operands cut into three bf16 terms (split_f32.h): 64 rows x 64 gate units
+// (features) per workgroup.  What bounds it: the six products' MFMAs (0.75 PFLOP/s of bf16 at 131,072 rows) beside the cut of the
+// operands and the fragments' trips from LDS.  The products of the leading terms have an accumulator of their own: the gate gradients' terms
+// cancel, and what a sum is off by is mostly the roundings of its additions, of which six products a step in one
+// accumulator would make six times as many; a row's dot product is added in 64 bits.  (The error against 64 bits is 1.00 of the kernels'
+// above, geometric mean over the gate gradients of bags of 4,500 to 40,000 rows, D = 384 and 768, M_h = 128 and 256.)
+// us, before / now, D = 768: 45,056 rows, M_h = 128: gates 421 / 145, G 293 / 140; whole step of 131,072 rows 2964 / 1602, M_h = 256
+// 6047 / 3132.  (128 x 128 results a workgroup: 151 and 133, nothing either way.)
+constexpr int NACC = 2;   // accumulators of a block
+constexpr int SBM = 64, SPB = 128;   // rows; columns of the second operand: 64 units of V and of U, or 128 features
+
+// acc[j][0] the leading products, acc[j][1] the others; blocks j are 32 rows of B
+__device__ __forceinline__ void split_mul(const bf16* s, int oa, int ob, int half, f32x16 (&acc)[2][NACC]) {
+#pragma unroll
+  for (int ks = 0; ks < SPLIT_BK / 16; ++ks) {
+    const Split fa = get_split<SBM + SPB>(s, oa, ks * 2 + half);
+    Split fb[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) fb[j] = get_split<SBM + SPB>(s, ob + j * 32, ks * 2 + half);
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        f32x16& c = acc[j][t < 5];
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j].t[TERM_B[t]], fa.t[TERM_A[t]], c, 0, 0, 0);
+      }
+  }
+}
+__device__ __forceinline__ Split split_of(f32x4 a, f32x4 b) {
+  return split8({a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
+}
+// row panels are dealt to the XCDs, a panel's column tiles to one: false past the end
+__device__ __forceinline__ bool split_tile(int MT, int NT, int& mt, int& nt) {
+  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  mt = (slot / NT) * 8 + xcd;
+  nt = slot % NT;
+  return mt < MT;
+}
+
+// pool_gate_f32_k<true, true> by tiles: Dp, and dwp[2 mt + i][j] the sums over 32 rows.  D a multiple of 32, M_h of 64.
+__global__ void __launch_bounds__(256, 3) pool_dgate_split_k(PoolArgs p, float* __restrict__ Dp, float* __restrict__ dwp, int MT, int NT) {
+  constexpr int ROWS = SBM + SPB;
+  __shared__ __attribute__((aligned(16))) bf16 st[3 * ROWS * SPLIT_BK];
+  __shared__ float da[SBM];
+  extern __shared__ __attribute__((aligned(16))) float zc[];   // [3][D]: z, dz, the rest of z
+  int mt, nt;
+  if (!split_tile(MT, NT, mt, nt)) return;
+  const int D = p.D, Mh = p.Mh, nk = D / SPLIT_BK;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int frow = lane & 31, half = lane >> 5, wm = wave >> 1, wn = wave & 1;
+  const long long m0 = (long long)mt * SBM;
+  for (int i = tid; i < 3 * D; i += 256) zc[i] = p.scal[pool_z_off(p.C) + i];
+  // the loader's rows: one of H (past the end the last one, never stored), then row tid / 4 of two blocks of 64: 32 gate units of V and the
+  // same of U each, so that a wavefront's two blocks belong together
+  const int lr = tid >> 2, lc = (tid & 3) * 8;
+  const float* src[3];
+  src[0] = p.H + (m0 + lr < p.N ? m0 + lr : p.N - 1) * D + lc;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) src[1 + j] = (lr < 32 ? p.VW : p.UW) + (size_t)(nt * 64 + j * 32 + (lr & 31)) * D + lc;
+  f32x4 x[3][2];
+  auto load = [&](int kt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      x[j][0] = *reinterpret_cast<const f32x4*>(src[j] + kt * SPLIT_BK);
+      x[j][1] = *reinterpret_cast<const f32x4*>(src[j] + kt * SPLIT_BK + 4);
+    }
+  };
+  f32x16 acc[2][NACC];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < NACC; ++i) acc[j][i] = zero16();
+  double dot = 0.0;   // (64 bits: what it is off by goes into every gate unit's gradient)
+  const int oa = wm * 32 + frow, ob = SBM + wn * 64 + frow;
+  load(0);
+  for (int kt = 0; kt < nk; ++kt) {
+    step_barrier();   // every wavefront is done with the step before (the first: the columns of z are there)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) put_split<ROWS>(st, j * 64 + lr, tid & 3, split_of(x[j][0], x[j][1]));
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float* c = zc + kt * SPLIT_BK + lc + q * 4;
+      const f32x4 z = *reinterpret_cast<const f32x4*>(c), dz = *reinterpret_cast<const f32x4*>(c + D), zl = *reinterpret_cast<const f32x4*>(c + 2 * D);
+      const f32x4 t = ((x[0][q] - z) - zl) * dz;
+      dot += (double)((t[0] + t[1]) + (t[2] + t[3]));
+    }
+    if (kt + 1 < nk) load(kt + 1);
+    step_barrier();
+    split_mul(st, oa, ob, half, acc);
+  }
+  {
+    dot += __shfl_xor(dot, 1, 64);
+    dot += __shfl_xor(dot, 2, 64);
+    const long long n = m0 + lr;
+    if ((tid & 3) == 0) da[lr] = n < p.N ? (float)dot * (__expf(p.a[n] - p.scal[0]) / p.scal[1]) : 0.f;
+  }
+  f32x16 r[2][1];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) r[j][0] = acc[j][0] + acc[j][1];
+  if (not_finite(r)) {   // (an infinite feature or weight has an infinite product, not none: in float32)
+    const long long n = m0 + oa < p.N ? m0 + oa : p.N - 1;
+    const float* ph = p.H + n * D + half * 4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float* pw = (j ? p.UW : p.VW) + (size_t)(nt * 64 + wn * 32 + frow) * D + half * 4;
+      r[j][0] = zero16();
+#pragma nounroll
+      for (int k = 0; k < D; k += 8) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(ph + k), v = *reinterpret_cast<const f32x4*>(pw + k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[j][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], u[e], r[j][0], 0, 0, 0);
+      }
+    }
+  }
+  __syncthreads();
+  const long long n = m0 + oa;
+  const bool ok = n < p.N;
+  const float g = da[oa];
+  float* row = Dp + n * 2 * Mh;
+  float* dwrow = dwp + (size_t)(2 * mt + wm) * Mh;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int j0 = nt * 64 + wn * 32 + q * 8 + half * 4;
+    f32x4 dv, du;
+    float dw[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = j0 + e;
+      const float t = tanhf(r[0][0][q * 4 + e] + p.Vb[j]), s = 1.0f / (1.0f + __expf(-(r[1][0][q * 4 + e] + p.Ub[j]))), wj = p.w[j];
+      dv[e] = g * wj * s * (1.f - t * t);
+      du[e] = g * wj * t * s * (1.f - s);
+      dw[e] = g * t * s;
+    }
+    if (ok) {
+      *reinterpret_cast<f32x4*>(row + j0) = dv;
+      *reinterpret_cast<f32x4*>(row + Mh + j0) = du;
+    }
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dw[e] += __shfl_xor(dw[e], o, 64);
+    if (frow == 0 && m0 + wm * 32 < p.N) *reinterpret_cast<f32x4*>(dwrow + j0) = f32x4{dw[0], dw[1], dw[2], dw[3]};
+  }
+}
+
+// pool_g_f32_k by tiles of 64 rows x 128 features
+__global__ void __launch_bounds__(256, 3) pool_g_split_k(PoolArgs p, const float* __restrict__ Dp, int MT, int NT) {
+  constexpr int ROWS = SBM + SPB;
+  __shared__ __attribute__((aligned(16))) bf16 st[3 * ROWS * SPLIT_BK];
+  pool_head_grads(p, (gridDim.x - 1 - blockIdx.x) * 256 + threadIdx.x, gridDim.x * 256);
+  int mt, nt;
+  if (!split_tile(MT, NT, mt, nt)) return;
+  const int D = p.D, Mh = p.Mh, K = 2 * Mh, nk = K / SPLIT_BK;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int frow = lane & 31, half = lane >> 5, wm = wave >> 1, wn = wave & 1;
+  const long long m0 = (long long)mt * SBM;
+  const int d0 = nt * SPB;
+  // the weights' rows are the contracted index here: a lane loads eight of them at its feature
+  const int lr = tid >> 2, lc = (tid & 3) * 8;
+  const float* ha = Dp + (m0 + lr < p.N ? m0 + lr : p.N - 1) * K + lc;
+  int dc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) dc[j] = d0 + j * 64 + lane < D ? d0 + j * 64 + lane : D - 1;
+  f32x4 x[2];
+  float w[2][8];
+  auto load = [&](int kt) __attribute__((always_inline)) {
+    x[0] = *reinterpret_cast<const f32x4*>(ha + kt * SPLIT_BK);
+    x[1] = *reinterpret_cast<const f32x4*>(ha + kt * SPLIT_BK + 4);
+    const int j0 = kt * SPLIT_BK + wave * 8;
+    const float* wr = j0 < Mh ? p.VW + (size_t)j0 * D : p.UW + (size_t)(j0 - Mh) * D;   // M_h is a multiple of 64
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[j][e] = wr[(size_t)e * D + dc[j]];
+  };
+  f32x16 acc[2][NACC];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < NACC; ++i) acc[j][i] = zero16();
+  const int oa = wm * 32 + frow, ob = SBM + wn * 64 + frow;
+  load(0);
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt) step_barrier();   // every wavefront is done with the step before
+    put_split<ROWS>(st, lr, tid & 3, split_of(x[0], x[1]));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) put_split<ROWS>(st, SBM + j * 64 + lane, wave, split8(w[j]));
+    if (kt + 1 < nk) load(kt + 1);
+    step_barrier();
+    split_mul(st, oa, ob, half, acc);
+  }
+  f32x16 r[2][1];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) r[j][0] = acc[j][0] + acc[j][1];
+  const long long n = m0 + oa < p.N ? m0 + oa : p.N - 1;
+  if (not_finite(r)) {
+    const float* pd = Dp + n * K + half * 4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int d = d0 + wn * 64 + j * 32 + frow < D ? d0 + wn * 64 + j * 32 + frow : D - 1;
+      r[j][0] = zero16();
+#pragma nounroll
+      for (int k = 0; k < K; k += 8) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(pd + k);
+        const int j0 = k + half * 4;
+        const float* wr = (j0 < Mh ? p.VW + (size_t)j0 * D : p.UW + (size_t)(j0 - Mh) * D) + d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[j][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[(size_t)e * D], u[e], r[j][0], 0, 0, 0);
+      }
+    }
+  }
+  if (m0 + oa >= p.N) return;
+  const float alpha = __expf(p.a[n] - p.scal[0]) / p.scal[1];
+  const float* dz = p.scal + pool_z_off(p.C) + D;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int d = d0 + wn * 64 + j * 32 + q * 8 + half * 4;
+      if (d >= D) continue;
+      const f32x16& v = r[j][0];
+      const f32x4 z = {dz[d], dz[d + 1], dz[d + 2], dz[d + 3]};
+      *reinterpret_cast<f32x4*>(p.G + n * D + d) = alpha * z + f32x4{v[q * 4], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]};
+    }
+}
+
 // ---- wide rows ----
 // D > 1536 is the feature row of a bottleneck encoder (2048).  The gradient that leaves here runs back through some fifty
 // batch-normalised layers whose parameter gradients are sums of terms that cancel: the last bit of G decides bf16 roundings all the
@@ -464,6 +692,9 @@ hipError_t launch_pool_gate_part_f32(const PoolArgs& p, hipStream_t s) {
 }
 
 // Dp: [N][2 M_h]; dwp: [ceil(N / 32)][M_h] partial sums of dw; writes p.G and the head's gradients
+// By tiles where the gates make more than 128 of them, half the chip: at 128 (4,096 rows, M_h = 128) both take 146 us for a step, at 256 it is
+// 225 / 166, at 32 106 / 134 (a tile is a chain of D / 32 steps, which the kernels above deal to their wavefronts).
+constexpr long long SPLIT_TILES = 128;
 hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStream_t s) {
   if (wide(p)) {
     // t and s once more: an earlier backward over the same forward has written over them
@@ -478,6 +709,15 @@ hipError_t launch_pool_bwd_f32(const PoolArgs& p, float* Dp, float* dwp, hipStre
   }
   const int parts = (p.Mh + 31) / 32;
   const bool vec = vec_ok(p);
+  if (vec && ((p.N + SBM - 1) / SBM) * (p.Mh / 64) > SPLIT_TILES && p.N < (1LL << 31) && p.D % SPLIT_BK == 0 && p.Mh % 64 == 0) {
+    const int MT = (int)((p.N + SBM - 1) / SBM), NTu = p.Mh / 64, NTd = (p.D + SPB - 1) / SPB;
+    const long long panels = (MT + 7) / 8 * 8;
+    hipLaunchKernelGGL(pool_dgate_split_k, dim3((unsigned)(panels * NTu)), dim3(256), (size_t)3 * p.D * 4, s, p, Dp, dwp, MT, NTu);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(pool_g_split_k, dim3((unsigned)(panels * NTd)), dim3(256), 0, s, p, Dp, MT, NTd);
+    return hipGetLastError();
+  }
   hipError_t e = vec ? go_gate<true, true>(p, Dp, dwp, parts, s) : go_gate<false, true>(p, Dp, dwp, parts, s);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)((p.N + 31) / 32), (p.D + 31) / 32);
