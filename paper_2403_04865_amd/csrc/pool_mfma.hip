@@ -12,10 +12,11 @@
 //     the feature rows, each read from HBM exactly once into fp32 registers (a bf16 image in LDS feeds the MFMAs;
 //     the weighted feature sum is taken from the unrounded registers).  The gate arithmetic of block i - 1 is
 //     issued between the MFMAs of block i.
-//   * pool_gate_part_mfma_k (the other built shapes, D = 768): rows in LDS as fp32, [V;U] streams from L2 through a double-buffered LDS ring, BK columns per step.
+//   * pool_gate_part_stream_k (D = 768): the weights are more than the registers hold and stream from L2, straight into fragments.
 //   Operands are passed swapped (weights first): a lane then owns one feature row and 16 gate units per
 //   accumulator, so the sum over gate units is in-lane plus one exchange between the lane halves.
 #include "slide_internal.h"
+#include "split_f32.h"
 
 namespace sl {
 
@@ -35,33 +36,19 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-__device__ __forceinline__ bf16x8 cvt8(float4 a, float4 b) {
-  f32x2 p0 = {a.x, a.y}, p1 = {a.z, a.w}, p2 = {b.x, b.y}, p3 = {b.z, b.w};
-  bf16x2 h0 = __builtin_convertvector(p0, bf16x2), h1 = __builtin_convertvector(p1, bf16x2);
-  bf16x2 h2 = __builtin_convertvector(p2, bf16x2), h3 = __builtin_convertvector(p3, bf16x2);
-  bf16x8 r = {h0[0], h0[1], h1[0], h1[1], h2[0], h2[1], h3[0], h3[1]};
-  return r;
-}
-
-// [V;U] fp32 -> bf16, rows 0..Mh-1 = V, Mh..2Mh-1 = U; clears the combine kernel's arrival counter
-__global__ void __launch_bounds__(256) pool_cast_vu_k(const float* __restrict__ V, const float* __restrict__ U,
-                                                      bf16* __restrict__ out, long long n, unsigned* __restrict__ ticket) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
-  long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) { out[i] = (bf16)V[i]; out[n + i] = (bf16)U[i]; }
-}
-
-// [V;U] of 128 gate units x 384 as the register-resident kernels hold them: every wavefront load of a fragment is 1 KB in a row
+// [V;U] of 128 gate units x D as the kernels take them: every wavefront load of a fragment is 1 KB in a row
 // (row-major, the lanes of a load touch 32 rows, which fills a compute unit's L1 at a third of the rate: 192 KB in 5 us
 // against 2).  Half h of the gate units (units 128 h .. + 127) at out + h * 2 * FRAG: FRAG elements of [V;U], for wavefront w,
 // slice ks, matrix m the 64 lanes' eight values (unit 32 w + l % 32, column 16 ks + 8 (l / 32) ..); then, if transposed, FRAG
 // elements of its transpose (column 32 b + l % 32, unit 16 ks + 8 (l / 32) .. of V's 128 and U's 128).  The second half starts at the same
 // place without transposes, so `out` has room for both copies in every call.
-constexpr int FRAG_D = 384, FRAG_MH = 128, FRAG = 2 * FRAG_MH * FRAG_D;
+constexpr int FRAG_D = 384, FRAG_MH = 128;
+constexpr int frag(int D) { return 2 * FRAG_MH * D; }
+template <int FRAG_D>
 __global__ void __launch_bounds__(256) pool_cast_frag_k(const float* __restrict__ V, const float* __restrict__ U, bf16* __restrict__ out,
                                                         int transposed, unsigned* __restrict__ ticket) {
   if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
-  constexpr int PIECES = FRAG / 8;
+  constexpr int FRAG = frag(FRAG_D), PIECES = FRAG / 8;
   const int per = transposed ? 2 * PIECES : PIECES, i = blockIdx.x * 256 + threadIdx.x;   // a whole number of workgroups
   const int h = i / per, r = i - h * per, l = r & 63;
   V += (size_t)h * FRAG_MH * FRAG_D;
@@ -86,178 +73,155 @@ __global__ void __launch_bounds__(256) pool_cast_frag_k(const float* __restrict_
 }
 
 constexpr int RB = 32;   // rows per block
-template <int MH, int BK>
-struct PoolCfg {
-  static constexpr int JG = 4;                // wavefronts along the gate units
-  static constexpr int JW = MH / JG;          // gate units per wavefront
-  static constexpr int NBK = JW / 32;         // 32 x 32 accumulators per wavefront for V (and as many for U)
-  static constexpr int LDW = BK + 8;          // LDS row stride of the weight ring (bf16)
-  static constexpr int WCH = 2 * MH * (BK / 8) / 256;  // 16-byte weight chunks per thread and step
-  static_assert(JW % 32 == 0 && WCH >= 1, "shape");
-  static size_t lds_bytes(int D) {
-    return (size_t)RB * (D + 4) * 4 + (size_t)2 * 2 * MH * LDW * 2 + (size_t)D * 8 + (size_t)3 * MH * 4 +
-           (size_t)JG * RB * 4 + (size_t)RB * 4 + 64;
-  }
-};
 
-template <int MH, int BK, int HCH>   // HCH: float4 chunks of the row block per thread (RB * D / 1024)
-__global__ void __launch_bounds__(256) pool_gate_part_mfma_k(PoolArgs p, const bf16* __restrict__ VU) {
-  using C = PoolCfg<MH, BK>;
-  constexpr int LDW = C::LDW, NBK = C::NBK, JW = C::JW;
+// D = 768: [V;U] is 384 KB per 128 gate units and streams from L2 for every block of 32 rows, four times the block's own bytes as
+// bf16 and as many clocks of a unit's L1 as the block needs of its share of HBM.  So nothing else may be in the way: the fragments go
+// from L2 into registers in their own order (no LDS, no barriers along K), requested four slices ahead and across the blocks'
+// ends, and a workgroup's serial parts (its rows' trip from memory, the gates, the softmax terms) are hidden by a second workgroup on the
+// unit: the rows are in registers as fp32 for the weighted sum, only their bf16 image is in LDS.  (Weights through an LDS ring with a barrier
+// per 32 columns, rows as fp32 in LDS, one workgroup per unit: 45,056 rows, M_h = 128 99 us, this
+// way 47 (2.9 TB/s of rows); serving 65,536 rows 129 / 69 us, M_h = 256 264 / 98, 1,037 rows 27 / 19.)
+template <int NH>   // sets of 128 gate units
+__global__ void __launch_bounds__(256, 2) pool_gate_part_stream_k(PoolArgs p, const bf16* __restrict__ VU) {
+  constexpr int D = 768, LDB = D + 8, KS = D / 16, CJ = D / 128, NR = 4 * CJ, PF = 4, MH = NH * FRAG_MH;
+  static_assert(KS % PF == 0 && PF % 2 == 0, "rings");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int D = p.D, LDH = D + 4;
-  float* Hs = reinterpret_cast<float*>(smem);                          // [RB][LDH]
-  bf16* Ws = reinterpret_cast<bf16*>(Hs + RB * LDH);                   // [2][2 MH][LDW]
-  double* zb = reinterpret_cast<double*>(Ws + 2 * 2 * MH * LDW);       // [D]
-  float* gb = reinterpret_cast<float*>(zb + D);                        // bV[MH], bU[MH], w[MH]
-  float* apart = gb + 3 * MH;                                          // [JG][RB]
-  float* er = apart + C::JG * RB;                                      // [RB]
-  float* misc = er + RB;                                               // run_m, resc; run_l as double behind
-  double* run_l = reinterpret_cast<double*>(misc + 2);
-
+  bf16* Hb = reinterpret_cast<bf16*>(smem);                            // [RB][LDB]
+  float* gb = reinterpret_cast<float*>(Hb + RB * LDB);                 // bV[MH], bU[MH], w[MH]
+  float* apart = gb + 3 * MH;                                          // [4][RB]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int jg = wave;
   const int li = lane & 31, h2 = lane >> 5;
-  const int nk = D / BK;
-  const float* H = p.H;
-  const long long total = p.N * (long long)D;   // feature elements
-
-  for (int d = tid; d < D; d += 256) zb[d] = 0.0;
-  for (int j = tid; j < MH; j += 256) { gb[j] = p.Vb[j]; gb[MH + j] = p.Ub[j]; gb[2 * MH + j] = p.w[j]; }
-  if (tid == 0) { misc[0] = -INFINITY; misc[1] = 0.f; *run_l = 0.0; }
-
+  const int rgrp = tid >> 5, cl = tid & 31;   // a thread's rows 4 rgrp .. + 3 of a block, column groups cl + 32 j
   const long long groups = (p.N + RB - 1) / RB;
-  // weight ring loader: chunk c = tid + i * 256 -> row c / (BK / 8), 16-byte column c % (BK / 8)
-  u32x4 rw[C::WCH];
-  auto issue_w = [&](int kt) {
-#pragma unroll
-    for (int i = 0; i < C::WCH; ++i) {
-      int c = tid + i * 256;
-      int row = c / (BK / 8), kc = c % (BK / 8);
-      rw[i] = *reinterpret_cast<const u32x4*>(VU + (size_t)row * D + kt * BK + kc * 8);
-    }
-  };
-  auto stash_w = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < C::WCH; ++i) {
-      int c = tid + i * 256;
-      int row = c / (BK / 8), kc = c % (BK / 8);
-      *reinterpret_cast<u32x4*>(Ws + ((size_t)buf * 2 * MH + row) * LDW + kc * 8) = rw[i];
-    }
-  };
-  // feature block loader: the block is one contiguous span of RB * D floats
-  float4 rh[HCH];
-  auto issue_h = [&](long long g) {
-    long long e0 = g * RB * (long long)D;
-#pragma unroll
-    for (int i = 0; i < HCH; ++i) {
-      long long e = e0 + (long long)(tid + i * 256) * 4;
-      rh[i] = e < total ? *reinterpret_cast<const float4*>(H + e) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  auto stash_h = [&]() {
-    int q4 = D / 4;
-#pragma unroll
-    for (int i = 0; i < HCH; ++i) {
-      int c = tid + i * 256;
-      int row = c / q4, col = (c - row * q4) * 4;
-      *reinterpret_cast<float4*>(Hs + row * LDH + col) = rh[i];
-    }
-  };
+  for (int j = tid; j < MH; j += 256) { gb[j] = p.Vb[j]; gb[MH + j] = p.Ub[j]; gb[2 * MH + j] = p.w[j]; }
 
-  long long gi = blockIdx.x;
-  if (gi < groups) issue_h(gi);
-  issue_w(0);
-  __syncthreads();
-  for (; gi < groups; gi += gridDim.x) {
-    const long long n0 = gi * RB;
-    stash_h();
-    long long gnext = gi + gridDim.x;
-    if (gnext < groups) issue_h(gnext);   // in flight during the whole block
+  float4 rs[NR];
+  auto load_rows = [&](long long g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      long long row = g * RB + 4 * rgrp + k;   // rows past the end re-read the last one (their softmax term is zero)
+      if (row > p.N - 1) row = p.N - 1;
+      const float* h = p.H + row * D + cl * 4;
+#pragma unroll
+      for (int j = 0; j < CJ; ++j) rs[k * CJ + j] = *reinterpret_cast<const float4*>(h + j * 128);
+    }
+  };
+  // fragments: set hf, this wavefront's 32 units, slice ks, V then U
+  const u32x4* wr = reinterpret_cast<const u32x4*>(VU) + (size_t)wave * KS * 2 * 64 + lane;
+  constexpr int SET = 2 * frag(D) / 8;   // pieces from one set to the next (the room is laid out for transposes behind each)
+  u32x4 wf[PF][2];
+  int opaque = 0;   // written anew for every block: the same fragments are not to be kept in registers from one to the next
+  auto load_w = [&](int slot, int hf, int ks) __attribute__((always_inline)) {
+    const u32x4* q = wr + opaque + hf * SET + ks * 128;
+    wf[slot][0] = q[0];
+    wf[slot][1] = q[64];
+  };
+  double z[4 * CJ];   // the weighted sum feeds a cancelling difference in the backward
+#pragma unroll
+  for (int i = 0; i < 4 * CJ; ++i) z[i] = 0.0;
+  float run_m = -INFINITY;
+  double lsum = 0.0;
 
-    f32x16 acc[2 * NBK];
+  load_rows(blockIdx.x);
 #pragma unroll
-    for (int b = 0; b < 2 * NBK; ++b)
+  for (int i = 0; i < PF; ++i) load_w(i, 0, i);
+  const bf16* hrow = Hb + li * LDB + h2 * 8;
+  for (long long g = blockIdx.x; g < groups; g += gridDim.x) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-
-    for (int kt = 0; kt < nk; ++kt) {
-      int buf = kt & 1;
-      stash_w(buf);
-      issue_w(kt + 1 < nk ? kt + 1 : 0);
-      __syncthreads();   // ring stage (and, at kt == 0, the feature block) visible; the other stage is free
-      const float* hrow = Hs + li * LDH + kt * BK + h2 * 8;
-      const bf16* wbase = Ws + (size_t)buf * 2 * MH * LDW + h2 * 8;
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) {
-        float4 a = *reinterpret_cast<const float4*>(hrow + ks * 16);
-        float4 b4 = *reinterpret_cast<const float4*>(hrow + ks * 16 + 4);
-        bf16x8 hf = cvt8(a, b4);
-#pragma unroll
-        for (int b = 0; b < 2 * NBK; ++b) {
-          int row = (b < NBK ? 0 : MH) + jg * JW + (b % NBK) * 32 + li;
-          bf16x8 wf = *reinterpret_cast<const bf16x8*>(wbase + row * LDW + ks * 16);
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, hf, acc[b], 0, 0, 0);
-        }
+      for (int j = 0; j < CJ; ++j) {
+        const float4 v = rs[k * CJ + j];
+        f32x2 p0 = {v.x, v.y}, p1 = {v.z, v.w};
+        uint2 w2;
+        w2.x = __builtin_bit_cast(unsigned, __builtin_convertvector(p0, bf16x2));
+        w2.y = __builtin_bit_cast(unsigned, __builtin_convertvector(p1, bf16x2));
+        *reinterpret_cast<uint2*>(Hb + (4 * rgrp + k) * LDB + (cl + 32 * j) * 4) = w2;
       }
-    }
-    // gate: lane = feature row li; accumulator register r = gate unit (r / 4) * 8 + h2 * 4 + r % 4 of its block
+    asm volatile("" : "+s"(opaque));
+    step_barrier();   // the image is visible, the last block's partial logits are read (loads stay in flight)
     float part = 0.f;
+#pragma unroll 1
+    for (int hf = 0; hf < NH; ++hf) {
+      f32x16 av, au;
 #pragma unroll
-    for (int b = 0; b < NBK; ++b)
+      for (int r = 0; r < 16; ++r) av[r] = au[r] = 0.f;
+      u32x4 hb[2];
+      hb[0] = *reinterpret_cast<const u32x4*>(hrow);
+      static_for<0, KS>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int ks = decltype(kc)::value, sl = ks % PF;
+        if constexpr (ks + 1 < KS) hb[(ks + 1) % 2] = *reinterpret_cast<const u32x4*>(hrow + (ks + 1) * 16);
+        const bf16x8 f = __builtin_bit_cast(bf16x8, hb[ks % 2]);
+        av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[sl][0]), f, av, 0, 0, 0);
+        au = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[sl][1]), f, au, 0, 0, 0);
+        if constexpr (ks + PF < KS) load_w(sl, hf, ks + PF);
+        else load_w(sl, hf + 1 < NH ? hf + 1 : 0, ks + PF - KS);   // the next set's, or the next block's
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      // accumulator register r of a lane = gate unit (r / 4) * 8 + h2 * 4 + r % 4 of the wavefront's 32, row li
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        int j = jg * JW + b * 32 + q * 8 + h2 * 4;
-        float4 bv = *reinterpret_cast<const float4*>(gb + j);
-        float4 bu = *reinterpret_cast<const float4*>(gb + MH + j);
-        float4 wj = *reinterpret_cast<const float4*>(gb + 2 * MH + j);
-        float bvv[4] = {bv.x, bv.y, bv.z, bv.w}, buu[4] = {bu.x, bu.y, bu.z, bu.w}, ww[4] = {wj.x, wj.y, wj.z, wj.w};
+        const int j = hf * FRAG_MH + wave * 32 + q * 8 + h2 * 4;
+        const float4 bv = *reinterpret_cast<const float4*>(gb + j), bu = *reinterpret_cast<const float4*>(gb + MH + j);
+        const float4 wj = *reinterpret_cast<const float4*>(gb + 2 * MH + j);
+        const float bvv[4] = {bv.x, bv.y, bv.z, bv.w}, buu[4] = {bu.x, bu.y, bu.z, bu.w}, ww[4] = {wj.x, wj.y, wj.z, wj.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float xv = acc[b][4 * q + e] + bvv[e], xu = acc[NBK + b][4 * q + e] + buu[e];
+          const float xv = av[4 * q + e] + bvv[e], xu = au[4 * q + e] + buu[e];
           // tanh(xv) * sigmoid(xu) = (1 - e1) / ((1 + e1) (1 + e2)), e1 = exp(-2 xv), e2 = exp(-xu)
-          float e1 = __expf(fminf(-2.0f * xv, 40.f)), e2 = __expf(fminf(-xu, 40.f));
+          const float e1 = __expf(fminf(-2.0f * xv, 40.f)), e2 = __expf(fminf(-xu, 40.f));
           part += ww[e] * ((1.0f - e1) * __builtin_amdgcn_rcpf((1.0f + e1) * (1.0f + e2)));
         }
       }
+    }
     part += __shfl_xor(part, 32, 64);
-    if (h2 == 0) apart[jg * RB + li] = part;
-    __syncthreads();
-    if (tid < 64) {   // wavefront 0: logits of the block, online softmax state
-      float a = 0.f;
-      if (tid < RB) {
+    if (h2 == 0) apart[wave * RB + li] = part;
+    step_barrier();   // the four partial logits of every row are there, the image is free
+    // softmax terms, by every wavefront for itself: lanes li and li + 32 have row li
+    const long long n0 = g * RB;
+    const bool ok = n0 + li < p.N;
+    float a = apart[li] + apart[RB + li] + apart[2 * RB + li] + apart[3 * RB + li];
+    if (wave == 0 && h2 == 0 && ok) p.a[n0 + li] = a;
+    a = ok ? a : -INFINITY;
+    const float m = fmaxf(run_m, wave_max(a));   // finite: the block has at least one row
+    const float e = __expf(a - m);
+    const double sc = (double)__expf(run_m - m);   // exp(-inf) = 0 on the first block
+    run_m = m;
+    lsum = lsum * sc + (double)e;   // summed over the rows once, at the end
+    double ek[4];
 #pragma unroll
-        for (int j = 0; j < C::JG; ++j) a += apart[j * RB + tid];
+    for (int k = 0; k < 4; ++k) ek[k] = (double)__shfl(e, 4 * (rgrp & 7) + k, 64);
+#pragma unroll
+    for (int j = 0; j < CJ; ++j) {
+      double s[4] = {z[4 * j] * sc, z[4 * j + 1] * sc, z[4 * j + 2] * sc, z[4 * j + 3] * sc};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 v = rs[k * CJ + j];
+        s[0] += ek[k] * (double)v.x; s[1] += ek[k] * (double)v.y; s[2] += ek[k] * (double)v.z; s[3] += ek[k] * (double)v.w;
       }
-      bool ok = tid < RB && n0 + tid < p.N;
-      if (ok) p.a[n0 + tid] = a;
-      a = ok ? a : -INFINITY;
-      float m_old = misc[0];
-      float m = fmaxf(m_old, wave_max(a));   // finite: the block has at least one row
-      float e = __expf(a - m);
-      if (tid < RB) er[tid] = e;
-      float es = wave_sum(e);
-      if (tid == 0) {
-        float sc = __expf(m_old - m);   // exp(-inf) = 0 on the first block
-        misc[0] = m; misc[1] = sc;
-        *run_l = *run_l * (double)sc + (double)es;
-      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) z[4 * j + c] = s[c];
     }
-    __syncthreads();
-    {
-      float sc = misc[1];
-      for (int d = tid; d < D; d += 256) {
-        double z = zb[d] * (double)sc;
-#pragma unroll 8
-        for (int r = 0; r < RB; ++r) z += (double)er[r] * (double)Hs[r * LDH + d];
-        zb[d] = z;
-      }
-    }
-    __syncthreads();   // the feature block and er are free again
+    __builtin_amdgcn_sched_barrier(0);
+    if (g + gridDim.x < groups) load_rows(g + gridDim.x);   // uniform
   }
+  // column sums over the 8 row groups (every wavefront is past the last barrier, so the image is dead)
+  double* zred = reinterpret_cast<double*>(smem);   // [8][D]
+  static_assert(8 * D * 8 <= RB * LDB * 2, "reduction buffer");
+#pragma unroll
+  for (int j = 0; j < CJ; ++j)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) zred[rgrp * D + (cl + 32 * j) * 4 + c] = z[4 * j + c];
+  __syncthreads();
   double* out = p.part + (size_t)blockIdx.x * (2 + D);
-  if (tid == 0) { out[0] = (double)misc[0]; out[1] = *run_l; }
-  for (int d = tid; d < D; d += 256) out[2 + d] = zb[d];
+  for (int o = 1; o < 32; o <<= 1) lsum += __shfl_xor(lsum, o, 64);   // one half has all rows
+  if (tid == 0) { out[0] = (double)run_m; out[1] = lsum; }
+  for (int d = tid; d < D; d += 256) {
+    double t = 0.0;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) t += zred[g * D + d];
+    out[2 + d] = t;
+  }
 }
 
 // Variant for the shape whose [V;U] fits the register file (D = 384, M_h = 128: 2 M_h * D bf16 = 192 KB, 192
@@ -296,6 +260,7 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
   const float* H = p.H;
   const long long groups = (p.N + RB - 1) / RB;
   constexpr float C1 = -2.0f * 1.44269504088896f, C2 = -1.44269504088896f;   // exp(-2x) and exp(-x) as exp2
+  constexpr int FRAG = frag(D);
   if (const int hf = blockIdx.y) {   // the second half of the gate units beside the first
     VU += (size_t)hf * 2 * FRAG;
     p.Vb += hf * MH; p.Ub += hf * MH; p.w += hf * MH;
@@ -602,16 +567,13 @@ hipError_t go_reg_halves(PoolArgs& p0, hipStream_t s) {
   return go_reg<2>(p, (const bf16*)p0.vub, s);
 }
 
-template <int MH, int BK, int HCH>
-hipError_t go(const PoolArgs& p, hipStream_t s) {
-  using C = PoolCfg<MH, BK>;
-  auto kern = pool_gate_part_mfma_k<MH, BK, HCH>;
-  size_t lds = C::lds_bytes(p.D);
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  long long n = (long long)p.Mh * p.D;
-  hipLaunchKernelGGL(pool_cast_vu_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, n, p.ticket);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+template <int NH>
+hipError_t go_stream(PoolArgs& p, hipStream_t s) {
+  auto kern = pool_gate_part_stream_k<NH>;
+  const size_t lds = (size_t)RB * (768 + 8) * 2 + (size_t)3 * NH * FRAG_MH * 4 + 4 * RB * 4;
+  const long long groups = (p.N + RB - 1) / RB;   // two workgroups per compute unit
+  p.blocks = groups < 2 * p.blocks ? (int)groups : 2 * p.blocks;
+  if (p.blocks > 1024) p.blocks = 1024;
   hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(256), lds, s, p, (const bf16*)p.vub);
   return hipGetLastError();
 }
@@ -630,20 +592,18 @@ bool pool_frag_fwd(const PoolArgs& p) {
 }
 
 hipError_t launch_pool_cast_frag(const PoolArgs& p, bool transposed, unsigned* ticket, hipStream_t s) {
-  const int pieces = p.Mh / FRAG_MH * (FRAG / 8) * (transposed ? 2 : 1);
-  hipLaunchKernelGGL(pool_cast_frag_k, dim3(pieces / 256), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, (int)transposed, ticket);
+  const int pieces = p.Mh / FRAG_MH * (frag(p.D) / 8) * (transposed ? 2 : 1);
+  auto kern = p.D == FRAG_D ? pool_cast_frag_k<FRAG_D> : pool_cast_frag_k<768>;
+  hipLaunchKernelGGL(kern, dim3(pieces / 256), dim3(256), 0, s, p.VW, p.UW, (bf16*)p.vub, (int)transposed, ticket);
   return hipGetLastError();
 }
 
 hipError_t launch_pool_gate_part_mfma(PoolArgs& p, hipStream_t s) {
-  if (pool_frag_fwd(p)) {
-    hipError_t e = launch_pool_cast_frag(p, p.G != nullptr, p.ticket, s);
-    if (e != hipSuccess) return e;
-    return p.Mh == FRAG_MH ? go_reg<1>(p, (const bf16*)p.vub, s) : go_reg_halves(p, s);
-  }
-  if (p.D == 768 && p.Mh == 128) return go<128, 32, 24>(p, s);
-  if (p.D == 768 && p.Mh == 256) return go<256, 16, 24>(p, s);
-  return hipErrorInvalidValue;
+  const bool narrow = pool_frag_fwd(p);
+  hipError_t e = launch_pool_cast_frag(p, narrow && p.G != nullptr, p.ticket, s);
+  if (e != hipSuccess) return e;
+  if (narrow) return p.Mh == FRAG_MH ? go_reg<1>(p, (const bf16*)p.vub, s) : go_reg_halves(p, s);
+  return p.Mh == FRAG_MH ? go_stream<1>(p, s) : go_stream<2>(p, s);
 }
 
 }  // namespace sl

@@ -1,5 +1,5 @@
-"""Aggregator over long bags where its kernels change: the float32 gate gradients and G as bf16 terms (pool_f32.hip), against float64
-(needs an MI355X)."""
+"""Aggregator over long bags where its kernels change: the float32 gate gradients and G as bf16 terms (pool_f32.hip), the forward whose
+weights stream (pool_mfma.hip), against float64 (needs an MI355X)."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +66,12 @@ def test_float32_gradients_with_an_infinite_weight():
         same = torch.isfinite(r)
         assert torch.equal(torch.isfinite(x), same), n
         assert _rel(x[same], r[same]) < 1e-4, n
+
+
+# Forward with streaming weights: one block, blocks with a last row of one, one and two rounds of workgroups, a ragged end.  Tolerance: the bound
+# of every bf16 parity test (the gates' operands are rounded to bf16).
+@pytest.mark.parametrize("Mh,N", [(128, 512), (128, 16384 + 1), (256, 8192 + 31), (256, 40000)])
+def test_streaming_forward(Mh, N):
+    errs = {n: _rel(*v) for n, v in _step(768, Mh, N, 1).items()}
+    print(errs, flush=True)
+    assert all(e < 2e-2 for e in errs.values()), errs
