@@ -242,11 +242,9 @@ __global__ void __launch_bounds__(attn_threads<NB>(), 2) attn_fwd_mfma_k(const b
 // backward, pass Q: dQ
 // --------------------------------------------------------------------------------------------
 template <int DH, int NB>
-__global__ void __launch_bounds__(attn_threads<NB>(), 2) attn_bwd_q_mfma_k(const bf16* __restrict__ qkv, const bf16* __restrict__ O,
-                                                         const float* __restrict__ lse, const bf16* __restrict__ dO,
-                                                         bf16* __restrict__ dqkv, float* __restrict__ delta_ws, int T, int H,
-                                                         long long ntiles, int cls_only) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+__device__ __forceinline__ void bwd_q(unsigned char* smem, const bf16* __restrict__ qkv, const bf16* __restrict__ O,
+                                      const float* __restrict__ lse, const bf16* __restrict__ dO, bf16* __restrict__ dqkv,
+                                      float* __restrict__ delta_ws, int T, int H, long long ntiles, int cls_only) {
   constexpr int TP = NB * 32, LDR = DH + 8, KS = DH / 16, DB = DH / 32;
   bf16* Ks = reinterpret_cast<bf16*>(smem);  // [TP][LDR]
   bf16* Vs = Ks + TP * LDR;                  // [TP][LDR]
@@ -387,13 +385,11 @@ __global__ void __launch_bounds__(attn_threads<NB>(), 2) attn_bwd_q_mfma_k(const
 // --------------------------------------------------------------------------------------------
 // backward, pass K: dK, dV
 // --------------------------------------------------------------------------------------------
-template <int DH, int NB>
-// (four wavefronts: this kernel needs more registers than seven wavefronts per workgroup, two workgroups per
-// compute unit, would leave it, and measured slower with seven and one workgroup)
-__global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* __restrict__ qkv, const float* __restrict__ delta_ws,
-                                                         const float* __restrict__ lse, const bf16* __restrict__ dO,
-                                                         bf16* __restrict__ dqkv, int T, int H, long long ntiles, int cls_only) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+// NW wavefronts.  OWN: delta is formed here, in pass Q's order of additions, instead of read (nothing then comes from that pass).
+template <int DH, int NB, int NW, bool OWN>
+__device__ __forceinline__ void bwd_k(unsigned char* smem, const bf16* __restrict__ qkv, const bf16* __restrict__ O,
+                                      const float* __restrict__ delta_ws, const float* __restrict__ lse, const bf16* __restrict__ dO,
+                                      bf16* __restrict__ dqkv, int T, int H, long long ntiles, int cls_only) {
   constexpr int TP = NB * 32, LDR = DH + 8, KS = DH / 16, DB = DH / 32;
   bf16* Qs = reinterpret_cast<bf16*>(smem);   // [TP][LDR]
   bf16* Gs = Qs + TP * LDR;                   // [TP][LDR]  dO
@@ -409,7 +405,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* __restri
   const bf16* base = qkv + tile * T * gs + h * DH;
   const bf16* gbase = dO + tile * T * (long long)D + h * DH;
   const int TG = cls_only ? 1 : T;   // rows of dO that are defined (cls_only: query 0 alone carries a gradient)
-  static_assert(TP <= 256, "one row of delta / lse per thread");
+  static_assert(TP <= NW * 64 && (!OWN || NB <= NW), "one row of delta / lse per thread, one block of a wavefront's");
   int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int li = lane & 31, h2 = lane >> 5;
   // Everything that comes from global memory before the main loop is requested up front, in one go, so that the
@@ -419,7 +415,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* __restri
   float d_row, l_row;   // delta_i = dO_i . O_i (left by the query-owned pass) and the log-sum-exp of row i = thread id
   {
     int i = threadIdx.x < TG ? threadIdx.x : TG - 1;
-    d_row = delta_ws[(tile * H + h) * T + i];
+    if constexpr (!OWN) d_row = delta_ws[(tile * H + h) * T + i];
     l_row = lse[(tile * H + h) * T + i];
   }
   bf16x8 fk[KS], fv[KS];
@@ -433,10 +429,31 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* __restri
     }
   };
   load_kv(wave, fk, fv);
-  load_rm2<DH, TP, 256, true>(base, gs, T, Qs, gbase, D, TG, Gs, [&] { l_row *= LOG2E; });
+  bf16x8 fdo[KS], fo[KS];
+  if constexpr (OWN) {
+    const int q = wave * 32 + li < TG ? wave * 32 + li : TG - 1;
+    const bf16 *orow = O + (tile * T + q) * D + h * DH, *gor = gbase + q * (long long)D;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      fdo[ks] = as_bf16x8(ldg16(gor + ks * 16 + h2 * 8));
+      fo[ks] = as_bf16x8(ldg16(orow + ks * 16 + h2 * 8));
+    }
+  }
+  load_rm2<DH, TP, NW * 64, true>(base, gs, T, Qs, gbase, D, TG, Gs, [&] {
+    l_row *= LOG2E;
+    if constexpr (OWN) {
+      float delta = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) delta += (float)fdo[ks][i] * (float)fo[ks][i];
+      delta += __shfl_xor(delta, 32, 64);
+      if (h2 == 0 && wave < NB) dl[wave * 32 + li] = wave * 32 + li < TG ? delta : 0.f;
+    }
+  });
   if (threadIdx.x < TP) {
     bool def = threadIdx.x < TG;
-    dl[threadIdx.x] = def ? d_row : 0.f;
+    if constexpr (!OWN) dl[threadIdx.x] = def ? d_row : 0.f;
     ls[threadIdx.x] = def ? l_row : INFINITY;   // +inf on padding rows: their probabilities come out as zero
   }
   __syncthreads();
@@ -447,12 +464,12 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* __restri
   const bf16* const qtr0 = Qs + tr_lane_off(LDR, lane);
   const bf16* const gtr0 = Gs + tr_lane_off(LDR, lane);
   const int nlast = T - (NB - 1) * 32;   // real queries in the last block (1 .. 32)
-  for (int kb = wave; kb < NB; kb += 4) {
+  for (int kb = wave; kb < NB; kb += NW) {
     int key = kb * 32 + li;
     // the fragments of the wavefront's next key block travel while this one is worked on
-    const bool more = kb + 4 < NB;   // uniform
+    const bool more = kb + NW < NB;   // uniform
     bf16x8 nk[KS], nv[KS];
-    if (more) load_kv(kb + 4, nk, nv);
+    if (more) load_kv(kb + NW, nk, nv);
     f32x16 dk[DB], dv[DB];
 #pragma unroll
     for (int d = 0; d < DB; ++d)
@@ -539,6 +556,32 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* __restri
   }
 }
 
+template <int DH, int NB>
+__global__ void __launch_bounds__(attn_threads<NB>(), 2) attn_bwd_q_mfma_k(const bf16* qkv, const bf16* O, const float* lse, const bf16* dO,
+                                                                         bf16* dqkv, float* delta_ws, int T, int H, long long ntiles,
+                                                                         int cls_only) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  bwd_q<DH, NB>(smem, qkv, O, lse, dO, dqkv, delta_ws, T, H, ntiles, cls_only);
+}
+// (four wavefronts: this pass needs more registers than seven wavefronts per workgroup, two workgroups per
+// compute unit, would leave it, and measured slower with seven and one workgroup where there is work for two)
+template <int DH, int NB>
+__global__ void __launch_bounds__(256, 2) attn_bwd_k_mfma_k(const bf16* qkv, const float* delta_ws, const float* lse, const bf16* dO,
+                                                            bf16* dqkv, int T, int H, long long ntiles, int cls_only) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  bwd_k<DH, NB, 4, false>(smem, qkv, nullptr, delta_ws, lse, dO, dqkv, T, H, ntiles, cls_only);
+}
+// Short bags, where a unit has a workgroup or two in all: both passes side by side (blockIdx.y), a wavefront per block of keys.
+// us a layer, two launches / this one, heads 64 wide: 8 tiles of 6 heads 23.2 / 13.6, 37 tiles 28.0 / 24.3.
+template <int DH, int NB>
+__global__ void __launch_bounds__(attn_threads<NB>(), 1) attn_bwd_short_k(const bf16* qkv, const bf16* O, const float* lse, const bf16* dO,
+                                                                          bf16* dqkv, float* delta_ws, int T, int H, long long ntiles,
+                                                                          int cls_only) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (blockIdx.y == 0) bwd_k<DH, NB, attn_threads<NB>() / 64, true>(smem, qkv, O, nullptr, lse, dO, dqkv, T, H, ntiles, cls_only);
+  else bwd_q<DH, NB>(smem, qkv, O, lse, dO, dqkv, delta_ws, T, H, ntiles, cls_only);
+}
+
 template <int DH, int NB> constexpr size_t fwd_lds() { return (size_t)2 * NB * 32 * (DH + 8) * 2; }
 template <int DH, int NB> constexpr size_t bq_lds() { return (size_t)2 * NB * 32 * (DH + 8) * 2; }
 template <int DH, int NB> constexpr size_t bk_lds() {
@@ -561,10 +604,20 @@ hipError_t fwd_go(const void* qkv, void* O, float* lse, long long n, int T, int 
   return hipGetLastError();
 }
 
+// Heads of all tiles together up to which both passes run side by side.  ViT-S steps of 64 tiles (384 heads) 4716 / 4673 us, ViT-B steps of 40
+// (480) 8169 / 8218; heads 32 wide, of which three workgroups fit a unit: 256 tiles (512) 256.7 / 253.7, larger bags not measured
+template <int NB> constexpr long long short_heads() { return NB >= 7 ? 384 : 512; }
 template <int DH, int NB>
 hipError_t bwd_go(const void* qkv, const void* O, const float* lse, const void* dO, void* dqkv, float* delta_ws,
                   long long n, int T, int H, int cls_only, hipStream_t s) {
   size_t lq = bq_lds<DH, NB>(), lk = bk_lds<DH, NB>();
+  if (n * H <= short_heads<NB>()) {
+    hipError_t e = set_lds(attn_bwd_short_k<DH, NB>, lk);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((attn_bwd_short_k<DH, NB>), dim3((unsigned)((n + 7) / 8 * 8 * H), 2), dim3(attn_threads<NB>()), lk, s,
+                       (const bf16*)qkv, (const bf16*)O, lse, (const bf16*)dO, (bf16*)dqkv, delta_ws, T, H, n, cls_only);
+    return hipGetLastError();
+  }
   hipError_t e = set_lds(attn_bwd_q_mfma_k<DH, NB>, lq);
   if (e != hipSuccess) return e;
   e = set_lds(attn_bwd_k_mfma_k<DH, NB>, lk);
