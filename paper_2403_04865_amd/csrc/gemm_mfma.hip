@@ -37,16 +37,21 @@ struct TnGroup {
     float *part, *cs_part;
     int N1, N2, per, block0;
   };
-  int n;
+  int n, blocks, each;   // workgroups; those of one XCD
   Prob p[TN_GROUP_MAX];
 };
 
 __global__ void __launch_bounds__(256, 3) gemm_tn_mfma_k(TnGroup G) {
   __shared__ __attribute__((aligned(16))) bf16 st0[STAGE], st1[STAGE];
+  // Workgroups are dealt round-robin to the XCDs: each XCD takes a run of consecutive ones, which are tiles of the same rows, so that
+  // its L2 fetches a panel once for all the tiles of it.  The four problems of a ViT-S block, 37 tiles: 48.9 us tile by tile over the
+  // XCDs, this way 43.8 (steps of 37 / 64 tiles 3276 / 4627 -> 3187 / 4455; of 4 to 8 within 0.5 % either way).
+  const int wg = (int)(blockIdx.x & 7) * G.each + (int)(blockIdx.x >> 3);
+  if (wg >= G.blocks) return;
   int pi = 0;
-  while (pi + 1 < G.n && (int)blockIdx.x >= G.p[pi + 1].block0) ++pi;
+  while (pi + 1 < G.n && wg >= G.p[pi + 1].block0) ++pi;
   const TnGroup::Prob& g = G.p[pi];
-  const int per = g.per, ti = (g.N1 + BT - 1) / BT, b = blockIdx.x - g.block0;
+  const int per = g.per, ti = (g.N1 + BT - 1) / BT, b = wg - g.block0;
   const int i0 = b % ti * BT, r = b / ti, tj = (g.N2 + BT - 1) / BT, j0 = r % tj * BT, slab = r / tj;
   const long long lo = (long long)slab * per, hi = lo + per < g.M ? lo + per : g.M;
   const int span = hi > lo ? (int)(hi - lo) : 0, nk = (span + BK - 1) / BK;
@@ -204,8 +209,10 @@ hipError_t launch_gemm_tn_mfma(const GemmTN* g, int n, hipStream_t s) {
     p.block0 = (int)blocks;
     blocks += (long long)((p.N1 + BT - 1) / BT) * ((p.N2 + BT - 1) / BT) * g[i].slabs;
   }
-  if (blocks >= (1LL << 31)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gemm_tn_mfma_k, dim3((unsigned)blocks), dim3(256), 0, s, G);
+  if (blocks >= (1LL << 31) - 8) return hipErrorInvalidValue;
+  G.blocks = (int)blocks;
+  G.each = (int)((blocks + 7) / 8);
+  hipLaunchKernelGGL(gemm_tn_mfma_k, dim3((unsigned)G.each * 8), dim3(256), 0, s, G);
   return hipGetLastError();
 }
 
