@@ -7,18 +7,24 @@ namespace sl {
 // fp32 master weights [R,C] -> T copies [R,C] (bf16 path) and T transposes [C,R], every matrix of the encoder in one
 // launch: a launch per matrix is 49 launches of 2 to 5 us for a 12-block encoder, more than the bytes take.
 // ---------------------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) cast_transpose_k(CastTable t, const float* __restrict__ params, char* __restrict__ shadow) {
-  __shared__ float tile[32][33];
-  int b = blockIdx.x, i = 0;
-  long long l = 0;
-  if (b >= t.blocks0) {   // matrices 1 .. 4 repeat per layer
+// workgroup -> matrix i of layer l, tile b of it; matrices 1 .. 4 repeat per layer
+__device__ __forceinline__ void cast_tile(const CastTable& t, int& b, int& i, long long& l) {
+  b = blockIdx.x; i = 0; l = 0;
+  if (b >= t.blocks0) {
     b -= t.blocks0;
     l = b / t.blocks_layer;
     b -= (int)l * t.blocks_layer;
     i = 1;
     while (i < 4 && b >= t.m[i].blocks) { b -= t.m[i].blocks; ++i; }
   }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) cast_transpose_k(CastTable t, const float* __restrict__ params, char* __restrict__ shadow) {
+  __shared__ float tile[32][33];
+  int b, i;
+  long long l;
+  cast_tile(t, b, i, l);
   const CastTable::Mat m = t.m[i];
   const float* src = params + m.poff + l * t.stride_p;
   T* dstW = sizeof(T) == 4 ? nullptr : (T*)(shadow + m.w + l * t.stride_s);
@@ -40,15 +46,72 @@ __global__ void __launch_bounds__(256) cast_transpose_k(CastTable t, const float
   }
 }
 
-hipError_t launch_cast_transpose(int dt, CastTable t, int layers, const float* params, char* shadow, hipStream_t s) {
+// The bf16 copies by 64 x 64 tiles, every access along a row of 128 bytes (rows of a multiple of 8 elements, 16-byte addresses): bound by
+// HBM.  TR: the transposes too, which only a backward reads.
+// us (32 x 32 tiles, two bytes a lane, always with the transposes / this way): ViT-B 192 / 121 (5.6 TB/s), without transposes 90; ViT-S 52 / 34.
+template <bool TR>
+__global__ void __launch_bounds__(256) cast_tiles_k(CastTable t, const float* __restrict__ params, char* __restrict__ shadow) {
+  constexpr int LD = 66;   // elements: an odd number of words
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) bf16 tile[64 * LD];
+  int b, i;
+  long long l;
+  cast_tile(t, b, i, l);
+  const CastTable::Mat m = t.m[i];
+  const float* src = params + m.poff + l * t.stride_p;
+  const int tc = (m.C + 63) / 64, c0 = b % tc * 64, r0 = b / tc * 64;
+  bf16* W = (bf16*)(shadow + m.w + l * t.stride_s);
+  const int lr = threadIdx.x >> 4, lc = (threadIdx.x & 15) * 4;
+  float4 v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = r0 + lr + 16 * k, c = c0 + lc;
+    v[k] = r < m.R && c < m.C ? *reinterpret_cast<const float4*>(src + (size_t)r * m.C + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = r0 + lr + 16 * k, c = c0 + lc;
+    const bf16x4 h = {(bf16)v[k].x, (bf16)v[k].y, (bf16)v[k].z, (bf16)v[k].w};
+    const u32x2 u = __builtin_bit_cast(u32x2, h);
+    if (r < m.R && c < m.C) *reinterpret_cast<u32x2*>(W + (size_t)r * m.C + c) = u;
+    if constexpr (TR) {
+      unsigned* q = reinterpret_cast<unsigned*>(tile + (lr + 16 * k) * LD + lc);
+      q[0] = u[0];
+      q[1] = u[1];
+    }
+  }
+  if constexpr (TR) {
+    bf16* WT = (bf16*)(shadow + m.wt + l * t.stride_s);
+    __syncthreads();
+    const int rr = (threadIdx.x & 7) * 8;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int cc = (threadIdx.x >> 3) + 32 * k;
+      bf16x8 h;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) h[j] = tile[(rr + j) * LD + cc];
+      if (c0 + cc < m.C && r0 + rr < m.R) *reinterpret_cast<u32x4*>(WT + (size_t)(c0 + cc) * m.R + r0 + rr) = __builtin_bit_cast(u32x4, h);
+    }
+  }
+}
+
+hipError_t launch_cast_transpose(int dt, CastTable t, int layers, const float* params, char* shadow, bool transposes, hipStream_t s) {
+  if (dt == DT_F32 && !transposes) return hipSuccess;
+  bool vec = dt == DT_BF16 && ((uintptr_t)params & 15) == 0 && ((uintptr_t)shadow & 15) == 0 && t.stride_p % 4 == 0 && t.stride_s % 16 == 0;
+  for (int i = 0; i < 5; ++i) vec = vec && t.m[i].R % 8 == 0 && t.m[i].C % 8 == 0 && t.m[i].poff % 4 == 0 && t.m[i].w % 16 == 0 && t.m[i].wt % 16 == 0;
+  const int side = vec ? 64 : 32;
   t.blocks_layer = 0;
   for (int i = 0; i < 5; ++i) {
-    t.m[i].blocks = ((t.m[i].C + 31) / 32) * ((t.m[i].R + 31) / 32);
+    t.m[i].blocks = ((t.m[i].C + side - 1) / side) * ((t.m[i].R + side - 1) / side);
     if (i) t.blocks_layer += t.m[i].blocks;
   }
   t.blocks0 = t.m[0].blocks;
   const dim3 grid((unsigned)(t.blocks0 + (long long)layers * t.blocks_layer));
-  if (dt == DT_F32) hipLaunchKernelGGL(cast_transpose_k<float>, grid, dim3(256), 0, s, t, params, shadow);
+  if (vec) {
+    if (transposes) hipLaunchKernelGGL(cast_tiles_k<true>, grid, dim3(256), 0, s, t, params, shadow);
+    else hipLaunchKernelGGL(cast_tiles_k<false>, grid, dim3(256), 0, s, t, params, shadow);
+  } else if (dt == DT_F32) hipLaunchKernelGGL(cast_transpose_k<float>, grid, dim3(256), 0, s, t, params, shadow);
   else hipLaunchKernelGGL(cast_transpose_k<bf16>, grid, dim3(256), 0, s, t, params, shadow);
   return hipGetLastError();
 }

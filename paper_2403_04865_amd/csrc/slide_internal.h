@@ -185,7 +185,8 @@ struct CastTable {
   long long stride_p, stride_s;
   int blocks0, blocks_layer;
 };
-hipError_t launch_cast_transpose(int dt, CastTable t, int layers, const float* params, char* shadow, hipStream_t s);
+// transposes: a backward follows
+hipError_t launch_cast_transpose(int dt, CastTable t, int layers, const float* params, char* shadow, bool transposes, hipStream_t s);
 // patches: [n * (g*g + lead)][3 P P], every tile's g*g patch rows behind `lead` rows of zeros
 hipError_t launch_patchify(int dt, const void* pixels, void* patches, long long n, int S, int P, hipStream_t s, int lead);
 // the inverse, from the same row layout (the `lead` rows of a tile are skipped)

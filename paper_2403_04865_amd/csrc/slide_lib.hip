@@ -221,7 +221,7 @@ const void* weight(const slide_ctx* c, int idx) {  // [out][in] in T
 }
 const void* weight_t(const slide_ctx* c, int idx) { return c->arena + c->sh[idx].wt; }  // [in][out] in T
 
-void cast_weights(Run& r) {
+void cast_weights(Run& r, bool transposes) {
   slide_ctx* c = r.c;
   CastTable t{};
   double elems = 0;
@@ -234,8 +234,8 @@ void cast_weights(Run& r) {
     t.stride_p = (long long)(c->sh[5].poff - c->sh[1].poff);
     t.stride_s = (long long)(c->sh[5].wt - c->sh[1].wt);
   }
-  launch(r, K_ELEMWISE, 0, elems * (4 + (c->dt == DT_BF16 ? 4 : 4)),
-         [&] { return launch_cast_transpose(c->dt, t, c->L, c->params, c->arena, r.s); });
+  launch(r, K_ELEMWISE, 0, elems * (c->dt == DT_BF16 && !transposes ? 6 : 8),
+         [&] { return launch_cast_transpose(c->dt, t, c->L, c->params, c->arena, transposes, r.s); });
 }
 
 // Slab partials that wait for their sum: kernels write them to room handed out here, the sums of as many results as fit the
@@ -575,9 +575,11 @@ void block_fwd(Run& r, const Layout& y, int l, long long n, bool replay, bool dg
 // ------------------------------------------------------------------------------------------
 // encoder forward
 // ------------------------------------------------------------------------------------------
-// cast: the low-precision and transposed weight copies are made first (false: an earlier pass of the same call has made them)
+// cast: the low-precision and transposed weight copies are made first (CAST_DONE: an earlier pass of the same call has made them;
+// CAST_FWD: without the transposes, which only a backward reads)
+enum { CAST_DONE, CAST_FWD, CAST_ALL };
 int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool save, long long pool_N,
-            hipStream_t s, bool cast = true) {
+            hipStream_t s, int cast) {
   if (c->pool_only) return SLIDE_EUNSUPPORTED;
   int keep = !save ? KEEP_NONE : (c->cfg.recompute ? KEEP_INPUTS : KEEP_ALL);
   Layout y = make_layout(c, n, pool_N, keep);
@@ -587,7 +589,7 @@ int enc_fwd(slide_ctx* c, const void* pixels, long long n, void* feats_out, bool
   Run r{c, s};
   char* ar = c->arena;
   int D = c->D, T = c->T, dt = c->dt;
-  if (cast) cast_weights(r);
+  if (cast != CAST_DONE) cast_weights(r, cast == CAST_ALL);
   launch(r, K_ELEMWISE, 0, 2.0 * n * 3 * c->cfg.tile * c->cfg.tile * elem_size(dt),
          [&] { return launch_patchify(dt, pixels, ar + y.e_patches, n, c->cfg.tile, c->cfg.patch, s, T - c->g2); });
   // the patch matrix has the token matrix's rows (a row of zeros in each tile's CLS slot): its weight gradient is
@@ -1031,7 +1033,7 @@ int encoder_fwd_tiles(slide_ctx* c, const void* pixels, int64_t n, void* feats_o
   int rc = check_bound(c);
   if (rc) return rc;
   if (!pixels || !feats_out || n <= 0) return SLIDE_EINVAL;
-  return enc_fwd(c, pixels, n, feats_out, save != 0, n, (hipStream_t)stream);
+  return enc_fwd(c, pixels, n, feats_out, save != 0, n, (hipStream_t)stream, save ? CAST_ALL : CAST_FWD);
 }
 
 int encoder_bwd_tiles(slide_ctx* c, const void* dfeats, int64_t n, int accumulate, void* pixel_grad, void* stream) {
@@ -1118,7 +1120,7 @@ int slide_step_fwd(slide_ctx* c, const void* pixels, int64_t N, int32_t label, f
   if (label < 0 || label >= (c->C == 1 ? 2 : c->C)) return SLIDE_EINVAL;
   Layout y = make_layout(c, N, N, c->cfg.recompute ? KEEP_INPUTS : KEEP_ALL);
   if (y.total > c->arena_bytes) return SLIDE_EARENA;
-  rc = enc_fwd(c, pixels, N, c->arena + y.p_H, true, N, (hipStream_t)stream);
+  rc = enc_fwd(c, pixels, N, c->arena + y.p_H, true, N, (hipStream_t)stream, CAST_ALL);
   if (rc) return rc;
   rc = pool_fwd(c, y, c->arena + y.p_H, N, label, loss, logits, alpha, (hipStream_t)stream);
   if (rc) { c->enc_saved = false; return rc; }
@@ -1168,7 +1170,7 @@ int slide_step_chunked(slide_ctx* c, const void* pixels, int64_t N, int64_t chun
   // and the aggregator in between works in its own part of the arena (1100 ViT-S tiles in chunks of 384: 67.4 -> 61.8 ms)
   auto chunk_fwd = [&](int64_t t0, bool save, bool cast) {
     const int64_t n = N - t0 < chunk_tiles ? N - t0 : chunk_tiles;
-    return enc_fwd(c, (const char*)pixels + t0 * tile_bytes, n, H + t0 * row_bytes, save, N, s, cast);
+    return enc_fwd(c, (const char*)pixels + t0 * tile_bytes, n, H + t0 * row_bytes, save, N, s, cast ? CAST_ALL : CAST_DONE);
   };
   const int64_t last = (N - 1) / chunk_tiles * chunk_tiles;
   for (int64_t t0 = last; t0 >= 0; t0 -= chunk_tiles)
