@@ -1,6 +1,6 @@
 // bf16 MFMA weight-gradient GEMM for gfx950, small and medium M: C[N1,N2] = sum_m A[m,N1]^T B[m,N2] (fp32 partials).
 //
-// The large-M kernel (gemm_tn_big.hip) takes whole slides; this one bags of up to a few dozen tiles, the CLS rows of the
+// The large-M kernel (gemm_tn_big.hip) takes whole slides; this one bags of up to some 240 tiles, the CLS rows of the
 // last block, narrow encoders and the aggregator.  128 x 128 of the result per workgroup (4 wavefronts as 2 x 2), M split
 // into slabs.  A 32-row step moves 16 KB for 256 clocks of MFMAs, the 64 bytes a clock that a compute unit gets from its
 // L2, and one trip there takes thousands of clocks: what bounds the kernel is how much a compute unit keeps in flight.
@@ -24,6 +24,7 @@ namespace sl {
 
 namespace {
 
+constexpr long long SLOTS = 1024, CHAIN = 5280;   // workgroups of a round of the chip; rows of a slab
 constexpr int BT = 128, BK = 32, STAGE = BK * 2 * BT;   // bf16 elements: [32 rows][128 columns] of A, then of B
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -178,8 +179,11 @@ bool gemm_tn_mfma_ok(const GemmTN& g) {
 // Rows of a slab, for problems that run as one launch: about two workgroups per compute unit over all of them, no slab of less
 // than 128 rows (64 where there are only a few tiles), since every slab's result is written and read again.  M = 7289, 384 x
 // 1536 alone (36 tiles), us: 4 slabs 33, 8 22.8, 11 22.4, 15 22.8, 29 28.3; 384 x 384: 15 slabs 12.6, 29 10.7, 57 11.9; M =
-// 1000, 1536 x 384: 8 slabs 8.7, 16 10.4.  Step of 37 ViT-S tiles, the four problems of a block together, by workgroups: 256 3.79
-// ms, 384 3.70, 512 3.69, 768 3.72, 1024 3.84; each problem on its own 3.86.
+// 1000, 1536 x 384: 8 slabs 8.7, 16 10.4.  Step of 37 ViT-S tiles, the four problems of a block together, by workgroups: 384 3.24
+// ms, 512 3.19, 768 3.21.
+// From 1,400 rows in each on as many slabs as fill whole rounds of the four workgroups that a unit holds, of 5,280 rows at most (a
+// slab is one chain of float32 additions).  ViT-S steps, ms, by two a unit / this way: 80 tiles 5.07 / 4.99, 135 7.85 / 7.67, 200 10.79 /
+// 10.49; ten slabs of 108 tiles (1,080 workgroups) 13.9 at 256 tiles, where eighteen take 12.98.
 void gemm_tn_mfma_slabs(GemmTN* g, int n, int max_slabs) {
   long long work = 0, tiles = 0;   // rows x tiles
   for (int i = 0; i < n; ++i) {
@@ -189,6 +193,15 @@ void gemm_tn_mfma_slabs(GemmTN* g, int n, int max_slabs) {
   }
   long long per = (work + 511) / 512, least = tiles <= 8 ? 64 : 128;
   if (per < least) per = least;
+  const long long rows = work / tiles;
+  for (long long r = 1; r <= 8; ++r) {   // rounds
+    const long long slabs = SLOTS * r / tiles;
+    if (slabs < 1) continue;
+    const long long p = (rows + slabs - 1) / slabs;
+    if (r == 1 && p < 1400) break;
+    per = p;
+    if (p <= CHAIN) break;
+  }
   for (int i = 0; i < n; ++i) {
     long long s = (g[i].M + per - 1) / per;
     if (s > max_slabs) s = max_slabs;

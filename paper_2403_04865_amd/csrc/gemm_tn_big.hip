@@ -323,9 +323,10 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
 // Shapes this kernel takes: identity row maps, an output that the tiles cover exactly with A on the side tiled by 128 (no
-// column is masked in the kernel), slabs short enough for 32-bit offsets, and enough work: below 72,000 rows x tiles (a
-// tenth of a round of the chip spent in prologue and partial results) the 128 x 128 kernel is the faster one.  M = 15,000, us,
-// this / that: 384 x 1536 29 / 38, 1152 x 384 24 / 32, 384 x 384 (3 tiles) 15.6 / 15.9; M = 7289: 20 / 22, 18.5 / 19.4, 13 / 10.7.
+// column is masked in the kernel), slabs short enough for 32-bit offsets, and enough work: below 48,000 rows and 200,000 rows x tiles the 128 x 128 kernel
+// is the faster one (its two workgroups a unit start and drain beside each other, and 128 columns on both sides leave no unit idle where 128 x 384 make
+// a round and a half).  Training steps of the aggregator, this / that: 512 x 384, 32,768 rows 185 / 182 us, 45,056 228 / 217, 65,536 292 / 302, 256 x 384
+// 45,056 137 / 135, 65,536 165 / 166, 90,000 228 / 236; ViT blocks: gemm_tn in slide_lib.hip.
 // Returns the number of slabs it will use (0: not taken).  Per XCD, spx slabs x tiles items over 32 workgroups: a round of
 // items takes its rows (12.5 ns each) and about 18 us of prologue, drain and partial results, a slab's partial result is read
 // again by the sum over the slabs at 4 to 5 TB/s.  M = 65,404, 384 x 1536 (12 tiles): spx = 1 144 us, 2 (one round) 95, 3 138, 8
@@ -336,7 +337,7 @@ int gemm_tn_big_slabs(const GemmTN& g, int max_slabs) {
   if ((long long)g.N1 * g.N2 >= (1LL << 31)) return 0;
   if (g.N1 % BX || g.N2 % BY) return 0;
   const int tiles = (g.N1 / BX) * (g.N2 / BY);
-  if (g.M * tiles < 72000) return 0;
+  if (g.M < TN_BIG_ROWS && g.M * tiles < 200000) return 0;
   int spx = 1;
   double best = 0.0;
   for (int c = 1; c <= 32 && 8 * c <= max_slabs; ++c) {

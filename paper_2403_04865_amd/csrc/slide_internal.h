@@ -164,6 +164,7 @@ struct GemmTN {
   float* cs_part;  // optional: column sums of A per slab, [slabs][N1] (only the MFMA kernels fill it)
   int big;         // use the large-M kernel (slabs was chosen by gemm_tn_big_slabs)
 };
+constexpr long long TN_BIG_ROWS = 48000;   // fewer: the 128 x 128 kernel
 int gemm_tn_big_slabs(const GemmTN& g, int max_slabs);   // 0: the large-M kernel does not take this problem
 // the 128 x 128 kernel, which takes several problems in one launch
 constexpr int TN_GROUP_MAX = 4;

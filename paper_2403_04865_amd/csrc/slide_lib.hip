@@ -338,10 +338,11 @@ void gemm_tn(Sums& q, const void* A, long long lda, const void* B, long long ldb
   g.cs_part = nullptr;
   g.big = 0;
   size_t fit = (q.cap - 64) / ((size_t)N1 * N2 + N1);
-  // Together up to 900,000 rows x 128 x 384 tiles of a block's four problems (25,000 rows at D = 384), beyond which the
-  // large-M kernel is the faster one on each.  Step of 90 ViT-S tiles (17,730 rows): 6.78 ms together, 6.83 with the large-M kernel.
-  const long long block_tiles = (4LL * r.c->D * r.c->D + 2LL * r.c->D * r.c->F) / (128 * 384);
-  if (wait && M * block_tiles < 900000 && dt == DT_BF16 && r.c->use_mfma && gemm_tn_mfma_ok(g)) {
+  // A block's four problems together up to 48,000 rows and 16 million rows x 128 x 128 tiles, beyond which the large-M kernel is the faster one
+  // on each.  Steps, ms, that / together: ViT-S of 135 tiles (26,595 rows) 8.17 / 7.67, 225 12.13 / 11.70, 256 13.01 / 12.98, 300 14.54 / 14.57;
+  // ViT-B of 32 (6,304 rows) 7.67 / 6.52, 100 16.23 / 15.45, 150 22.41 / 22.17, 200 28.87 / 28.96.
+  const long long block_tiles = (4LL * r.c->D * r.c->D + 2LL * r.c->D * r.c->F) / (128 * 128);
+  if (wait && M < TN_BIG_ROWS && M * block_tiles < 16000000 && dt == DT_BF16 && r.c->use_mfma && gemm_tn_mfma_ok(g)) {
     if (q.ngroup == TN_GROUP_MAX) run_group(q);
     q.later[q.ngroup] = {out, bias_out, accumulate};
     q.group[q.ngroup++] = g;
