@@ -298,14 +298,15 @@ __device__ __forceinline__ void ln_fwd_rows16(const bf16* __restrict__ x, long l
 #pragma unroll
       for (int e = 0; e < 8; ++e) sum += v[k][e];
     }
-    const float mean = ln_mean(sum16(sum), D);
+    sum = sum16(sum);
     float sq = 0.f;
 #pragma unroll
     for (int k = 0; k < NP; ++k)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        v[k][e] -= mean;
-        sq = fmaf(v[k][e], v[k][e], sq);
+        v[k][e] = ln_centre(v[k][e], sum, D);
+        if (k == 0 && e == 1) sq = ln_squares(v[0][0], v[0][1]);
+        else if (k + e > 0) sq = fmaf(v[k][e], v[k][e], sq);
       }
     const float rstd = ln_rstd(sum16(sq), D, eps);
     if (r < rows) {

@@ -345,7 +345,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
         for (int e = 0; e < 8; ++e) s[j] += v[e];
       }
     }
-    const float mean = ln_mean(total(s), D);
+    const float sum = total(s);
     again();
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -354,10 +354,11 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
       for (int i = 0; i < 3; ++i) {
         un(j + 8 * i, v);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float d = v[e] - mean;
-          s[j] = fmaf(d, d, s[j]);
-        }
+        for (int e = 0; e < 8; ++e) v[e] = ln_centre(v[e], sum, D);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (i > 0 || e > 1) s[j] = fmaf(v[e], v[e], s[j]);
+          else if (e == 1) s[j] = ln_squares(v[0], v[1]);
       }
     }
     const float rstd = ln_rstd(total(s), D, g.eps);
@@ -372,7 +373,7 @@ __global__ void __launch_bounds__(NTH, 1) mlp_k(MlpArgs g, int tiles) {
         *reinterpret_cast<f32x4*>(gb + 8 + 4 * q) = *reinterpret_cast<const f32x4*>(lbet + k * 16 + half * 8 + 4 * q);
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) U[k][e] = (bf16)fmaf((v[e] - mean) * rstd, gb[e], gb[8 + e]);
+      for (int e = 0; e < 8; ++e) U[k][e] = (bf16)fmaf(ln_centre(v[e], sum, D) * rstd, gb[e], gb[8 + e]);
       __builtin_amdgcn_sched_barrier(0);
     }
   };

@@ -227,18 +227,12 @@ struct MlpArgs {
 bool mlp_ok(const MlpArgs& g, int D, bool grad);
 hipError_t launch_mlp(const MlpArgs& g, bool grad, hipStream_t s);
 
-// mean and 1 / deviation from a row's sums, in one form wherever a forward LayerNorm is taken: results are made opaque, so that no
-// caller's next operation swallows a rounding
-__device__ __forceinline__ float ln_mean(float sum, int D) {
-  float m = sum * (1.0f / (float)D);
-  asm volatile("" : "+v"(m));
-  return m;
-}
-__device__ __forceinline__ float ln_rstd(float sq, int D, float eps) {
-  float r = 1.0f / sqrtf(fmaf(sq, 1.0f / (float)D, eps));
-  asm volatile("" : "+v"(r));
-  return r;
-}
+// The arithmetic of the forward LayerNorm on rows of 384 and 768 columns, in one form wherever it is taken, with every fused operation
+// written out (left to the compiler, which products it fuses changes from one kernel to the next): an element less its row's mean,
+// whose product is not rounded; a lane's first two squares; 1 / deviation
+__device__ __forceinline__ float ln_centre(float x, float sum, int D) { return fmaf(sum, -1.0f / (float)D, x); }
+__device__ __forceinline__ float ln_squares(float a, float b) { return fmaf(a, a, b * b); }
+__device__ __forceinline__ float ln_rstd(float sq, int D, float eps) { return 1.0f / sqrtf(fmaf(sq, 1.0f / (float)D, eps)); }
 
 // LayerNorm.  x rows at x + r*x_stride (RS), out rows at out + r*out_stride (T, or fp32 when out_f32).
 hipError_t launch_ln_fwd(int dt, const void* x, long long x_stride, const float* gam, const float* bet, void* out,
