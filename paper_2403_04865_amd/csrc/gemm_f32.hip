@@ -137,11 +137,13 @@ __global__ void __launch_bounds__(256 * KG, BM + BN == 192 ? 3 : 4) gemm_nt_f32_
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma nounroll
-        for (int k = grp * 8; k < g.K; k += 8 * KG) {
-          const f32x4 u = *reinterpret_cast<const f32x4*>(pa + k), v = *reinterpret_cast<const f32x4*>(pb + k);
+        for (int kt = grp; kt < nk; kt += KG)   // this group's steps and no others: the other groups' blocks stand as they are
+#pragma nounroll
+          for (int k = kt * BK; k < kt * BK + BK; k += 8) {
+            const f32x4 u = *reinterpret_cast<const f32x4*>(pa + k), v = *reinterpret_cast<const f32x4*>(pb + k);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], u[e], acc[i][j], 0, 0, 0);
-        }
+            for (int e = 0; e < 4; ++e) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], u[e], acc[i][j], 0, 0, 0);
+          }
       }
   }
 

@@ -67,3 +67,45 @@ def test_products_that_are_infinite(tiles):
     assert bool((x == key).all())
     first = rows[last - 3 * cfg.dim:last].reshape(3, cfg.dim).cpu().numpy()
     assert np.isposinf(first[0]).all() and np.isposinf(first[1]).all() and np.isnan(first[2]).all()
+
+
+# One operand that is no finite number, in a column of each group of wavefronts that K is dealt to (two groups: columns 0 .. 31, 64 .. 95, ...
+# are the first one's; four: 0 .. 31, 128 .. 159, ...), in blocks of 64 rows of their own, dense weights: its row has what float32
+# products give, every other row what it has anyway.  Patch embedding of ViT-S, K = 768: 1 tile takes 32 x 32 blocks, 5 four groups, 20
+# two, 65 one, 70 the 64 x 128 tiles.
+@pytest.mark.parametrize("tiles", [1, 5, 20, 65, 70])
+def test_rows_beside_one_that_is_not_finite(tiles):
+    from slide_harness import GpuSlide
+    cfg = replace(gen.CONFIGS["small"][0], layers=0)
+    ds, ws, _ = gen.SEEDS["small"]
+    prm = gen.make_params(cfg, ws, perturbed=True)
+    X = gen.make_pixels(cfg, tiles, ds)
+    P, g2, bad = cfg.patch, cfg.grid ** 2, {}
+    for i, col in enumerate([0, 33, 40, 70, 100, 135, 200, 767][:max(3, tiles)]):
+        row = 5 + 64 * i   # of the patch matrix; a patch is [3][P][P]
+        n, j, (c, y, x) = row // g2, row % g2, np.unravel_index(col, (3, P, P))
+        X[n, c, j // cfg.grid * P + y, j % cfg.grid * P + x] = bad[row] = (np.inf, np.nan, -np.inf)[i % 3]
+    print(f"case rows beside one that is not finite n={tiles}", flush=True)
+    g = GpuSlide(cfg, prm, 0, tiles)
+    torch = g.torch
+    px = g.to_dev(X)
+    g.lib.encoder_fwd_tiles(px, tiles, torch.zeros((tiles, cfg.dim), device=g.dev), 1)
+    torch.cuda.synchronize()
+    # the stream behind the embedding: the arena's tensor whose first row is class token and position
+    mem = g.arena[:g.arena.numel() // 256 * 256].view(torch.float32)
+    key = torch.from_numpy(prm["cls"].reshape(-1) + prm["pos"][0]).to(g.dev)
+    near = (mem.view(-1, 64) == key[:64]).all(1).nonzero().flatten().tolist()
+    near = [o * 64 for o in near if bool((mem[o * 64:o * 64 + cfg.dim] == key).all())]
+    got = mem[near[0]:near[0] + tiles * cfg.tokens * cfg.dim].view(tiles, cfg.tokens, cfg.dim)[:, 1:].double().cpu().numpy().reshape(-1, cfg.dim)
+    p = X.astype(np.float64).reshape(tiles, 3, cfg.grid, P, cfg.grid, P).transpose(0, 2, 4, 1, 3, 5).reshape(tiles * g2, -1)
+    with np.errstate(invalid="ignore"):
+        want = p @ prm["pe.W"].astype(np.float64).T + prm["pe.b"] + np.tile(prm["pos"][1:], (tiles, 1))
+    for row in bad:
+        w = prm["pe.W"][:, int(np.flatnonzero(~np.isfinite(p[row]))[0])]
+        assert np.array_equal(got[row], bad[row] * np.sign(w), equal_nan=True), (row, got[row][:4])
+    rest = np.setdiff1d(np.arange(tiles * g2), list(bad))
+    # a row's products are off by 2^-24 each, its 768 additions by as much of a partial sum: 2 sqrt(768) 2^-24 = 3.3e-6 of the terms' norm
+    norm = np.sqrt((p[rest] ** 2) @ (prm["pe.W"].astype(np.float64) ** 2).T) + np.abs(want[rest])
+    err = np.abs(got[rest] - want[rest]) / norm
+    print("worst", err.max(), flush=True)
+    assert err.max() < 4e-6
