@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g_k(PoolArgs p, const bf16* __re
   long long gi = blockIdx.x;
   const long long st = gridDim.x;
   issue(gi);
-  pool_head_grads(p, (gridDim.x - 1 - blockIdx.x) * 256 + tid, gridDim.x * 256);
+  pool_head_grads(p);
   {
     const float* dz = p.scal + pool_z_off(p.C) + D;
     u32x4 a[NT][KS];   // all requested before the first is waited for
@@ -429,7 +429,7 @@ __global__ void __launch_bounds__(256) pool_bwd_g2_k(PoolArgs p, const bf16* __r
   long long gi = blockIdx.x >> 1;
   const long long st = gridDim.x >> 1;
   static_for<0, CH + 1>([&](auto ic) __attribute__((always_inline)) { issue_one(gi, ic); });
-  pool_head_grads(p, (gridDim.x - 1 - blockIdx.x) * 256 + tid, gridDim.x * 256);
+  pool_head_grads(p);
   bf16x8 wt[NT][KS];
   float dzr[NT];
   {

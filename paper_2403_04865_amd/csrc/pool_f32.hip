@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __r
   const bool ok = n < p.N;
   const int d = blockIdx.y * 32 + li, dc = d < D ? d : D - 1;
   const float* drow = Dp + (ok ? n : p.N - 1) * K;
-  pool_head_grads(p, ((gridDim.x - 1 - blockIdx.x) * gridDim.y + blockIdx.y) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
+  pool_head_grads(p);
   f32x16 acc = zero16();
   for (int c0 = wave; c0 < nc; c0 += 4 * UG) {
     f32x4 g[UG];
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(256, 3) pool_dgate_split_k(PoolArgs p, float* 
 __global__ void __launch_bounds__(256, 3) pool_g_split_k(PoolArgs p, const float* __restrict__ Dp, int MT, int NT) {
   constexpr int ROWS = SBM + SPB;
   __shared__ __attribute__((aligned(16))) bf16 st[3 * ROWS * SPLIT_BK];
-  pool_head_grads(p, (gridDim.x - 1 - blockIdx.x) * 256 + threadIdx.x, gridDim.x * 256);
+  pool_head_grads(p);
   int mt, nt;
   if (!split_tile(MT, NT, mt, nt)) return;
   const int D = p.D, Mh = p.Mh, K = 2 * Mh, nk = K / SPLIT_BK;
@@ -613,7 +613,7 @@ __global__ void __launch_bounds__(256) pool_wide_g_k(PoolArgs p, const float* __
   extern __shared__ float dl[];   // [WR][2 Mh]
   const int D = p.D, Mh = p.Mh;
   const long long n0 = (long long)blockIdx.x * WR;
-  pool_head_grads(p, ((gridDim.x - 1 - blockIdx.x) * gridDim.y + blockIdx.y) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
+  pool_head_grads(p);
   for (int i = threadIdx.x; i < WR * 2 * Mh; i += 256) dl[i] = n0 * 2 * Mh + i < p.N * 2 * Mh ? Dp[n0 * 2 * Mh + i] : 0.f;
   __syncthreads();
   const int d = blockIdx.y * 256 + threadIdx.x;

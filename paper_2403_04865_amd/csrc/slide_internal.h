@@ -287,13 +287,20 @@ struct PoolArgs {
   int fwd_only;       // no backward will read the scalars behind the logits
   unsigned* ticket;   // arrival counter of the combine kernel's workgroups, cleared by the kernels of stage 1
 };
-// head.W grad = dy z^T, head.b grad = dy: elements i, i + stride, ...; rides in the kernels that write G (as a launch of its own 4.5 us of
-// 262 at 45,056 rows)
-__device__ __forceinline__ void pool_head_grads(const PoolArgs& p, int i, int stride) {
+// A thread's elements first, first + step, ... of something that rides in a launch of 256 threads a workgroup, its last workgroups first.  64
+// bits: a launch of a workgroup per 32 rows and 32 features has 2^31 threads at 2^33 features (8.4 million rows of 1024).
+struct Share { long long first, step; };
+__host__ __device__ inline Share wg_share(unsigned x, unsigned y, unsigned grid_x, unsigned grid_y, unsigned thread) {
+  return {((long long)(grid_x - 1 - x) * grid_y + y) * 256 + thread, (long long)grid_x * grid_y * 256};
+}
+// head.W grad = dy z^T, head.b grad = dy; rides in the kernels that write G (as a launch of its own 4.5 us of 262 at 45,056 rows)
+__device__ __forceinline__ void pool_head_grads(const PoolArgs& p) {
   const int D = p.D, C = p.C;
   const float* dy = p.scal + 4 + C;
   const float* z = p.scal + pool_z_off(C);
-  for (; i < C * (D + 1); i += stride) {
+  const Share sh = wg_share(blockIdx.x, blockIdx.y, gridDim.x, gridDim.y, threadIdx.x);
+  for (long long n = sh.first; n < C * (D + 1); n += sh.step) {
+    const int i = (int)n;
     const bool w = i < C * D;
     const float v = w ? dy[i / D] * z[i % D] : dy[i - C * D];
     float* g = p.grads + (w ? p.ocW + i : p.ocb + (i - C * D));
