@@ -560,15 +560,20 @@ hipError_t go_reg(const PoolArgs& p, const bf16* vu, hipStream_t s, int halves =
   return hipGetLastError();
 }
 
-// M_h = 256 as two passes over the rows (the features are read twice, against the weights streaming from L2 for every block of rows in
-// a one-pass kernel, which took the calls below 32,768 rows before: serving 16,384 rows 36.8 us, as two launches 31.0).  Where both halves
-// fit the chip side by side (up to 4,096 rows) they run so and leave their partial logits, and the softmax partials are a launch
-// of their own: serving 1,037 rows 29.6 -> 21.9 us, 4,096 28.9 -> 23.0.
+// M_h = 256.  Below 32,768 rows both halves of the gate units run side by side, 128 workgroups each, and leave their partial logits; the
+// softmax partials are a launch of their own, with the largest logit as the shift and the weighted sum in float64.  From there on both
+// halves are passes of one launch over the rows, with the logits' bound as the shift and a lane's sums in float32: faster, but the softmax weights
+// are off by 1.3e-7 instead of 0.4e-7 (operands on the bf16 grid, against 64 bits), so it does not go below the line from which on it has
+// always been so.  us, side by side / one launch: serving 1,037 rows 21.5 / 29.6, 4,096 22.7 / 24.6, 8,192 26.2 / 25.6, 16,384 33.5 / 29.0,
+// 32,000 45.5 / 40.2; training step 16,384 141 / 130, 32,000 192 / 178.  (With the weights streaming from L2 for every block of rows:
+// serving 16,384 rows 36.1, 32,000 63; training 166 and 253.)
+constexpr long long SIDE_BY_SIDE_ROWS = 32768;
 hipError_t go_reg_halves(PoolArgs& p0, hipStream_t s) {
   PoolArgs p = p0;
   p.Mh = FRAG_MH;
-  if (p.N <= 4096 && (size_t)p.N * 2 <= p.a_room) {
+  if (p.N < SIDE_BY_SIDE_ROWS && (size_t)p.N * 2 <= p.a_room) {
     p.partial = 1;
+    if (p.blocks > 128) p.blocks = 128;   // half of the chip each
     p.a = p0.a_tmp;
     hipError_t e = go_reg<1>(p, (const bf16*)p0.vub, s, 2);
     if (e != hipSuccess) return e;
