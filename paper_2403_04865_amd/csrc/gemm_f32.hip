@@ -4,13 +4,17 @@
 //
 // The float32 form of the MFMA does 256 flops a clock and compute unit, a sixteenth of the bf16 rate, and bounded these products
 // (105 of the 140 TFLOP/s that it sustains).  So an operand is cut into three bf16 terms of eight bits, whose sum it is exactly, and
-// of the nine products of terms the six that reach the 24th bit are added in float32: 2.7 times the rate.  What is left out is below
-// 2^-23 of a product, and there are fewer additions: against 64 bits the results are 0.86 as far off as the float32 MFMA's
-// (K = 384 .. 1536: 3.0e-7 .. 6.1e-7, 3.5e-7 .. 7.0e-7 before; sums over M = 12,017 rows in 14 slabs 4.8e-7, 4.9e-7 in 16).
+// six of the nine products of terms are added in float32: 2.7 times the rate.  What is left out is at most 2^-24 of a product and of either
+// sign (terms that are cut off instead of rounded leave out up to 2^-21, always of the product's own sign: sums of positive numbers came out
+// 1.35 times as far off as the float32 MFMA's).  Errors against 64 bits, this / the float32 MFMA, normal operands: K = 384 1.1e-7 to 2.9e-7 (by how
+// many groups K is dealt to) / 3.5e-7, K = 1536 2.1e-7 to 4.3e-7 / 7.0e-7, sums over M = 12,017 rows 4.8e-7 in 14 slabs / 4.9e-7 in 16; positive
+// operands 0.6e-7 to 2.4e-7 / 3.0e-7, 0.8e-7 to 2.2e-7 / 6.0e-7, 0.94e-7 / 1.10e-7; geometric means of the ratio over the encoder's shapes 0.54
+// (NT) and 0.88 (TN), positive 0.36 and 0.90.  (The bf16 MFMA adds a step's products with a slight pull downwards: results are 3e-8 to 2e-7 of
+// their mean size low.)
 // Operands are cut once per workgroup, on their way through registers into LDS, the next step's loads in flight meanwhile; the
 // vector work of one workgroup (a fifth to a third of the MFMAs' clocks) hides behind the MFMAs of the others, of which three to six fit a
 // compute unit with one stage each (two stages and half the workgroups were a quarter slower).  us, before / now: M = 12,017: N = 1536, K = 384
-// 130 / 91 (155 TFLOP/s, 0.93 PFLOP/s of bf16), N = 384, K = 1536 130 / 102, weight gradient 1536 x 384 136 / 88.
+// 122 / 90 (158 TFLOP/s, 0.95 PFLOP/s of bf16), N = 384, K = 1536 123 / 100, weight gradient 1536 x 384 132 / 84.
 #include "gemm_epi.h"
 #include "lds_dma.h"
 #include "split_f32.h"

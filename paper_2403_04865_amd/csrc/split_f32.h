@@ -14,30 +14,28 @@ __device__ __forceinline__ void step_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Eight floats as three bf16 vectors whose sum they are, bit for bit: each takes the next eight significant bits (cut off, not
-// rounded, so that the largest finite float stays finite).
+// Eight floats as three bf16 vectors whose sum they are, bit for bit, from 2^-110 in size on (a trailing term ends at 2^-133).  Each term is
+// the rest rounded to nearest, so that the next one is at most half a unit of its last place and has either sign.  (A float that rounds up to
+// an infinite leading term has no trailing ones: not_finite.)
 struct Split { bf16x8 t[3]; };   // leading, middle, trailing bits
-__device__ __forceinline__ Split split8(const float (&x)[8]) {
-  unsigned w[3][4];
+__host__ __device__ __forceinline__ Split split8(const float (&x)[8]) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 w[3];
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    float a = x[2 * p], b = x[2 * p + 1];
+    f32x2 v = {x[2 * p], x[2 * p + 1]};
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
-      w[i][p] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);   // the upper halves of b and a
-      if (i < 2) {
-        a -= __uint_as_float(ua & 0xffff0000u);
-        b -= __uint_as_float(ub & 0xffff0000u);
-      }
+      w[i][p] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+      v[0] -= __builtin_bit_cast(float, w[i][p] << 16);
+      v[1] -= __builtin_bit_cast(float, w[i][p] & 0xffff0000u);
     }
   }
   Split s;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    s.t[i] = __builtin_bit_cast(bf16x8, u32x4{w[i][0], w[i][1], w[i][2], w[i][3]});
-  }
+  for (int i = 0; i < 3; ++i) s.t[i] = __builtin_bit_cast(bf16x8, w[i]);
   return s;
 }
 // A step's operands in LDS: 3 planes (terms) of ROWS rows of 32 bf16; the 16-byte pieces of a row are slot-permuted (piece c of row R
@@ -54,7 +52,7 @@ __device__ __forceinline__ Split get_split(const bf16* s, int row, int piece) {
   for (int i = 0; i < 3; ++i) v.t[i] = *reinterpret_cast<const bf16x8*>(s + (i * ROWS + row) * SPLIT_BK + (piece ^ ((row >> 2) & 3)) * 8);
   return v;
 }
-// the six of the nine products of terms that reach the 24th bit, the smallest first
+// the six of the nine products of terms that are taken, the smallest first: what is left out is at most 2^-24 of a product and of either sign
 constexpr int TERM_A[6] = {0, 2, 1, 0, 1, 0}, TERM_B[6] = {2, 0, 1, 1, 0, 0};
 // whether a wavefront's results are anything but finite numbers: an infinite operand (whose other terms are no numbers, where the
 // product of floats may be infinite) or an overflow.  Such blocks are taken again, in float32 products.
