@@ -107,8 +107,7 @@ __global__ void __launch_bounds__(256 * KG, BM + BN == 192 ? 3 : 4) gemm_nt_f32_
   auto store = [&](bf16* s) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NU; ++j)
-      put_split<ROWS>(s, j * 64 + (tid >> 2), tid & 3,
-                      split8({x[j][0][0], x[j][0][1], x[j][0][2], x[j][0][3], x[j][1][0], x[j][1][1], x[j][1][2], x[j][1][3]}));
+      put_split<ROWS>(s, j * 64 + (tid >> 2), tid & 3, j < BM / 64 ? split_of<true>(x[j][0], x[j][1]) : split_of<false>(x[j][0], x[j][1]));
   };
   f32x16 acc[WBM][WBN];
 #pragma unroll
@@ -129,7 +128,9 @@ __global__ void __launch_bounds__(256 * KG, BM + BN == 192 ? 3 : 4) gemm_nt_f32_
     step_barrier();
     if (kt < nk) mul_step<ROWS>(st, oa, ob, half, acc);
   }
-  if (not_finite(acc)) {
+  if (!not_finite(acc)) {
+    scale_down(acc);
+  } else {
 #pragma unroll
     for (int i = 0; i < WBM; ++i)
 #pragma unroll
@@ -213,13 +214,15 @@ __global__ void __launch_bounds__(64 * SW) gemm_nt_f32_few_k(GemmNT g, int NTL) 
 #pragma unroll
     for (int u = 0; u < SU; ++u)
       if (c0 + u * W < nk) {
-        const Split fa = split8({x[u][0][0], x[u][0][1], x[u][0][2], x[u][0][3], x[u][1][0], x[u][1][1], x[u][1][2], x[u][1][3]});
-        const Split fb = split8({y[u][0][0], y[u][0][1], y[u][0][2], y[u][0][3], y[u][1][0], y[u][1][1], y[u][1][2], y[u][1][3]});
+        const Split fa = split_of<true>(x[u][0], x[u][1]);
+        const Split fb = split_of<false>(y[u][0], y[u][1]);
 #pragma unroll
         for (int t = 0; t < 6; ++t) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb.t[TERM_B[t]], fa.t[TERM_A[t]], acc[0][0], 0, 0, 0);
       }
   }
-  if (not_finite(acc)) {
+  if (!not_finite(acc)) {
+    scale_down(acc);
+  } else {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
 #pragma nounroll
@@ -321,8 +324,8 @@ __global__ void __launch_bounds__(256, TB == 128 ? 3 : 4) gemm_tn_f32_k(GemmTN g
     for (int j = 0; j < NU / 2; ++j) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) c += x[j][e];
-      put_split<ROWS>(s, col, grp + j * GS, split8(x[j]));
-      put_split<ROWS>(s, TB + col, grp + j * GS, split8(x[NU / 2 + j]));
+      put_split<ROWS>(s, col, grp + j * GS, split8<true>(x[j]));
+      put_split<ROWS>(s, TB + col, grp + j * GS, split8<false>(x[NU / 2 + j]));
     }
     cs0 += odd ? 0.f : c;
     cs1 += odd ? c : 0.f;
@@ -349,7 +352,9 @@ __global__ void __launch_bounds__(256, TB == 128 ? 3 : 4) gemm_tn_f32_k(GemmTN g
       g.cs_part[(size_t)slab * g.N1 + i0 + tid] = c;
     }
   }
-  if (not_finite(acc)) {
+  if (!not_finite(acc)) {
+    scale_down(acc);
+  } else {
 #pragma unroll
     for (int i = 0; i < WB; ++i)
 #pragma unroll

@@ -322,9 +322,6 @@ __device__ __forceinline__ void split_mul(const bf16* s, int oa, int ob, int hal
       }
   }
 }
-__device__ __forceinline__ Split split_of(f32x4 a, f32x4 b) {
-  return split8({a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
-}
 // row panels are dealt to the XCDs, a panel's column tiles to one: false past the end
 __device__ __forceinline__ bool split_tile(int MT, int NT, int& mt, int& nt) {
   const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
@@ -372,7 +369,7 @@ __global__ void __launch_bounds__(256, 3) pool_dgate_split_k(PoolArgs p, float* 
   for (int kt = 0; kt < nk; ++kt) {
     step_barrier();   // every wavefront is done with the step before (the first: the columns of z are there)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) put_split<ROWS>(st, j * 64 + lr, tid & 3, split_of(x[j][0], x[j][1]));
+    for (int j = 0; j < 3; ++j) put_split<ROWS>(st, j * 64 + lr, tid & 3, split_of<false>(x[j][0], x[j][1]));
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const float* c = zc + kt * SPLIT_BK + lc + q * 4;
@@ -478,9 +475,9 @@ __global__ void __launch_bounds__(256, 3) pool_g_split_k(PoolArgs p, const float
   load(0);
   for (int kt = 0; kt < nk; ++kt) {
     if (kt) step_barrier();   // every wavefront is done with the step before
-    put_split<ROWS>(st, lr, tid & 3, split_of(x[0], x[1]));
+    put_split<ROWS>(st, lr, tid & 3, split_of<true>(x[0], x[1]));
 #pragma unroll
-    for (int j = 0; j < 2; ++j) put_split<ROWS>(st, SBM + j * 64 + lane, wave, split8(w[j]));
+    for (int j = 0; j < 2; ++j) put_split<ROWS>(st, SBM + j * 64 + lane, wave, split8<false>(w[j]));
     if (kt + 1 < nk) load(kt + 1);
     step_barrier();
     split_mul(st, oa, ob, half, acc);
@@ -489,7 +486,9 @@ __global__ void __launch_bounds__(256, 3) pool_g_split_k(PoolArgs p, const float
 #pragma unroll
   for (int j = 0; j < 2; ++j) r[j][0] = acc[j][0] + acc[j][1];
   const long long n = m0 + oa < p.N ? m0 + oa : p.N - 1;
-  if (not_finite(r)) {
+  if (!not_finite(r)) {
+    scale_down(r);
+  } else {
     const float* pd = Dp + n * K + half * 4;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {

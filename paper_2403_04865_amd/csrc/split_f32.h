@@ -17,7 +17,12 @@ __device__ __forceinline__ void step_barrier() {
 // Eight floats as three bf16 vectors whose sum they are, bit for bit, from 2^-110 in size on (a trailing term ends at 2^-133).  Each term is
 // the rest rounded to nearest, so that the next one is at most half a unit of its last place and has either sign.  (A float that rounds up to
 // an infinite leading term has no trailing ones: not_finite.)
+// UP: the vectors of 2^48 times the floats, exact for all of them.  So go a product's first operands, where gradients are: those of a
+// tile that the attention has all but left out may be as small as floats get, while weights and activations are not.  The results are
+// scaled back (scale_down); operands of 2^80 and results as large are infinite on the way, and those blocks are taken again.
 struct Split { bf16x8 t[3]; };   // leading, middle, trailing bits
+constexpr float SPLIT_UP = 0x1p48f;
+template <bool UP>
 __host__ __device__ __forceinline__ Split split8(const float (&x)[8]) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -26,6 +31,7 @@ __host__ __device__ __forceinline__ Split split8(const float (&x)[8]) {
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     f32x2 v = {x[2 * p], x[2 * p + 1]};
+    if constexpr (UP) { v[0] *= SPLIT_UP; v[1] *= SPLIT_UP; }
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       w[i][p] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
@@ -37,6 +43,10 @@ __host__ __device__ __forceinline__ Split split8(const float (&x)[8]) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) s.t[i] = __builtin_bit_cast(bf16x8, w[i]);
   return s;
+}
+template <bool UP>
+__device__ __forceinline__ Split split_of(f32x4 a, f32x4 b) {
+  return split8<UP>({a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
 }
 // A step's operands in LDS: 3 planes (terms) of ROWS rows of 32 bf16; the 16-byte pieces of a row are slot-permuted (piece c of row R
 // in slot c ^ ((R >> 2) & 3)), so that 16-byte accesses to 16 consecutive rows fall on 64 different banks.
@@ -66,6 +76,16 @@ __device__ __forceinline__ bool not_finite(const f32x16 (&acc)[NA][NB]) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) worst = fmaf(acc[i][j][r], 0.f, worst);   // 0, or no number
   return __any(worst != worst);
+}
+
+template <int NA, int NB>
+__device__ __forceinline__ void scale_down(f32x16 (&acc)[NA][NB]) {
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] *= 1.0f / SPLIT_UP;
 }
 
 }  // namespace sl

@@ -69,13 +69,41 @@ def test_products_that_are_infinite(tiles):
     assert np.isposinf(first[0]).all() and np.isposinf(first[1]).all() and np.isnan(first[2]).all()
 
 
+def _embedding(cfg, prm, X):
+    """Patch rows of the stream behind the patch embedding (float32), and the patches and results in float64."""
+    from slide_harness import GpuSlide
+    tiles, P, g2 = X.shape[0], cfg.patch, cfg.grid ** 2
+    g = GpuSlide(cfg, prm, 0, tiles)
+    torch = g.torch
+    px = g.to_dev(X)
+    g.lib.encoder_fwd_tiles(px, tiles, torch.zeros((tiles, cfg.dim), device=g.dev), 1)
+    torch.cuda.synchronize()
+    # the arena's tensor whose first row is class token and position
+    mem = g.arena[:g.arena.numel() // 256 * 256].view(torch.float32)
+    key = torch.from_numpy(prm["cls"].reshape(-1) + prm["pos"][0]).to(g.dev)
+    near = (mem.view(-1, 64) == key[:64]).all(1).nonzero().flatten().tolist()
+    near = [o * 64 for o in near if bool((mem[o * 64:o * 64 + cfg.dim] == key).all())]
+    got = mem[near[0]:near[0] + tiles * cfg.tokens * cfg.dim].view(tiles, cfg.tokens, cfg.dim)[:, 1:].double().cpu().numpy().reshape(-1, cfg.dim)
+    p = X.astype(np.float64).reshape(tiles, 3, cfg.grid, P, cfg.grid, P).transpose(0, 2, 4, 1, 3, 5).reshape(tiles * g2, -1)
+    with np.errstate(invalid="ignore"):
+        want = p @ prm["pe.W"].astype(np.float64).T + prm["pe.b"] + np.tile(prm["pos"][1:], (tiles, 1))
+    return got, p, want
+
+
+# A row's products are off by 2^-24 each, its 768 additions by as much of a partial sum: 2 sqrt(768) 2^-24 = 3.3e-6 of the terms' norm
+def _worst(cfg, prm, got, p, want):
+    norm = np.sqrt((p ** 2) @ (prm["pe.W"].astype(np.float64) ** 2).T) + np.abs(want)
+    err = (np.abs(got - want) / norm).max()
+    print("worst", err, flush=True)
+    return err
+
+
 # One operand that is no finite number, in a column of each group of wavefronts that K is dealt to (two groups: columns 0 .. 31, 64 .. 95, ...
 # are the first one's; four: 0 .. 31, 128 .. 159, ...), in blocks of 64 rows of their own, dense weights: its row has what float32
 # products give, every other row what it has anyway.  Patch embedding of ViT-S, K = 768: 1 tile takes 32 x 32 blocks, 5 four groups, 20
 # two, 65 one, 70 the 64 x 128 tiles.
 @pytest.mark.parametrize("tiles", [1, 5, 20, 65, 70])
 def test_rows_beside_one_that_is_not_finite(tiles):
-    from slide_harness import GpuSlide
     cfg = replace(gen.CONFIGS["small"][0], layers=0)
     ds, ws, _ = gen.SEEDS["small"]
     prm = gen.make_params(cfg, ws, perturbed=True)
@@ -86,26 +114,24 @@ def test_rows_beside_one_that_is_not_finite(tiles):
         n, j, (c, y, x) = row // g2, row % g2, np.unravel_index(col, (3, P, P))
         X[n, c, j // cfg.grid * P + y, j % cfg.grid * P + x] = bad[row] = (np.inf, np.nan, -np.inf)[i % 3]
     print(f"case rows beside one that is not finite n={tiles}", flush=True)
-    g = GpuSlide(cfg, prm, 0, tiles)
-    torch = g.torch
-    px = g.to_dev(X)
-    g.lib.encoder_fwd_tiles(px, tiles, torch.zeros((tiles, cfg.dim), device=g.dev), 1)
-    torch.cuda.synchronize()
-    # the stream behind the embedding: the arena's tensor whose first row is class token and position
-    mem = g.arena[:g.arena.numel() // 256 * 256].view(torch.float32)
-    key = torch.from_numpy(prm["cls"].reshape(-1) + prm["pos"][0]).to(g.dev)
-    near = (mem.view(-1, 64) == key[:64]).all(1).nonzero().flatten().tolist()
-    near = [o * 64 for o in near if bool((mem[o * 64:o * 64 + cfg.dim] == key).all())]
-    got = mem[near[0]:near[0] + tiles * cfg.tokens * cfg.dim].view(tiles, cfg.tokens, cfg.dim)[:, 1:].double().cpu().numpy().reshape(-1, cfg.dim)
-    p = X.astype(np.float64).reshape(tiles, 3, cfg.grid, P, cfg.grid, P).transpose(0, 2, 4, 1, 3, 5).reshape(tiles * g2, -1)
-    with np.errstate(invalid="ignore"):
-        want = p @ prm["pe.W"].astype(np.float64).T + prm["pe.b"] + np.tile(prm["pos"][1:], (tiles, 1))
+    got, p, want = _embedding(cfg, prm, X)
     for row in bad:
         w = prm["pe.W"][:, int(np.flatnonzero(~np.isfinite(p[row]))[0])]
         assert np.array_equal(got[row], bad[row] * np.sign(w), equal_nan=True), (row, got[row][:4])
     rest = np.setdiff1d(np.arange(tiles * g2), list(bad))
-    # a row's products are off by 2^-24 each, its 768 additions by as much of a partial sum: 2 sqrt(768) 2^-24 = 3.3e-6 of the terms' norm
-    norm = np.sqrt((p[rest] ** 2) @ (prm["pe.W"].astype(np.float64) ** 2).T) + np.abs(want[rest])
-    err = np.abs(got[rest] - want[rest]) / norm
-    print("worst", err.max(), flush=True)
-    assert err.max() < 4e-6
+    assert _worst(cfg, prm, got[rest], p[rest], want[rest]) < 4e-6
+
+
+# First operands of about 2^-120, whose trailing bits no bf16 number holds as they are, and of about 2^84, which are infinite when scaled
+@pytest.mark.parametrize("tiles", [1, 5, 20, 65, 70])
+@pytest.mark.parametrize("power", [-120, 84])
+def test_operands_at_the_ends_of_the_range(tiles, power):
+    cfg = replace(gen.CONFIGS["small"][0], layers=0)
+    ds, ws, _ = gen.SEEDS["small"]
+    prm = gen.make_params(cfg, ws, perturbed=True)
+    prm["pe.W"] = prm["pe.W"] * np.float32(64)
+    prm["pe.b"] = np.zeros_like(prm["pe.b"])
+    prm["pos"][1:] = 0
+    X = np.ldexp(gen.make_pixels(cfg, tiles, ds), power)
+    print(f"case operands at the ends of the range n={tiles} 2^{power}", flush=True)
+    assert _worst(cfg, prm, *_embedding(cfg, prm, X)) < 4e-6
