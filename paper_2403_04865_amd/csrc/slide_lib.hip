@@ -1176,18 +1176,18 @@ int slide_step_chunked(slide_ctx* c, const void* pixels, int64_t N, int64_t chun
   const int64_t last = (N - 1) / chunk_tiles * chunk_tiles;
   for (int64_t t0 = last; t0 >= 0; t0 -= chunk_tiles)
     if ((rc = chunk_fwd(t0, t0 == 0, t0 == last))) return rc;
+  // a step that fails from here on leaves no activations to run a backward on
+  auto fail = [&](int e) { c->enc_saved = false; return e; };
   // aggregator and loss on the whole slide, then the gradient of every feature row
-  rc = pool_fwd(c, y, H, N, label, loss, logits, alpha, s);
-  if (rc) return rc;
-  rc = pool_bwd(c, y, H, N, label, G, accumulate, s, true);
-  if (rc) return rc;
+  if ((rc = pool_fwd(c, y, H, N, label, loss, logits, alpha, s))) return fail(rc);
+  if ((rc = pool_bwd(c, y, H, N, label, G, accumulate, s, true))) return fail(rc);
   // pass 2: chunk by chunk, forward again (but for the first) with the activations kept, backward seeded with the chunk's rows of G
   for (int64_t t0 = 0; t0 < N; t0 += chunk_tiles) {
     const int64_t n = N - t0 < chunk_tiles ? N - t0 : chunk_tiles;
-    if (t0 > 0 && (rc = chunk_fwd(t0, true, false))) return rc;
+    if (t0 > 0 && (rc = chunk_fwd(t0, true, false))) return fail(rc);
     rc = enc_bwd(c, G + t0 * row_bytes, n, (accumulate || t0 > 0) ? 1 : 0,
                  pixel_grad ? (char*)pixel_grad + t0 * tile_bytes : nullptr, s);
-    if (rc) return rc;
+    if (rc) return fail(rc);
   }
   c->enc_saved = false;
   c->step_saved = false;
