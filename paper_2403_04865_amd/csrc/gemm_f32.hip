@@ -7,10 +7,9 @@
 // six of the nine products of terms are added in float32: 2.7 times the rate.  What is left out is at most 2^-24 of a product and of either
 // sign (terms that are cut off instead of rounded leave out up to 2^-21, always of the product's own sign: sums of positive numbers came out
 // 1.35 times as far off as the float32 MFMA's).  Errors against 64 bits, this / the float32 MFMA, normal operands: K = 384 1.1e-7 to 2.9e-7 (by how
-// many groups K is dealt to) / 3.5e-7, K = 1536 2.1e-7 to 4.3e-7 / 7.0e-7, sums over M = 12,017 rows 4.8e-7 in 14 slabs / 4.9e-7 in 16; positive
-// operands 0.6e-7 to 2.4e-7 / 3.0e-7, 0.8e-7 to 2.2e-7 / 6.0e-7, 0.94e-7 / 1.10e-7; geometric means of the ratio over the encoder's shapes 0.54
-// (NT) and 0.88 (TN), positive 0.36 and 0.90.  (The bf16 MFMA adds a step's products with a slight pull downwards: results are 3e-8 to 2e-7 of
-// their mean size low.)
+// many groups K is dealt to) / 3.5e-7, K = 1536 2.1e-7 to 4.2e-7 / 7.0e-7, sums over M = 12,017 rows 4.5e-7 in 14 slabs / 4.9e-7 in 16; positive
+// operands 0.6e-7 to 2.4e-7 / 3.0e-7, 0.8e-7 to 2.2e-7 / 6.0e-7, 0.90e-7 / 1.10e-7; geometric means of the ratio over the encoder's shapes 0.53
+// (NT) and 0.85 (TN), positive 0.35 and 0.89.
 // Operands are cut once per workgroup, on their way through registers into LDS, the next step's loads in flight meanwhile; the
 // vector work of one workgroup (a fifth to a third of the MFMAs' clocks) hides behind the MFMAs of the others, of which three to six fit a
 // compute unit with one stage each (two stages and half the workgroups were a quarter slower).  us, before / now: M = 12,017: N = 1536, K = 384
@@ -104,10 +103,11 @@ __global__ void __launch_bounds__(256 * KG, BM + BN == 192 ? 3 : 4) gemm_nt_f32_
       x[j][1] = *reinterpret_cast<const f32x4*>(src[j] + kt * BK + 4);
     }
   };
+  const float up = split_up(grp);
   auto store = [&](bf16* s) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NU; ++j)
-      put_split<ROWS>(s, j * 64 + (tid >> 2), tid & 3, j < BM / 64 ? split_of<true>(x[j][0], x[j][1]) : split_of<false>(x[j][0], x[j][1]));
+      put_split<ROWS>(s, j * 64 + (tid >> 2), tid & 3, split_of(x[j][0], x[j][1], j < BM / 64 ? up : 1.f));
   };
   f32x16 acc[WBM][WBN];
 #pragma unroll
@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(256 * KG, BM + BN == 192 ? 3 : 4) gemm_nt_f32_
     if (kt < nk) mul_step<ROWS>(st, oa, ob, half, acc);
   }
   if (!not_finite(acc)) {
-    scale_down(acc);
+    scale_down(acc, up);
   } else {
 #pragma unroll
     for (int i = 0; i < WBM; ++i)
@@ -202,6 +202,7 @@ __global__ void __launch_bounds__(64 * SW) gemm_nt_f32_few_k(GemmNT g, int NTL) 
   f32x16 acc[1][1];
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+  const float up = split_up(wave);
   for (int c0 = wave; c0 < nk; c0 += SU * W) {
     f32x4 x[SU][2], y[SU][2];
 #pragma unroll
@@ -214,14 +215,14 @@ __global__ void __launch_bounds__(64 * SW) gemm_nt_f32_few_k(GemmNT g, int NTL) 
 #pragma unroll
     for (int u = 0; u < SU; ++u)
       if (c0 + u * W < nk) {
-        const Split fa = split_of<true>(x[u][0], x[u][1]);
-        const Split fb = split_of<false>(y[u][0], y[u][1]);
+        const Split fa = split_of(x[u][0], x[u][1], up);
+        const Split fb = split_of(y[u][0], y[u][1]);
 #pragma unroll
         for (int t = 0; t < 6; ++t) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb.t[TERM_B[t]], fa.t[TERM_A[t]], acc[0][0], 0, 0, 0);
       }
   }
   if (!not_finite(acc)) {
-    scale_down(acc);
+    scale_down(acc, up);
   } else {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
@@ -318,14 +319,15 @@ __global__ void __launch_bounds__(256, TB == 128 ? 3 : 4) gemm_tn_f32_k(GemmTN g
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   float cs0 = 0.f, cs1 = 0.f;
+  const float up = split_up(slab);
   auto store = [&](bf16* s, bool odd) __attribute__((always_inline)) {
     float c = 0.f;
 #pragma unroll
     for (int j = 0; j < NU / 2; ++j) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) c += x[j][e];
-      put_split<ROWS>(s, col, grp + j * GS, split8<true>(x[j]));
-      put_split<ROWS>(s, TB + col, grp + j * GS, split8<false>(x[NU / 2 + j]));
+      put_split<ROWS>(s, col, grp + j * GS, split8(x[j], up));
+      put_split<ROWS>(s, TB + col, grp + j * GS, split8(x[NU / 2 + j]));
     }
     cs0 += odd ? 0.f : c;
     cs1 += odd ? c : 0.f;
@@ -353,7 +355,7 @@ __global__ void __launch_bounds__(256, TB == 128 ? 3 : 4) gemm_tn_f32_k(GemmTN g
     }
   }
   if (!not_finite(acc)) {
-    scale_down(acc);
+    scale_down(acc, up);
   } else {
 #pragma unroll
     for (int i = 0; i < WB; ++i)

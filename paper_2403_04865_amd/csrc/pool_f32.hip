@@ -298,8 +298,7 @@ __global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __r
 // (features) per workgroup.  What bounds it: the six products' MFMAs (0.75 PFLOP/s of bf16 at 131,072 rows) beside the cut of the
 // operands and the fragments' trips from LDS.  The products of the leading terms have an accumulator of their own: the gate gradients' terms
 // cancel, and what a sum is off by is mostly the roundings of its additions, of which six products a step in one
-// accumulator would make six times as many; a row's dot product is added in 64 bits.  (The error against 64 bits is 1.00 of the kernels'
-// above, geometric mean over the gate gradients of bags of 4,500 to 40,000 rows, D = 384 and 768, M_h = 128 and 256.)
+// accumulator would make six times as many; a row's dot product is added in 64 bits.
 // us, before / now, D = 768: 45,056 rows, M_h = 128: gates 421 / 145, G 293 / 140; whole step of 131,072 rows 2964 / 1602, M_h = 256
 // 6047 / 3132.  (128 x 128 results a workgroup: 151 and 133, nothing either way.)
 constexpr int NACC = 2;   // accumulators of a block
@@ -369,7 +368,7 @@ __global__ void __launch_bounds__(256, 3) pool_dgate_split_k(PoolArgs p, float* 
   for (int kt = 0; kt < nk; ++kt) {
     step_barrier();   // every wavefront is done with the step before (the first: the columns of z are there)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) put_split<ROWS>(st, j * 64 + lr, tid & 3, split_of<false>(x[j][0], x[j][1]));
+    for (int j = 0; j < 3; ++j) put_split<ROWS>(st, j * 64 + lr, tid & 3, split_of(x[j][0], x[j][1]));
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const float* c = zc + kt * SPLIT_BK + lc + q * 4;
@@ -475,9 +474,9 @@ __global__ void __launch_bounds__(256, 3) pool_g_split_k(PoolArgs p, const float
   load(0);
   for (int kt = 0; kt < nk; ++kt) {
     if (kt) step_barrier();   // every wavefront is done with the step before
-    put_split<ROWS>(st, lr, tid & 3, split_of<true>(x[0], x[1]));
+    put_split<ROWS>(st, lr, tid & 3, split_of(x[0], x[1], SPLIT_UP));
 #pragma unroll
-    for (int j = 0; j < 2; ++j) put_split<ROWS>(st, SBM + j * 64 + lane, wave, split8<false>(w[j]));
+    for (int j = 0; j < 2; ++j) put_split<ROWS>(st, SBM + j * 64 + lane, wave, split8(w[j]));
     if (kt + 1 < nk) load(kt + 1);
     step_barrier();
     split_mul(st, oa, ob, half, acc);
@@ -487,7 +486,7 @@ __global__ void __launch_bounds__(256, 3) pool_g_split_k(PoolArgs p, const float
   for (int j = 0; j < 2; ++j) r[j][0] = acc[j][0] + acc[j][1];
   const long long n = m0 + oa < p.N ? m0 + oa : p.N - 1;
   if (!not_finite(r)) {
-    scale_down(r);
+    scale_down(r, SPLIT_UP);
   } else {
     const float* pd = Dp + n * K + half * 4;
 #pragma unroll

@@ -25,7 +25,7 @@ int main() {
   double worst = 0, sum = 0;
   float x[8], y[8];
   auto look = [&](bool products) {
-    const Split a = split8<false>(x), b = split8<false>(y);
+    const Split a = split8(x), b = split8(y);
     for (int e = 0; e < 8; ++e) {
       inexact += ((double)term(a, 0, e) + term(a, 1, e)) + term(a, 2, e) != x[e];
       double taken = 0;   // every term of it is exact in 64 bits, and so nearly is the sum
@@ -58,8 +58,8 @@ int main() {
   for (int i = 0; i < 1 << 16; ++i) {   // scaled: down to the smallest float
     for (int e = 0; e < 8; ++e)
       do x[e] = __builtin_bit_cast(float, (unsigned)r()); while (!(std::fabs(x[e]) < 0x1p79f));
-    const Split a = split8<true>(x);
-    for (int e = 0; e < 8; ++e) inexact += ((double)term(a, 0, e) + term(a, 1, e)) + term(a, 2, e) != x[e] * (double)SPLIT_UP;
+    const Split a = split8(x, -SPLIT_UP);
+    for (int e = 0; e < 8; ++e) inexact += ((double)term(a, 0, e) + term(a, 1, e)) + term(a, 2, e) != x[e] * -(double)SPLIT_UP;
   }
   std::printf("%lld %.17g %.17g\n", inexact, worst, sum / n);
 }
