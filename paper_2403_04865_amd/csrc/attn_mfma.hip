@@ -604,8 +604,9 @@ hipError_t fwd_go(const void* qkv, void* O, float* lse, long long n, int T, int 
   return hipGetLastError();
 }
 
-// Heads of all tiles together up to which both passes run side by side.  ViT-S steps of 64 tiles (384 heads) 4716 / 4673 us, ViT-B steps of 40
-// (480) 8169 / 8218; heads 32 wide, of which three workgroups fit a unit: 256 tiles (512) 256.7 / 253.7, larger bags not measured
+// Heads of all tiles together up to which both passes run side by side, for the two shapes that are built (attn_mfma_ok).  Two launches /
+// side by side, us: 64 wide, seven blocks of tokens: ViT-S steps of 64 tiles (384 heads) 4716 / 4673, ViT-B steps of 40 (480) 8169 / 8218; 32
+// wide, one block, of which three workgroups fit a unit: 256 tiles (512) 256.7 / 253.7 (larger bags were not measured and take two launches)
 template <int NB> constexpr long long short_heads() { return NB >= 7 ? 384 : 512; }
 template <int DH, int NB>
 hipError_t bwd_go(const void* qkv, const void* O, const float* lse, const void* dO, void* dqkv, float* delta_ws,

@@ -191,7 +191,7 @@ hipError_t launch_pool_fwd(const PoolArgs& p0, hipStream_t s) {
   PoolArgs p = p0;
   hipError_t e;
   if (p.use_mfma && pool_mfma_ok(p)) {
-    // persistent grid: one workgroup per compute unit (it owns almost all of the unit's LDS)
+    // persistent grid: one workgroup per compute unit (the register-resident kernel fills it; the launchers of the others change the number)
     static int cus = 0;
     if (!cus) {
       int dev = 0;

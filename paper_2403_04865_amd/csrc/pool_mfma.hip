@@ -6,7 +6,8 @@
 // unrounded features: the softmax over tiles is a two-level online reduction (every workgroup keeps a running
 // max, sum and weighted feature sum over its row blocks; one workgroup combines them afterwards).
 // Two kernels:
-//   * pool_gate_part_reg_k (D = 384, M_h = 128; M_h = 256 as two halves of the gate units): the main one.  One persistent workgroup (4 wavefronts) per compute unit; the bf16 copy of
+//   * pool_gate_part_reg_k (D = 384, M_h = 128; M_h = 256 as two halves of the gate units, side by side or one after the other): the main
+//     one.  One persistent workgroup (4 wavefronts) per compute unit; the bf16 copy of
 //     [V;U] is 192 kB, which is what the accumulation half of a compute unit's register file holds, so every
 //     wavefront keeps the fragments of its 32 gate units in registers for the whole kernel and the only traffic is
 //     the feature rows, each read from HBM exactly once into fp32 registers (a bf16 image in LDS feeds the MFMAs;
@@ -44,27 +45,27 @@ __device__ __forceinline__ void static_for(F&& f) {
 // place without transposes, so `out` has room for both copies in every call.
 constexpr int FRAG_D = 384, FRAG_MH = 128;
 constexpr int frag(int D) { return 2 * FRAG_MH * D; }
-template <int FRAG_D>
+template <int D>
 __global__ void __launch_bounds__(256) pool_cast_frag_k(const float* __restrict__ V, const float* __restrict__ U, bf16* __restrict__ out,
                                                         int transposed, unsigned* __restrict__ ticket) {
   if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
-  constexpr int FRAG = frag(FRAG_D), PIECES = FRAG / 8;
+  constexpr int FRAG = frag(D), PIECES = FRAG / 8;
   const int per = transposed ? 2 * PIECES : PIECES, i = blockIdx.x * 256 + threadIdx.x;   // a whole number of workgroups
   const int h = i / per, r = i - h * per, l = r & 63;
-  V += (size_t)h * FRAG_MH * FRAG_D;
-  U += (size_t)h * FRAG_MH * FRAG_D;
+  V += (size_t)h * FRAG_MH * D;
+  U += (size_t)h * FRAG_MH * D;
   float v[8];
   if (r < PIECES) {
-    const int q = r >> 6, m = q & 1, ks = (q >> 1) % (FRAG_D / 16), w = (q >> 1) / (FRAG_D / 16);
-    const float* src = (m ? U : V) + (size_t)(32 * w + (l & 31)) * FRAG_D + ks * 16 + (l >> 5) * 8;
+    const int q = r >> 6, m = q & 1, ks = (q >> 1) % (D / 16), w = (q >> 1) / (D / 16);
+    const float* src = (m ? U : V) + (size_t)(32 * w + (l & 31)) * D + ks * 16 + (l >> 5) * 8;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = src[e];
   } else {
     const int q = (r - PIECES) >> 6, ks = q % (2 * FRAG_MH / 16), b = q / (2 * FRAG_MH / 16);
     const int u = ks * 16 + (l >> 5) * 8, d = 32 * b + (l & 31);
-    const float* src = (u < FRAG_MH ? V + (size_t)u * FRAG_D : U + (size_t)(u - FRAG_MH) * FRAG_D) + d;
+    const float* src = (u < FRAG_MH ? V + (size_t)u * D : U + (size_t)(u - FRAG_MH) * D) + d;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = src[(size_t)e * FRAG_D];
+    for (int e = 0; e < 8; ++e) v[e] = src[(size_t)e * D];
   }
   bf16x8 t;
 #pragma unroll
@@ -227,11 +228,11 @@ __global__ void __launch_bounds__(256, 2) pool_gate_part_stream_k(PoolArgs p, co
 // Variant for the shape whose [V;U] fits the register file (D = 384, M_h = 128: 2 M_h * D bf16 = 192 KB, 192
 // registers per lane): each wavefront holds the MFMA fragments of its 32 gate units for the whole kernel, so the only
 // traffic per block of 32 feature rows is the block itself (the kernel above re-reads the weights from L2 for every
-// block, twice the bytes of the features).
+// block, four times the bytes of the features).
 //   * A thread owns 4 rows x 12 columns of every block (fixed columns), in fp32 registers.  LDS holds only the bf16
 //     image of a block (double buffered) for the MFMA fragments; the weighted feature sum is taken from the fp32
-//     registers: per lane in fp32 (4 rows per block, a few thousand terms at most), over row groups and workgroups
-//     in fp64 (z feeds a cancelling difference in the backward).
+//     registers: per lane in fp32 (4 rows per block: one term per 2,048 rows of the bag, 64 at 131,072 rows), over row groups and
+//     workgroups in fp64 (z feeds a cancelling difference in the backward).
 //   * The gate of block i - 1 runs under the MFMAs of block i inside each wavefront (the matrix pipe and the vector
 //     ALU are separate, and with one wavefront per SIMD nothing else overlaps them).  The pre-activations of two
 //     blocks are alive (two accumulator sets), and the softmax terms, hence the weighted sum, of a block come one
@@ -320,8 +321,8 @@ __global__ void __launch_bounds__(256) pool_gate_part_reg_k(PoolArgs p, const bf
         *reinterpret_cast<uint2*>(Hb + (buf * RB + 4 * rgrp + k) * LDB + (cl + 32 * j) * 4) = w2;
       }
   };
-  // fp32 partial sums: a lane adds 4 rows per block, a few thousand terms at most (N < 2^31, 256 workgroups x 8 row
-  // groups), before the fp64 reduction over row groups and workgroups
+  // fp32 partial sums: a lane adds 4 rows per block, N / 2048 terms in all (256 workgroups x 8 row groups), before the fp64 reduction over row
+  // groups and workgroups
   float z[4 * CJ];
   float wabs = 0.f;
   for (int j = lane; j < NH * MH; j += 64) wabs += fabsf(p.w[j]);

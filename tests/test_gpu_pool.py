@@ -98,6 +98,14 @@ def test_pool_bf16_large_logit_weights():  # sum |w| > 40: the logit bound is no
     _pool_case("medium", 4096 + 77, 1, w_scale=30.0)
 
 
+# the same with 256 gate units: halves side by side and a softmax launch; two passes of a launch, the second with the running maximum (four or
+# five blocks a workgroup).  sum |w| = 87: 256 gate values, each off by some 2^-9 from its bf16 operands, times weights of 0.4 put a logit off
+# by 16 * 0.4 * 2^-9 = 1.2e-2 at most and softmax weights and gradients by as much (at five times the weights it would be 6e-2)
+@pytest.mark.parametrize("rows", [4000, 8192 + 7, 32768 + 7, 40000])
+def test_pool_bf16_mh256_large_logit_weights(rows):
+    _pool_case("large", rows, 1, w_scale=6.0)
+
+
 def test_pool_bf16_vit_b_shape():          # 768-wide features (32-row blocks), M_h 256
     _pool_case("full", 4096 + 5, 1)
 
