@@ -302,8 +302,8 @@ __global__ void __launch_bounds__(256) pool_g_f32_k(PoolArgs p, const float* __r
 // taken off the differences h - z, which lie on a coarse grid, it would be rounded the same way in every row, and the gate units' sums over
 // the rows, which cancel, would show that.  (Errors against 64 bits over those of the kernels above, geometric means over bags of 8,192 to 65,536
 // rows, D = 384, M_h = 128: V.W 0.84, b_V 0.81, U.W 0.85, b_U 0.85, w 0.92.)
-// us, before / now, D = 768: 45,056 rows, M_h = 128: gates 421 / 145, G 293 / 140; whole step of 131,072 rows 2964 / 1602, M_h = 256
-// 6047 / 3132.  (128 x 128 results a workgroup: 151 and 133, nothing either way.)
+// us, before / now, D = 768: 45,056 rows, M_h = 128: gates 421 / 145, G 293 / 140; whole step of 131,072 rows 3092 / 1352, M_h = 256
+// 6340 / 2400.  (128 x 128 results a workgroup: 151 and 133, nothing either way.)
 constexpr int NACC = 2;   // accumulators of a block
 constexpr int SBM = 64, SPB = 128;   // rows; columns of the second operand: 64 units of V and of U, or 128 features
 

@@ -135,3 +135,23 @@ def test_operands_at_the_ends_of_the_range(tiles, power):
     X = np.ldexp(gen.make_pixels(cfg, tiles, ds), power)
     print(f"case operands at the ends of the range n={tiles} 2^{power}", flush=True)
     assert _worst(cfg, prm, *_embedding(cfg, prm, X)) < 4e-6
+
+
+# Positive operands, whose products' errors a bias would line up: what is left out of a product has either sign, and what the matrix core's
+# additions pull downwards cancels where several groups of wavefronts share K (1e-9 of the result is left) and is 2e-8 of it over 48 steps in one
+# group.  Limit: half as much again (terms cut off instead of rounded: 4e-8 in several groups, 1.9e-7 in one).
+@pytest.mark.parametrize("tiles", [1, 5, 20, 65, 70])
+def test_positive_operands_have_no_bias(tiles):
+    cfg = replace(gen.CONFIGS["small"][0], layers=0)
+    ds, ws, _ = gen.SEEDS["small"]
+    prm = gen.make_params(cfg, ws, perturbed=True)
+    prm["pe.W"] = np.abs(prm["pe.W"])
+    prm["pe.b"] = np.zeros_like(prm["pe.b"])
+    prm["pos"][1:] = 0
+    X = np.abs(gen.make_pixels(cfg, tiles, ds))
+    print(f"case positive operands n={tiles}", flush=True)
+    got, p, want = _embedding(cfg, prm, X)
+    bias = float((got - want).sum() / want.sum())
+    print("bias", bias, flush=True)
+    assert abs(bias) < 3e-8
+    assert _worst(cfg, prm, got, p, want) < 4e-6
